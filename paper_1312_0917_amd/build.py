@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsvt.so")
 SOURCES = ["svt_api.hip", "svt_stages.hip", "svt_fused.hip", "svt_prepass.hip", "svt_events.hip",
-           "svt_onepass.hip"]
+           "svt_onepass.hip", "svt_units.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

@@ -71,10 +71,23 @@ struct BatchWs {
     int64_t *kb;
     int64_t kbn;
     int16_t *coords;
-    int64_t *nw_copy;   // the batch's word count, copied to device memory by the reset
+    int64_t *nw_copy;   // the batch's word count, copied to device memory by the first kernel
+    void *sets;         // unit kernels: the packed bank,
+    void *tot;          // totals per range of units,
+    uint32_t *dealers;  // counters of the units dealt out late,
+    void *rec;          // running counts per unit,
+    void *acc;          // what the slices of a large unit share,
+    uint32_t *copy;     // and the words, when the caller's are in host memory
 };
+// What the unit kernels need besides, in bytes.
+int64_t unit_bytes(int64_t word_cap, int64_t combo_cap) {
+    return align_up(unit_bank_bytes()) + align_up(unit_range_bytes()) +
+           align_up(unit_ticket_bytes()) + align_up(unit_acc_bytes(combo_cap)) +
+           align_up(unit_rec_bytes(word_cap > 0 ? word_cap : 1));
+}
+// `copy`: with room for a copy of the words
 BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo_cap,
-                    int64_t tile) {
+                    int64_t tile, bool copy) {
     BatchWs w;
     w.tickets = c.take<uint32_t>(4);
     w.n_events = c.take<int64_t>(2);
@@ -94,7 +107,19 @@ BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo
     w.kb = c.take<int64_t>(w.kbn);
     w.coords = c.take<int16_t>(word_cap + 16);  // slack for 16-byte reads of the last span
     w.nw_copy = c.take<int64_t>(1);
+    w.sets = c.take<char>(unit_bank_bytes());
+    w.tot = c.take<char>(unit_range_bytes());
+    w.dealers = c.take<uint32_t>(unit_ticket_bytes() / 4);
+    w.rec = c.take<char>(unit_rec_bytes(word_cap > 0 ? word_cap : 1));
+    w.acc = c.take<char>(unit_acc_bytes(combo_cap));
+    w.copy = copy ? c.take<uint32_t>(word_cap) : nullptr;
     return w;
+}
+int64_t batch_bytes(int64_t word_cap, int64_t road_cap, int64_t combo_cap, int64_t tile,
+                    bool copy) {
+    Carver c{nullptr};
+    carve_batch(c, word_cap, road_cap, combo_cap, tile, copy);
+    return c.used;
 }
 
 // Batches of at most this many words (capacity) run the one-pass kernel by default, larger ones
@@ -275,9 +300,7 @@ int64_t svt_batch_workspace(int64_t word_cap, int64_t road_cap, int64_t combo_ca
     if (word_cap < 0 || word_cap > kMaxBatchWords || road_cap < 0 || combo_cap < 0) return -1;
     const svt_tune t = resolve_tune(tune, word_cap);
     if (!tune_ok(tune, word_cap)) return -1;
-    Carver c{nullptr};
-    carve_batch(c, word_cap, road_cap, combo_cap, t.tile_combos);
-    return c.used;
+    return batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, true);
 }
 
 svt_status svt_unpack(const uint32_t *words, int64_t n_words, const svt_config *cfg,
@@ -388,6 +411,53 @@ static svt_status batch_sequence(const FusedLaunch &f, const BatchWs &w, int64_t
     const Sizes nw_dev{0, w.nw_copy, word_cap};
     const Sizes nr{0, f.d_n_roads, road_cap};
     const Sizes nc{0, f.d_n_combos, combo_cap};
+    uint64_t *err = f.err;
+    if (f.tune.schedule != SVT_SCHEDULE_EVENTS) {
+        // the unit kernels, and with a kept list its scan and compaction
+        UnitsLaunch o{};
+        o.bank = f.bank;
+        o.cfg = f.cfg;
+        o.words = f.words;
+        o.d_n_words = f.d_n_words;
+        o.word_cap = word_cap;
+        o.roads = f.roads;
+        o.road_cap = road_cap;
+        o.out = f.rec;
+        o.accept = f.accept;
+        o.best = f.best;
+        o.combo_cap = combo_cap;
+        o.d_n_roads = const_cast<int64_t *>(f.d_n_roads);
+        o.d_n_combos = const_cast<int64_t *>(f.d_n_combos);
+        o.err = err;
+        o.kb_counts = d_n_kept ? w.kb : nullptr;
+        o.n_kb = w.kbn;
+        o.kept_only = f.kept_only;
+        o.coords = w.coords;
+        o.tile_first_road = w.tfr;
+        o.tiles_cap = w.tiles_cap;
+        o.nw_copy = w.nw_copy;
+        o.ticket = w.dealers;
+        o.acc = w.acc;
+        o.sets = w.sets;
+        o.rec = w.rec;
+        o.tot = w.tot;
+        o.copy = w.copy;
+        o.num_cus = f.num_cus;
+        SVT_TRY(launch_units(o, stream, timing ? g_ev_start : nullptr,
+                             timing ? g_ev_stop : nullptr));
+        if (d_n_kept) {
+            SVT_TRY(launch_scan(w.kb, 0, 1, nc, kKeptBlock, d_n_kept, nullptr,
+                                kept ? kept_cap : -1, 2, err, true, stream));
+            if (kept && f.kept_only)
+                SVT_TRY(launch_kept_refit(f.accept, nc, nr, w.kbn, w.kb, f.roads, w.tfr,
+                                          kKeptBlock, f.bank, f.cfg.n_sets, f.coords,
+                                          f.cfg.shift, kept, f.rec, kept_cap, err, stream));
+            else if (kept)
+                SVT_TRY(launch_kept_write(f.accept, nc, w.kbn, w.kb, kept, kept_cap, err,
+                                          stream));
+        }
+        return SVT_OK;
+    }
     PrepassLaunch p{};
     p.words = f.words;
     p.nw = nw;
@@ -409,53 +479,6 @@ static svt_status batch_sequence(const FusedLaunch &f, const BatchWs &w, int64_t
     p.event_first_road = w.efr;
     p.event_cap = w.events_cap;
     p.d_n_events = w.n_events;
-    uint64_t *err = f.err;
-    if (f.tune.schedule == SVT_SCHEDULE_ONEPASS) {
-        // reset, the one-pass kernel, and with a kept list its scan and compaction
-        p.nb_cap = w.nb;
-        p.status_words = 2 * w.nb;
-        SVT_TRY(launch_batch_reset(p, w.nw_copy, d_n_kept, d_n_kept ? w.kb : nullptr,
-                                   d_n_kept ? w.kbn : 0, stream));
-        OnepassLaunch o{};
-        o.bank = f.bank;
-        o.cfg = f.cfg;
-        o.words = f.words;
-        o.nw = nw_dev;
-        o.roads = f.roads;
-        o.road_cap = road_cap;
-        o.rec = f.rec;
-        o.accept = f.accept;
-        o.best = f.best;
-        o.combo_cap = combo_cap;
-        o.d_n_roads = p.d_n_roads;
-        o.d_n_combos = p.d_n_combos;
-        o.kb_counts = d_n_kept ? w.kb : nullptr;
-        o.status = w.status;
-        o.nb_cap = w.nb;
-        o.tickets = w.tickets;
-        o.err = err;
-        o.kept_only = f.kept_only;
-        o.coords = w.coords;
-        o.tile_first_road = w.tfr;
-        o.tiles_cap = w.tiles_cap;
-        o.num_cus = f.num_cus;
-        o.wgs_per_cu = f.tune.wgs_per_cu;
-        if (timing) SVT_TRY(hipEventRecord(g_ev_start, stream));
-        SVT_TRY(launch_onepass(o, stream));
-        if (timing) SVT_TRY(hipEventRecord(g_ev_stop, stream));
-        if (d_n_kept) {
-            SVT_TRY(launch_scan(w.kb, 0, 1, nc, kKeptBlock, d_n_kept, nullptr,
-                                kept ? kept_cap : -1, 2, err, true, stream));
-            if (kept && f.kept_only)
-                SVT_TRY(launch_kept_refit(f.accept, nc, nr, w.kbn, w.kb, f.roads, w.tfr,
-                                          kKeptBlock, f.bank, f.cfg.n_sets, f.coords,
-                                          f.cfg.shift, kept, f.rec, kept_cap, err, stream));
-            else if (kept)
-                SVT_TRY(launch_kept_write(f.accept, nc, w.kbn, w.kb, kept, kept_cap, err,
-                                          stream));
-        }
-        return SVT_OK;
-    }
     // (the kept-list block counts are cleared with the rest: the fused kernel adds to them)
     p.nb_cap = ceil_div(word_cap > 0 ? word_cap : 1, kPrepassBlockWords);
     p.status_words = prepass_status_words(p.nb_cap);
@@ -501,7 +524,11 @@ namespace {
 // One array per GPU in this library's code object, held until the process ends.  In host code
 // its name is only the runtime's handle for it: the device address is taken once per device
 // with hipGetSymbolAddress and used everywhere instead.
-static __device__ __align__(256) char scratch[SVT_STATIC_WORK_BYTES];
+// (The unit kernels' part comes on top of SVT_STATIC_WORK_BYTES.  A batch that the rest admits has
+// fewer than 2^24 words and 12e9 combinations, for they take 2 bytes a word and 12 bytes per 4096
+// combinations there: 1 MiB for the units, 24 MB and 2 MiB for the slices.)
+constexpr int64_t kStaticUnitBytes = 28ll << 20;
+static __device__ __align__(256) char scratch[SVT_STATIC_WORK_BYTES + kStaticUnitBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
@@ -517,6 +544,15 @@ svt_status static_workspace(void **out) {
     }
     *out = g_scratch_ptr[dev];
     return SVT_OK;
+}
+
+bool in_host_memory(const void *p) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();  // not an address the runtime knows: take it as the caller's word
+        return false;
+    }
+    return at.type == hipMemoryTypeHost;
 }
 
 // work_bytes value that selects the static workspace (d_work is then ignored)
@@ -552,20 +588,27 @@ svt_status process_batch(const svt_fconst *bank, const svt_config *cfg, const sv
     if (!tune_ok(tune, word_cap)) return SVT_ERR_ARG;
     if (work_bytes == kStaticWork) {  // svt_process_batch_static
         if (flags & SVT_BATCH_GRAPH) return SVT_ERR_ARG;  // instantiating a graph allocates
-        if (svt_batch_workspace(word_cap, road_cap, combo_cap, &t) > SVT_STATIC_WORK_BYTES)
+        const int64_t limit = SVT_STATIC_WORK_BYTES + unit_bytes(word_cap, combo_cap);
+        if (batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, false) > limit)
             return SVT_ERR_CAPACITY;
         const svt_status st = static_workspace(&d_work);
         if (st != SVT_OK) return st;
-        work_bytes = SVT_STATIC_WORK_BYTES;
-    } else if (!d_work || work_bytes < svt_batch_workspace(word_cap, road_cap, combo_cap, &t) ||
+        work_bytes = limit;
+    } else if (!d_work ||
+               work_bytes < batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, false) ||
                !aligned(d_work, kAlign)) {
         return SVT_ERR_ARG;
     }
+    // words in host memory are read once over the bus: the counting kernel leaves a copy, where
+    // the workspace has room for one (else both kernels read them in place)
+    const bool copy =
+        in_host_memory(words) &&
+        work_bytes >= batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, true);
     const int cus = num_cus();
     if (cus <= 0) return SVT_ERR_HIP;
 
     Carver c{static_cast<char *>(d_work)};
-    const BatchWs w = carve_batch(c, word_cap, road_cap, combo_cap, t.tile_combos);
+    const BatchWs w = carve_batch(c, word_cap, road_cap, combo_cap, t.tile_combos, copy);
     FusedLaunch f{};
     f.bank = bank;
     f.cfg = *cfg;
@@ -674,7 +717,12 @@ svt_status svt_static_workspace_need(int64_t word_cap, int64_t road_cap, int64_t
     if (!need || !limit) return SVT_ERR_ARG;
     *limit = SVT_STATIC_WORK_BYTES;
     *need = svt_batch_workspace(word_cap, road_cap, combo_cap, tune);
-    return *need < 0 ? SVT_ERR_ARG : *need > *limit ? SVT_ERR_CAPACITY : SVT_OK;
+    if (*need < 0) return SVT_ERR_ARG;
+    *limit += unit_bytes(word_cap, combo_cap);
+    if (*need > *limit)  // without room for a copy of the words
+        *need = batch_bytes(word_cap, road_cap, combo_cap,
+                            resolve_tune(tune, word_cap).tile_combos, false);
+    return *need > *limit ? SVT_ERR_CAPACITY : SVT_OK;
 }
 void svt_release_graphs(void) {
     std::lock_guard<std::mutex> lock(g_graph_mu);

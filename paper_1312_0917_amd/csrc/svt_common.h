@@ -298,4 +298,43 @@ struct OnepassLaunch {
 };
 hipError_t launch_onepass(const OnepassLaunch &p, hipStream_t s);
 
+// The batched pass over wave-sized units of words: a counting kernel and a fitting kernel
+// (svt_units.hip), with `start` / `stop` (nullable) recorded around the second.
+struct UnitsLaunch {
+    const svt_fconst *bank;
+    svt_config cfg;
+    const uint32_t *words;
+    const int64_t *d_n_words;
+    int64_t word_cap;
+    svt_roads roads;
+    int64_t road_cap;
+    svt_fitrec out;
+    uint8_t *accept;
+    svt_best best;
+    int64_t combo_cap;
+    int64_t *d_n_roads;
+    int64_t *d_n_combos;
+    uint64_t *err;
+    int64_t *kb_counts;        // accepted count per kKeptBlock combinations (null: no kept list)
+    int64_t n_kb;
+    bool kept_only;            // no records; grouped coordinates and block marks for the refit
+    int16_t *coords;
+    int32_t *tile_first_road;
+    int64_t tiles_cap;
+    int64_t *nw_copy;          // workspace: the word count in device memory,
+    uint32_t *ticket;          // counters (unit_ticket_bytes),
+    void *sets;                // the packed bank (unit_bank_bytes),
+    void *rec;                 // running counts per unit (unit_rec_bytes),
+    void *tot;                 // totals per range of units (unit_range_bytes),
+    void *acc;                 // what slices of units share (unit_acc_bytes),
+    uint32_t *copy;            // and the words, when the caller's are in host memory (else null)
+    int num_cus;
+};
+int64_t unit_rec_bytes(int64_t words);
+int64_t unit_range_bytes();
+int64_t unit_acc_bytes(int64_t combos);
+int64_t unit_ticket_bytes();
+int64_t unit_bank_bytes();
+hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+
 }  // namespace svt

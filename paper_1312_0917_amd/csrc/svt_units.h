@@ -1,0 +1,244 @@
+// Wave-sized units of the batched pass: what the counting kernel and the fitting kernel share.
+//
+// A unit is 256 consecutive hit words and belongs to one wave.  The wave stages 64 words more:
+// a road that starts among the unit's words may run past them, and a road with combinations has
+// at most 5 * 8 = 40 words.  A lane holds five consecutive words of the 320, so one wave-wide
+// scan of packed counts gives every word its road, its event and its rank among its road's hits
+// on its layer; nothing is walked word by word.
+#pragma once
+
+#include "svt_common.h"
+
+namespace svt {
+
+constexpr int kUnitWords = 256;                      // words a unit owns
+constexpr int kUnitSpan = 320;                       // words staged
+constexpr int kUnitLane = kUnitSpan / kWaveSize;     // 5 consecutive words per lane
+constexpr int kUnitFitRoads = 64;  // roads with combinations that start in a unit: each has at
+                                   // least 5 words, so at most (256 + 35) / 5 = 58
+constexpr int kUnitWaves = 16;     // waves of a workgroup of either kernel
+constexpr int kDealers = 32;       // counters that deal out the last units,
+constexpr int kDealerStride = 32;  // a 128-byte line apart
+constexpr int kMaxRanges = 512;    // contiguous ranges of units whose totals are scanned together
+
+// A unit with many combinations is cut into slices of this many, so that no wave works long after
+// the others have finished (a unit of the largest roads holds 2e5 combinations, a usual one 800 to
+// 3000); a batch too small to fill the chip is cut finer.
+constexpr int kSliceCombos = 8192, kSliceCombosSmall = 1024;
+constexpr int kSmallUnits = 64;
+__host__ __device__ inline int slice_combos(int64_t nu) {
+    return nu <= kSmallUnits ? kSliceCombosSmall : kSliceCombos;
+}
+// Counts before a unit, from the start of its range.
+struct alignas(16) UnitRec {
+    uint32_t roads, events;
+    uint64_t combos;     // 40 bits; above them the slices past each unit's first
+};
+constexpr int kExtraShift = 40;
+// What the slices of a unit find out together about a road cut by a slice's end, at the first such
+// end: zero to start with.
+struct alignas(16) SliceAcc {
+    unsigned long long key;  // complement of the smallest key
+    uint32_t nacc;
+    uint32_t arrived;        // slices that have added theirs
+};
+// Totals of a range of units, and the first errors in it (all ones: none).
+struct alignas(16) RangeTot {
+    uint32_t roads, events;
+    uint64_t combos;     // as in UnitRec
+    uint32_t bad_word;   // word with a layer field out of range (index in the batch)
+    uint32_t over_road;  // road with too many hits on a layer (index in the range)
+    uint32_t set_road;   // road whose tag has no constant set (index in the range)
+    uint32_t pad;
+};
+
+// A constant set as the fit reads it: row j is f0|f1, f2|f3, f4|0 (int16 pairs) and the offset.
+// 112 bytes: with a stride of 28 dwords the 16-byte reads of the sets one wave works on start in
+// different LDS banks.
+struct alignas(16) UnitSet {
+    uint4 row[6];
+    uint32_t narrow;  // the set's bounds allow 32-bit sums (narrow_ok)
+    uint32_t pad[3];
+};
+static_assert(sizeof(UnitSet) == 112, "LDS bank spread of the staged constant sets");
+
+// ---- cross-lane helpers ------------------------------------------------------------------------
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t dpp(uint32_t x, uint32_t old = 0) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+        static_cast<int>(old), static_cast<int>(x), CTRL, ROWS, 0xF, false));
+}
+constexpr int kDppNext = 0x130;  // lane i reads lane i + 1 (lane 63: the given default)
+constexpr int kDppPrev = 0x138;  // lane i reads lane i - 1 (lane 0: the given default)
+
+// Inclusive scan over the wave's 64 lanes, all of them active.
+__device__ __forceinline__ uint32_t scan64(uint32_t x) {
+    x += dpp<0x111>(x);
+    x += dpp<0x112>(x);
+    x += dpp<0x114>(x);
+    x += dpp<0x118>(x);
+    x += dpp<0x142, 0xA>(x);
+    x += dpp<0x143, 0xC>(x);
+    return x;
+}
+// The same over the first 16 lanes (each row of 16 on its own).
+__device__ __forceinline__ uint32_t scan16(uint32_t x) {
+    x += dpp<0x111>(x);
+    x += dpp<0x112>(x);
+    x += dpp<0x114>(x);
+    x += dpp<0x118>(x);
+    return x;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), lane));
+}
+__device__ __forceinline__ uint32_t uni(uint32_t x) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x)));
+}
+__device__ __forceinline__ uint64_t uni(uint64_t x) {
+    return static_cast<uint64_t>(uni(static_cast<uint32_t>(x))) |
+           (static_cast<uint64_t>(uni(static_cast<uint32_t>(x >> 32))) << 32);
+}
+// number of set bits of m below the calling lane
+__device__ __forceinline__ int bits_below(uint64_t m) {
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+        static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0)));
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+#pragma unroll
+    for (int d = kWaveSize / 2; d > 0; d >>= 1) {
+        const uint32_t o = __shfl_xor(v, d, kWaveSize);
+        v = o < v ? o : v;
+    }
+    return v;
+}
+// One wave's LDS writes before its own later LDS reads (the hardware keeps a wave's LDS accesses in
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// ---- a unit's words ---------------------------------------------------------------------------
+struct UnitWords {
+    uint32_t w[kUnitLane];  // words 5 * lane + e of the span (0 past the input)
+    uint32_t before;        // the word before the unit; for the first unit one that differs from
+                            // its first word in both tags
+};
+
+// nloc: words of the batch from the unit's first on, at most kUnitSpan
+__device__ __forceinline__ UnitWords load_unit(const uint32_t *__restrict__ words, int64_t base,
+                                               int nloc) {
+    UnitWords u;
+    const uint32_t *p = words + base;
+    const int j0 = kUnitLane * lane_id();
+    if (nloc == kUnitSpan) {
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) u.w[e] = p[j0 + e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) u.w[e] = j0 + e < nloc ? p[j0 + e] : 0u;
+    }
+    u.before = base > 0 ? p[-1] : ~p[0];
+    return u;
+}
+
+// Hits are counted per layer in one 32-bit word, 6 bits a layer.  Running counts over a unit
+// overflow their fields, but the difference of two of them is the sum of 2^(6 l) over the hits in
+// between all the same, and its fields are the hits per layer wherever none reaches 64 (a road
+// longer than 5 * 8 words is illegal whatever they hold).
+__device__ __forceinline__ uint32_t layer_unit(uint32_t w) { return 1u << (6 * w_layer(w)); }
+
+// Where roads and events start, and the running counts before each lane's words.
+struct UnitScan {
+    uint32_t starts;        // bit e: word e starts a road; bit 8 + e: it starts an event
+    uint32_t hit[kUnitLane];  // what word e adds to the hit counts
+    uint32_t hits;          // hit counts before the lane's first word
+    uint32_t rd;            // roads started before it | events started before it << 16
+    uint32_t tot_hits, tot_rd;  // over the span (uniform)
+    uint32_t own;           // roads | events << 16 started among the unit's own words (uniform)
+};
+
+// CHECK: the span may hold words past the input or layer fields out of range, which count nothing.
+template <bool CHECK>
+__device__ __forceinline__ UnitScan scan_unit(const UnitWords &u, int nloc) {
+    UnitScan s;
+    const int j0 = kUnitLane * lane_id();
+    uint32_t prev = dpp<kDppPrev>(u.w[kUnitLane - 1], u.before);
+    uint32_t starts = 0, hits = 0, rd = 0;
+#pragma unroll
+    for (int e = 0; e < kUnitLane; ++e) {
+        const uint32_t x = u.w[e], d = x ^ prev;
+        const bool in = !CHECK || j0 + e < nloc;
+        const bool r = in && d > 0xFFFFu, v = in && d > 0xFFFFFFu;
+        starts |= (r ? 1u << e : 0u) | (v ? 256u << e : 0u);
+        rd += (r ? 1u : 0u) + (v ? 1u << 16 : 0u);
+        s.hit[e] = layer_unit(x);
+        if (CHECK && (!in || w_layer(x) >= SVT_N_LAYERS)) s.hit[e] = 0;
+        hits += s.hit[e];
+        prev = x;
+    }
+    const uint32_t ih = scan64(hits), ird = scan64(rd);
+    s.starts = starts;
+    s.hits = ih - hits;
+    s.rd = ird - rd;
+    s.tot_hits = lane_value(ih, 63);
+    s.tot_rd = lane_value(ird, 63);
+    // the first word past the unit is word `past` of lane `at`
+    constexpr int at = kUnitWords / kUnitLane, past = kUnitWords % kUnitLane;
+    uint32_t own = s.rd;
+#pragma unroll
+    for (int e = 0; e < past; ++e)
+        own += ((starts >> e) & 1u) + (((starts >> (8 + e)) & 1u) << 16);
+    s.own = lane_value(own, at);
+    return s;
+}
+
+// A road's entry: x = hit counts before its first word; y = that word's index in the unit (9
+// bits), bit 9: it starts an event, bits 16..23: its road tag.  The road ends where the next
+// entry starts; entry [roads owned] is the end of the last one: the first road start past the
+// unit, or the end of the staged words.
+__device__ __forceinline__ uint32_t entry_pos(uint2 e) { return e.y & 0x1FFu; }
+
+__device__ __forceinline__ void write_entries(uint2 *S, const UnitWords &u, const UnitScan &s,
+                                              uint32_t nr, int nloc) {
+    uint32_t hits = s.hits, rl = s.rd & 0xFFFFu;
+    const uint32_t j0 = kUnitLane * lane_id();
+#pragma unroll
+    for (int e = 0; e < kUnitLane; ++e) {
+        if ((s.starts >> e) & 1u) {
+            if (rl <= nr)
+                S[rl] = make_uint2(hits, (j0 + e) | (((s.starts >> (8 + e)) & 1u) << 9) |
+                                             (u.w[e] & 0xFF0000u));
+            ++rl;
+        }
+        hits += s.hit[e];
+    }
+    if ((s.tot_rd & 0xFFFFu) == nr && lane_id() == 0)
+        S[nr] = make_uint2(s.tot_hits, static_cast<uint32_t>(nloc));
+}
+
+// Hits of the road between two entries: 4 bits per layer, and whether it is illegal (too many
+// words, or hits on a layer; such a road has no combinations).
+__device__ __forceinline__ uint32_t road_hits(uint2 e0, uint2 e1, int max_hits, bool &over) {
+    const uint32_t d = e1.x - e0.x;
+    const uint32_t c0 = d & 63u, c1 = (d >> 6) & 63u, c2 = (d >> 12) & 63u, c3 = (d >> 18) & 63u,
+                   c4 = (d >> 24) & 63u;
+    const uint32_t m = static_cast<uint32_t>(max_hits);
+    over = static_cast<int>(entry_pos(e1) - entry_pos(e0)) > SVT_N_LAYERS * max_hits || c0 > m ||
+           c1 > m || c2 > m || c3 > m || c4 > m;
+    return (c0 & 0xFu) | ((c1 & 0xFu) << 4) | ((c2 & 0xFu) << 8) | ((c3 & 0xFu) << 12) |
+           ((c4 & 0xFu) << 16);
+}
+__device__ __forceinline__ uint32_t road_combos(uint32_t nh) {
+    return nh_of(nh, 0) * nh_of(nh, 1) * nh_of(nh, 2) * nh_of(nh, 3) * nh_of(nh, 4);
+}
+
+// Units of a range when nu units are dealt to at most `ranges` of them: a multiple of the waves
+// of a workgroup.
+__host__ __device__ inline int64_t units_per_range(int64_t nu, int64_t ranges) {
+    const int64_t per = (nu + ranges - 1) / ranges;
+    return (per + kUnitWaves - 1) / kUnitWaves * kUnitWaves;
+}
+
+}  // namespace svt

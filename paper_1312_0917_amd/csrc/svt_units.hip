@@ -1,0 +1,1104 @@
+// The batched pass in two kernels over wave-sized units of hit words.
+//
+//   k_unit_count   reads every word once and counts, per unit of 256 words, the roads and events
+//                  that start there and the combinations of those roads; the counts become
+//                  running counts inside each of at most 512 ranges of units, and range totals.
+//   k_unit_fit     one workgroup of 16 waves per compute unit; each scans the range totals, and
+//                  then every wave takes units on its own and runs the loop nest of section II-A
+//                  on them: unpack the words, write the road table, build the coordinate tables
+//                  of the unit's roads, fit every combination, write the records, pick each
+//                  road's best track.
+//
+// The end of the first kernel is the only point where waves wait for each other's counts, so no
+// status words have to be cleared before a pass or polled in it, and the words, which are a
+// twentieth of the records written, are read a second time instead of travelling to the second
+// kernel as a road table and grouped coordinates.  Inside the fitting kernel nothing is shared
+// between waves but the constant bank: a wave's chain of loads, LDS writes and scans overlaps
+// the arithmetic and the stores of the 15 others.
+#include "svt_fit.h"
+#include "svt_units.h"
+
+namespace svt {
+namespace {
+
+constexpr int kThreads = kUnitWaves * kWaveSize;
+constexpr int kEntries = kUnitWords + 1;  // roads that start in a unit, and the end of the last
+
+// ---- counting -----------------------------------------------------------------------------------
+struct CArgs {
+    const uint32_t *words;
+    Sizes nw;
+    int64_t *nw_copy;        // the word count for the later kernels
+    uint32_t *ticket;        // units dealt out late, cleared here
+    svt_config cfg;
+    const svt_fconst *bank;
+    UnitSet *sets;           // the packed bank
+    UnitRec *rec;            // per unit
+    RangeTot *tot;           // per range
+    uint32_t *copy;          // words in device memory (nullable: they are there already)
+    unsigned long long *kb;  // kept-list block counts to clear (nullable)
+    int64_t n_kb;
+    SliceAcc *acc;           // to clear
+    int64_t n_acc;
+};
+
+// Row j of a constant set in the fit's layout, for every set of the bank.
+__device__ void pack_bank(const CArgs &a) {
+    for (int s = threadIdx.x; s < a.cfg.n_sets; s += kThreads) {
+        const svt_fconst &F = a.bank[s];
+        int32_t f[30], q[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+#pragma unroll
+            for (int l = 0; l < 5; ++l) f[5 * j + l] = F.f[j][l];
+            q[j] = F.q[j];
+        }
+        UnitSet &o = a.sets[s];
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+            o.row[j] = make_uint4(static_cast<uint32_t>(pack16(f[5 * j], f[5 * j + 1])),
+                                  static_cast<uint32_t>(pack16(f[5 * j + 2], f[5 * j + 3])),
+                                  static_cast<uint32_t>(pack16(f[5 * j + 4], 0)),
+                                  static_cast<uint32_t>(q[j]));
+        o.narrow = narrow_ok(f, q, a.cfg.shift) ? 1u : 0u;
+    }
+}
+
+__device__ __forceinline__ uint64_t with_extra(uint32_t combos, uint32_t extra) {
+    return combos | (static_cast<uint64_t>(extra) << kExtraShift);
+}
+
+__global__ __launch_bounds__(kThreads) void k_unit_count(CArgs a) {
+    __shared__ uint2 s_ent[kUnitWaves][kEntries + 1];
+    __shared__ uint2 s_agg[2][kUnitWaves];
+    __shared__ uint32_t s_err[3][kUnitWaves];
+    const int wave = threadIdx.x / kWaveSize, lane = lane_id();
+    const int64_t n = load_size(a.nw);
+    const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
+    const int ranges = static_cast<int>(gridDim.x) - 1;
+    if (a.kb)
+        for (int64_t i = gtid(); i < a.n_kb; i += gstride()) a.kb[i] = 0;
+    for (int64_t i = gtid(); i < a.n_acc; i += gstride()) a.acc[i] = SliceAcc{0, 0, 0};
+    if (static_cast<int>(blockIdx.x) == ranges) {  // the last workgroup packs the bank
+        if (threadIdx.x == 0) {
+            *a.nw_copy = a.nw.dev ? *a.nw.dev : a.nw.host;
+        }
+        if (threadIdx.x < kDealers) a.ticket[threadIdx.x * kDealerStride] = 0;
+        pack_bank(a);
+        return;
+    }
+    const int64_t per = units_per_range(nu, ranges);
+    const int64_t lo_u = per * blockIdx.x;
+    const int64_t hi_u = lo_u + per < nu ? lo_u + per : nu;
+    if (lo_u >= hi_u) return;
+    uint2 *S = s_ent[wave];
+    const uint32_t slice = static_cast<uint32_t>(slice_combos(nu));
+    uint32_t roads = 0, events = 0;  // of the range, before the units in hand
+    uint64_t combos = 0;
+    uint32_t bad_word = ~0u, over_road = ~0u, set_road = ~0u;
+    int buf = 0;
+    for (int64_t u0 = lo_u; u0 < hi_u; u0 += kUnitWaves, buf ^= 1) {
+        const int64_t u = u0 + wave;
+        uint32_t agg = 0, cs = 0, my_over = ~0u, my_set = ~0u;
+        if (u < hi_u) {
+            const int64_t base = u * kUnitWords;
+            const int nloc = static_cast<int>(n - base < kUnitSpan ? n - base : kUnitSpan);
+            const UnitWords uw = load_unit(a.words, base, nloc);
+            const int j0 = kUnitLane * lane;
+            bool any_bad = false;
+#pragma unroll
+            for (int e = 0; e < kUnitLane; ++e)
+                any_bad |= w_layer(uw.w[e]) >= static_cast<uint32_t>(SVT_N_LAYERS);
+            const bool bad = __ballot(any_bad) != 0;
+            UnitScan sc;
+            if (nloc < kUnitSpan || bad)
+                sc = scan_unit<true>(uw, nloc);
+            else
+                sc = scan_unit<false>(uw, nloc);
+            agg = sc.own;
+            const uint32_t nr = sc.own & 0xFFFFu;
+            lds_order();
+            write_entries(S, uw, sc, nr, nloc);
+            lds_order();
+            if (a.copy) {
+#pragma unroll
+                for (int e = 0; e < kUnitLane; ++e)
+                    if (j0 + e < kUnitWords && j0 + e < nloc) a.copy[base + j0 + e] = uw.w[e];
+            }
+            if (bad) {  // the first of the unit's own words with a bad layer
+                uint32_t b = ~0u;
+#pragma unroll
+                for (int e = kUnitLane - 1; e >= 0; --e)
+                    if (j0 + e < kUnitWords && j0 + e < nloc &&
+                        w_layer(uw.w[e]) >= static_cast<uint32_t>(SVT_N_LAYERS))
+                        b = static_cast<uint32_t>(base + j0 + e);
+                b = wave_min(b);
+                bad_word = b < bad_word ? b : bad_word;
+            }
+            if (a.cfg.n_sets < 256) {
+                uint32_t rl = sc.rd & 0xFFFFu, b = ~0u;
+#pragma unroll
+                for (int e = 0; e < kUnitLane; ++e)
+                    if ((sc.starts >> e) & 1u) {
+                        if (rl < nr && b == ~0u &&
+                            w_rtag(uw.w[e]) >= static_cast<uint32_t>(a.cfg.n_sets))
+                            b = rl;
+                        ++rl;
+                    }
+                my_set = wave_min(b);
+            }
+            uint32_t csum = 0;
+            for (uint32_t r0 = 0; r0 < nr; r0 += kWaveSize) {
+                const uint32_t rl = r0 + lane;
+                bool over = false;
+                uint32_t c = 0;
+                if (rl < nr) {
+                    const uint32_t nh = road_hits(S[rl], S[rl + 1], a.cfg.max_hits, over);
+                    c = over ? 0 : road_combos(nh);
+                }
+                csum += c;
+                const uint64_t m = __ballot(over);
+                if (m && my_over == ~0u) my_over = r0 + __builtin_ctzll(m);
+            }
+            cs = lane_value(scan64(csum), 63);
+        }
+        if (lane == 0) s_agg[buf][wave] = make_uint2(agg, cs);
+        __syncthreads();  // (the other buffer takes the next round's counts)
+        // this wave's running counts: the waves before it, from 16 lanes (at most 16 * 256 roads
+        // or events: 16 bits each)
+        uint2 v = make_uint2(0, 0);
+        if (lane < kUnitWaves) v = s_agg[buf][lane];
+        const uint32_t more = v.y > 0 ? (v.y - 1) / slice : 0;  // slices past the first
+        const uint32_t sre = scan16(v.x), scn = scan16(v.y), sme = scan16(more);
+        const uint32_t ex = lane_value(sre - v.x, wave), ex_c = lane_value(scn - v.y, wave),
+                       ex_m = lane_value(sme - more, wave);
+        const uint32_t ex_r = ex & 0xFFFFu, ex_e = ex >> 16;
+        if (u < hi_u) {
+            if (lane == 0) a.rec[u] = UnitRec{roads + ex_r, events + ex_e, combos + with_extra(ex_c, ex_m)};
+            if (my_over != ~0u && over_road == ~0u) over_road = roads + ex_r + my_over;
+            if (my_set != ~0u && set_road == ~0u) set_road = roads + ex_r + my_set;
+        }
+        const uint32_t all = lane_value(sre, kUnitWaves - 1);
+        roads += all & 0xFFFFu;
+        events += all >> 16;
+        combos += with_extra(lane_value(scn, kUnitWaves - 1), lane_value(sme, kUnitWaves - 1));
+    }
+    if (lane == 0) {
+        s_err[0][wave] = bad_word;
+        s_err[1][wave] = over_road;
+        s_err[2][wave] = set_road;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kUnitWaves; ++w) {
+            bad_word = s_err[0][w] < bad_word ? s_err[0][w] : bad_word;
+            over_road = s_err[1][w] < over_road ? s_err[1][w] : over_road;
+            set_road = s_err[2][w] < set_road ? s_err[2][w] : set_road;
+        }
+        a.tot[blockIdx.x] = RangeTot{roads, events, combos, bad_word, over_road, set_road, 0};
+    }
+}
+
+// ---- fitting ------------------------------------------------------------------------------------
+struct UArgs {
+    const uint32_t *words;   // in device memory
+    const int64_t *d_nw;     // the word count (nw_copy)
+    int64_t word_cap;
+    uint32_t *ticket;
+    int32_t ranges;          // ranges the counting kernel dealt units to
+    svt_config cfg;
+    const UnitSet *sets;
+    const UnitRec *rec;
+    const RangeTot *tot;
+    svt_roads roads;
+    int64_t road_cap;
+    svt_fitrec out;
+    uint8_t *accept;
+    svt_best best;
+    int64_t combo_cap;
+    int64_t *d_n_roads;
+    int64_t *d_n_combos;
+    uint64_t *err;
+    unsigned long long *kb;  // accepted count per kKeptBlock combinations (nullable)
+    int16_t *coords;         // kept-only mode: grouped coordinates for the refit pass
+    int32_t *tile_first_road;
+    int64_t tiles_cap;
+    SliceAcc *acc;
+};
+
+constexpr int kTabCap = 768;   // coordinate-pair table entries of the roads fitted together
+constexpr int kTabPad = 8;     // a dummy slot reads up to 3 entries before or after its table
+
+// Per road with combinations, while its tables are in LDS (two 16-byte reads per lane):
+//   a: division magic of n4 | n4 << 24; the same of n2 * n3; table of the (h0, h1) pairs | of the
+//      (h2, h3) pairs << 16; table of layer 4 | constant set << 16
+//   b: first combination, end (from GB, the unit's first combination rounded down to a multiple
+//      of 4), its first group less its first item, hits per layer
+struct RoadRow {
+    uint4 a, b;
+};
+
+struct alignas(16) WaveLds {
+    union {
+        uint2 ent[kEntries + 1];
+        int32_t xt[kTabPad + kTabCap + kTabPad];
+    };
+    uint32_t chi[4 * kWaveSize];
+    RoadRow road[kUnitFitRoads];
+    unsigned long long key[kUnitFitRoads];
+    uint32_t nacc[kUnitFitRoads];
+    uint32_t mark[kWaveSize];  // window item -> a road starts there (zero between uses)
+    uint8_t fi[kUnitWords];    // road -> its index among the roads with combinations
+};
+
+constexpr uint64_t kComboMask = (1ull << kExtraShift) - 1;
+struct RangeBase {
+    uint32_t roads, events;
+    uint64_t combos;
+    uint32_t extra;   // slices past their unit's first, before the range
+    uint32_t pad;
+};
+
+struct ULds {
+    // The kernel's arguments, for what a unit uses once: held in scalar registers they would all
+    // be live through the fit, which spills them and then vector registers too.
+    UArgs args;
+    UnitSet bank[256];
+    RangeBase base[kMaxRanges];
+    WaveLds w[kUnitWaves];
+    uint32_t magic[72];
+    uint64_t tmp64[kUnitWaves];
+    uint64_t tmp64b[kUnitWaves];
+    uint32_t tmp32[kUnitWaves];
+    uint64_t err[kUnitWaves];
+    uint32_t next;
+};
+static_assert(sizeof(ULds) <= 160 * 1024, "LDS of a compute unit");
+
+// The rows of four consecutive combinations from their coordinate pairs.  J0..5: rows computed
+// (the kept-only mode needs the chi-square rows only).
+template <int MODE, int J0>
+struct Fit4 {
+    int32_t v[6][4];
+    uint64_t chi2[4];  // MODE == kFitNarrow: below 2^32
+};
+
+// One row of four combinations: (seed + three dot products) >> shift.  Written out because the
+// compiler picks the accumulate-in-place form of the dot product, which copies the seed into
+// every accumulator first (18 of about 130 instructions), and in this order because a dot
+// product's result may be read by another kind of instruction only after three others.
+__device__ __forceinline__ void row4(uint32_t f01, uint32_t f23, uint32_t f4, uint32_t seed,
+                                     const int32_t *x01, const int32_t *x23, const int32_t *x4,
+                                     int32_t shift, int32_t *v) {
+    asm("v_dot2_i32_i16 %0, %4, %8, %7\n\t"
+        "v_dot2_i32_i16 %1, %4, %9, %7\n\t"
+        "v_dot2_i32_i16 %2, %4, %10, %7\n\t"
+        "v_dot2_i32_i16 %3, %4, %11, %7\n\t"
+        "v_dot2_i32_i16 %0, %5, %12, %0\n\t"
+        "v_dot2_i32_i16 %1, %5, %13, %1\n\t"
+        "v_dot2_i32_i16 %2, %5, %14, %2\n\t"
+        "v_dot2_i32_i16 %3, %5, %15, %3\n\t"
+        "v_dot2_i32_i16 %0, %6, %16, %0\n\t"
+        "v_dot2_i32_i16 %1, %6, %17, %1\n\t"
+        "v_dot2_i32_i16 %2, %6, %18, %2\n\t"
+        "v_dot2_i32_i16 %3, %6, %19, %3\n\t"
+        "v_ashrrev_i32 %0, %20, %0\n\t"
+        "v_ashrrev_i32 %1, %20, %1\n\t"
+        "v_ashrrev_i32 %2, %20, %2\n\t"
+        "v_ashrrev_i32 %3, %20, %3"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+        : "v"(f01), "v"(f23), "v"(f4), "v"(seed), "v"(x01[0]), "v"(x01[1]), "v"(x01[2]),
+          "v"(x01[3]), "v"(x23[0]), "v"(x23[1]), "v"(x23[2]), "v"(x23[3]), "v"(x4[0]), "v"(x4[1]),
+          "v"(x4[2]), "v"(x4[3]), "s"(shift));
+}
+
+template <int MODE, int J0>
+__device__ __forceinline__ void fit_rows(const UnitSet &c, const int32_t *x01, const int32_t *x23,
+                                         const int32_t *x4, int32_t shift, uint32_t qlmask,
+                                         Fit4<MODE, J0> &f) {
+#pragma unroll
+    for (int j = J0; j < 6; ++j) {
+        const uint4 r = c.row[j];
+        const uint32_t seed = MODE == kFitNarrow ? r.w : r.w & qlmask;
+        row4(r.x, r.y, r.z, seed, x01, x23, x4, shift, f.v[j]);
+        if (MODE != kFitNarrow) {
+            const int32_t qh = static_cast<int32_t>(r.w) >> shift;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f.v[j][e] += qh;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (MODE == kFitNarrow)
+            f.chi2[e] = static_cast<uint32_t>(
+                mad_i24(f.v[5][e], f.v[5][e],
+                        mad_i24(f.v[3][e], f.v[3][e], mad_i24(f.v[4][e], f.v[4][e], 0))));
+        else
+            f.chi2[e] = static_cast<uint64_t>(static_cast<int64_t>(f.v[3][e]) * f.v[3][e] +
+                                              static_cast<int64_t>(f.v[4][e]) * f.v[4][e] +
+                                              static_cast<int64_t>(f.v[5][e]) * f.v[5][e]);
+    }
+}
+
+// One combination of a road from its tables, with 64-bit chi-square.
+__device__ __forceinline__ Fit fit_one(const RoadRow &r, const UnitSet &c, const int32_t *xt,
+                                       uint32_t k, int32_t shift, uint32_t qlmask) {
+    const uint32_t n4 = r.a.x >> 24, n23 = r.a.y >> 24;
+    const uint32_t q4 = div_small(k, r.a.x), h4 = k - q4 * n4;
+    const uint32_t i01 = div_small(q4, r.a.y), i23 = q4 - i01 * n23;
+    const int32_t x01 = xt[(r.a.z & 0xFFFFu) + i01], x23 = xt[(r.a.z >> 16) + i23],
+                  x4 = xt[(r.a.w & 0xFFFFu) + h4];
+    Fit f;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const uint4 w = c.row[j];
+        int32_t acc = dot2(static_cast<int32_t>(w.x), x01, static_cast<int32_t>(w.w & qlmask));
+        acc = dot2(static_cast<int32_t>(w.y), x23, acc);
+        acc = dot2(static_cast<int32_t>(w.z), x4, acc);
+        f.v[j] = (acc >> shift) + (static_cast<int32_t>(w.w) >> shift);
+    }
+    f.chi2 = static_cast<int64_t>(f.v[3]) * f.v[3] + static_cast<int64_t>(f.v[4]) * f.v[4] +
+             static_cast<int64_t>(f.v[5]) * f.v[5];
+    return f;
+}
+
+// Fit the combinations of roads c0 .. c1 - 1 of the unit, whose tables are in LDS, in windows of
+// up to 64 items, from item from_item to before n_items.  An item is the part of a group of 4 consecutive combinations (a 16-byte
+// store) that lies in one road: item j of a road covers its group j, so a lane finds its road
+// among the window's few by comparing with their first items, and fits with one road's
+// constants.  A group cut by a road boundary is two or more neighbouring items; the lane of its
+// first one collects the others' slots from the lanes after it, so that every group of the
+// window is written by one lane with the same store instructions as its neighbours.
+template <int MODE, int REC>
+__device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveLds &W, int c0,
+                                            int c1, uint32_t first_item, uint32_t from_item,
+                                            uint32_t n_items, int64_t GB, int32_t shift, uint32_t qlmask) {
+    constexpr int J0 = REC == kRecNone ? 3 : 0;
+    // Windows end where a 128-byte line of the int32 record arrays does (8 groups): a line
+    // written in two parts reaches memory in parts.  On 4000 events of 2048 roads windows that
+    // end anywhere took 5.09 ms, at 8 groups 4.05 ms, at 32 (a line of accept bytes too) 4.34 ms.
+    // Without records there is less to win and the lanes left idle weigh more.
+    constexpr int kLineGroups = REC == kRecNone ? 4 : 8;
+    const int lane = lane_id();
+    const int32_t *xt = W.xt + kTabPad;
+    const uint32_t cut32 = a.cfg.chi2_cut < 0xFFFFFFFFll ? static_cast<uint32_t>(a.cfg.chi2_cut)
+                                                         : 0xFFFFFFFFu;
+    const int32_t g_abs = static_cast<int32_t>(GB >> 2) & (kLineGroups - 1);
+    int rcur = c0 - 1 + static_cast<int>(__popcll(
+                            __ballot(lane >= c0 && lane < c1 && first_item <= from_item)));
+    for (uint32_t i0 = from_item; i0 < n_items;) {
+        int nit = n_items - i0 < kWaveSize ? static_cast<int>(n_items - i0) : kWaveSize;
+        const uint32_t i = i0 + lane;
+        // the lane's road: the roads that start at or before its item, marked in LDS
+        if (lane > rcur && lane < c1 && first_item - i0 < kWaveSize) W.mark[first_item - i0] = 1;
+        lds_order();
+        const uint32_t mk = W.mark[lane];
+        const uint64_t starts = __ballot(mk != 0);
+        if (mk) W.mark[lane] = 0;
+        const int ri = rcur + bits_below(starts) + static_cast<int>(mk);
+        const uint4 ma = W.road[ri].a, mb = W.road[ri].b;
+        const int32_t rb = static_cast<int32_t>(mb.x), end = static_cast<int32_t>(mb.y);
+        const int32_t g = static_cast<int32_t>(i + mb.z);
+        if (i0 + nit < n_items) {
+            // end the window where a line of the record arrays ends, and at a whole group
+            const int32_t gl = static_cast<int32_t>(lane_value(g, nit - 1)) + g_abs;
+            const int32_t stop = (gl & ~(kLineGroups - 1)) - g_abs;
+            nit = __popcll(__ballot(lane < nit && g < stop));
+        }
+        const bool active = lane < nit;
+        const int32_t rel = 4 * g;
+        const int32_t k0 = active ? rel - rb : 0;
+        uint32_t slots = 0;
+        {
+            const int32_t lo = k0 < 0 ? -k0 : 0;
+            int32_t out = rel + 4 - end;  // slots past the road's end
+            out = out < 0 ? 0 : out > 4 ? 4 : out;
+            slots = active ? (0xFu << lo) & (0xFu >> out) : 0u;
+        }
+        // ---- the four combinations' table entries, stepped with carries (a slot outside the
+        // road reads a neighbouring entry and is not written)
+        int32_t x01[4], x23[4], x4[4];
+        {
+            const uint32_t kc = k0 < 0 ? 0u : static_cast<uint32_t>(k0);
+            const uint32_t n4 = ma.x >> 24, n23 = ma.y >> 24;
+            const uint32_t q4 = div_small(kc, ma.x);
+            int32_t h4 = k0 - static_cast<int32_t>(mul_u24(q4, n4));  // < 0 before the road
+            uint32_t i01 = div_small(q4, ma.y);
+            uint32_t i23 = q4 - mul_u24(i01, n23);
+            const int32_t *t01 = xt + (ma.z & 0xFFFFu), *t23 = xt + (ma.z >> 16),
+                          *t4 = xt + (ma.w & 0xFFFFu);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x01[e] = t01[i01];
+                x23[e] = t23[i23];
+                x4[e] = t4[h4];
+                if (e < 3) {
+                    ++h4;
+                    const bool c4 = h4 == static_cast<int32_t>(n4);
+                    h4 = c4 ? 0 : h4;
+                    i23 += c4 ? 1u : 0u;
+                    const bool c23 = i23 == n23;
+                    i23 = c23 ? 0u : i23;
+                    i01 += c23 ? 1u : 0u;
+                }
+            }
+        }
+        Fit4<MODE, J0> f;
+        fit_rows<MODE, J0>(L.bank[ma.w >> 16], x01, x23, x4, shift, qlmask, f);
+        uint32_t acc = 0;
+        bool near;
+        if (MODE == kFitNarrow) {
+            const uint32_t c0 = static_cast<uint32_t>(f.chi2[0]),
+                           c1_ = static_cast<uint32_t>(f.chi2[1]),
+                           c2 = static_cast<uint32_t>(f.chi2[2]),
+                           c3 = static_cast<uint32_t>(f.chi2[3]);
+            const uint32_t m01 = c0 < c1_ ? c0 : c1_, m23 = c2 < c3 ? c2 : c3;
+            near = (m01 < m23 ? m01 : m23) <= cut32 && a.cfg.chi2_cut >= 0;
+        } else {
+            near = true;
+        }
+        if (__ballot(near)) {  // a chi-square of the window may pass
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc |= static_cast<int64_t>(f.chi2[e]) <= a.cfg.chi2_cut ? 1u << e : 0u;
+            acc &= slots;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((acc >> e) & 1u)
+                    atomicMin(&W.key[ri], static_cast<unsigned long long>(
+                                              best_key(static_cast<int64_t>(f.chi2[e]),
+                                                       static_cast<uint32_t>(k0 + e))));
+            if (acc) {
+                atomicAdd(&W.nacc[ri], static_cast<uint32_t>(__popc(acc)));
+                if (a.kb)
+                    atomicAdd(a.kb + (GB + rel) / kKeptBlock,
+                              static_cast<unsigned long long>(__popc(acc)));
+            }
+        }
+        // ---- groups cut by a road boundary: the first item's lane takes the others' slots
+        const uint32_t gp = dpp<kDppPrev>(static_cast<uint32_t>(g), ~0u);
+        const bool cont = active && lane > 0 && static_cast<uint32_t>(g) == gp;
+        for (uint64_t m = __ballot(cont); m; m &= m >> 1) {
+            // (a lane whose source is switched off keeps its value, so the lanes that give a
+            // slot stay on with those that take it; what the givers are left with is not read)
+            const uint32_t take = dpp<kDppNext>(cont ? slots | (acc << 8) : 0u);
+            const uint32_t on = (take & ~slots) | (cont ? slots : 0u);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((on >> e) & 1u) {
+#pragma unroll
+                    for (int j = J0; j < (REC == kRecRows ? 6 : 3); ++j)
+                        f.v[j][e] = static_cast<int32_t>(
+                            dpp<kDppNext>(static_cast<uint32_t>(f.v[j][e]),
+                                          static_cast<uint32_t>(f.v[j][e])));
+                    if (REC != kRecNone) {
+                        const uint32_t l = static_cast<uint32_t>(f.chi2[e]);
+                        uint32_t h = static_cast<uint32_t>(f.chi2[e] >> 32);
+                        if (MODE != kFitNarrow) h = dpp<kDppNext>(h, h);
+                        f.chi2[e] = (static_cast<uint64_t>(h) << 32) | dpp<kDppNext>(l, l);
+                    }
+                }
+            slots |= take & 0xFFu;
+            acc |= take >> 8;
+        }
+        // ---- records
+        const bool head = active && !cont;
+        const uint32_t at = static_cast<uint32_t>(rel);  // from GB
+        int32_t *p0 = a.out.p0 + GB, *p1 = a.out.p1 + GB, *p2 = a.out.p2 + GB;
+        int64_t *pc = a.out.chi2 + GB;
+        uint8_t *pa = a.accept + GB;
+        if (head && slots == 0xFu) {
+            if (REC != kRecNone) {
+                store_nt(p0 + at, f.v[0]);
+                store_nt(p1 + at, f.v[1]);
+                store_nt(p2 + at, f.v[2]);
+                if (MODE != kFitNarrow) {
+                    store_nt(pc + at, static_cast<int64_t>(f.chi2[0]),
+                             static_cast<int64_t>(f.chi2[1]));
+                    store_nt(pc + at + 2, static_cast<int64_t>(f.chi2[2]),
+                             static_cast<int64_t>(f.chi2[3]));
+                }
+            }
+            if (REC == kRecRows) {
+                if (a.out.c0) store_nt(a.out.c0 + GB + at, f.v[3]);
+                if (a.out.c1) store_nt(a.out.c1 + GB + at, f.v[4]);
+                if (a.out.c2) store_nt(a.out.c2 + GB + at, f.v[5]);
+            }
+            *reinterpret_cast<uint32_t *>(pa + at) = mul_u24(acc, 0x204081u) & 0x01010101u;
+        } else if (head) {  // a group shared with the unit before or after this one
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((slots >> e) & 1u) {
+                    if (REC != kRecNone) {
+                        p0[at + e] = f.v[0][e];
+                        p1[at + e] = f.v[1][e];
+                        p2[at + e] = f.v[2][e];
+                        if (MODE != kFitNarrow) pc[at + e] = static_cast<int64_t>(f.chi2[e]);
+                    }
+                    if (REC == kRecRows) {
+                        if (a.out.c0) a.out.c0[GB + at + e] = f.v[3][e];
+                        if (a.out.c1) a.out.c1[GB + at + e] = f.v[4][e];
+                        if (a.out.c2) a.out.c2[GB + at + e] = f.v[5][e];
+                    }
+                    pa[at + e] = (acc >> e) & 1u;
+                }
+        }
+        if (REC != kRecNone && MODE == kFitNarrow) {
+            // A lane's four chi-squares are 32 bytes: stored from where they are, the wave's two
+            // store instructions would each write every other 16 bytes of the lines they touch.
+            // Through LDS each instruction writes whole lines.
+            const int32_t g0 = static_cast<int32_t>(lane_value(g, 0));
+            if (head)
+                *reinterpret_cast<uint4 *>(W.chi + 4 * (g - g0)) =
+                    make_uint4(static_cast<uint32_t>(f.chi2[0]), static_cast<uint32_t>(f.chi2[1]),
+                               static_cast<uint32_t>(f.chi2[2]), static_cast<uint32_t>(f.chi2[3]));
+            const int32_t first = rb > rel ? rb : rel, past = end < rel + 4 ? end : rel + 4;
+            const int32_t w0 = static_cast<int32_t>(lane_value(first, 0)) - 4 * g0,
+                          w1 = static_cast<int32_t>(lane_value(past, nit - 1)) - 4 * g0;
+            lds_order();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int32_t t = 2 * lane + 2 * kWaveSize * h;
+                const uint2 c = *reinterpret_cast<const uint2 *>(W.chi + t);
+                int64_t *q = pc + 4 * g0;
+                if (t >= w0 && t + 2 <= w1)
+                    store_nt(q + static_cast<uint32_t>(t), static_cast<int64_t>(c.x),
+                             static_cast<int64_t>(c.y));
+                else if (t + 1 >= w0 && t < w1) {
+                    if (t >= w0) q[t] = c.x;
+                    if (t + 1 < w1) q[t + 1] = c.y;
+                }
+            }
+            lds_order();
+        }
+        rcur = static_cast<int>(lane_value(static_cast<uint32_t>(ri), nit - 1));
+        i0 += nit;
+    }
+}
+
+// One unit, or with SLICED (a batch that has units cut into slices) one slice of a unit: its roads
+// with combinations from the c0-th on, as many as the tables have room for.  Returns the first one
+// left over, for a further call, or 0.
+template <int REC, bool SLICED>
+__device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds &W, int64_t u,
+                                        uint32_t slice, uint32_t slice_len, int c0, int64_t n,
+                                        int64_t per) {
+    const int lane = lane_id();
+    const int32_t shift = hot.cfg.shift;
+    const uint32_t qlmask = (1u << shift) - 1u;
+    const int64_t base = u * kUnitWords;
+    const int nloc = static_cast<int>(n - base < kUnitSpan ? n - base : kUnitSpan);
+    const UnitWords uw = load_unit(hot.words, base, nloc);
+    const UnitRec rec = L.args.rec[u];
+    const RangeBase rbase = L.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)];
+    const bool table = c0 == 0 && (!SLICED || slice == 0);  // the unit's road table is to be written
+    const uint32_t R0 = uni(rec.roads) + uni(rbase.roads);
+    const int64_t CB0 = static_cast<int64_t>(uni(rec.combos) & kComboMask) +
+                        static_cast<int64_t>(uni(rbase.combos));
+    const int64_t GB = CB0 & ~static_cast<int64_t>(3);
+    const uint32_t o = static_cast<uint32_t>(CB0 - GB);
+
+    // ---- roads: entries, hits per layer, combinations, road table -------------------------------
+    UnitScan sc;
+    if (nloc < kUnitSpan)
+        sc = scan_unit<true>(uw, nloc);
+    else
+        sc = scan_unit<false>(uw, nloc);
+    const uint32_t nr = sc.own & 0xFFFFu;
+    if (nr == 0) return 0;
+    write_entries(W.ent, uw, sc, nr, nloc);
+    lds_order();
+    uint32_t c_run = 0, ev_run = rec.events + rbase.events - 1;
+    int nf = 0;
+    for (uint32_t r0 = 0; r0 < nr; r0 += kWaveSize) {
+        const uint32_t rl = r0 + lane;
+        const bool mine = rl < nr;
+        uint32_t nh = 0, c = 0, tag = 0, pos = 0;
+        bool ev = false;
+        if (mine) {
+            const uint2 e0 = W.ent[rl];
+            bool over;
+            nh = road_hits(e0, W.ent[rl + 1], hot.cfg.max_hits, over);
+            c = over ? 0 : road_combos(nh);
+            pos = entry_pos(e0);
+            ev = (e0.y >> 9) & 1u;
+            tag = (e0.y >> 16) & 0xFFu;
+        }
+        const uint32_t cs = scan64(c);
+        const uint32_t cb = c_run + cs - c;
+        c_run += lane_value(cs, 63);
+        const uint64_t em = __ballot(ev), fm = __ballot(c > 0);
+        const int fi = nf + bits_below(fm);
+        nf += __popcll(fm);
+        const uint32_t evn = ev_run + bits_below(em) + (ev ? 1u : 0u);
+        ev_run += __popcll(em);
+        if (mine) {
+            W.fi[rl] = static_cast<uint8_t>(c > 0 ? fi : 255);
+            if (c > 0) W.road[fi].b = make_uint4(o + cb, pos, tag, nh | (rl << 24));
+        }
+        if (mine && table) {
+            const UArgs &a = L.args;
+            const int64_t r = R0 + rl;
+            a.roads.event[r] = static_cast<int32_t>(evn);
+            a.roads.set[r] = static_cast<int32_t>(tag);
+            a.roads.hit_begin[r] = base + pos;
+            a.roads.nhits[r] = nh;
+            a.roads.ncombo[r] = static_cast<int32_t>(c);
+            a.roads.combo_begin[r] = CB0 + cb;
+            if (c == 0) {
+                a.best.n_accept[r] = 0;
+                a.best.k[r] = -1;
+                a.best.p0[r] = INT32_MIN;
+                a.best.p1[r] = INT32_MIN;
+                a.best.p2[r] = INT32_MIN;
+                a.best.chi2[r] = INT64_MAX;
+            } else if (REC == kRecNone) {  // the first road of each block of the kept list
+                const int64_t b = CB0 + cb;
+                for (int64_t t = (b + kKeptBlock - 1) / kKeptBlock; t * kKeptBlock < b + c; ++t)
+                    if (t < a.tiles_cap) a.tile_first_road[t] = static_cast<int32_t>(r);
+            }
+        }
+    }
+    if (nf == 0) return 0;
+    lds_order();
+
+    // ---- words: rank among the road's hits on the layer; coordinate and layer (16 bits),
+    // rank << 16, road with combinations << 24 (255: none)
+    uint32_t wd[kUnitLane];
+    {
+        uint32_t hits = sc.hits, rl = (sc.rd & 0xFFFFu) - 1u;
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) {
+            rl += (sc.starts >> e) & 1u;
+            const uint32_t x = uw.w[e];
+            uint32_t v = 255u << 24;
+            if (rl < nr && kUnitLane * lane + e < nloc) {
+                const uint32_t d = hits - W.ent[rl].x;
+                v = (x & 0xFFFFu) | (((d >> (6 * w_layer(x))) & 0xFu) << 16) |
+                    (static_cast<uint32_t>(W.fi[rl]) << 24);
+            }
+            wd[e] = v;
+            hits += sc.hit[e];
+        }
+    }
+    if (REC == kRecNone && table) {  // the kept list's refit reads the grouped coordinates
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) {
+            const uint32_t f = wd[e] >> 24;
+            if (f != 255u) {
+                const uint4 b = W.road[f].b;
+                const uint32_t l = (wd[e] >> 13) & 7u;
+                uint32_t p = b.y + ((wd[e] >> 16) & 0xFu);
+#pragma unroll
+                for (int q = 0; q < SVT_N_LAYERS - 1; ++q)
+                    p += static_cast<uint32_t>(q) < l ? nh_of(b.w, q) : 0u;
+                L.args.coords[base + p] = static_cast<int16_t>(w_coord(wd[e]));
+            }
+        }
+    }
+
+    // ---- one road with combinations per lane: roads c0 .. c1 - 1 are fitted now -----------------
+    const bool road = lane < nf && lane >= c0;
+    W.mark[lane] = 0;
+    W.key[lane] = ~0ull;
+    W.nacc[lane] = 0;
+    const uint4 pre = road ? W.road[lane].b : make_uint4(0, 0, 0, 0);
+    lds_order();
+    const uint32_t nh = pre.w, n4 = nh_of(nh, 4), n01 = nh_of(nh, 0) * nh_of(nh, 1),
+                   n23 = nh_of(nh, 2) * nh_of(nh, 3);
+    const uint32_t ntab = n01 + n23 + n4, rb = pre.x, end = rb + n01 * n23 * n4;
+    const uint32_t n_it = road ? ((end - 1) >> 2) - (rb >> 2) + 1 : 0;
+    const uint32_t tend = scan64(ntab);
+    const bool take = road && tend <= kTabCap;
+    const int c1 = c0 + __popcll(__ballot(take));
+    const uint32_t it_end = scan64(take ? n_it : 0);
+    const uint32_t item = it_end - n_it;
+    uint32_t n_items = lane_value(it_end, 63), from_item = 0;
+    const bool narrow = __ballot(take && !L.bank[pre.z].narrow) == 0;
+    // groups ga .. gb - 1 of the unit are this slice's (the last slice takes what is left over)
+    const uint32_t slices = SLICED && c_run > slice_len ? (c_run - 1) / slice_len + 1 : 1;
+    const uint32_t slice_groups = slice_len / 4;
+    const uint32_t ga = slice * slice_groups,
+                   gb = slice + 1 < slices ? ga + slice_groups : ~0u >> 1;
+    if (SLICED && slices > 1) {
+        // the items are in the order of their groups: count those before ga and before gb
+        const uint32_t g = rb >> 2;
+        uint32_t before = ga > g ? ga - g : 0, upto = gb > g ? gb - g : 0;
+        before = take ? (before < n_it ? before : n_it) : 0;
+        upto = take ? (upto < n_it ? upto : n_it) : 0;
+        from_item = lane_value(scan64(before), 63);
+        n_items = lane_value(scan64(upto), 63);
+        if (from_item == n_items) return c1 < nf ? c1 : 0;
+    }
+    if (take) {
+        RoadRow row;
+        const uint32_t t = tend - ntab;
+        row.a = make_uint4(L.magic[n4] | (n4 << 24), L.magic[n23] | (n23 << 24),
+                           t | ((t + n01) << 16), (t + n01 + n23) | (pre.z << 16));
+        row.b = make_uint4(rb, end, (rb >> 2) - item, nh);
+        W.road[lane] = row;
+    }
+    lds_order();
+    // Tables of coordinate pairs, (x0 | x1 << 16) at h0 * n1 + h1 and the same for layers 2 and 3,
+    // and of layer 4: each word writes its half of the entries it belongs to.
+    {
+        int16_t *xh = reinterpret_cast<int16_t *>(W.xt + kTabPad);
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) {
+            const uint32_t f = wd[e] >> 24;
+            if (f >= static_cast<uint32_t>(c0) && f < static_cast<uint32_t>(c1)) {
+                const uint4 ra = W.road[f].a;
+                const uint32_t l = (wd[e] >> 13) & 7u, rank = (wd[e] >> 16) & 0xFu;
+                const uint32_t h = W.road[f].b.w >> (l & 2u ? 8 : 0);  // its pair's hits
+                const uint32_t na = h & 0xFu, nb = (h >> 4) & 0xFu;
+                const uint32_t tb = l & 2u ? ra.z >> 16 : ra.z & 0xFFFFu;
+                const bool odd = l & 1u;
+                uint32_t cnt = odd ? na : nb;
+                const uint32_t step = odd ? 2 * nb : 2u;
+                uint32_t p = 2 * tb + (odd ? 2 * rank + 1 : 2 * rank * nb);
+                if (l == 4) {
+                    cnt = 1;
+                    p = 2 * ((ra.w & 0xFFFFu) + rank);
+                }
+                const int16_t x = static_cast<int16_t>(w_coord(wd[e]));
+                do {
+                    xh[p] = x;
+                    p += step;
+                } while (--cnt);
+            }
+        }
+    }
+    lds_order();
+    if (narrow)
+        fit_windows<kFitNarrow, REC>(hot, L, W, c0, c1, item, from_item, n_items, GB, shift,
+                                     qlmask);
+    else
+        fit_windows<kFitSplit, REC>(hot, L, W, c0, c1, item, from_item, n_items, GB, shift,
+                                    qlmask);
+    lds_order();
+
+    // ---- best tracks ----------------------------------------------------------------------------
+    if (lane >= c0 && lane < c1) {
+        const RoadRow row = W.road[lane];
+        unsigned long long key = W.key[lane];
+        uint32_t nacc = W.nacc[lane];
+        bool whole = true;
+        if (SLICED && slices > 1) {
+            // a road with groups in other slices too: every one of them adds what it found, and
+            // the last to do so has the whole of it
+            const uint32_t g_first = row.b.x >> 2, g_last = (row.b.y - 1) >> 2;
+            const bool touched = g_last >= ga && g_first < gb;
+            const bool cut = touched && (g_first < ga || g_last >= gb);
+            whole = touched && !cut;
+            if (cut) {
+                const uint32_t s0 = g_first / slice_groups;
+                uint32_t s1 = g_last / slice_groups;
+                s1 = s1 < slices ? s1 : slices - 1;
+                // the batch's number of the slice after the road's first one
+                const UnitRec rc = L.args.rec[u];
+                const uint32_t x = static_cast<uint32_t>(rc.combos >> kExtraShift) +
+                                   L.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)]
+                                       .extra + s0;
+                SliceAcc *acc = L.args.acc + x;
+                atomicMax(&acc->key, ~key);
+                atomicAdd(&acc->nacc, nacc);
+                __threadfence();
+                whole = atomicAdd(&acc->arrived, 1u) == s1 - s0;
+                __threadfence();
+                if (whole) {
+                    key = ~__hip_atomic_load(&acc->key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    nacc = __hip_atomic_load(&acc->nacc, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        }
+        if (whole) {
+            const UArgs &a = L.args;
+            const int64_t r = R0 + (row.b.w >> 24);
+            const UnitSet &c = L.bank[row.a.w >> 16];
+            const int32_t *xt = W.xt + kTabPad;
+            int32_t k = -1, v0 = INT32_MIN, v1 = INT32_MIN, v2 = INT32_MIN;
+            int64_t chi2 = INT64_MAX;
+            if (key != ~0ull && (key >> kKeyKBits) == kKeyChiMax) {
+                // saturated key (chi2 >= 2^49 - 1, extreme constants only): exact rescan
+                for (uint32_t q = 0; q < row.b.y - row.b.x; ++q) {
+                    const int64_t c2 = fit_one(row, c, xt, q, shift, qlmask).chi2;
+                    if (c2 <= a.cfg.chi2_cut && c2 < chi2) {
+                        chi2 = c2;
+                        k = static_cast<int32_t>(q);
+                    }
+                }
+            } else if (key != ~0ull) {
+                k = static_cast<int32_t>(key & ((1u << kKeyKBits) - 1));
+                chi2 = static_cast<int64_t>(key >> kKeyKBits);
+            }
+            if (k >= 0) {
+                const Fit f = fit_one(row, c, xt, static_cast<uint32_t>(k), shift, qlmask);
+                v0 = f.v[0];
+                v1 = f.v[1];
+                v2 = f.v[2];
+            }
+            a.best.n_accept[r] = static_cast<int32_t>(nacc);
+            a.best.k[r] = k;
+            a.best.p0[r] = v0;
+            a.best.p1[r] = v1;
+            a.best.p2[r] = v2;
+            a.best.chi2[r] = chi2;
+        }
+    }
+    lds_order();
+    return c1 < nf ? c1 : 0;
+}
+
+// The unit and slice of the batch's extra slice number e (slices past their unit's first, counted
+// in the units' order).  One wave; 64 units or ranges are compared at a time.
+__device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t nu, int64_t per,
+                              int n_ranges, uint32_t &slice) {
+    const int lane = lane_id();
+    int r = -1;  // last range whose extras start at or before e
+    for (int r0 = 0; r0 < n_ranges; r0 += kWaveSize)
+        r += __popcll(__ballot(r0 + lane < n_ranges && L.base[r0 + lane].extra <= e));
+    e -= uni(L.base[r].extra);
+    const int64_t lo = r * per, hi = lo + per < nu ? lo + per : nu;
+    int64_t u = lo - 1;  // last unit whose extras start at or before e
+    uint32_t first = 0;
+    for (int64_t u0 = lo; u0 < hi; u0 += kWaveSize) {
+        uint32_t x = ~0u;
+        if (u0 + lane < hi) x = static_cast<uint32_t>(a.rec[u0 + lane].combos >> kExtraShift);
+        const uint64_t m = __ballot(x <= e);  // a prefix of the lanes
+        if (m == 0) break;
+        u += __popcll(m);
+        first = lane_value(x, 63 - __builtin_clzll(m));
+    }
+    slice = e - first + 1;
+    return u;
+}
+
+// The wave's units.  Seven eighths of them are dealt to the workgroups in contiguous ranges, so that
+// the record lines two neighbouring units share are written from one compute unit; the rest is
+// divided among the dealers and goes by ticket to the waves that finish first (one counter for all
+// of them would hand out a unit every 12 ns).  Slices past their unit's first come before
+// everything else, dealt out to the workgroups in turn.
+template <int REC, bool SLICED>
+__device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, int64_t nu,
+                                          int64_t per, int n_ranges, uint32_t extra) {
+    const int wave = threadIdx.x / kWaveSize, lane = lane_id();
+    const int64_t fixed = nu <= static_cast<int64_t>(gridDim.x) * kUnitWaves ? nu : nu - nu / 8;
+    const int64_t lo = fixed * blockIdx.x / gridDim.x, hi = fixed * (blockIdx.x + 1) / gridDim.x;
+    const int dealer = static_cast<int>(blockIdx.x) % kDealers;
+    const int64_t pool = nu - fixed, p_lo = fixed + pool * dealer / kDealers,
+                  p_hi = fixed + pool * (dealer + 1) / kDealers;
+    const int64_t batch = 1 + pool / (kDealers * 512);
+    const uint32_t slice_len = static_cast<uint32_t>(slice_combos(nu));
+    const uint32_t my_extra =
+        SLICED && extra > blockIdx.x ? (extra - blockIdx.x - 1) / gridDim.x + 1 : 0;
+    bool late = false;
+    int64_t u = 0, past = 0;
+    while (true) {
+        uint32_t slice = 0;
+        if (u >= past) {
+            uint32_t k = 0;
+            if (!late) {
+                if (lane == 0) k = atomicAdd(&L.next, 1u);
+                k = uni(k);
+                if (SLICED && k < my_extra) {
+                    u = find_extra(a, L, blockIdx.x + k * gridDim.x, nu, per, n_ranges, slice);
+                } else {
+                    u = lo + (k - my_extra);
+                    late = u >= hi;
+                }
+                past = u + 1;
+            }
+            if (late) {
+                if (p_lo >= p_hi) break;
+                if (lane == 0) k = atomicAdd(a.ticket + dealer * kDealerStride, 1u);
+                u = p_lo + uni(k) * batch;
+                past = u + batch < p_hi ? u + batch : p_hi;
+                if (u >= p_hi) break;
+            }
+        }
+        int c = 0;
+        do {
+            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, slice_len, c, n, per);
+        } while (c != 0);
+        ++u;
+    }
+}
+
+template <int REC>
+__global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
+    __shared__ ULds L;
+    const int tid = threadIdx.x, wave = tid / kWaveSize, lane = lane_id();
+    const int64_t nw = *a.d_nw;
+    const int64_t n = nw < 0 ? 0 : nw > a.word_cap ? a.word_cap : nw;
+    const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
+    const int64_t per = units_per_range(nu, a.ranges);
+    const int n_ranges = nu > 0 ? static_cast<int>((nu + per - 1) / per) : 0;
+
+    // ---- running counts at the start of every range, totals, errors ----------------------------
+    uint64_t re = 0, cc = 0;
+    uint32_t ee = 0;
+    RangeTot t{};
+    if (tid < n_ranges) {
+        t = a.tot[tid];
+        re = static_cast<uint64_t>(t.roads) | (static_cast<uint64_t>(t.events) << 32);
+        cc = t.combos & kComboMask;
+        ee = static_cast<uint32_t>(t.combos >> kExtraShift);
+    }
+    {
+        const uint4 *src = reinterpret_cast<const uint4 *>(a.sets);
+        uint4 *dst = reinterpret_cast<uint4 *>(L.bank);
+        const int n16 = a.cfg.n_sets * static_cast<int>(sizeof(UnitSet) / 16);
+        for (int i = tid; i < n16; i += kThreads) dst[i] = src[i];
+    }
+    if (tid < 72) L.magic[tid] = magic_of(tid > 0 ? static_cast<uint32_t>(tid) : 1u);
+    if (tid == 0) L.next = 0;
+    {
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(
+            (const void *)__builtin_amdgcn_kernarg_segment_ptr());
+        if (tid < static_cast<int>(sizeof(UArgs) / 4))
+            reinterpret_cast<uint32_t *>(&L.args)[tid] = src[tid];
+    }
+    const uint64_t ire = wave_incl_scan(re), icc = wave_incl_scan(cc);
+    const uint32_t iee = scan64(ee);
+    if (lane == kWaveSize - 1) {
+        L.tmp32[wave] = iee;
+        L.tmp64[wave] = ire;
+        L.tmp64b[wave] = icc;
+    }
+    __syncthreads();
+    uint64_t bre = 0, bcc = 0, tre = 0, tcc = 0;
+    uint32_t bee = 0, tee = 0;
+    for (int w = 0; w < kUnitWaves; ++w) {
+        if (w == wave) {
+            bee = tee;
+            bre = tre;
+            bcc = tcc;
+        }
+        tre += L.tmp64[w];
+        tcc += L.tmp64b[w];
+        tee += L.tmp32[w];
+    }
+    uint64_t err = SVT_NO_ERROR;
+    if (tid < n_ranges) {
+        const uint64_t ex = bre + ire - re;
+        L.base[tid] = RangeBase{static_cast<uint32_t>(ex), static_cast<uint32_t>(ex >> 32),
+                                bcc + icc - cc, bee + iee - ee, 0};
+        auto note = [&](uint32_t cls, uint32_t idx, uint32_t add) {
+            if (idx == ~0u) return;
+            const uint64_t v = (static_cast<uint64_t>(cls) << 56) |
+                               (static_cast<uint64_t>(idx) + add);
+            err = v < err ? v : err;
+        };
+        note(SVT_ERRCLASS_LAYER, t.bad_word, 0);
+        note(SVT_ERRCLASS_HITS, t.over_road, static_cast<uint32_t>(ex));
+        note(SVT_ERRCLASS_SET, t.set_road, static_cast<uint32_t>(ex));
+    }
+#pragma unroll
+    for (int d = kWaveSize / 2; d > 0; d >>= 1) {
+        const uint64_t ov = __shfl_xor(err, d, kWaveSize);
+        err = ov < err ? ov : err;
+    }
+    if (lane == 0) L.err[wave] = err;
+    __syncthreads();
+    const int64_t n_roads = static_cast<int64_t>(tre & 0xFFFFFFFFull);
+    const int64_t n_combos = static_cast<int64_t>(tcc);
+    auto cap_err = [](uint64_t i) {
+        return (static_cast<uint64_t>(SVT_ERRCLASS_CAPACITY) << 56) | i;
+    };
+    err = nw > a.word_cap ? cap_err(3) : SVT_NO_ERROR;
+    if (n_combos > a.combo_cap) err = cap_err(1);
+    if (n_roads > a.road_cap) err = cap_err(0);
+    for (int w = 0; w < kUnitWaves; ++w) err = L.err[w] < err ? L.err[w] : err;
+    if (blockIdx.x == 0 && tid == 0) {
+        *a.err = err;
+        *a.d_n_roads = n_roads;
+        *a.d_n_combos = n_combos;
+    }
+    if (err != SVT_NO_ERROR) return;
+
+    const uint32_t extra = uni(tee);
+    if (extra == 0)
+        run_units<REC, false>(a, L, n, nu, per, n_ranges, extra);
+    else
+        run_units<REC, true>(a, L, n, nu, per, n_ranges, extra);
+}
+
+}  // namespace
+
+int64_t unit_count(int64_t words) { return (words + kUnitWords - 1) / kUnitWords; }
+int64_t unit_rec_bytes(int64_t words) {
+    return static_cast<int64_t>(sizeof(UnitRec)) * unit_count(words);
+}
+int64_t unit_range_bytes() { return static_cast<int64_t>(sizeof(RangeTot)) * kMaxRanges; }
+int64_t unit_slices(int64_t combos) {
+    const int64_t small = combos / kSliceCombosSmall, most = int64_t{kSmallUnits} * 2048;
+    return combos / kSliceCombos + (small < most ? small : most) + 1;
+}
+int64_t unit_acc_bytes(int64_t combos) {
+    return static_cast<int64_t>(sizeof(SliceAcc)) * unit_slices(combos);
+}
+int64_t unit_ticket_bytes() { return 4ll * kDealers * kDealerStride; }
+int64_t unit_bank_bytes() { return static_cast<int64_t>(sizeof(UnitSet)) * 256; }
+
+hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+    const int64_t units = unit_count(p.word_cap > 0 ? p.word_cap : 1);
+    int64_t ranges = (units + kUnitWaves - 1) / kUnitWaves;
+    if (ranges > kMaxRanges) ranges = kMaxRanges;
+    CArgs c{};
+    c.words = p.words;
+    c.nw = Sizes{0, p.d_n_words, p.word_cap};
+    c.nw_copy = p.nw_copy;
+    c.ticket = p.ticket;
+    c.cfg = p.cfg;
+    c.bank = p.bank;
+    c.sets = static_cast<UnitSet *>(p.sets);
+    c.rec = static_cast<UnitRec *>(p.rec);
+    c.tot = static_cast<RangeTot *>(p.tot);
+    c.copy = p.copy;
+    c.kb = reinterpret_cast<unsigned long long *>(p.kb_counts);
+    c.n_kb = p.kb_counts ? p.n_kb : 0;
+    c.acc = static_cast<SliceAcc *>(p.acc);
+    c.n_acc = unit_slices(p.combo_cap);
+    hipLaunchKernelGGL(k_unit_count, dim3(static_cast<unsigned>(ranges + 1)), dim3(kThreads), 0, s,
+                       c);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    UArgs a{};
+    a.words = p.copy ? p.copy : p.words;
+    a.d_nw = p.nw_copy;
+    a.word_cap = p.word_cap;
+    a.ticket = p.ticket;
+    a.ranges = static_cast<int32_t>(ranges);
+    a.cfg = p.cfg;
+    a.sets = c.sets;
+    a.rec = c.rec;
+    a.tot = c.tot;
+    a.roads = p.roads;
+    a.road_cap = p.road_cap;
+    a.out = p.out;
+    a.accept = p.accept;
+    a.best = p.best;
+    a.combo_cap = p.combo_cap;
+    a.d_n_roads = p.d_n_roads;
+    a.d_n_combos = p.d_n_combos;
+    a.err = p.err;
+    a.kb = c.kb;
+    a.acc = c.acc;
+    a.coords = p.kept_only ? p.coords : nullptr;
+    a.tile_first_road = p.kept_only ? p.tile_first_road : nullptr;
+    a.tiles_cap = p.tiles_cap;
+    const int grid = static_cast<int>(units < p.num_cus ? units : p.num_cus);
+    if (start && (e = hipEventRecord(start, s)) != hipSuccess) return e;
+    if (p.kept_only)
+        hipLaunchKernelGGL((k_unit_fit<kRecNone>), dim3(grid), dim3(kThreads), 0, s, a);
+    else if (p.out.c0 || p.out.c1 || p.out.c2)
+        hipLaunchKernelGGL((k_unit_fit<kRecRows>), dim3(grid), dim3(kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_unit_fit<kRecFit>), dim3(grid), dim3(kThreads), 0, s, a);
+    e = hipGetLastError();
+    if (e == hipSuccess && stop) e = hipEventRecord(stop, s);
+    return e;
+}
+
+}  // namespace svt
