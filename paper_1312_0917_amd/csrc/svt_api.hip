@@ -46,15 +46,13 @@ struct Carver {
 };
 
 struct UnpackWs {
-    int64_t *scalars;  // [0] event total
-    int64_t *wb;       // [2][nb]
-    int64_t nb;
+    void *rec;  // running counts per unit
+    void *tot;  // totals per range of units
 };
 UnpackWs carve_unpack(Carver &c, int64_t n_words) {
     UnpackWs w;
-    w.nb = ceil_div(n_words > 0 ? n_words : 1, kSegBlockWords);
-    w.scalars = c.take<int64_t>(4);
-    w.wb = c.take<int64_t>(2 * w.nb);
+    w.rec = c.take<char>(unit_rec_bytes(n_words > 0 ? n_words : 1));
+    w.tot = c.take<char>(unit_range_bytes());
     return w;
 }
 
@@ -316,14 +314,10 @@ svt_status svt_unpack(const uint32_t *words, int64_t n_words, const svt_config *
         return SVT_ERR_ARG;
     Carver c{static_cast<char *>(d_work)};
     UnpackWs w = carve_unpack(c, n_words);
-    const Sizes nw{n_words, nullptr, n_words};
-    SVT_TRY(launch_init_err(d_err, stream));
-    SVT_TRY(launch_seg_count(words, nw, w.nb, cfg->n_layers, w.wb, d_err, stream));
-    SVT_TRY(launch_scan(w.wb, w.nb, 2, nw, kSegBlockWords, d_n_roads, w.scalars, road_cap, 0,
-                        d_err, false, stream));
-    SVT_TRY(launch_seg_emit(words, nw, w.nb, w.wb, *roads, road_cap, d_err, stream));
-    SVT_TRY(launch_road_fill(words, nw, d_n_roads, road_cap, *roads, *cfg, hit_coord, nullptr,
-                             d_err, stream));
+    const int cus = num_cus();
+    if (cus <= 0) return SVT_ERR_HIP;
+    SVT_TRY(launch_unpack(words, n_words, *cfg, *roads, road_cap, hit_coord, d_n_roads, d_err,
+                          w.rec, w.tot, cus, stream));
     return SVT_OK;
 }
 
@@ -344,7 +338,8 @@ svt_status svt_combine(const svt_roads *roads, int64_t n_roads, const svt_config
     SVT_TRY(launch_combo_count(*roads, nr, rbn, rb, d_err, stream));
     SVT_TRY(launch_scan(rb, 0, 1, nr, kRoadBlock, d_n_combos, nullptr, listing ? combo_cap : -1,
                         1, d_err, true, stream));
-    SVT_TRY(launch_combo_begin(*roads, nr, rbn, rb, 0, nullptr, 0, nullptr, d_err, stream));
+    SVT_TRY(launch_combo_begin(*roads, nr, rbn, rb, listing ? combo_road : nullptr, combo_cap,
+                               d_err, stream));
     if (listing)
         SVT_TRY(launch_materialize(*roads, n_roads, d_n_combos, combo_cap, combo_road, combo_hits,
                                    d_err, stream));
@@ -361,8 +356,10 @@ svt_status svt_fit(const svt_fconst *bank, const svt_config *cfg, const svt_road
                          !out->p1 || !out->p2 || !out->chi2 || !roads->nhits ||
                          !roads->hit_begin || !roads->set))
         return SVT_ERR_ARG;
+    const int cus = num_cus();
+    if (cus <= 0) return SVT_ERR_HIP;
     SVT_TRY(launch_fit_plain(bank, *cfg, *roads, n_roads, hit_coord, n_hits, combo_road,
-                             combo_hits, n_combos, *out, d_err, stream));
+                             combo_hits, n_combos, *out, d_err, cus, stream));
     return SVT_OK;
 }
 

@@ -9,9 +9,7 @@
 namespace svt {
 
 constexpr int kWaveSize = 64;
-constexpr int kSegThreads = 256;          // threads of the word-segmentation kernels
-constexpr int kSegWordsPerThread = 16;
-constexpr int kSegBlockWords = kSegThreads * kSegWordsPerThread;  // 4096 words per block
+constexpr int kSegThreads = 256;          // threads of the selection kernels
 constexpr int kPrepassBlockWords = 2048;  // words per block of the batched single-pass pre-pass
 constexpr int kLookGroup = 64;            // pre-pass blocks per group of its two-level look-back
 // look-back status words of the pre-pass: two per block, then two per group of kLookGroup blocks
@@ -139,9 +137,6 @@ __device__ inline int64_t load_size(const Sizes &s) {
     return v < 0 ? 0 : v;
 }
 
-hipError_t launch_init_err(uint64_t *d_err, hipStream_t s);
-hipError_t launch_seg_count(const uint32_t *words, Sizes n_words, int64_t grid_blocks,
-                            int32_t n_layers, int64_t *wb_counts, uint64_t *err, hipStream_t s);
 // In-place exclusive scan of ncols (1 or 2) int64 columns of ceil(n / items_div) entries,
 // one workgroup per column; column c's total goes to tot[c] (may be null).  When the total
 // of column 0 exceeds cap0 (>= 0), a capacity error with index cap_index is reported.  With
@@ -149,20 +144,13 @@ hipError_t launch_seg_count(const uint32_t *words, Sizes n_words, int64_t grid_b
 hipError_t launch_scan(int64_t *data, int64_t col_stride, int ncols, Sizes n,
                        int64_t items_div, int64_t *tot0, int64_t *tot1, int64_t cap0,
                        uint32_t cap_index, uint64_t *err, bool skip_if_error, hipStream_t s);
-hipError_t launch_seg_emit(const uint32_t *words, Sizes n_words, int64_t grid_blocks,
-                           const int64_t *wb_prefix, const svt_roads &roads, int64_t road_cap,
-                           uint64_t *err, hipStream_t s);
-hipError_t launch_road_fill(const uint32_t *words, Sizes n_words, const int64_t *d_n_roads,
-                            int64_t road_cap, const svt_roads &roads, const svt_config &cfg,
-                            int16_t *hit_coord, int64_t *rb_sums, uint64_t *err,
-                            hipStream_t s);
 hipError_t launch_combo_count(const svt_roads &roads, Sizes n_roads, int64_t grid_blocks,
                               int64_t *rb_sums, uint64_t *err, hipStream_t s);
-// best_init (nullable): every road's best key := none, n_accept := 0
+// combo_road (nullable): receives the road of every listing tile's first combination, which
+// launch_materialize starts from
 hipError_t launch_combo_begin(const svt_roads &roads, Sizes n_roads, int64_t grid_blocks,
-                              const int64_t *rb_prefix, int64_t tile_combos,
-                              int32_t *tile_first_road, int64_t tiles_cap,
-                              const svt_best *best_init, uint64_t *err, hipStream_t s);
+                              const int64_t *rb_prefix, int32_t *combo_road, int64_t combo_cap,
+                              uint64_t *err, hipStream_t s);
 hipError_t launch_materialize(const svt_roads &roads, int64_t n_roads, const int64_t *d_n_combos,
                               int64_t combo_cap, int32_t *combo_road, uint32_t *combo_hits,
                               uint64_t *err, hipStream_t s);
@@ -170,7 +158,7 @@ hipError_t launch_fit_plain(const svt_fconst *bank, const svt_config &cfg,
                             const svt_roads &roads, int64_t n_roads, const int16_t *hit_coord,
                             int64_t n_hits, const int32_t *combo_road,
                             const uint32_t *combo_hits, int64_t n_combos, const svt_fitrec &out,
-                            uint64_t *err, hipStream_t s);
+                            uint64_t *err, int num_cus, hipStream_t s);
 hipError_t launch_select(const svt_config &cfg, const svt_roads &roads, int64_t n_roads,
                          const int32_t *combo_road, const svt_fitrec &rec, int64_t n_combos,
                          uint8_t *accept, const svt_best &best, int64_t *kb_counts,
@@ -330,6 +318,12 @@ struct UnitsLaunch {
     uint32_t *copy;            // and the words, when the caller's are in host memory (else null)
     int num_cus;
 };
+// The unpack stage: the same counting kernel, and one that writes the road table (event, set,
+// hit_begin, nhits) and the grouped coordinates.  rec and tot as in UnitsLaunch.
+hipError_t launch_unpack(const uint32_t *words, int64_t n_words, const svt_config &cfg,
+                         const svt_roads &roads, int64_t road_cap, int16_t *hit_coord,
+                         int64_t *d_n_roads, uint64_t *err, void *rec, void *tot, int num_cus,
+                         hipStream_t s);
 int64_t unit_rec_bytes(int64_t words);
 int64_t unit_range_bytes();
 int64_t unit_acc_bytes(int64_t combos);

@@ -1,69 +1,14 @@
-// Stage kernels of libsvt: unpack (segment, emit, road fill), combine (count, scan, list),
-// plain fit (one lane per listed combination), select (cut, best track, kept list).
+// Stage kernels of libsvt: combine (count, scan, list), plain fit (one lane per listed
+// combination), select (cut, best track, kept list); the batched pass shares the kept-list and
+// best-track kernels.
 //
 // Section II-A of the paper splits the serial code into unpack / combine / fit; these are the
-// one-launch-per-stage GPU forms of those functions, kept simple: they are the baseline the
-// fused persistent pass is compared with and share none of its code beyond the field
-// decoders and scans in svt_common.h.
-#include "svt_common.h"
+// GPU forms of the last two, a few launches each (the unpack stage is k_unit_count and
+// k_unit_table in svt_units.hip).
+#include "svt_fit.h"
 
 namespace svt {
 namespace {
-
-__global__ void k_init_err(uint64_t *err) { *err = SVT_NO_ERROR; }
-
-// ---- unpack 1: per 4096-word block, count road starts and event starts ------------------
-// A new event starts where the event tag changes, a new road where either tag changes.
-__global__ __launch_bounds__(kSegThreads) void k_seg_count(const uint32_t *__restrict__ words,
-                                                           Sizes n_words_s, int32_t n_layers,
-                                                           int64_t *wb_counts, int64_t nb_stride,
-                                                           uint64_t *err) {
-    __shared__ int64_t tmp[kSegThreads / kWaveSize + 1];
-    const int64_t n = load_size(n_words_s);
-    if (blockIdx.x == 0 && threadIdx.x == 0 && n_words_s.dev && *n_words_s.dev > n_words_s.cap)
-        report(err, SVT_ERRCLASS_CAPACITY, 3);
-    const int64_t nb = (n + kSegBlockWords - 1) / kSegBlockWords;
-    const bool aligned = (reinterpret_cast<uintptr_t>(words) & 15) == 0;
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int64_t base =
-            b * kSegBlockWords + static_cast<int64_t>(threadIdx.x) * kSegWordsPerThread;
-        uint32_t w[kSegWordsPerThread];
-        if (aligned && base + kSegWordsPerThread <= n) {
-            const uint4 *p = reinterpret_cast<const uint4 *>(words + base);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                uint4 t = p[v];
-                w[4 * v] = t.x; w[4 * v + 1] = t.y; w[4 * v + 2] = t.z; w[4 * v + 3] = t.w;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < kSegWordsPerThread; ++e)
-                w[e] = (base + e < n) ? words[base + e] : 0u;
-        }
-        uint32_t prev = (base > 0 && base <= n) ? words[base - 1] : 0u;
-        int64_t nr = 0, ne = 0;
-        int64_t bad = -1;
-#pragma unroll
-        for (int e = 0; e < kSegWordsPerThread; ++e) {
-            const int64_t i = base + e;
-            if (i < n) {
-                const uint32_t x = w[e];
-                const bool first = (i == 0);
-                nr += (first || w_tags(x) != w_tags(prev)) ? 1 : 0;
-                ne += (first || w_etag(x) != w_etag(prev)) ? 1 : 0;
-                if (bad < 0 && static_cast<int32_t>(w_layer(x)) >= n_layers) bad = i;
-                prev = x;
-            }
-        }
-        if (bad >= 0) report(err, SVT_ERRCLASS_LAYER, static_cast<uint64_t>(bad));
-        const int64_t br = block_sum<int64_t, kSegThreads>(nr, tmp);
-        const int64_t be = block_sum<int64_t, kSegThreads>(ne, tmp);
-        if (threadIdx.x == 0) {
-            wb_counts[b] = br;
-            wb_counts[nb_stride + b] = be;
-        }
-    }
-}
 
 // ---- single-workgroup in-place exclusive scan ---------------------------------------------
 // Exclusive scan of col[0 .. n) in place by one workgroup of NT threads; the total goes to *tot
@@ -114,122 +59,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int64_t *data, int64_t co
         report(err, SVT_ERRCLASS_CAPACITY, cap_index);
 }
 
-// ---- unpack 2: write each road's first word, tag and event ordinal -----------------------
-__global__ __launch_bounds__(kSegThreads) void k_seg_emit(const uint32_t *__restrict__ words,
-                                                          Sizes n_words_s,
-                                                          const int64_t *__restrict__ wb_prefix,
-                                                          int64_t nb_stride, svt_roads roads,
-                                                          int64_t road_cap, uint64_t *err) {
-    __shared__ int64_t tmp[kSegThreads / kWaveSize + 1];
-    if (has_error(err)) return;
-    const int64_t n = load_size(n_words_s);
-    const int64_t nb = (n + kSegBlockWords - 1) / kSegBlockWords;
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int64_t base =
-            b * kSegBlockWords + static_cast<int64_t>(threadIdx.x) * kSegWordsPerThread;
-        uint32_t w[kSegWordsPerThread];
-#pragma unroll
-        for (int e = 0; e < kSegWordsPerThread; ++e) w[e] = (base + e < n) ? words[base + e] : 0u;
-        const uint32_t prev0 = (base > 0 && base <= n) ? words[base - 1] : 0u;
-        uint32_t flags = 0;  // bit 2e: new road, bit 2e+1: new event
-        int64_t nr = 0, ne = 0;
-        uint32_t prev = prev0;
-#pragma unroll
-        for (int e = 0; e < kSegWordsPerThread; ++e) {
-            const int64_t i = base + e;
-            if (i < n) {
-                const bool first = (i == 0);
-                const bool r = first || w_tags(w[e]) != w_tags(prev);
-                const bool v = first || w_etag(w[e]) != w_etag(prev);
-                flags |= (r ? 1u : 0u) << (2 * e);
-                flags |= (v ? 1u : 0u) << (2 * e + 1);
-                nr += r;
-                ne += v;
-                prev = w[e];
-            }
-        }
-        int64_t tr, te;
-        int64_t rc = block_excl_scan<int64_t, kSegThreads>(nr, tmp, tr) + wb_prefix[b];
-        int64_t ec = block_excl_scan<int64_t, kSegThreads>(ne, tmp, te) + wb_prefix[nb_stride + b];
-#pragma unroll
-        for (int e = 0; e < kSegWordsPerThread; ++e) {
-            const int64_t i = base + e;
-            if (i < n) {
-                if (flags & (2u << (2 * e))) ++ec;
-                if (flags & (1u << (2 * e))) {
-                    const int64_t r = rc++;
-                    if (r < road_cap) {
-                        roads.hit_begin[r] = i;
-                        roads.set[r] = static_cast<int32_t>(w_rtag(w[e]));
-                        roads.event[r] = static_cast<int32_t>(ec - 1);
-                    }
-                }
-            }
-        }
-    }
-}
-
-// ---- unpack 3: per road, count hits per layer, check, regroup coordinates by layer -------
-__global__ __launch_bounds__(kRoadBlock) void k_road_fill(const uint32_t *__restrict__ words,
-                                                          Sizes n_words_s,
-                                                          const int64_t *d_n_roads,
-                                                          int64_t road_cap, svt_roads roads,
-                                                          svt_config cfg, int16_t *hit_coord,
-                                                          uint64_t *err) {
-    if (has_error(err)) return;
-    const int64_t n = load_size(n_words_s);
-    const int64_t nr_all = *d_n_roads;
-    if (nr_all > road_cap || nr_all < 0) return;  // capacity error already reported
-    const int64_t nr = nr_all;
-    const int64_t max_len = static_cast<int64_t>(cfg.n_layers) * cfg.max_hits;
-    for (int64_t r = gtid(); r < nr; r += gstride()) {
-        const int64_t b = roads.hit_begin[r];
-        const int64_t e = (r + 1 < nr_all) ? roads.hit_begin[r + 1] : n;
-        const int64_t len = e - b;
-        if (len <= 0 || len > max_len || b < 0 || e > n) {
-            report(err, SVT_ERRCLASS_HITS, static_cast<uint64_t>(r));
-            continue;
-        }
-        uint64_t cnt = 0;  // 8 bits per layer
-        for (int64_t i = b; i < e; ++i) {
-            const uint32_t l = w_layer(words[i]);
-            if (l < SVT_N_LAYERS) cnt += 1ull << (8 * l);
-        }
-        bool over = false;
-        uint32_t packed = 0;
-        for (int l = 0; l < SVT_N_LAYERS; ++l) {
-            const uint32_t c = static_cast<uint32_t>((cnt >> (8 * l)) & 0xFF);
-            over |= c > static_cast<uint32_t>(cfg.max_hits);
-            packed |= (c & 0xFu) << (4 * l);
-        }
-        if (over) {
-            report(err, SVT_ERRCLASS_HITS, static_cast<uint64_t>(r));
-            continue;
-        }
-        if (static_cast<uint32_t>(roads.set[r]) >= static_cast<uint32_t>(cfg.n_sets))
-            report(err, SVT_ERRCLASS_SET, static_cast<uint64_t>(r));
-        roads.nhits[r] = packed;
-        if (hit_coord) {
-            uint32_t off[SVT_N_LAYERS];
-            uint32_t run = 0;
-            for (int l = 0; l < SVT_N_LAYERS; ++l) {
-                off[l] = run;
-                run += nh_of(packed, l);
-            }
-            for (int64_t i = b; i < e; ++i) {
-                const uint32_t w = words[i];
-                const uint32_t l = w_layer(w);
-                if (l >= SVT_N_LAYERS) continue;
-                uint32_t o = 0;
-                // select off[l] without dynamic register indexing
-                for (int k = 0; k < SVT_N_LAYERS; ++k)
-                    if (static_cast<uint32_t>(k) == l) { o = off[k]; off[k] = o + 1; }
-                hit_coord[b + o] = static_cast<int16_t>(w_coord(w));
-            }
-        }
-    }
-}
-
 // ---- combine 1: combinations per road and per-block sums ---------------------------------
 __global__ __launch_bounds__(kRoadBlock) void k_combo_count(svt_roads roads, Sizes n_roads_s,
                                                             int64_t *rb_sums, uint64_t *err) {
@@ -249,14 +78,13 @@ __global__ __launch_bounds__(kRoadBlock) void k_combo_count(svt_roads roads, Siz
     if (threadIdx.x == 0) rb_sums[blockIdx.x] = s;
 }
 
-// ---- combine 2: combo_begin, tile marks, defaults of roads without combinations ----------
+constexpr int kListTile = 2048;  // combinations a workgroup of k_materialize lists
+
+// ---- combine 2: combo_begin, marks for the listing -----------------------------------------
 __global__ __launch_bounds__(kRoadBlock) void k_combo_begin(svt_roads roads, Sizes n_roads_s,
                                                             const int64_t *rb_prefix,
-                                                            int64_t tile_combos,
-                                                            int32_t *tile_first_road,
-                                                            int64_t tiles_cap, svt_best best,
-                                                            int32_t init_best,
-                                                            uint64_t *err) {
+                                                            int32_t *combo_road,
+                                                            int64_t combo_cap, uint64_t *err) {
     __shared__ int64_t tmp[kRoadBlock / kWaveSize + 1];
     if (has_error(err)) return;
     const int64_t nr = load_size(n_roads_s);
@@ -267,111 +95,287 @@ __global__ __launch_bounds__(kRoadBlock) void k_combo_begin(svt_roads roads, Siz
     const int64_t begin = block_excl_scan<int64_t, kRoadBlock>(c, tmp, tot) + rb_prefix[blockIdx.x];
     if (r >= nr) return;
     roads.combo_begin[r] = begin;
-    if (tile_combos > 0 && c > 0) {
-        // this road holds the first combination of every tile that starts inside it
-        for (int64_t t = (begin + tile_combos - 1) / tile_combos; t * tile_combos < begin + c; ++t)
-            if (t < tiles_cap) tile_first_road[t] = static_cast<int32_t>(r);
-    }
-    if (init_best) {  // best-track key "none" (all ones) and no accepted combination yet
-        reinterpret_cast<uint64_t *>(best.chi2)[r] = UINT64_MAX;
-        best.n_accept[r] = 0;
+    if (combo_road && c > 0) {
+        // the road of each listing tile's first combination, where the listing will put it
+        for (int64_t t = (begin + kListTile - 1) / kListTile; t * kListTile < begin + c; ++t)
+            if (t * kListTile < combo_cap) combo_road[t * kListTile] = static_cast<int32_t>(r);
     }
 }
 
 // ---- combine 3 (plain path): list every combination --------------------------------------
-__global__ __launch_bounds__(kRoadBlock) void k_materialize(svt_roads roads, int64_t n_roads,
-                                                            const int64_t *d_n_combos,
-                                                            int64_t combo_cap,
-                                                            int32_t *combo_road,
-                                                            uint32_t *combo_hits,
-                                                            uint64_t *err) {
-    __shared__ int64_t s_begin[kRoadBlock + 1];
-    __shared__ uint32_t s_nh[kRoadBlock];
+// A workgroup lists kListTile consecutive combinations, however few or many roads they belong
+// to: by blocks of 256 roads, the workgroup with the largest roads took most of the time (190 us
+// for 1500 uneven events, now 19; 51 and 20 us for 3000 events of 64 roads, whose list is 49 MB).  k_combo_begin has left the road of the tile's first
+// combination in combo_road; the tile's roads are staged in LDS, up to kListRoads at a time.
+constexpr int kListRoads = 512;
+constexpr int kListThreads = 256;
+
+__global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, int64_t n_roads,
+                                                              const int64_t *d_n_combos,
+                                                              int64_t combo_cap,
+                                                              int32_t *combo_road,
+                                                              uint32_t *combo_hits,
+                                                              uint64_t *err) {
+    __shared__ int32_t s_begin[kListRoads];  // first combination, from the tile's first
+    __shared__ uint32_t s_nh[kListRoads];
+    __shared__ uint32_t s_magic[16];
+    __shared__ int64_t s_first;
+    __shared__ int32_t s_end;
     if (has_error(err)) return;
+    if (threadIdx.x < 16) s_magic[threadIdx.x] = magic_of(threadIdx.x ? threadIdx.x : 1u);
+    const bool wide = ((reinterpret_cast<uintptr_t>(combo_road) |
+                        reinterpret_cast<uintptr_t>(combo_hits)) & 15) == 0;
     const int64_t total = *d_n_combos;
     if (total > combo_cap) return;
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kRoadBlock;
-    if (r0 >= n_roads) return;
-    const int nloc = static_cast<int>((n_roads - r0) < kRoadBlock ? (n_roads - r0) : kRoadBlock);
-    if (threadIdx.x < nloc) {
-        s_begin[threadIdx.x] = roads.combo_begin[r0 + threadIdx.x];
-        s_nh[threadIdx.x] = roads.nhits[r0 + threadIdx.x];
-    }
+    const int64_t c_lo = static_cast<int64_t>(blockIdx.x) * kListTile;
+    if (c_lo >= total) return;
+    const int len = static_cast<int>(total - c_lo < kListTile ? total - c_lo : kListTile);
     if (threadIdx.x == 0) {
-        const int64_t rl = r0 + nloc - 1;
-        s_begin[nloc] = roads.combo_begin[rl] + roads.ncombo[rl];
+        int64_t r;
+        if (combo_road) {
+            r = combo_road[c_lo];
+        } else {  // last road that starts at or before the tile
+            int64_t lo = 0, hi = n_roads - 1;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi + 1) >> 1;
+                if (roads.combo_begin[mid] <= c_lo) lo = mid; else hi = mid - 1;
+            }
+            r = lo;
+        }
+        s_first = r;
     }
     __syncthreads();
-    const int64_t c_lo = s_begin[0], c_hi = s_begin[nloc];
-    for (int64_t c = c_lo + threadIdx.x; c < c_hi; c += kRoadBlock) {
-        int lo = 0, hi = nloc - 1;  // last road with begin <= c
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_begin[mid] <= c) lo = mid; else hi = mid - 1;
+    int64_t r0 = s_first;
+    for (int done = 0; done < len; r0 += kListRoads) {
+        const int nr = static_cast<int>(n_roads - r0 < kListRoads ? n_roads - r0 : kListRoads);
+        if (nr <= 0) break;  // (never on a consistent table)
+        for (int j = threadIdx.x; j < nr; j += kListThreads) {
+            const int64_t rel = roads.combo_begin[r0 + j] - c_lo;
+            const uint32_t nh = roads.nhits[r0 + j];
+            s_begin[j] = static_cast<int32_t>(rel < kListTile ? rel : kListTile);
+            s_nh[j] = nh;
+            if (j == nr - 1) {
+                const int64_t e = rel + roads.ncombo[r0 + j];
+                s_end = static_cast<int32_t>(e < len ? e : len);
+            }
         }
-        uint32_t k = static_cast<uint32_t>(c - s_begin[lo]);
-        const uint32_t p = s_nh[lo];
-        uint32_t h[SVT_N_LAYERS];
-        for (int l = SVT_N_LAYERS - 1; l >= 0; --l) {  // layer 0 most significant
-            const uint32_t nl = nh_of(p, l);
-            h[l] = k % nl;
-            k /= nl;
+        __syncthreads();
+        const int end = s_end;
+        // four consecutive combinations per lane: one search, then steps
+        for (int i0 = (done & ~3) + 4 * static_cast<int>(threadIdx.x); i0 < end;
+             i0 += 4 * kListThreads) {
+            const int first = i0 > done ? i0 : done;
+            int lo = 0, hi = nr - 1;  // last road with begin <= first (it has combinations)
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_begin[mid] <= first) lo = mid; else hi = mid - 1;
+            }
+            uint32_t nh = s_nh[lo], digits = 0;
+            uint32_t k = static_cast<uint32_t>(first - s_begin[lo]);
+#pragma unroll
+            for (int l = SVT_N_LAYERS - 1; l > 0; --l) {  // layer 0 most significant
+                const uint32_t nl = nh_of(nh, l);
+                // floor(k / nl) for k < 2^15, nl <= 8 (see div_small)
+                const uint32_t q = div_small(k, s_magic[nl]);
+                digits |= (k - q * nl) << (4 * l);
+                k = q;
+            }
+            digits |= k;
+            int32_t rd[4] = {0, 0, 0, 0};
+            uint32_t ht[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = i0 + e;
+                if (i < first || i >= end) continue;
+                rd[e] = static_cast<int32_t>(r0 + lo);
+                ht[e] = digits;
+                // the next combination: carry from layer 4 to layer 0, then the next road that
+                // has combinations
+                digits += 1u << 16;
+                bool past = false;
+#pragma unroll
+                for (int l = SVT_N_LAYERS - 1; l >= 0; --l)
+                    if (nh_of(digits, l) == nh_of(nh, l)) {
+                        digits &= ~(0xFu << (4 * l));
+                        if (l > 0) digits += 1u << (4 * (l - 1));
+                        past = l == 0;
+                    } else {
+                        break;
+                    }
+                if (past && i + 1 < end) {
+                    do ++lo;
+                    while (lo < nr - 1 && s_begin[lo + 1] <= i + 1);
+                    nh = s_nh[lo];
+                    digits = 0;
+                }
+            }
+            if (wide && i0 >= done && i0 + 4 <= end) {
+                if (combo_road)
+                    *reinterpret_cast<int4 *>(combo_road + c_lo + i0) =
+                        make_int4(rd[0], rd[1], rd[2], rd[3]);
+                if (combo_hits)
+                    *reinterpret_cast<uint4 *>(combo_hits + c_lo + i0) =
+                        make_uint4(ht[0], ht[1], ht[2], ht[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i0 + e >= first && i0 + e < end) {
+                        if (combo_road) combo_road[c_lo + i0 + e] = rd[e];
+                        if (combo_hits) combo_hits[c_lo + i0 + e] = ht[e];
+                    }
+            }
         }
-        uint32_t packed = 0;
-        for (int l = 0; l < SVT_N_LAYERS; ++l) packed |= h[l] << (4 * l);
-        if (combo_road) combo_road[c] = static_cast<int32_t>(r0 + lo);
-        if (combo_hits) combo_hits[c] = packed;
+        done = end > done ? end : done;
+        __syncthreads();
     }
 }
 
-// ---- plain fit: one lane per listed combination, 64-bit accumulation -----------------------
-__global__ __launch_bounds__(256) void k_fit_plain(const svt_fconst *__restrict__ bank,
-                                                   svt_config cfg, svt_roads roads,
-                                                   int64_t n_roads,
-                                                   const int16_t *__restrict__ hit_coord,
-                                                   int64_t n_hits,
-                                                   const int32_t *__restrict__ combo_road,
-                                                   const uint32_t *__restrict__ combo_hits,
-                                                   int64_t n_combos, svt_fitrec out,
-                                                   uint64_t *err) {
-    for (int64_t i = gtid(); i < n_combos; i += gstride()) {
-        const int32_t r = combo_road[i];
-        if (r < 0 || r >= n_roads) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
-        const uint32_t ph = combo_hits[i];
-        const uint32_t pn = roads.nhits[r];
-        const int64_t hb = roads.hit_begin[r];
-        const int32_t s = roads.set[r];
-        bool ok = (s >= 0 && s < cfg.n_sets);
-        int32_t x[SVT_N_LAYERS];
-        int64_t off = hb;
-        for (int l = 0; l < SVT_N_LAYERS; ++l) {
-            const uint32_t d = (ph >> (4 * l)) & 0xFu;
-            const uint32_t nl = nh_of(pn, l);
-            const int64_t idx = off + d;
-            ok &= (d < nl) && idx >= 0 && idx < n_hits;
-            x[l] = ok ? hit_coord[idx] : 0;
-            off += nl;
+// ---- plain fit: one lane per listed combination ------------------------------------------------
+// The list may hold any combinations in any order; where it is the combine stage's, a tile of
+// 2048 names few roads, whose table entries and coordinates then come from LDS (every lane
+// gathering its own from memory took 86 us at 6.2e6 combinations, now 61 for 246 MB).  The constant bank is packed
+// into LDS once per workgroup, in the pairs of the 16-bit dot products; with the offset split as
+// q = qh * 2^s + ql every sum stays inside int32 (svt_fit.h), where 64-bit products ran at a
+// quarter of the rate.
+constexpr int kFitThreads = 256;
+constexpr int kFitLane = 8;
+constexpr int kFitTile = kFitThreads * kFitLane;
+constexpr int kFitRoads = 512;
+constexpr int kFitCoords = 4096;
+
+struct alignas(16) PlainSet {  // row j: f0|f1, f2|f3, f4|0, q; 112 bytes spread the LDS banks
+    uint4 row[6];
+    uint32_t pad[4];
+};
+struct PlainRoad {
+    int64_t hb;
+    uint32_t nh;
+    int32_t set;
+};
+
+__global__ __launch_bounds__(kFitThreads) void k_fit_plain(
+    const svt_fconst *__restrict__ bank, svt_config cfg, svt_roads roads, int64_t n_roads,
+    const int16_t *__restrict__ hit_coord, int64_t n_hits, const int32_t *__restrict__ combo_road,
+    const uint32_t *__restrict__ combo_hits, int64_t n_combos, svt_fitrec out, uint64_t *err) {
+    __shared__ PlainSet s_bank[256];
+    __shared__ PlainRoad s_road[kFitRoads];
+    __shared__ int16_t s_coord[kFitCoords];
+    __shared__ int32_t s_lo[2], s_hi[2];
+    const int tid = threadIdx.x;
+    const int32_t shift = cfg.shift;
+    const uint32_t qlmask = (1u << shift) - 1u;
+    for (int i = tid; i < 6 * cfg.n_sets; i += kFitThreads) {
+        const int set = i / 6, j = i - 6 * set;
+        const int16_t *f = bank[set].f[j];
+        s_bank[set].row[j] =
+            make_uint4(static_cast<uint32_t>(pack16(f[0], f[1])),
+                       static_cast<uint32_t>(pack16(f[2], f[3])),
+                       static_cast<uint32_t>(pack16(f[4], 0)),
+                       static_cast<uint32_t>(bank[set].q[j]));
+    }
+    if (tid < 2) {
+        s_lo[tid] = INT32_MAX;
+        s_hi[tid] = -1;
+    }
+    __syncthreads();
+    int par = 0;
+    for (int64_t t0 = static_cast<int64_t>(blockIdx.x) * kFitTile; t0 < n_combos;
+         t0 += static_cast<int64_t>(gridDim.x) * kFitTile, par ^= 1) {
+        int32_t r[kFitLane];
+        uint32_t ph[kFitLane];
+        int32_t lo = INT32_MAX, hi = -1;
+#pragma unroll
+        for (int e = 0; e < kFitLane; ++e) {
+            const int64_t i = t0 + e * kFitThreads + tid;
+            r[e] = i < n_combos ? combo_road[i] : -1;
+            ph[e] = i < n_combos ? combo_hits[i] : 0;
+            if (r[e] >= 0 && r[e] < n_roads) {
+                lo = r[e] < lo ? r[e] : lo;
+                hi = r[e] > hi ? r[e] : hi;
+            }
         }
-        if (!ok) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
-        const svt_fconst &F = bank[s];
-        int32_t v[6];
-        for (int j = 0; j < 6; ++j) {
-            int64_t a = 0;
-            for (int l = 0; l < SVT_N_LAYERS; ++l)
-                a += static_cast<int64_t>(F.f[j][l]) * static_cast<int64_t>(x[l]);
-            a += static_cast<int64_t>(F.q[j]);
-            v[j] = static_cast<int32_t>(a >> cfg.shift);  // arithmetic shift = floor
+#pragma unroll
+        for (int d = kWaveSize / 2; d > 0; d >>= 1) {
+            const int32_t l2 = __shfl_xor(lo, d), h2 = __shfl_xor(hi, d);
+            lo = l2 < lo ? l2 : lo;
+            hi = h2 > hi ? h2 : hi;
         }
-        const int64_t chi2 = static_cast<int64_t>(v[3]) * v[3] +
-                             static_cast<int64_t>(v[4]) * v[4] +
-                             static_cast<int64_t>(v[5]) * v[5];
-        out.p0[i] = v[0];
-        out.p1[i] = v[1];
-        out.p2[i] = v[2];
-        out.chi2[i] = chi2;
-        if (out.c0) out.c0[i] = v[3];
-        if (out.c1) out.c1[i] = v[4];
-        if (out.c2) out.c2[i] = v[5];
+        if (lane_id() == 0) {
+            atomicMin(&s_lo[par], lo);
+            atomicMax(&s_hi[par], hi);
+        }
+        __syncthreads();
+        lo = s_lo[par];
+        hi = s_hi[par];
+        const int span = hi >= lo && hi - lo < kFitRoads ? hi - lo + 1 : 0;
+        int64_t w_lo = 0;  // coordinates staged: w_lo .. w_lo + wn - 1
+        int wn = 0;
+        if (tid == 0) {  // the other tile's bounds, for its next turn
+            s_lo[par ^ 1] = INT32_MAX;
+            s_hi[par ^ 1] = -1;
+        }
+        if (span > 0) {
+            for (int j = tid; j < span; j += kFitThreads) {
+                const int64_t q = lo + j;
+                s_road[j] = PlainRoad{roads.hit_begin[q], roads.nhits[q], roads.set[q]};
+            }
+            w_lo = roads.hit_begin[lo];
+            const int64_t w_hi = roads.hit_begin[hi] + SVT_N_LAYERS * SVT_MAX_HITS;
+            if (w_lo >= 0 && w_lo < n_hits && w_hi > w_lo) {
+                const int64_t stop = w_hi < n_hits ? w_hi : n_hits;
+                wn = static_cast<int>(stop - w_lo < kFitCoords ? stop - w_lo : kFitCoords);
+                for (int j = tid; j < wn; j += kFitThreads) s_coord[j] = hit_coord[w_lo + j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kFitLane; ++e) {
+            const int64_t i = t0 + e * kFitThreads + tid;
+            if (i >= n_combos) break;
+            if (r[e] < 0 || r[e] >= n_roads) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
+            PlainRoad rd;
+            if (span > 0)
+                rd = s_road[r[e] - lo];
+            else
+                rd = PlainRoad{roads.hit_begin[r[e]], roads.nhits[r[e]], roads.set[r[e]]};
+            bool ok = rd.set >= 0 && rd.set < cfg.n_sets;
+            int32_t x[SVT_N_LAYERS];
+            int64_t off = rd.hb;
+#pragma unroll
+            for (int l = 0; l < SVT_N_LAYERS; ++l) {
+                const uint32_t d = (ph[e] >> (4 * l)) & 0xFu;
+                const uint32_t nl = nh_of(rd.nh, l);
+                const int64_t idx = off + d;
+                ok &= (d < nl) && idx >= 0 && idx < n_hits;
+                x[l] = 0;
+                if (ok) {
+                    const uint64_t w = static_cast<uint64_t>(idx - w_lo);
+                    x[l] = w < static_cast<uint64_t>(wn) ? s_coord[w] : hit_coord[idx];
+                }
+                off += nl;
+            }
+            if (!ok) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
+            const PlainSet &F = s_bank[rd.set];
+            const int32_t x01 = pack16(x[0], x[1]), x23 = pack16(x[2], x[3]);
+            int32_t v[6];
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                const uint4 w = F.row[j];
+                int32_t acc = dot2(static_cast<int32_t>(w.x), x01,
+                                   static_cast<int32_t>(w.w & qlmask));
+                acc = dot2(static_cast<int32_t>(w.y), x23, acc);
+                acc = dot2(static_cast<int32_t>(w.z), x[4], acc);
+                v[j] = (acc >> shift) + (static_cast<int32_t>(w.w) >> shift);
+            }
+            out.p0[i] = v[0];
+            out.p1[i] = v[1];
+            out.p2[i] = v[2];
+            out.chi2[i] = static_cast<int64_t>(v[3]) * v[3] + static_cast<int64_t>(v[4]) * v[4] +
+                          static_cast<int64_t>(v[5]) * v[5];
+            if (out.c0) out.c0[i] = v[3];
+            if (out.c1) out.c1[i] = v[4];
+            if (out.c2) out.c2[i] = v[5];
+        }
     }
 }
 
@@ -390,34 +394,80 @@ __global__ __launch_bounds__(kSegThreads) void k_select_mark(svt_config cfg, svt
                                                              int64_t n_combos, uint8_t *accept,
                                                              svt_best best, int64_t *kb_counts,
                                                              uint64_t *err) {
-    __shared__ int64_t tmp[kSegThreads / kWaveSize + 1];
+    // four consecutive combinations per lane and load: each thread taking 16 of them one by one
+    // read every line of chi2 from many instructions (93 us at 6.2e6 combinations, now 20)
+    constexpr int kPer = kKeptBlock / kSegThreads / 4;
+    __shared__ int32_t s_cnt[kSegThreads / kWaveSize];
     const int64_t nb = (n_combos + kKeptBlock - 1) / kKeptBlock;
     uint64_t *key = reinterpret_cast<uint64_t *>(best.chi2);
+    const bool wide = (reinterpret_cast<uintptr_t>(chi2) & 15) == 0 &&
+                      (reinterpret_cast<uintptr_t>(accept) & 3) == 0;
     for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int64_t base = b * kKeptBlock + static_cast<int64_t>(threadIdx.x) * 16;
-        int64_t cnt = 0;
-        for (int e = 0; e < 16; ++e) {
-            const int64_t i = base + e;
-            if (i >= n_combos) break;
-            const int64_t c2 = chi2[i];
-            const bool acc = c2 <= cfg.chi2_cut;
-            accept[i] = acc ? 1 : 0;
-            if (acc) {
-                ++cnt;
-                const int32_t r = combo_road[i];
-                if (r < 0 || r >= n_roads) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
-                const int64_t k = i - roads.combo_begin[r];
-                if (k < 0 || k >= (1 << kKeyKBits) || c2 < 0) {
-                    report(err, SVT_ERRCLASS_INDEX, i);
+        const int64_t base = b * kKeptBlock + 4 * static_cast<int64_t>(threadIdx.x);
+        const bool full = wide && (b + 1) * kKeptBlock <= n_combos;
+        int64_t c2[kPer][4];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int64_t i = base + q * 4 * kSegThreads;
+            if (full) {
+                const longlong2 u = *reinterpret_cast<const longlong2 *>(chi2 + i);
+                const longlong2 v = *reinterpret_cast<const longlong2 *>(chi2 + i + 2);
+                c2[q][0] = u.x;
+                c2[q][1] = u.y;
+                c2[q][2] = v.x;
+                c2[q][3] = v.y;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    c2[q][e] = i + e < n_combos ? chi2[i + e] : INT64_MAX;
+            }
+        }
+        int cnt = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int64_t i = base + q * 4 * kSegThreads;
+            uint32_t bits = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                bits |= c2[q][e] <= cfg.chi2_cut && i + e < n_combos ? 1u << e : 0u;
+            if (full) {
+                *reinterpret_cast<uint32_t *>(accept + i) = mul_u24(bits, 0x204081u) & 0x01010101u;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < n_combos) accept[i + e] = (bits >> e) & 1u;
+            }
+            if (bits == 0) continue;
+            cnt += __popc(bits);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (!((bits >> e) & 1u)) continue;
+                const int32_t r = combo_road[i + e];
+                if (r < 0 || r >= n_roads) {
+                    report(err, SVT_ERRCLASS_INDEX, i + e);
                     continue;
                 }
-                const uint64_t kv = best_key(c2, static_cast<uint32_t>(k));
+                const int64_t k = i + e - roads.combo_begin[r];
+                if (k < 0 || k >= (1 << kKeyKBits) || c2[q][e] < 0) {
+                    report(err, SVT_ERRCLASS_INDEX, i + e);
+                    continue;
+                }
+                const uint64_t kv = best_key(c2[q][e], static_cast<uint32_t>(k));
                 atomicMin(reinterpret_cast<unsigned long long *>(key + r), kv);
                 atomicAdd(best.n_accept + r, 1);
             }
         }
-        const int64_t s = block_sum<int64_t, kSegThreads>(cnt, tmp);
-        if (threadIdx.x == 0 && kb_counts) kb_counts[b] = s;
+        if (kb_counts) {
+            const int s = wave_sum(cnt);
+            if (lane_id() == 0) s_cnt[threadIdx.x / kWaveSize] = s;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                int64_t t = 0;
+                for (int w = 0; w < kSegThreads / kWaveSize; ++w) t += s_cnt[w];
+                kb_counts[b] = t;
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -734,44 +784,11 @@ inline int64_t clamp_grid(int64_t blocks, int64_t maxb) {
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
-hipError_t launch_init_err(uint64_t *d_err, hipStream_t s) {
-    hipLaunchKernelGGL(k_init_err, dim3(1), dim3(1), 0, s, d_err);
-    return hipGetLastError();
-}
-
-hipError_t launch_seg_count(const uint32_t *words, Sizes n_words, int64_t grid_blocks,
-                            int32_t n_layers, int64_t *wb_counts, uint64_t *err, hipStream_t s) {
-    const int64_t g = clamp_grid(grid_blocks, 1 << 16);
-    hipLaunchKernelGGL(k_seg_count, dim3(g), dim3(kSegThreads), 0, s, words, n_words, n_layers,
-                       wb_counts, grid_blocks, err);
-    return hipGetLastError();
-}
-
 hipError_t launch_scan(int64_t *data, int64_t col_stride, int ncols, Sizes n, int64_t div,
                        int64_t *tot0, int64_t *tot1, int64_t cap0, uint32_t cap_index,
                        uint64_t *err, bool skip_if_error, hipStream_t s) {
     hipLaunchKernelGGL(k_scan, dim3(ncols), dim3(kScanThreads), 0, s, data, col_stride, n, div,
                        tot0, tot1, cap0, cap_index, err, static_cast<int32_t>(skip_if_error));
-    return hipGetLastError();
-}
-
-hipError_t launch_seg_emit(const uint32_t *words, Sizes n_words, int64_t grid_blocks,
-                           const int64_t *wb_prefix, const svt_roads &roads, int64_t road_cap,
-                           uint64_t *err, hipStream_t s) {
-    const int64_t g = clamp_grid(grid_blocks, 1 << 16);
-    hipLaunchKernelGGL(k_seg_emit, dim3(g), dim3(kSegThreads), 0, s, words, n_words, wb_prefix,
-                       grid_blocks, roads, road_cap, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_road_fill(const uint32_t *words, Sizes n_words, const int64_t *d_n_roads,
-                            int64_t road_cap, const svt_roads &roads, const svt_config &cfg,
-                            int16_t *hit_coord, int64_t *rb_sums, uint64_t *err,
-                            hipStream_t s) {
-    (void)rb_sums;
-    const int64_t g = clamp_grid((road_cap + kRoadBlock - 1) / kRoadBlock, 8192);
-    hipLaunchKernelGGL(k_road_fill, dim3(g), dim3(kRoadBlock), 0, s, words, n_words, d_n_roads,
-                       road_cap, roads, cfg, hit_coord, err);
     return hipGetLastError();
 }
 
@@ -784,14 +801,11 @@ hipError_t launch_combo_count(const svt_roads &roads, Sizes n_roads, int64_t gri
 }
 
 hipError_t launch_combo_begin(const svt_roads &roads, Sizes n_roads, int64_t grid_blocks,
-                              const int64_t *rb_prefix, int64_t tile_combos,
-                              int32_t *tile_first_road, int64_t tiles_cap,
-                              const svt_best *best_defaults, uint64_t *err, hipStream_t s) {
+                              const int64_t *rb_prefix, int32_t *combo_road, int64_t combo_cap,
+                              uint64_t *err, hipStream_t s) {
     const int64_t g = grid_blocks < 1 ? 1 : grid_blocks;
-    svt_best b = best_defaults ? *best_defaults : svt_best{};
     hipLaunchKernelGGL(k_combo_begin, dim3(g), dim3(kRoadBlock), 0, s, roads, n_roads, rb_prefix,
-                       tile_combos, tile_first_road, tiles_cap, b,
-                       static_cast<int32_t>(best_defaults != nullptr), err);
+                       combo_road, combo_cap, err);
     return hipGetLastError();
 }
 
@@ -799,9 +813,10 @@ hipError_t launch_materialize(const svt_roads &roads, int64_t n_roads, const int
                               int64_t combo_cap, int32_t *combo_road, uint32_t *combo_hits,
                               uint64_t *err, hipStream_t s) {
     if (n_roads <= 0 || (!combo_road && !combo_hits)) return hipSuccess;
-    const int64_t g = (n_roads + kRoadBlock - 1) / kRoadBlock;
-    hipLaunchKernelGGL(k_materialize, dim3(g), dim3(kRoadBlock), 0, s, roads, n_roads, d_n_combos,
-                       combo_cap, combo_road, combo_hits, err);
+    const int64_t g = (combo_cap + kListTile - 1) / kListTile;
+    if (g < 1) return hipSuccess;
+    hipLaunchKernelGGL(k_materialize, dim3(static_cast<unsigned>(g)), dim3(kListThreads), 0, s,
+                       roads, n_roads, d_n_combos, combo_cap, combo_road, combo_hits, err);
     return hipGetLastError();
 }
 
@@ -809,10 +824,11 @@ hipError_t launch_fit_plain(const svt_fconst *bank, const svt_config &cfg,
                             const svt_roads &roads, int64_t n_roads, const int16_t *hit_coord,
                             int64_t n_hits, const int32_t *combo_road,
                             const uint32_t *combo_hits, int64_t n_combos, const svt_fitrec &out,
-                            uint64_t *err, hipStream_t s) {
+                            uint64_t *err, int num_cus, hipStream_t s) {
     if (n_combos <= 0) return hipSuccess;
-    const int64_t g = clamp_grid((n_combos + 255) / 256, 1 << 20);
-    hipLaunchKernelGGL(k_fit_plain, dim3(g), dim3(256), 0, s, bank, cfg, roads, n_roads,
+    // 45 KB of LDS: three workgroups a compute unit
+    const int64_t g = clamp_grid((n_combos + kFitTile - 1) / kFitTile, 3 * num_cus);
+    hipLaunchKernelGGL(k_fit_plain, dim3(g), dim3(kFitThreads), 0, s, bank, cfg, roads, n_roads,
                        hit_coord, n_hits, combo_road, combo_hits, n_combos, out, err);
     return hipGetLastError();
 }

@@ -46,7 +46,7 @@ struct alignas(16) SliceAcc {
 struct alignas(16) RangeTot {
     uint32_t roads, events;
     uint64_t combos;     // as in UnitRec
-    uint32_t bad_word;   // word with a layer field out of range (index in the batch)
+    uint32_t bad_word;   // word with a layer field out of range (index in the range)
     uint32_t over_road;  // road with too many hits on a layer (index in the range)
     uint32_t set_road;   // road whose tag has no constant set (index in the range)
     uint32_t pad;

@@ -31,7 +31,7 @@ struct CArgs {
     int64_t *nw_copy;        // the word count for the later kernels
     uint32_t *ticket;        // units dealt out late, cleared here
     svt_config cfg;
-    const svt_fconst *bank;
+    const svt_fconst *bank;  // nullable: unpack only
     UnitSet *sets;           // the packed bank
     UnitRec *rec;            // per unit
     RangeTot *tot;           // per range
@@ -68,18 +68,19 @@ __device__ __forceinline__ uint64_t with_extra(uint32_t combos, uint32_t extra) 
     return combos | (static_cast<uint64_t>(extra) << kExtraShift);
 }
 
-__global__ __launch_bounds__(kThreads) void k_unit_count(CArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_unit_count(CArgs a) {
     __shared__ uint2 s_ent[kUnitWaves][kEntries + 1];
     __shared__ uint2 s_agg[2][kUnitWaves];
     __shared__ uint32_t s_err[3][kUnitWaves];
     const int wave = threadIdx.x / kWaveSize, lane = lane_id();
     const int64_t n = load_size(a.nw);
     const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
-    const int ranges = static_cast<int>(gridDim.x) - 1;
+    // with a bank, the last workgroup packs it and counts nothing
+    const int ranges = static_cast<int>(gridDim.x) - (a.bank ? 1 : 0);
     if (a.kb)
         for (int64_t i = gtid(); i < a.n_kb; i += gstride()) a.kb[i] = 0;
     for (int64_t i = gtid(); i < a.n_acc; i += gstride()) a.acc[i] = SliceAcc{0, 0, 0};
-    if (static_cast<int>(blockIdx.x) == ranges) {  // the last workgroup packs the bank
+    if (static_cast<int>(blockIdx.x) == ranges) {
         if (threadIdx.x == 0) {
             *a.nw_copy = a.nw.dev ? *a.nw.dev : a.nw.host;
         }
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(kThreads) void k_unit_count(CArgs a) {
                 for (int e = kUnitLane - 1; e >= 0; --e)
                     if (j0 + e < kUnitWords && j0 + e < nloc &&
                         w_layer(uw.w[e]) >= static_cast<uint32_t>(SVT_N_LAYERS))
-                        b = static_cast<uint32_t>(base + j0 + e);
+                        b = static_cast<uint32_t>(base - lo_u * kUnitWords) + j0 + e;
                 b = wave_min(b);
                 bad_word = b < bad_word ? b : bad_word;
             }
@@ -253,10 +254,21 @@ struct alignas(16) WaveLds {
 
 constexpr uint64_t kComboMask = (1ull << kExtraShift) - 1;
 struct RangeBase {
-    uint32_t roads, events;
+    uint64_t roads;
     uint64_t combos;
+    uint32_t events;
     uint32_t extra;   // slices past their unit's first, before the range
-    uint32_t pad;
+};
+// Running counts at the start of every range, as each workgroup works them out for itself.
+struct RangeLds {
+    RangeBase base[kMaxRanges];
+    uint64_t roads[kUnitWaves], combos[kUnitWaves], err[kUnitWaves];
+    uint32_t events[kUnitWaves], extra[kUnitWaves];
+};
+struct BatchTotals {
+    int64_t n_roads, n_combos;
+    uint64_t err;    // the first error found in the words, or a capacity that is too small
+    uint32_t extra;
 };
 
 struct ULds {
@@ -264,13 +276,9 @@ struct ULds {
     // be live through the fit, which spills them and then vector registers too.
     UArgs args;
     UnitSet bank[256];
-    RangeBase base[kMaxRanges];
+    RangeLds range;
     WaveLds w[kUnitWaves];
     uint32_t magic[72];
-    uint64_t tmp64[kUnitWaves];
-    uint64_t tmp64b[kUnitWaves];
-    uint32_t tmp32[kUnitWaves];
-    uint64_t err[kUnitWaves];
     uint32_t next;
 };
 static_assert(sizeof(ULds) <= 160 * 1024, "LDS of a compute unit");
@@ -590,9 +598,9 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     const int nloc = static_cast<int>(n - base < kUnitSpan ? n - base : kUnitSpan);
     const UnitWords uw = load_unit(hot.words, base, nloc);
     const UnitRec rec = L.args.rec[u];
-    const RangeBase rbase = L.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)];
+    const RangeBase rbase = L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)];
     const bool table = c0 == 0 && (!SLICED || slice == 0);  // the unit's road table is to be written
-    const uint32_t R0 = uni(rec.roads) + uni(rbase.roads);
+    const int64_t R0 = static_cast<int64_t>(uni(rec.roads) + uni(rbase.roads));
     const int64_t CB0 = static_cast<int64_t>(uni(rec.combos) & kComboMask) +
                         static_cast<int64_t>(uni(rbase.combos));
     const int64_t GB = CB0 & ~static_cast<int64_t>(3);
@@ -797,7 +805,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 // the batch's number of the slice after the road's first one
                 const UnitRec rc = L.args.rec[u];
                 const uint32_t x = static_cast<uint32_t>(rc.combos >> kExtraShift) +
-                                   L.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)]
+                                   L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)]
                                        .extra + s0;
                 SliceAcc *acc = L.args.acc + x;
                 atomicMax(&acc->key, ~key);
@@ -857,8 +865,8 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
     const int lane = lane_id();
     int r = -1;  // last range whose extras start at or before e
     for (int r0 = 0; r0 < n_ranges; r0 += kWaveSize)
-        r += __popcll(__ballot(r0 + lane < n_ranges && L.base[r0 + lane].extra <= e));
-    e -= uni(L.base[r].extra);
+        r += __popcll(__ballot(r0 + lane < n_ranges && L.range.base[r0 + lane].extra <= e));
+    e -= uni(L.range.base[r].extra);
     const int64_t lo = r * per, hi = lo + per < nu ? lo + per : nu;
     int64_t u = lo - 1;  // last unit whose extras start at or before e
     uint32_t first = 0;
@@ -925,26 +933,74 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
     }
 }
 
+// Scan the totals of the n_ranges ranges (`per` units each); all threads of the workgroup.
+__device__ __forceinline__ BatchTotals scan_ranges(const RangeTot *tot, int n_ranges, int64_t per,
+                                                   int64_t nw, int64_t word_cap, int64_t road_cap,
+                                                   int64_t combo_cap, RangeLds &L) {
+    const int tid = threadIdx.x, wave = tid / kWaveSize, lane = lane_id();
+    RangeTot t{};
+    if (tid < n_ranges) t = tot[tid];
+    const uint64_t cc = t.combos & kComboMask;
+    const uint32_t ee = static_cast<uint32_t>(t.combos >> kExtraShift);
+    const uint64_t ir = wave_incl_scan(static_cast<uint64_t>(t.roads)), ic = wave_incl_scan(cc);
+    const uint32_t iv = scan64(t.events), ie = scan64(ee);
+    if (lane == kWaveSize - 1) {
+        L.roads[wave] = ir;
+        L.combos[wave] = ic;
+        L.events[wave] = iv;
+        L.extra[wave] = ie;
+    }
+    __syncthreads();
+    RangeBase b{ir - t.roads, ic - cc, iv - t.events, ie - ee};
+    BatchTotals all{0, 0, SVT_NO_ERROR, 0};
+    for (int w = 0; w < kUnitWaves; ++w) {
+        if (w < wave) {
+            b.roads += L.roads[w];
+            b.combos += L.combos[w];
+            b.events += L.events[w];
+            b.extra += L.extra[w];
+        }
+        all.n_roads += static_cast<int64_t>(L.roads[w]);
+        all.n_combos += static_cast<int64_t>(L.combos[w]);
+        all.extra += L.extra[w];
+    }
+    uint64_t err = SVT_NO_ERROR;
+    if (tid < n_ranges) {
+        L.base[tid] = b;
+        auto note = [&](uint64_t cls, uint32_t idx, uint64_t from) {
+            const uint64_t v = (cls << 56) | (from + idx);
+            if (idx != ~0u && v < err) err = v;
+        };
+        note(SVT_ERRCLASS_LAYER, t.bad_word, static_cast<uint64_t>(tid * per) * kUnitWords);
+        note(SVT_ERRCLASS_HITS, t.over_road, b.roads);
+        note(SVT_ERRCLASS_SET, t.set_road, b.roads);
+    }
+#pragma unroll
+    for (int d = kWaveSize / 2; d > 0; d >>= 1) {
+        const uint64_t ov = __shfl_xor(err, d, kWaveSize);
+        err = ov < err ? ov : err;
+    }
+    if (lane == 0) L.err[wave] = err;
+    __syncthreads();
+    auto cap_err = [](uint64_t i) {
+        return (static_cast<uint64_t>(SVT_ERRCLASS_CAPACITY) << 56) | i;
+    };
+    if (nw > word_cap) all.err = cap_err(3);
+    if (all.n_combos > combo_cap) all.err = cap_err(1);
+    if (all.n_roads > road_cap) all.err = cap_err(0);
+    for (int w = 0; w < kUnitWaves; ++w) all.err = L.err[w] < all.err ? L.err[w] : all.err;
+    return all;
+}
+
 template <int REC>
 __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
     __shared__ ULds L;
-    const int tid = threadIdx.x, wave = tid / kWaveSize, lane = lane_id();
+    const int tid = threadIdx.x;
     const int64_t nw = *a.d_nw;
     const int64_t n = nw < 0 ? 0 : nw > a.word_cap ? a.word_cap : nw;
     const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
     const int64_t per = units_per_range(nu, a.ranges);
     const int n_ranges = nu > 0 ? static_cast<int>((nu + per - 1) / per) : 0;
-
-    // ---- running counts at the start of every range, totals, errors ----------------------------
-    uint64_t re = 0, cc = 0;
-    uint32_t ee = 0;
-    RangeTot t{};
-    if (tid < n_ranges) {
-        t = a.tot[tid];
-        re = static_cast<uint64_t>(t.roads) | (static_cast<uint64_t>(t.events) << 32);
-        cc = t.combos & kComboMask;
-        ee = static_cast<uint32_t>(t.combos >> kExtraShift);
-    }
     {
         const uint4 *src = reinterpret_cast<const uint4 *>(a.sets);
         uint4 *dst = reinterpret_cast<uint4 *>(L.bank);
@@ -959,69 +1015,119 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
         if (tid < static_cast<int>(sizeof(UArgs) / 4))
             reinterpret_cast<uint32_t *>(&L.args)[tid] = src[tid];
     }
-    const uint64_t ire = wave_incl_scan(re), icc = wave_incl_scan(cc);
-    const uint32_t iee = scan64(ee);
-    if (lane == kWaveSize - 1) {
-        L.tmp32[wave] = iee;
-        L.tmp64[wave] = ire;
-        L.tmp64b[wave] = icc;
-    }
-    __syncthreads();
-    uint64_t bre = 0, bcc = 0, tre = 0, tcc = 0;
-    uint32_t bee = 0, tee = 0;
-    for (int w = 0; w < kUnitWaves; ++w) {
-        if (w == wave) {
-            bee = tee;
-            bre = tre;
-            bcc = tcc;
-        }
-        tre += L.tmp64[w];
-        tcc += L.tmp64b[w];
-        tee += L.tmp32[w];
-    }
-    uint64_t err = SVT_NO_ERROR;
-    if (tid < n_ranges) {
-        const uint64_t ex = bre + ire - re;
-        L.base[tid] = RangeBase{static_cast<uint32_t>(ex), static_cast<uint32_t>(ex >> 32),
-                                bcc + icc - cc, bee + iee - ee, 0};
-        auto note = [&](uint32_t cls, uint32_t idx, uint32_t add) {
-            if (idx == ~0u) return;
-            const uint64_t v = (static_cast<uint64_t>(cls) << 56) |
-                               (static_cast<uint64_t>(idx) + add);
-            err = v < err ? v : err;
-        };
-        note(SVT_ERRCLASS_LAYER, t.bad_word, 0);
-        note(SVT_ERRCLASS_HITS, t.over_road, static_cast<uint32_t>(ex));
-        note(SVT_ERRCLASS_SET, t.set_road, static_cast<uint32_t>(ex));
-    }
-#pragma unroll
-    for (int d = kWaveSize / 2; d > 0; d >>= 1) {
-        const uint64_t ov = __shfl_xor(err, d, kWaveSize);
-        err = ov < err ? ov : err;
-    }
-    if (lane == 0) L.err[wave] = err;
-    __syncthreads();
-    const int64_t n_roads = static_cast<int64_t>(tre & 0xFFFFFFFFull);
-    const int64_t n_combos = static_cast<int64_t>(tcc);
-    auto cap_err = [](uint64_t i) {
-        return (static_cast<uint64_t>(SVT_ERRCLASS_CAPACITY) << 56) | i;
-    };
-    err = nw > a.word_cap ? cap_err(3) : SVT_NO_ERROR;
-    if (n_combos > a.combo_cap) err = cap_err(1);
-    if (n_roads > a.road_cap) err = cap_err(0);
-    for (int w = 0; w < kUnitWaves; ++w) err = L.err[w] < err ? L.err[w] : err;
+    const BatchTotals all = scan_ranges(a.tot, n_ranges, per, nw, a.word_cap, a.road_cap,
+                                        a.combo_cap, L.range);
     if (blockIdx.x == 0 && tid == 0) {
-        *a.err = err;
-        *a.d_n_roads = n_roads;
-        *a.d_n_combos = n_combos;
+        *a.err = all.err;
+        *a.d_n_roads = all.n_roads;
+        *a.d_n_combos = all.n_combos;
     }
-    if (err != SVT_NO_ERROR) return;
+    if (all.err != SVT_NO_ERROR) return;
 
-    const uint32_t extra = uni(tee);
+    const uint32_t extra = uni(all.extra);
     if (extra == 0)
         run_units<REC, false>(a, L, n, nu, per, n_ranges, extra);
     else
         run_units<REC, true>(a, L, n, nu, per, n_ranges, extra);
+}
+
+// ---- the unpack stage on its own ------------------------------------------------------------------
+// The road table (event, set, hit_begin, nhits) and every word's coordinate at its place among its
+// road's hits grouped by layer.  No bank and no tables: two workgroups of 16 waves fit a compute
+// unit, and the waves take the units in turn.
+struct TArgs {
+    const uint32_t *words;
+    int64_t n;
+    int32_t ranges;
+    int32_t max_hits;
+    const UnitRec *rec;
+    const RangeTot *tot;
+    svt_roads roads;
+    int64_t road_cap;
+    int16_t *hit_coord;
+    int64_t *d_n_roads;
+    uint64_t *err;
+};
+struct TWaveLds {
+    uint2 ent[kEntries + 1];
+    uint32_t nh[kUnitWords];
+    int16_t coord[kUnitSpan];
+};
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_unit_table(TArgs a) {
+    __shared__ RangeLds s_range;
+    __shared__ TWaveLds s_wave[kUnitWaves];
+    const int lane = lane_id(), wave = threadIdx.x / kWaveSize;
+    TWaveLds &W = s_wave[wave];
+    const int64_t nu = (a.n + kUnitWords - 1) / kUnitWords;
+    const int64_t per = units_per_range(nu, a.ranges);
+    const int n_ranges = nu > 0 ? static_cast<int>((nu + per - 1) / per) : 0;
+    const BatchTotals all = scan_ranges(a.tot, n_ranges, per, a.n, a.n, a.road_cap, INT64_MAX,
+                                        s_range);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *a.err = all.err;
+        *a.d_n_roads = all.n_roads;
+    }
+    if (all.err != SVT_NO_ERROR) return;
+    for (int64_t u = static_cast<int64_t>(blockIdx.x) * kUnitWaves + wave; u < nu;
+         u += static_cast<int64_t>(gridDim.x) * kUnitWaves) {
+        const int64_t base = u * kUnitWords;
+        const int nloc = static_cast<int>(a.n - base < kUnitSpan ? a.n - base : kUnitSpan);
+        const UnitWords uw = load_unit(a.words, base, nloc);
+        const UnitRec rec = a.rec[u];
+        const RangeBase rb = s_range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)];
+        UnitScan sc;
+        if (nloc < kUnitSpan)
+            sc = scan_unit<true>(uw, nloc);
+        else
+            sc = scan_unit<false>(uw, nloc);
+        const uint32_t nr = sc.own & 0xFFFFu;
+        if (nr == 0) continue;
+        lds_order();
+        write_entries(W.ent, uw, sc, nr, nloc);
+        lds_order();
+        uint32_t ev_run = rec.events + rb.events - 1;
+        for (uint32_t r0 = 0; r0 < nr; r0 += kWaveSize) {
+            const uint32_t rl = r0 + lane;
+            uint2 e0 = make_uint2(0, 0);
+            if (rl < nr) e0 = W.ent[rl];
+            const bool ev = (e0.y >> 9) & 1u;
+            const uint64_t em = __ballot(ev);
+            const uint32_t evn = ev_run + bits_below(em) + (ev ? 1u : 0u);
+            ev_run += __popcll(em);
+            if (rl < nr) {
+                bool over;
+                const uint32_t nh = road_hits(e0, W.ent[rl + 1], a.max_hits, over);
+                const int64_t r = static_cast<int64_t>(rec.roads + rb.roads) + rl;
+                W.nh[rl] = nh;
+                a.roads.event[r] = static_cast<int32_t>(evn);
+                a.roads.set[r] = static_cast<int32_t>((e0.y >> 16) & 0xFFu);
+                a.roads.hit_begin[r] = base + entry_pos(e0);
+                a.roads.nhits[r] = nh;
+            }
+        }
+        lds_order();
+        uint32_t hits = sc.hits, rl = (sc.rd & 0xFFFFu) - 1u;
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) {
+            rl += (sc.starts >> e) & 1u;
+            if (rl < nr && kUnitLane * lane + e < nloc) {
+                const uint2 ent = W.ent[rl];
+                const uint32_t l = w_layer(uw.w[e]), nh = W.nh[rl];
+                uint32_t p = entry_pos(ent) + (((hits - ent.x) >> (6 * l)) & 0x3Fu);
+#pragma unroll
+                for (int q = 0; q < SVT_N_LAYERS - 1; ++q)
+                    p += static_cast<uint32_t>(q) < l ? nh_of(nh, q) : 0u;
+                W.coord[p] = static_cast<int16_t>(w_coord(uw.w[e]));
+            }
+            hits += sc.hit[e];
+        }
+        lds_order();
+        const int lo = static_cast<int>(entry_pos(W.ent[0])),
+                  hi = static_cast<int>(entry_pos(W.ent[nr]));
+        for (int j = lo + lane; j < hi; j += kWaveSize) a.hit_coord[base + j] = W.coord[j];
+        lds_order();
+    }
 }
 
 }  // namespace
@@ -1041,10 +1147,37 @@ int64_t unit_acc_bytes(int64_t combos) {
 int64_t unit_ticket_bytes() { return 4ll * kDealers * kDealerStride; }
 int64_t unit_bank_bytes() { return static_cast<int64_t>(sizeof(UnitSet)) * 256; }
 
+// Ranges the units of a capacity are counted in: one workgroup each.
+static int unit_ranges(int64_t words) {
+    const int64_t r = (unit_count(words > 0 ? words : 1) + kUnitWaves - 1) / kUnitWaves;
+    return static_cast<int>(r < kMaxRanges ? r : kMaxRanges);
+}
+
+hipError_t launch_unpack(const uint32_t *words, int64_t n_words, const svt_config &cfg,
+                         const svt_roads &roads, int64_t road_cap, int16_t *hit_coord,
+                         int64_t *d_n_roads, uint64_t *err, void *rec, void *tot, int num_cus,
+                         hipStream_t s) {
+    const int ranges = unit_ranges(n_words);
+    CArgs c{};
+    c.words = words;
+    c.nw = Sizes{n_words, nullptr, n_words};
+    c.cfg = cfg;
+    c.rec = static_cast<UnitRec *>(rec);
+    c.tot = static_cast<RangeTot *>(tot);
+    hipLaunchKernelGGL(k_unit_count, dim3(ranges), dim3(kThreads), 0, s, c);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    TArgs t{words, n_words, ranges, cfg.max_hits, c.rec, c.tot, roads, road_cap, hit_coord,
+            d_n_roads, err};
+    const int64_t groups = (unit_count(n_words > 0 ? n_words : 1) + kUnitWaves - 1) / kUnitWaves;
+    const int grid = static_cast<int>(groups < 2 * num_cus ? groups : 2 * num_cus);
+    hipLaunchKernelGGL(k_unit_table, dim3(grid), dim3(kThreads), 0, s, t);
+    return hipGetLastError();
+}
+
 hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
     const int64_t units = unit_count(p.word_cap > 0 ? p.word_cap : 1);
-    int64_t ranges = (units + kUnitWaves - 1) / kUnitWaves;
-    if (ranges > kMaxRanges) ranges = kMaxRanges;
+    const int ranges = unit_ranges(p.word_cap);
     CArgs c{};
     c.words = p.words;
     c.nw = Sizes{0, p.d_n_words, p.word_cap};
@@ -1060,7 +1193,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     c.n_kb = p.kb_counts ? p.n_kb : 0;
     c.acc = static_cast<SliceAcc *>(p.acc);
     c.n_acc = unit_slices(p.combo_cap);
-    hipLaunchKernelGGL(k_unit_count, dim3(static_cast<unsigned>(ranges + 1)), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(k_unit_count, dim3(ranges + 1), dim3(kThreads), 0, s,
                        c);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1069,7 +1202,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     a.d_nw = p.nw_copy;
     a.word_cap = p.word_cap;
     a.ticket = p.ticket;
-    a.ranges = static_cast<int32_t>(ranges);
+    a.ranges = ranges;
     a.cfg = p.cfg;
     a.sets = c.sets;
     a.rec = c.rec;
