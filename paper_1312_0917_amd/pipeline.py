@@ -88,8 +88,10 @@ class PlainRunner:
         self.cfg, self.bank, self.device = cfg, bank, device
         self.with_c, self.want_kept = with_c, want_kept
         self.caps = dict(words=-1, roads=-1, combos=-1)
-        self.d_n = torch.zeros(4, dtype=I64, device=device)  # roads, combos, kept
-        self.d_err = torch.zeros(1, dtype=I64, device=device)
+        # roads, combos, kept, then the error word: one copy brings all of them back
+        self.d_state = torch.zeros(5, dtype=I64, device=device)
+        self.d_n = self.d_state[0:4]
+        self.d_err = self.d_state[4:5]
         self.stage_events = None
 
     def _grow(self, kind, n):
@@ -113,8 +115,12 @@ class PlainRunner:
             self.ws_select = _ws(L.svt_select_workspace(cap), d)
         self.caps[kind] = cap
 
-    def _check(self, where):
-        err = _err_value(self.d_err)
+    def _read(self):
+        """The counts and the error word, one host synchronisation for all of them."""
+        v = self.d_state.tolist()
+        return v[:4], v[4] & L.SVT_NO_ERROR
+
+    def _check(self, err, where):
         if err != L.SVT_NO_ERROR:
             st, idx = L.error_decode(err)
             raise DeviceError(st, idx, where)
@@ -130,8 +136,8 @@ class PlainRunner:
         L.check(L.svt_unpack(words, n_words, self.cfg, self.roads, self.caps["roads"],
                              self.hit_coord, self.d_n[0:1], self.d_err, self.ws_unpack), "svt_unpack")
         if ev: ev[1].record(st)
-        n_roads = int(self.d_n[0].item())  # host sync: size of the next stage
-        self._check("svt_unpack")
+        (n_roads, *_), err = self._read()  # host sync: size of the next stage
+        self._check(err, "svt_unpack")
         while True:
             listing = self.caps["combos"] > 0
             L.check(L.svt_combine(self.roads, n_roads, self.cfg,
@@ -139,13 +145,13 @@ class PlainRunner:
                                   self.combo_hits if listing else None,
                                   max(self.caps["combos"], 0), self.d_n[1:2], self.d_err,
                                   self.ws_combine), "svt_combine")
-            n_combos = int(self.d_n[1].item())  # host sync: size of the next stage
+            (_, n_combos, *_), err = self._read()  # host sync: size of the next stage
             if listing and n_combos <= self.caps["combos"]:
                 break
             # first run or a larger input: grow the lists and list again
             self._grow("combos", n_combos)
             self.d_err.fill_(-1)
-        self._check("svt_combine")
+        self._check(err, "svt_combine")
         if ev: ev[2].record(st)
         L.check(L.svt_fit(self.bank, self.cfg, self.roads, n_roads, self.hit_coord, n_words,
                           self.combo_road, self.combo_hits, n_combos, self.rec, self.d_err),
@@ -165,10 +171,10 @@ class PlainRunner:
 
     def result(self, check=True) -> dict:
         torch.cuda.synchronize()
+        (_, _, nk, _), err = self._read()
         if check:
-            self._check("svt_select")
+            self._check(err, "svt_select")
         nr, nc = self.n_roads, self.n_combos
-        nk = int(self.d_n[2].item())
         out = {f"road_{k}": v[:nr] for k, v in self.roads.items()}
         out["hit_coord"] = self.hit_coord[:self.n_words]
         out["combo_road"] = self.combo_road[:nc]
