@@ -75,15 +75,23 @@ struct BatchWs {
     uint32_t *dealers;  // counters of the units dealt out late,
     void *rec;          // running counts per unit,
     void *acc;          // what the slices of a large unit share,
-    uint32_t *copy;     // and the words, when the caller's are in host memory
+    void *keep;         // accepted combinations per unit
+    int64_t *keep_groups;  // and per group of units,
+    // 4 bytes a word that a workspace may do without: a copy of the words when the caller's are in
+    // host memory, else more room for accepted combinations
+    uint32_t *copy;
+    bool host_words;
 };
 // What the unit kernels need besides, in bytes.
 int64_t unit_bytes(int64_t word_cap, int64_t combo_cap) {
     return align_up(unit_bank_bytes()) + align_up(unit_range_bytes()) +
            align_up(unit_ticket_bytes()) + align_up(unit_acc_bytes(combo_cap)) +
-           align_up(unit_rec_bytes(word_cap > 0 ? word_cap : 1));
+           align_up(unit_rec_bytes(word_cap > 0 ? word_cap : 1)) +
+           align_up(unit_keep_bytes(word_cap > 0 ? word_cap : 1)) +
+           align_up(unit_keep_group_bytes(word_cap > 0 ? word_cap : 1)) +
+           2 * kAlign;  // (slots for the last unit, a whole one, in the coordinates' place)
 }
-// `copy`: with room for a copy of the words
+// `copy`: with those 4 bytes a word
 BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo_cap,
                     int64_t tile, bool copy) {
     BatchWs w;
@@ -103,14 +111,20 @@ BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo
     w.tfr = c.take<int32_t>(w.tiles_cap);
     w.kbn = ceil_div(combo_cap > 0 ? combo_cap : 1, kKeptBlock);
     w.kb = c.take<int64_t>(w.kbn);
-    w.coords = c.take<int16_t>(word_cap + 16);  // slack for 16-byte reads of the last span
+    // grouped coordinates, with slack for 16-byte reads of the last span; the unit kernels keep
+    // their accepted combinations there when they have no better place
+    const int64_t slots = unit_slot_bytes(word_cap > 0 ? word_cap : 1, true) / 2;
+    w.coords = c.take<int16_t>(word_cap + 16 > slots ? word_cap + 16 : slots);
     w.nw_copy = c.take<int64_t>(1);
     w.sets = c.take<char>(unit_bank_bytes());
     w.tot = c.take<char>(unit_range_bytes());
     w.dealers = c.take<uint32_t>(unit_ticket_bytes() / 4);
     w.rec = c.take<char>(unit_rec_bytes(word_cap > 0 ? word_cap : 1));
     w.acc = c.take<char>(unit_acc_bytes(combo_cap));
-    w.copy = copy ? c.take<uint32_t>(word_cap) : nullptr;
+    w.keep = c.take<char>(unit_keep_bytes(word_cap > 0 ? word_cap : 1));
+    w.keep_groups = c.take<int64_t>(unit_keep_group_bytes(word_cap > 0 ? word_cap : 1) / 8);
+    w.copy = copy ? c.take<uint32_t>(unit_slot_bytes(word_cap > 0 ? word_cap : 1, false) / 4)
+                  : nullptr;
     return w;
 }
 int64_t batch_bytes(int64_t word_cap, int64_t road_cap, int64_t combo_cap, int64_t tile,
@@ -410,7 +424,7 @@ static svt_status batch_sequence(const FusedLaunch &f, const BatchWs &w, int64_t
     const Sizes nc{0, f.d_n_combos, combo_cap};
     uint64_t *err = f.err;
     if (f.tune.schedule != SVT_SCHEDULE_EVENTS) {
-        // the unit kernels, and with a kept list its scan and compaction
+        // two kernels, and with a kept list a third
         UnitsLaunch o{};
         o.bank = f.bank;
         o.cfg = f.cfg;
@@ -426,33 +440,24 @@ static svt_status batch_sequence(const FusedLaunch &f, const BatchWs &w, int64_t
         o.d_n_roads = const_cast<int64_t *>(f.d_n_roads);
         o.d_n_combos = const_cast<int64_t *>(f.d_n_combos);
         o.err = err;
-        o.kb_counts = d_n_kept ? w.kb : nullptr;
-        o.n_kb = w.kbn;
+        o.d_n_kept = d_n_kept;
+        o.kept = kept;
+        o.kept_cap = kept_cap;
         o.kept_only = f.kept_only;
-        o.coords = w.coords;
-        o.tile_first_road = w.tfr;
-        o.tiles_cap = w.tiles_cap;
+        o.keep = w.keep;
+        o.keep_groups = w.keep_groups;
+        o.less_slots = !w.copy || w.host_words;
+        o.slots = o.less_slots ? static_cast<void *>(w.coords) : w.copy;
         o.nw_copy = w.nw_copy;
         o.ticket = w.dealers;
         o.acc = w.acc;
         o.sets = w.sets;
         o.rec = w.rec;
         o.tot = w.tot;
-        o.copy = w.copy;
+        o.copy = w.host_words ? w.copy : nullptr;
         o.num_cus = f.num_cus;
         SVT_TRY(launch_units(o, stream, timing ? g_ev_start : nullptr,
                              timing ? g_ev_stop : nullptr));
-        if (d_n_kept) {
-            SVT_TRY(launch_scan(w.kb, 0, 1, nc, kKeptBlock, d_n_kept, nullptr,
-                                kept ? kept_cap : -1, 2, err, true, stream));
-            if (kept && f.kept_only)
-                SVT_TRY(launch_kept_refit(f.accept, nc, nr, w.kbn, w.kb, f.roads, w.tfr,
-                                          kKeptBlock, f.bank, f.cfg.n_sets, f.coords,
-                                          f.cfg.shift, kept, f.rec, kept_cap, err, stream));
-            else if (kept)
-                SVT_TRY(launch_kept_write(f.accept, nc, w.kbn, w.kb, kept, kept_cap, err,
-                                          stream));
-        }
         return SVT_OK;
     }
     PrepassLaunch p{};
@@ -523,8 +528,8 @@ namespace {
 // with hipGetSymbolAddress and used everywhere instead.
 // (The unit kernels' part comes on top of SVT_STATIC_WORK_BYTES.  A batch that the rest admits has
 // fewer than 2^24 words and 12e9 combinations, for they take 2 bytes a word and 12 bytes per 4096
-// combinations there: 1 MiB for the units, 24 MB and 2 MiB for the slices.)
-constexpr int64_t kStaticUnitBytes = 28ll << 20;
+// combinations there: 3 MiB for the units, 24 MB and 2 MiB for the slices.)
+constexpr int64_t kStaticUnitBytes = 30ll << 20;
 static __device__ __align__(256) char scratch[SVT_STATIC_WORK_BYTES + kStaticUnitBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -599,13 +604,13 @@ svt_status process_batch(const svt_fconst *bank, const svt_config *cfg, const sv
     // words in host memory are read once over the bus: the counting kernel leaves a copy, where
     // the workspace has room for one (else both kernels read them in place)
     const bool copy =
-        in_host_memory(words) &&
         work_bytes >= batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, true);
     const int cus = num_cus();
     if (cus <= 0) return SVT_ERR_HIP;
 
     Carver c{static_cast<char *>(d_work)};
-    const BatchWs w = carve_batch(c, word_cap, road_cap, combo_cap, t.tile_combos, copy);
+    BatchWs w = carve_batch(c, word_cap, road_cap, combo_cap, t.tile_combos, copy);
+    w.host_words = copy && in_host_memory(words);
     FusedLaunch f{};
     f.bank = bank;
     f.cfg = *cfg;

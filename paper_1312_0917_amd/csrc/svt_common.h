@@ -303,18 +303,20 @@ struct UnitsLaunch {
     int64_t *d_n_roads;
     int64_t *d_n_combos;
     uint64_t *err;
-    int64_t *kb_counts;        // accepted count per kKeptBlock combinations (null: no kept list)
-    int64_t n_kb;
-    bool kept_only;            // no records; grouped coordinates and block marks for the refit
-    int16_t *coords;
-    int32_t *tile_first_road;
-    int64_t tiles_cap;
+    int64_t *d_n_kept;         // null: no count and no kept list
+    int64_t *kept;             // null: the count alone
+    int64_t kept_cap;
+    bool kept_only;            // no records but those of the kept list
     int64_t *nw_copy;          // workspace: the word count in device memory,
     uint32_t *ticket;          // counters (unit_ticket_bytes),
     void *sets;                // the packed bank (unit_bank_bytes),
     void *rec;                 // running counts per unit (unit_rec_bytes),
     void *tot;                 // totals per range of units (unit_range_bytes),
     void *acc;                 // what slices of units share (unit_acc_bytes),
+    void *keep;                // accepted combinations per unit (unit_keep_bytes),
+    int64_t *keep_groups;      // and per group of units (unit_keep_group_bytes),
+    void *slots;               // accepted combinations (unit_slot_bytes, 16-byte aligned;
+    bool less_slots;           // the smaller number of them),
     uint32_t *copy;            // and the words, when the caller's are in host memory (else null)
     int num_cus;
 };
@@ -327,6 +329,9 @@ hipError_t launch_unpack(const uint32_t *words, int64_t n_words, const svt_confi
 int64_t unit_rec_bytes(int64_t words);
 int64_t unit_range_bytes();
 int64_t unit_acc_bytes(int64_t combos);
+int64_t unit_keep_bytes(int64_t words);
+int64_t unit_keep_group_bytes(int64_t words);
+int64_t unit_slot_bytes(int64_t words, bool less);
 int64_t unit_ticket_bytes();
 int64_t unit_bank_bytes();
 hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, hipEvent_t stop);

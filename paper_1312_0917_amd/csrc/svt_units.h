@@ -42,6 +42,22 @@ struct alignas(16) SliceAcc {
     uint32_t nacc;
     uint32_t arrived;        // slices that have added theirs
 };
+// What a unit's wave leaves for the kept list: the number of its accepted combinations, and where
+// its roads and combinations are.  The accepted combinations themselves wait in the unit's slots,
+// as indices (4 bytes) or with their coordinates (16).  A unit that accepts more than it has slots,
+// or is cut into slices, has kKeepSearch set, and they are found again from the accept flags.
+// With 1024 bytes of slots that is one unit in 1000 of 2048-road events and one in 200 of the
+// uneven ones (512 bytes, where the workspace has no more: 4 and 9 in 100).
+struct UnitKeep {
+    uint32_t count;   // | kKeepSearch
+    uint32_t roads;
+    uint64_t combo, road;  // the unit's first of either
+};
+constexpr uint32_t kKeepSearch = 1u << 31;
+constexpr int kKeepSlots = 1024, kKeepSlotsLess = 512;  // bytes per unit
+constexpr int kKeepGroup = 256;   // units a workgroup of k_unit_keep takes, with a common count,
+constexpr int kKeepStride = 16;   // a 128-byte line apart: every unit adds to one (side by side
+                                  // they held up the fits of 7500 units for 26 us)
 // Totals of a range of units, and the first errors in it (all ones: none).
 struct alignas(16) RangeTot {
     uint32_t roads, events;

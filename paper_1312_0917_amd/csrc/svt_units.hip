@@ -36,8 +36,9 @@ struct CArgs {
     UnitRec *rec;            // per unit
     RangeTot *tot;           // per range
     uint32_t *copy;          // words in device memory (nullable: they are there already)
-    unsigned long long *kb;  // kept-list block counts to clear (nullable)
-    int64_t n_kb;
+    UnitKeep *keep;          // to start at no accepted combination (nullable: no kept list),
+    unsigned long long *group;  // and the counts per kKeepGroup units
+    int64_t n_group;
     SliceAcc *acc;           // to clear
     int64_t n_acc;
 };
@@ -77,8 +78,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
     // with a bank, the last workgroup packs it and counts nothing
     const int ranges = static_cast<int>(gridDim.x) - (a.bank ? 1 : 0);
-    if (a.kb)
-        for (int64_t i = gtid(); i < a.n_kb; i += gstride()) a.kb[i] = 0;
+    if (a.keep)
+        for (int64_t i = gtid(); i < a.n_group; i += gstride()) a.group[i * kKeepStride] = 0;
     for (int64_t i = gtid(); i < a.n_acc; i += gstride()) a.acc[i] = SliceAcc{0, 0, 0};
     if (static_cast<int>(blockIdx.x) == ranges) {
         if (threadIdx.x == 0) {
@@ -175,7 +176,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                        ex_m = lane_value(sme - more, wave);
         const uint32_t ex_r = ex & 0xFFFFu, ex_e = ex >> 16;
         if (u < hi_u) {
-            if (lane == 0) a.rec[u] = UnitRec{roads + ex_r, events + ex_e, combos + with_extra(ex_c, ex_m)};
+            if (lane == 0) {
+                a.rec[u] = UnitRec{roads + ex_r, events + ex_e, combos + with_extra(ex_c, ex_m)};
+                if (a.keep) a.keep[u].count = cs > slice ? kKeepSearch : 0u;
+            }
             if (my_over != ~0u && over_road == ~0u) over_road = roads + ex_r + my_over;
             if (my_set != ~0u && set_road == ~0u) set_road = roads + ex_r + my_set;
         }
@@ -220,10 +224,10 @@ struct UArgs {
     int64_t *d_n_roads;
     int64_t *d_n_combos;
     uint64_t *err;
-    unsigned long long *kb;  // accepted count per kKeptBlock combinations (nullable)
-    int16_t *coords;         // kept-only mode: grouped coordinates for the refit pass
-    int32_t *tile_first_road;
-    int64_t tiles_cap;
+    UnitKeep *keep;          // nullable: no kept list
+    unsigned long long *group;
+    uint32_t *slots;         // slot_bytes per unit
+    uint32_t slot_bytes;
     SliceAcc *acc;
 };
 
@@ -380,7 +384,8 @@ __device__ __forceinline__ Fit fit_one(const RoadRow &r, const UnitSet &c, const
 template <int MODE, int REC>
 __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveLds &W, int c0,
                                             int c1, uint32_t first_item, uint32_t from_item,
-                                            uint32_t n_items, int64_t GB, int32_t shift, uint32_t qlmask) {
+                                            uint32_t n_items, int64_t GB, int32_t shift,
+                                            uint32_t qlmask, uint32_t *keep_at, uint32_t &kept) {
     constexpr int J0 = REC == kRecNone ? 3 : 0;
     // Windows end where a 128-byte line of the int32 record arrays does (8 groups): a line
     // written in two parts reaches memory in parts.  On 4000 events of 2048 roads windows that
@@ -470,17 +475,39 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             for (int e = 0; e < 4; ++e)
                 acc |= static_cast<int64_t>(f.chi2[e]) <= a.cfg.chi2_cut ? 1u << e : 0u;
             acc &= slots;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if ((acc >> e) & 1u)
-                    atomicMin(&W.key[ri], static_cast<unsigned long long>(
-                                              best_key(static_cast<int64_t>(f.chi2[e]),
-                                                       static_cast<uint32_t>(k0 + e))));
-            if (acc) {
-                atomicAdd(&W.nacc[ri], static_cast<uint32_t>(__popc(acc)));
-                if (a.kb)
-                    atomicAdd(a.kb + (GB + rel) / kKeptBlock,
-                              static_cast<unsigned long long>(__popc(acc)));
+            const uint32_t cnt = static_cast<uint32_t>(__popc(acc));
+            uint32_t pos = 0;
+            if (REC == kRecNone || a.keep) {
+                // in the order of the combinations: the lanes' items are, and their slots
+                const uint32_t upto = scan64(cnt);
+                pos = kept + upto - cnt;
+                kept += lane_value(upto, 63);
+            }
+            if (acc) atomicAdd(&W.nacc[ri], cnt);
+            for (uint32_t m = acc; m; m &= m - 1, ++pos) {  // seldom more than one
+                const bool odd = (m & 5u) == 0 || (m & 3u) == 2u, high = (m & 3u) == 0;
+                auto pick = [&](auto v0, auto v1, auto v2, auto v3) {
+                    const auto l = odd ? v1 : v0, h = odd ? v3 : v2;
+                    return high ? h : l;
+                };
+                const uint32_t e = (odd ? 1u : 0u) + (high ? 2u : 0u);
+                const uint64_t c2 = pick(f.chi2[0], f.chi2[1], f.chi2[2], f.chi2[3]);
+                atomicMin(&W.key[ri],
+                          static_cast<unsigned long long>(best_key(static_cast<int64_t>(c2),
+                                                                   static_cast<uint32_t>(k0) + e)));
+                if ((REC == kRecNone || a.keep) && keep_at) {
+                    const uint32_t c = static_cast<uint32_t>(rel) + e;
+                    if (REC == kRecNone) {
+                        if (pos < a.slot_bytes / 16)
+                            reinterpret_cast<uint4 *>(keep_at)[pos] = make_uint4(
+                                c | (ma.w >> 16 << 24),
+                                static_cast<uint32_t>(pick(x01[0], x01[1], x01[2], x01[3])),
+                                static_cast<uint32_t>(pick(x23[0], x23[1], x23[2], x23[3])),
+                                static_cast<uint32_t>(pick(x4[0], x4[1], x4[2], x4[3])));
+                    } else if (pos < a.slot_bytes / 4) {
+                        keep_at[pos] = c;
+                    }
+                }
             }
         }
         // ---- groups cut by a road boundary: the first item's lane takes the others' slots
@@ -589,8 +616,8 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
 // left over, for a further call, or 0.
 template <int REC, bool SLICED>
 __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds &W, int64_t u,
-                                        uint32_t slice, uint32_t slice_len, int c0, int64_t n,
-                                        int64_t per) {
+                                        uint32_t slice, uint32_t slice_len, int c0, uint32_t &kept,
+                                        int64_t n, int64_t per) {
     const int lane = lane_id();
     const int32_t shift = hot.cfg.shift;
     const uint32_t qlmask = (1u << shift) - 1u;
@@ -660,10 +687,6 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 a.best.p1[r] = INT32_MIN;
                 a.best.p2[r] = INT32_MIN;
                 a.best.chi2[r] = INT64_MAX;
-            } else if (REC == kRecNone) {  // the first road of each block of the kept list
-                const int64_t b = CB0 + cb;
-                for (int64_t t = (b + kKeptBlock - 1) / kKeptBlock; t * kKeptBlock < b + c; ++t)
-                    if (t < a.tiles_cap) a.tile_first_road[t] = static_cast<int32_t>(r);
             }
         }
     }
@@ -689,22 +712,6 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
             hits += sc.hit[e];
         }
     }
-    if (REC == kRecNone && table) {  // the kept list's refit reads the grouped coordinates
-#pragma unroll
-        for (int e = 0; e < kUnitLane; ++e) {
-            const uint32_t f = wd[e] >> 24;
-            if (f != 255u) {
-                const uint4 b = W.road[f].b;
-                const uint32_t l = (wd[e] >> 13) & 7u;
-                uint32_t p = b.y + ((wd[e] >> 16) & 0xFu);
-#pragma unroll
-                for (int q = 0; q < SVT_N_LAYERS - 1; ++q)
-                    p += static_cast<uint32_t>(q) < l ? nh_of(b.w, q) : 0u;
-                L.args.coords[base + p] = static_cast<int16_t>(w_coord(wd[e]));
-            }
-        }
-    }
-
     // ---- one road with combinations per lane: roads c0 .. c1 - 1 are fitted now -----------------
     const bool road = lane < nf && lane >= c0;
     W.mark[lane] = 0;
@@ -736,7 +743,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         upto = take ? (upto < n_it ? upto : n_it) : 0;
         from_item = lane_value(scan64(before), 63);
         n_items = lane_value(scan64(upto), 63);
-        if (from_item == n_items) return c1 < nf ? c1 : 0;
+        if (from_item == n_items && c1 < nf) return c1;
     }
     if (take) {
         RoadRow row;
@@ -777,12 +784,15 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         }
     }
     lds_order();
+    uint32_t *keep_at = nullptr;
+    if ((REC == kRecNone || hot.keep) && slices == 1)
+        keep_at = L.args.slots + u * (hot.slot_bytes / 4);
     if (narrow)
         fit_windows<kFitNarrow, REC>(hot, L, W, c0, c1, item, from_item, n_items, GB, shift,
-                                     qlmask);
+                                     qlmask, keep_at, kept);
     else
         fit_windows<kFitSplit, REC>(hot, L, W, c0, c1, item, from_item, n_items, GB, shift,
-                                    qlmask);
+                                    qlmask, keep_at, kept);
     lds_order();
 
     // ---- best tracks ----------------------------------------------------------------------------
@@ -855,7 +865,20 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         }
     }
     lds_order();
-    return c1 < nf ? c1 : 0;
+    if (c1 < nf) return c1;
+    if ((REC == kRecNone || hot.keep) && kept > 0 && lane == 0) {
+        UnitKeep &k = L.args.keep[u];
+        const uint32_t most = hot.slot_bytes / (REC == kRecNone ? 16 : 4);
+        if (slices > 1)
+            atomicAdd(&k.count, kept);
+        else
+            k.count = kept | (kept > most ? kKeepSearch : 0u);
+        k.roads = nr;
+        k.combo = static_cast<uint64_t>(CB0);
+        k.road = static_cast<uint64_t>(R0);
+        atomicAdd(L.args.group + u / kKeepGroup * kKeepStride, static_cast<unsigned long long>(kept));
+    }
+    return 0;
 }
 
 // The unit and slice of the batch's extra slice number e (slices past their unit's first, counted
@@ -926,8 +949,9 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
             }
         }
         int c = 0;
+        uint32_t kept = 0;
         do {
-            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, slice_len, c, n, per);
+            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, slice_len, c, kept, n, per);
         } while (c != 0);
         ++u;
     }
@@ -1029,6 +1053,202 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
         run_units<REC, false>(a, L, n, nu, per, n_ranges, extra);
     else
         run_units<REC, true>(a, L, n, nu, per, n_ranges, extra);
+}
+
+// ---- the kept list ---------------------------------------------------------------------------------
+// The accepted combinations in ascending order, and in kept-only mode (ONLY) their fit values.  A
+// workgroup takes kKeepGroup units: the groups' counts before it give its place in the list, its
+// units' counts theirs.  The accepted combinations of all its units are then spread over the
+// threads, each fitting from the coordinates that the unit's wave left (neither the accept flags
+// nor the road table is read: with those, scan and refit took 410 us behind the fits of 4e8
+// combinations).
+struct KArgs {
+    const int64_t *d_nw;
+    int64_t word_cap;
+    const UnitKeep *keep;
+    const unsigned long long *group;
+    const uint32_t *slots;
+    uint32_t slot_bytes;
+    const UnitSet *sets;
+    const uint32_t *words;
+    svt_roads roads;
+    const uint8_t *accept;
+    svt_fitrec rec;
+    int32_t shift;
+    int64_t *kept;      // nullable: the count alone
+    int64_t kept_cap;
+    int64_t *d_n_kept;
+    uint64_t *err;
+    int32_t parts;      // workgroups that share a group
+};
+
+__device__ __forceinline__ void keep_record(const KArgs &a, const UnitSet &c, int64_t pos,
+                                            int32_t x01, int32_t x23, int32_t x4) {
+    const uint32_t qlmask = (1u << a.shift) - 1u;
+    int32_t v[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const uint4 w = c.row[j];
+        int32_t acc = dot2(static_cast<int32_t>(w.x), x01, static_cast<int32_t>(w.w & qlmask));
+        acc = dot2(static_cast<int32_t>(w.y), x23, acc);
+        acc = dot2(static_cast<int32_t>(w.z), x4, acc);
+        v[j] = (acc >> a.shift) + (static_cast<int32_t>(w.w) >> a.shift);
+    }
+    a.rec.p0[pos] = v[0];
+    a.rec.p1[pos] = v[1];
+    a.rec.p2[pos] = v[2];
+    a.rec.chi2[pos] = static_cast<int64_t>(v[3]) * v[3] + static_cast<int64_t>(v[4]) * v[4] +
+                      static_cast<int64_t>(v[5]) * v[5];
+    if (a.rec.c0) a.rec.c0[pos] = v[3];
+    if (a.rec.c1) a.rec.c1[pos] = v[4];
+    if (a.rec.c2) a.rec.c2[pos] = v[5];
+}
+
+template <bool ONLY>
+__global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
+    __shared__ uint32_t s_pre[kKeepGroup];    // accepted before the unit, in the group
+    __shared__ uint32_t s_quick[kKeepGroup];  // those of them that wait in slots
+    __shared__ uint64_t s_first[kKeepGroup];  // the unit's first combination
+    __shared__ int32_t s_cb[kKeepGroup];      // a searched unit's roads: first combination
+    __shared__ uint8_t s_list[kKeepGroup];    // the units to be searched
+    __shared__ uint64_t s_tmp[kKeepGroup / kWaveSize + 1];
+    const int tid = threadIdx.x;
+    if (has_error(a.err)) {
+        if (blockIdx.x == 0 && tid == 0) *a.d_n_kept = -1;
+        return;
+    }
+    const int64_t nw = *a.d_nw;
+    const int64_t n = nw < 0 ? 0 : nw > a.word_cap ? a.word_cap : nw;
+    const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
+    const int64_t groups = (nu + kKeepGroup - 1) / kKeepGroup;
+    const int64_t g = blockIdx.x / a.parts;
+    const int part = static_cast<int>(blockIdx.x) % a.parts;
+    if (blockIdx.x == 0) {  // the total, and whether the list has room for it
+        uint64_t sum = 0;
+        for (int64_t i = tid; i < groups; i += kKeepGroup) sum += a.group[i * kKeepStride];
+        sum = block_sum<uint64_t, kKeepGroup>(sum, s_tmp);
+        if (tid == 0) {
+            *a.d_n_kept = static_cast<int64_t>(sum);
+            if (a.kept && static_cast<int64_t>(sum) > a.kept_cap)
+                report(a.err, SVT_ERRCLASS_CAPACITY, 2);
+        }
+    }
+    if (g >= groups || !a.kept || a.group[g * kKeepStride] == 0) return;
+    uint64_t before = 0;
+    for (int64_t i = tid; i < g; i += kKeepGroup) before += a.group[i * kKeepStride];
+    const int64_t base =
+        static_cast<int64_t>(block_sum<uint64_t, kKeepGroup>(before, s_tmp));
+    const int64_t u0 = g * kKeepGroup;
+    UnitKeep mine{};
+    if (u0 + tid < nu) mine = a.keep[u0 + tid];
+    const uint32_t cnt = mine.count & ~kKeepSearch;
+    const uint32_t quick = mine.count & kKeepSearch ? 0 : cnt;
+    uint64_t tot;
+    // (26 bits of accepted combinations and 17 of those in slots are what 256 units can hold)
+    const bool search = cnt > quick;
+    const uint64_t ex = block_excl_scan<uint64_t, kKeepGroup>(
+        cnt | (static_cast<uint64_t>(quick) << 28) | (static_cast<uint64_t>(search) << 48), s_tmp,
+        tot);
+    s_pre[tid] = static_cast<uint32_t>(ex & 0xFFFFFFFu);
+    s_quick[tid] = static_cast<uint32_t>(ex >> 28) & 0xFFFFFu;
+    s_first[tid] = mine.combo;
+    if (search) s_list[ex >> 48] = static_cast<uint8_t>(tid);
+    __syncthreads();
+    const uint32_t n_quick = static_cast<uint32_t>(tot >> 28) & 0xFFFFFu;
+    const int n_search = static_cast<int>(tot >> 48);
+    for (uint32_t i = part * kKeepGroup + tid; i < n_quick; i += a.parts * kKeepGroup) {
+        int lo = 0, hi = kKeepGroup - 1;  // last unit that starts at or before i
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_quick[mid] <= i) lo = mid; else hi = mid - 1;
+        }
+        const uint32_t k = i - s_quick[lo];
+        const int64_t pos = base + s_pre[lo] + k;
+        if (pos >= a.kept_cap) continue;
+        const int64_t GB = static_cast<int64_t>(s_first[lo] & ~uint64_t{3});
+        const uint32_t *slot = a.slots + (u0 + lo) * (a.slot_bytes / 4);
+        if (ONLY) {
+            const uint4 v = reinterpret_cast<const uint4 *>(slot)[k];
+            a.kept[pos] = GB + (v.x & 0xFFFFFFu);
+            keep_record(a, a.sets[v.x >> 24], pos, static_cast<int32_t>(v.y),
+                        static_cast<int32_t>(v.z), static_cast<int32_t>(v.w));
+        } else {
+            a.kept[pos] = GB + slot[k];
+        }
+    }
+    // ---- units whose accepted combinations are found again: their accept flags in order, each
+    // one's road by its first combination and its hits by walking the road's words
+    for (int sq = part; sq < n_search; sq += a.parts) {
+        const int q = s_list[sq];
+        const UnitKeep k = a.keep[u0 + q];
+        const int nr = static_cast<int>(k.roads);
+        const int64_t CB0 = static_cast<int64_t>(k.combo), R0 = static_cast<int64_t>(k.road);
+        __syncthreads();
+        if (tid < nr) s_cb[tid] = static_cast<int32_t>(a.roads.combo_begin[R0 + tid] - CB0);
+        __syncthreads();
+        const int len = s_cb[nr - 1] + a.roads.ncombo[R0 + nr - 1];
+        int64_t at = base + s_pre[q];
+        // up to 64 flags per thread, in whole 4-byte words where those lie inside the unit's flags
+        const int off = static_cast<int>(CB0 & 3);
+        int per = (len + off + kKeepGroup - 1) / kKeepGroup;
+        per = per > 60 ? 64 : (per + 3) & ~3;
+        for (int i0 = -off; i0 < len; i0 += per * kKeepGroup) {
+            const int mine0 = i0 + per * tid;
+            uint64_t bits = 0;
+            for (int v = 0; 4 * v < per; ++v) {
+                const int i = mine0 + 4 * v;
+                uint32_t w = 0;
+                if (i >= 0 && i + 4 <= len) {
+                    w = *reinterpret_cast<const uint32_t *>(a.accept + CB0 + i);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (i + e >= 0 && i + e < len)
+                            w |= static_cast<uint32_t>(a.accept[CB0 + i + e]) << (8 * e);
+                }
+                // flag bytes are 0 or 1: bits 0, 8, 16, 24 to 4 v .. 4 v + 3
+                bits |= static_cast<uint64_t>(((w * 0x10204080u) >> 28) & 0xFu) << (4 * v);
+            }
+            uint64_t all;
+            int64_t pos = at + static_cast<int64_t>(block_excl_scan<uint64_t, kKeepGroup>(
+                                   static_cast<uint64_t>(__popcll(bits)), s_tmp, all));
+            at += static_cast<int64_t>(all);
+            for (; bits && pos < a.kept_cap; bits &= bits - 1, ++pos) {
+                const int i = mine0 + __builtin_ctzll(bits);
+                a.kept[pos] = CB0 + i;
+                if (!ONLY) continue;
+                int lo = 0, hi = nr - 1;  // last road that starts at or before i
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (s_cb[mid] <= i) lo = mid; else hi = mid - 1;
+                }
+                const int64_t r = R0 + lo;
+                const uint32_t nh = a.roads.nhits[r];
+                uint32_t c = static_cast<uint32_t>(i - s_cb[lo]);
+                uint32_t want = 0, words = 0;  // hit index per layer, 6 bits a layer
+#pragma unroll
+                for (int l = SVT_N_LAYERS - 1; l >= 0; --l) {  // layer 0 most significant
+                    const uint32_t nl = nh_of(nh, l);
+                    want |= (c % nl) << (6 * l);
+                    c /= nl;
+                    words += nl;
+                }
+                const uint32_t *w = a.words + a.roads.hit_begin[r];
+                int32_t x[SVT_N_LAYERS] = {0, 0, 0, 0, 0};
+                uint32_t seen = 0;
+                for (uint32_t j = 0; j < words; ++j) {
+                    const uint32_t y = w[j], l = w_layer(y);
+                    const bool hit = ((seen >> (6 * l)) & 63u) == ((want >> (6 * l)) & 63u);
+                    seen += 1u << (6 * l);
+#pragma unroll
+                    for (int q2 = 0; q2 < SVT_N_LAYERS; ++q2)
+                        if (hit && l == static_cast<uint32_t>(q2)) x[q2] = w_coord(y);
+                }
+                keep_record(a, a.sets[a.roads.set[r]], pos, pack16(x[0], x[1]), pack16(x[2], x[3]),
+                            x[4]);
+            }
+        }
+    }
 }
 
 // ---- the unpack stage on its own ------------------------------------------------------------------
@@ -1144,6 +1364,15 @@ int64_t unit_slices(int64_t combos) {
 int64_t unit_acc_bytes(int64_t combos) {
     return static_cast<int64_t>(sizeof(SliceAcc)) * unit_slices(combos);
 }
+int64_t unit_keep_bytes(int64_t words) {
+    return static_cast<int64_t>(sizeof(UnitKeep)) * unit_count(words);
+}
+int64_t unit_keep_group_bytes(int64_t words) {
+    return 8 * kKeepStride * ((unit_count(words) + kKeepGroup - 1) / kKeepGroup);
+}
+int64_t unit_slot_bytes(int64_t words, bool less) {
+    return (less ? kKeepSlotsLess : kKeepSlots) * unit_count(words);
+}
 int64_t unit_ticket_bytes() { return 4ll * kDealers * kDealerStride; }
 int64_t unit_bank_bytes() { return static_cast<int64_t>(sizeof(UnitSet)) * 256; }
 
@@ -1189,8 +1418,9 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     c.rec = static_cast<UnitRec *>(p.rec);
     c.tot = static_cast<RangeTot *>(p.tot);
     c.copy = p.copy;
-    c.kb = reinterpret_cast<unsigned long long *>(p.kb_counts);
-    c.n_kb = p.kb_counts ? p.n_kb : 0;
+    c.keep = p.d_n_kept ? static_cast<UnitKeep *>(p.keep) : nullptr;
+    c.group = reinterpret_cast<unsigned long long *>(p.keep_groups);
+    c.n_group = (units + kKeepGroup - 1) / kKeepGroup;
     c.acc = static_cast<SliceAcc *>(p.acc);
     c.n_acc = unit_slices(p.combo_cap);
     hipLaunchKernelGGL(k_unit_count, dim3(ranges + 1), dim3(kThreads), 0, s,
@@ -1216,11 +1446,11 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     a.d_n_roads = p.d_n_roads;
     a.d_n_combos = p.d_n_combos;
     a.err = p.err;
-    a.kb = c.kb;
+    a.keep = c.keep;
+    a.group = c.group;
+    a.slots = static_cast<uint32_t *>(p.slots);
+    a.slot_bytes = p.less_slots ? kKeepSlotsLess : kKeepSlots;
     a.acc = c.acc;
-    a.coords = p.kept_only ? p.coords : nullptr;
-    a.tile_first_road = p.kept_only ? p.tile_first_road : nullptr;
-    a.tiles_cap = p.tiles_cap;
     const int grid = static_cast<int>(units < p.num_cus ? units : p.num_cus);
     if (start && (e = hipEventRecord(start, s)) != hipSuccess) return e;
     if (p.kept_only)
@@ -1231,7 +1461,34 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
         hipLaunchKernelGGL((k_unit_fit<kRecFit>), dim3(grid), dim3(kThreads), 0, s, a);
     e = hipGetLastError();
     if (e == hipSuccess && stop) e = hipEventRecord(stop, s);
-    return e;
+    if (e != hipSuccess || !p.d_n_kept) return e;
+    KArgs k{};
+    k.d_nw = p.nw_copy;
+    k.word_cap = p.word_cap;
+    k.keep = c.keep;
+    k.group = c.group;
+    k.slots = a.slots;
+    k.slot_bytes = a.slot_bytes;
+    k.sets = c.sets;
+    k.words = a.words;
+    k.roads = p.roads;
+    k.accept = p.accept;
+    k.rec = p.out;
+    k.shift = p.cfg.shift;
+    k.kept = p.kept;
+    k.kept_cap = p.kept_cap;
+    k.d_n_kept = p.d_n_kept;
+    k.err = p.err;
+    // few groups are shared by several workgroups each, to fill the chip and for the sliced units
+    // of a small batch
+    k.parts = c.n_group < 2048 ? static_cast<int32_t>(2048 / c.n_group) : 1;
+    if (k.parts > 32) k.parts = 32;
+    const int kgrid = p.kept ? static_cast<int>(c.n_group) * k.parts : 1;
+    if (p.kept_only)
+        hipLaunchKernelGGL(k_unit_keep<true>, dim3(kgrid), dim3(kKeepGroup), 0, s, k);
+    else
+        hipLaunchKernelGGL(k_unit_keep<false>, dim3(kgrid), dim3(kKeepGroup), 0, s, k);
+    return hipGetLastError();
 }
 
 }  // namespace svt
