@@ -97,6 +97,20 @@ __device__ __forceinline__ uint32_t scan64(uint32_t x) {
     x += dpp<0x143, 0xC>(x);
     return x;
 }
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint64_t dpp64(uint64_t x) {
+    return dpp<CTRL, ROWS>(static_cast<uint32_t>(x)) |
+           (static_cast<uint64_t>(dpp<CTRL, ROWS>(static_cast<uint32_t>(x >> 32))) << 32);
+}
+__device__ __forceinline__ uint64_t scan64(uint64_t x) {
+    x += dpp64<0x111>(x);
+    x += dpp64<0x112>(x);
+    x += dpp64<0x114>(x);
+    x += dpp64<0x118>(x);
+    x += dpp64<0x142, 0xA>(x);
+    x += dpp64<0x143, 0xC>(x);
+    return x;
+}
 // The same over the first 16 lanes (each row of 16 on its own).
 __device__ __forceinline__ uint32_t scan16(uint32_t x) {
     x += dpp<0x111>(x);

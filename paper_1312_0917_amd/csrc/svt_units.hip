@@ -92,7 +92,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     const int64_t per = units_per_range(nu, ranges);
     const int64_t lo_u = per * blockIdx.x;
     const int64_t hi_u = lo_u + per < nu ? lo_u + per : nu;
-    if (lo_u >= hi_u) return;
+    if (lo_u >= hi_u) {
+        if (threadIdx.x == 0) a.tot[blockIdx.x] = RangeTot{0, 0, 0, ~0u, ~0u, ~0u, 0};
+        return;
+    }
     uint2 *S = s_ent[wave];
     const uint32_t slice = static_cast<uint32_t>(slice_combos(nu));
     uint32_t roads = 0, events = 0;  // of the range, before the units in hand
@@ -272,7 +275,7 @@ struct RangeLds {
 struct BatchTotals {
     int64_t n_roads, n_combos;
     uint64_t err;    // the first error found in the words, or a capacity that is too small
-    uint32_t extra;
+    uint32_t extra, events;
 };
 
 struct ULds {
@@ -957,62 +960,73 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
     }
 }
 
-// Scan the totals of the n_ranges ranges (`per` units each); all threads of the workgroup.
-__device__ __forceinline__ BatchTotals scan_ranges(const RangeTot *tot, int n_ranges, int64_t per,
+// Scan the totals of the ranges, whose totals t the first threads have loaded (`per` units each);
+// all threads of the workgroup.
+__device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges, int64_t per,
                                                    int64_t nw, int64_t word_cap, int64_t road_cap,
                                                    int64_t combo_cap, RangeLds &L) {
     const int tid = threadIdx.x, wave = tid / kWaveSize, lane = lane_id();
-    RangeTot t{};
-    if (tid < n_ranges) t = tot[tid];
+    const int waves = (ranges + kWaveSize - 1) / kWaveSize;  // that hold ranges, at most 8
     const uint64_t cc = t.combos & kComboMask;
     const uint32_t ee = static_cast<uint32_t>(t.combos >> kExtraShift);
-    const uint64_t ir = wave_incl_scan(static_cast<uint64_t>(t.roads)), ic = wave_incl_scan(cc);
-    const uint32_t iv = scan64(t.events), ie = scan64(ee);
-    if (lane == kWaveSize - 1) {
-        L.roads[wave] = ir;
-        L.combos[wave] = ic;
-        L.events[wave] = iv;
-        L.extra[wave] = ie;
+    RangeBase b{};
+    if (wave < waves) {
+        const uint64_t ir = scan64(static_cast<uint64_t>(t.roads)), ic = scan64(cc);
+        const uint32_t iv = scan64(t.events), ie = scan64(ee);
+        b = RangeBase{ir - t.roads, ic - cc, iv - t.events, ie - ee};
+        if (lane == kWaveSize - 1) {
+            L.roads[wave] = ir;
+            L.combos[wave] = ic;
+            L.events[wave] = iv;
+            L.extra[wave] = ie;
+        }
+        // the first error, in the ranges' order; a road's index from the wave's first range
+        uint64_t err = SVT_NO_ERROR;
+        const bool bad = tid < ranges && (t.bad_word & t.over_road & t.set_road) != ~0u;
+        if (__ballot(bad)) {
+            auto note = [&](uint64_t cls, uint32_t idx, uint64_t from) {
+                const uint64_t v = (cls << 56) | (from + idx);
+                if (bad && idx != ~0u && v < err) err = v;
+            };
+            note(SVT_ERRCLASS_LAYER, t.bad_word, static_cast<uint64_t>(tid * per) * kUnitWords);
+            note(SVT_ERRCLASS_HITS, t.over_road, b.roads);
+            note(SVT_ERRCLASS_SET, t.set_road, b.roads);
+#pragma unroll
+            for (int d = kWaveSize / 2; d > 0; d >>= 1) {
+                const uint64_t ov = __shfl_xor(err, d, kWaveSize);
+                err = ov < err ? ov : err;
+            }
+        }
+        if (lane == 0) L.err[wave] = err;
     }
     __syncthreads();
-    RangeBase b{ir - t.roads, ic - cc, iv - t.events, ie - ee};
-    BatchTotals all{0, 0, SVT_NO_ERROR, 0};
-    for (int w = 0; w < kUnitWaves; ++w) {
-        if (w < wave) {
-            b.roads += L.roads[w];
-            b.combos += L.combos[w];
-            b.events += L.events[w];
-            b.extra += L.extra[w];
+    BatchTotals all{0, 0, SVT_NO_ERROR, 0, 0};
+    uint64_t first = SVT_NO_ERROR;
+    for (int w = 0; w < waves; ++w) {
+        uint64_t e = L.err[w];
+        if (e != SVT_NO_ERROR && (e >> 56) != SVT_ERRCLASS_LAYER)
+            e += static_cast<uint64_t>(all.n_roads);  // roads before the wave's ranges
+        first = e < first ? e : first;
+        if (w == wave) {
+            b.roads += static_cast<uint64_t>(all.n_roads);
+            b.combos += static_cast<uint64_t>(all.n_combos);
+            b.events += all.events;
+            b.extra += all.extra;
         }
         all.n_roads += static_cast<int64_t>(L.roads[w]);
         all.n_combos += static_cast<int64_t>(L.combos[w]);
+        all.events += L.events[w];
         all.extra += L.extra[w];
     }
-    uint64_t err = SVT_NO_ERROR;
-    if (tid < n_ranges) {
-        L.base[tid] = b;
-        auto note = [&](uint64_t cls, uint32_t idx, uint64_t from) {
-            const uint64_t v = (cls << 56) | (from + idx);
-            if (idx != ~0u && v < err) err = v;
-        };
-        note(SVT_ERRCLASS_LAYER, t.bad_word, static_cast<uint64_t>(tid * per) * kUnitWords);
-        note(SVT_ERRCLASS_HITS, t.over_road, b.roads);
-        note(SVT_ERRCLASS_SET, t.set_road, b.roads);
-    }
-#pragma unroll
-    for (int d = kWaveSize / 2; d > 0; d >>= 1) {
-        const uint64_t ov = __shfl_xor(err, d, kWaveSize);
-        err = ov < err ? ov : err;
-    }
-    if (lane == 0) L.err[wave] = err;
-    __syncthreads();
+    if (tid < ranges) L.base[tid] = b;
     auto cap_err = [](uint64_t i) {
         return (static_cast<uint64_t>(SVT_ERRCLASS_CAPACITY) << 56) | i;
     };
     if (nw > word_cap) all.err = cap_err(3);
     if (all.n_combos > combo_cap) all.err = cap_err(1);
     if (all.n_roads > road_cap) all.err = cap_err(0);
-    for (int w = 0; w < kUnitWaves; ++w) all.err = L.err[w] < all.err ? L.err[w] : all.err;
+    all.err = first < all.err ? first : all.err;
+    __syncthreads();
     return all;
 }
 
@@ -1020,11 +1034,10 @@ template <int REC>
 __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
     __shared__ ULds L;
     const int tid = threadIdx.x;
+    // everything from memory at once: nothing here waits for the word count
+    RangeTot t{};
+    if (tid < a.ranges) t = a.tot[tid];
     const int64_t nw = *a.d_nw;
-    const int64_t n = nw < 0 ? 0 : nw > a.word_cap ? a.word_cap : nw;
-    const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
-    const int64_t per = units_per_range(nu, a.ranges);
-    const int n_ranges = nu > 0 ? static_cast<int>((nu + per - 1) / per) : 0;
     {
         const uint4 *src = reinterpret_cast<const uint4 *>(a.sets);
         uint4 *dst = reinterpret_cast<uint4 *>(L.bank);
@@ -1039,8 +1052,12 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
         if (tid < static_cast<int>(sizeof(UArgs) / 4))
             reinterpret_cast<uint32_t *>(&L.args)[tid] = src[tid];
     }
-    const BatchTotals all = scan_ranges(a.tot, n_ranges, per, nw, a.word_cap, a.road_cap,
-                                        a.combo_cap, L.range);
+    const int64_t n = nw < 0 ? 0 : nw > a.word_cap ? a.word_cap : nw;
+    const int64_t nu = (n + kUnitWords - 1) / kUnitWords;
+    const int64_t per = units_per_range(nu, a.ranges);
+    const int n_ranges = a.ranges;
+    const BatchTotals all =
+        scan_ranges(t, a.ranges, per, nw, a.word_cap, a.road_cap, a.combo_cap, L.range);
     if (blockIdx.x == 0 && tid == 0) {
         *a.err = all.err;
         *a.d_n_roads = all.n_roads;
@@ -1281,9 +1298,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     TWaveLds &W = s_wave[wave];
     const int64_t nu = (a.n + kUnitWords - 1) / kUnitWords;
     const int64_t per = units_per_range(nu, a.ranges);
-    const int n_ranges = nu > 0 ? static_cast<int>((nu + per - 1) / per) : 0;
-    const BatchTotals all = scan_ranges(a.tot, n_ranges, per, a.n, a.n, a.road_cap, INT64_MAX,
-                                        s_range);
+    RangeTot t{};
+    if (static_cast<int>(threadIdx.x) < a.ranges) t = a.tot[threadIdx.x];
+    const BatchTotals all =
+        scan_ranges(t, a.ranges, per, a.n, a.n, a.road_cap, INT64_MAX, s_range);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *a.err = all.err;
         *a.d_n_roads = all.n_roads;
