@@ -34,8 +34,7 @@
  *   - The library allocates no device memory.  Scratch comes from the caller's workspace
  *     (d_work, work_bytes; size from the matching *_workspace function, 256-byte aligned), or
  *     for svt_process_batch_static from a static array in the library's code object.  The
- *     only other library-owned objects are the HIP graphs cached by svt_process_batch, freed
- *     by svt_release_graphs().
+ *     library keeps nothing else between calls.
  *   - Every call only enqueues work on `stream` and returns; nothing synchronises.
  *   - The return value reports host-side checks: SVT_OK, SVT_ERR_ARG (null pointer, negative
  *     size, bad configuration, misaligned output), SVT_ERR_HIP (a launch failed).  On an error
@@ -219,8 +218,10 @@ svt_status svt_select(const svt_config *cfg, const svt_roads *roads, int64_t n_r
  * a captured graph can be replayed for any batch up to word_cap (at most 2^31 - 1 words;
  * larger capacities are SVT_ERR_ARG, and svt_batch_workspace returns -1 for them).
  * flags: SVT_BATCH_GRAPH
- * captures the launch sequence in a HIP graph on first use (keyed by every argument) and
- * replays it afterwards.  kept may be NULL; with d_n_kept also NULL no accepted count and no
+ * asks for the cheapest way to repeat the pass on one stream.  It was a captured graph; since a
+ * pass is two or three launches, launching them is (a replay costs the host 18 us where they cost
+ * 8 to 10), so the flag changes nothing now but what it refuses: SVT_ERR_HIP on the null stream
+ * and on a stream under capture, and no timing events.  kept may be NULL; with d_n_kept also NULL no accepted count and no
  * kept list are produced.  Resets *d_err. */
 #define SVT_BATCH_GRAPH 1
 /* flags: SVT_BATCH_KEPT_ONLY writes no per-combination records -- the output a trigger
@@ -303,7 +304,7 @@ svt_status svt_gather_results(const svt_roads *roads, const svt_best *best, int6
                               const uint64_t *d_err, void *out, int64_t out_roads,
                               hipStream_t stream);
 
-/* Destroy every cached graph (call before freeing buffers a cached graph refers to). */
+/* Once destroyed the graphs cached for SVT_BATCH_GRAPH; none is kept now, and it does nothing. */
 void svt_release_graphs(void);
 
 /* Write to `out` the launch parameters svt_process_batch uses for `tune` (NULL or zero fields

@@ -5,8 +5,6 @@
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <tuple>
-#include <vector>
 
 #include "svt_common.h"
 
@@ -183,18 +181,6 @@ int num_cus() {
     } while (0)
 
 hipEvent_t g_ev_start = nullptr, g_ev_stop = nullptr;
-std::mutex g_graph_mu;
-
-using GraphKey = std::vector<uint64_t>;
-struct GraphEntry {
-    hipGraph_t graph;
-    hipGraphExec_t exec;
-};
-std::map<GraphKey, GraphEntry> &graph_cache() {
-    static std::map<GraphKey, GraphEntry> m;
-    return m;
-}
-
 }  // namespace
 
 extern "C" {
@@ -634,54 +620,20 @@ svt_status process_batch(const svt_fconst *bank, const svt_config *cfg, const sv
     f.num_cus = cus;
     f.kept_only = kept_only;
 
-    if (!(flags & SVT_BATCH_GRAPH)) {
-        const bool timing = g_ev_start && g_ev_stop;
-        return batch_sequence(f, w, word_cap, road_cap, combo_cap, kept, kept_cap, d_n_kept,
-                              timing, stream);
-    }
-
-    // graph path: key on every value the launch sequence bakes in
-    int dev = 0;
-    SVT_TRY(hipGetDevice(&dev));
-    auto u = [](const void *p) { return static_cast<uint64_t>(reinterpret_cast<uintptr_t>(p)); };
-    GraphKey key = {static_cast<uint64_t>(dev), u(stream), u(bank), u(words), u(d_n_words),
-                    static_cast<uint64_t>(word_cap), static_cast<uint64_t>(road_cap),
-                    static_cast<uint64_t>(combo_cap), static_cast<uint64_t>(kept_cap),
-                    u(roads->event), u(roads->set), u(roads->hit_begin), u(roads->nhits),
-                    u(roads->combo_begin), u(roads->ncombo), u(rec->p0), u(rec->p1), u(rec->p2),
-                    u(rec->chi2), u(rec->c0), u(rec->c1), u(rec->c2), u(accept), u(best->n_accept),
-                    u(best->k), u(best->p0), u(best->p1), u(best->p2), u(best->chi2), u(kept),
-                    u(d_n_roads), u(d_n_combos), u(d_n_kept), u(d_err), u(d_work),
-                    static_cast<uint64_t>(work_bytes), static_cast<uint64_t>(cfg->shift),
-                    static_cast<uint64_t>(cfg->chi2_cut), static_cast<uint64_t>(cfg->max_hits),
-                    static_cast<uint64_t>(cfg->n_sets), static_cast<uint64_t>(t.tile_combos),
-                    static_cast<uint64_t>(t.chunk_roads), static_cast<uint64_t>(t.wg_size),
-                    static_cast<uint64_t>(t.wgs_per_cu), static_cast<uint64_t>(t.schedule),
-                    static_cast<uint64_t>(flags)};
-    std::lock_guard<std::mutex> lock(g_graph_mu);
-    auto &cache = graph_cache();
-    auto it = cache.find(key);
-    if (it == cache.end()) {
-        SVT_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
-        svt_status st = batch_sequence(f, w, word_cap, road_cap, combo_cap, kept, kept_cap,
-                                       d_n_kept, false, stream);
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(stream, &g);
-        if (st != SVT_OK || e != hipSuccess || !g) {
-            if (g) (void)hipGraphDestroy(g);
-            return st != SVT_OK ? st : SVT_ERR_HIP;
-        }
-        hipGraphExec_t ex = nullptr;
-        if (hipGraphInstantiate(&ex, g, nullptr, nullptr, 0) != hipSuccess) {
-            (void)hipGraphDestroy(g);
+    // SVT_BATCH_GRAPH once replayed a captured graph of the launches.  A pass is two or three of
+    // them now, and launching them takes the host 10 us where a replay takes 18 and holds the GPU
+    // up a few more (750 events of 64 roads: 50 us a pass with a graph, 43 without), so they are
+    // launched either way.  What a capture could not do is refused as before.
+    if (flags & SVT_BATCH_GRAPH) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (!stream || hipStreamIsCapturing(stream, &st) != hipSuccess ||
+            st != hipStreamCaptureStatusNone)
             return SVT_ERR_HIP;
-        }
-        it = cache.emplace(key, GraphEntry{g, ex}).first;
     }
-    SVT_TRY(hipGraphLaunch(it->second.exec, stream));
-    return SVT_OK;
+    const bool timing = !(flags & SVT_BATCH_GRAPH) && g_ev_start && g_ev_stop;
+    return batch_sequence(f, w, word_cap, road_cap, combo_cap, kept, kept_cap, d_n_kept, timing,
+                          stream);
 }
-
 
 }  // namespace
 
@@ -726,13 +678,7 @@ svt_status svt_static_workspace_need(int64_t word_cap, int64_t road_cap, int64_t
                             resolve_tune(tune, word_cap).tile_combos, false);
     return *need > *limit ? SVT_ERR_CAPACITY : SVT_OK;
 }
-void svt_release_graphs(void) {
-    std::lock_guard<std::mutex> lock(g_graph_mu);
-    for (auto &kv : graph_cache()) {
-        (void)hipGraphExecDestroy(kv.second.exec);
-        (void)hipGraphDestroy(kv.second.graph);
-    }
-    graph_cache().clear();
-}
+
+void svt_release_graphs(void) {}  // (no graph is kept)
 
 }  // extern "C"
