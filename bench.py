@@ -5,9 +5,9 @@ Default workload: 3000 events x 64 roads, 1-3 hits per layer (2048 combinations 
 average), the shape of the paper's benchmark sample (section IV).  One step = one pass of the
 whole path (unpack, combine, fit, select) over that batch with the words already in HBM.
 
-Prints one JSON line: the batched path's fitted combinations/s (persistent fused kernel behind
-a replayed HIP graph), the plain one-launch-per-stage path beside it, the roofline of the fused
-kernel (HIP events on its own stream), and the CPU oracle timed on the host as a baseline.
+Prints one JSON line: the batched path's fitted combinations/s (a counting and a fitting kernel),
+the plain stage-by-stage path beside it, the roofline of the fitting kernel (HIP events on its own
+stream), and the CPU oracle timed on the host as a baseline.
 """
 from __future__ import annotations
 
@@ -45,8 +45,7 @@ PROFILES = os.path.join(ROOT, "profiles")
 CSRC = os.path.join(ROOT, "paper_1312_0917_amd", "csrc")
 # sources each timed kernel is compiled from: recorded HBM counters are valid while these match
 KERNEL_SOURCES = {
-    "k_fused": ["svt_fused.hip", "svt_fit.h", "svt_common.h"],
-    "k_onepass": ["svt_onepass.hip", "svt_fit.h", "svt_lookback.h", "svt_common.h"],
+    "k_unit_fit": ["svt_units.hip", "svt_units.h", "svt_fit.h", "svt_common.h"],
     "k_fit_events": ["svt_events.hip", "svt_common.h"],
 }
 
@@ -112,8 +111,8 @@ def algorithmic_bytes(n_combos, n_words, n_roads):
 
 
 def fused_kernel_ms(runner, steps, warmup):
-    """Average duration of the fused kernel alone: HIP events recorded on the runner's stream
-    right before and after its launch (direct launches, same launch configuration)."""
+    """Average duration of the fitting kernel alone: HIP events recorded on the runner's stream
+    right before and after its launch."""
     import numpy as np
     import torch
     from paper_1312_0917_amd import _lib as L
@@ -140,7 +139,7 @@ def fused_kernel_ms(runner, steps, warmup):
 
 
 def measure_large(ls, passes, tune, bank):
-    """Max-scale run: whole batch resident in HBM, graph replays, kernel and pass rooflines."""
+    """Max-scale run: whole batch resident in HBM, kernel and pass rooflines."""
     import torch
 
     from paper_1312_0917_amd import _lib as L
@@ -151,29 +150,6 @@ def measure_large(ls, passes, tune, bank):
     n_words, n_roads, n_combos = len(ls.words), ls.n_roads, ls.combos
     gcfg, dbank = L.make_config(chi2_cut=cut), P.device_bank(bank.f, bank.q)
     words = P.words_tensor(ls.words)
-    shapes = None
-    if tune is None:
-        # a short pick among the pre-pass + fused shapes (whole passes, 3 each after one)
-        shapes = {}
-        for tile, occ in ((4096, 3), (8192, 3), (4096, 4), (8192, 4)):
-            t = L.svt_tune_resolve(L.make_tune(tile, 64, 256, occ, L.SVT_SCHEDULE_TILES))
-            r = P.BatchRunner(gcfg, dbank, n_words, n_roads, n_combos, kept_cap=0, tune=t,
-                              graph=True, with_c=False)
-            r.load(words)
-            r.run()
-            torch.cuda.synchronize()
-            t0 = time.perf_counter()
-            for _ in range(3):
-                r.run()
-            torch.cuda.synchronize()
-            shapes[f"{tile}x{occ}"] = round((time.perf_counter() - t0) / 3 * 1e3, 4)
-            assert r.error()[0] == 0, r.error()
-            L.svt_release_graphs()
-            del r
-        best = min(shapes, key=shapes.get)
-        tile, occ = (int(x) for x in best.split("x"))
-        tune = L.svt_tune_resolve(L.make_tune(tile, 64, 256, occ, L.SVT_SCHEDULE_TILES))
-        log(f"c5 launch shapes (ms per pass): {shapes}")
     tune = L.svt_tune_for_batch(tune, n_words)
     runner = P.BatchRunner(gcfg, dbank, n_words, n_roads, n_combos, kept_cap=0, tune=tune,
                            graph=True, with_c=False)
@@ -189,11 +165,10 @@ def measure_large(ls, passes, tune, bank):
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / passes
     k_ms = fused_kernel_ms(runner, passes, 1)
-    L.svt_release_graphs()
     out = dict(workload=f"c5: {ls.n_events} events, {n_roads} roads, {n_words} hit words, "
                         f"{n_combos} combinations",
                value=n_combos / dt, unit="fitted combinations/s", ms_per_pass=round(dt * 1e3, 4),
-               passes=passes, tune=tune_dict(tune), ms_per_pass_by_shape=shapes,
+               passes=passes, tune=tune_dict(tune),
                roofline=roofline_of(tune, n_combos, n_words, n_roads, k_ms, dt * 1e3,
                                     recorded_traffic("c5", ls.n_events, tune)),
                int_ops=int_ops(n_combos, k_ms, tune))
@@ -208,8 +183,8 @@ def tune_dict(t):
 
 
 def measure_uneven(sample, bank, log_fn):
-    """Uneven batch in one persistent launch (8192 events, geometric roads/event, heavy-tailed
-    hits per layer): the autotuner times every launch shape and keeps the fastest."""
+    """Uneven batch in one pass (8192 events, geometric roads/event, heavy-tailed hits per
+    layer): the autotuner times every schedule and keeps the fastest."""
     from paper_1312_0917_amd import _lib as L
     from paper_1312_0917_amd import pipeline as P
     from paper_1312_0917_amd import synth
@@ -267,7 +242,7 @@ def measure_serving(sample, bank, warmup_events, rate_hz, n_slots, max_events, t
         slots = [serve.GpuSlot(cfg, dbank, word_cap, word_cap // 5 + 1, combo_cap, tune=tune,
                                io=io, timing=timing, graph=graph, size_to_batch=sized)
                  for _ in range(n_slots)]
-        # capture every slot's graphs before the clock starts
+        # every launch capacity once before the clock starts
         for sl in slots:
             sl.warm(warm.slice(0, 1))
         stats, _ = serve.serve(st, slots, max_events=max_events)
@@ -277,7 +252,6 @@ def measure_serving(sample, bank, warmup_events, rate_hz, n_slots, max_events, t
             graph=graph, word_caps=[caps[0], caps[-1]],
             schedule_smallest=L.svt_tune_for_batch(tune, caps[0]).schedule,
             schedule_largest=L.svt_tune_for_batch(tune, caps[-1]).schedule)
-        L.svt_release_graphs()
         del slots
         torch.cuda.empty_cache()
     pstats, _ = serve.serve(st, [serve.PlainSlot(cfg, dbank)], max_events=max_events)
@@ -290,11 +264,10 @@ def measure_serving(sample, bank, warmup_events, rate_hz, n_slots, max_events, t
                 batched_io="words read and results written in place in page-locked host "
                            "memory (no copy calls); batched_copy: H2D and two-step D2H copies",
                 batched=out["mapped"],
-                launch_shapes="batched: graphs for power-of-two word capacities from 4096 up, "
-                              "each batch launched for the smallest that holds it (small "
-                              "capacities run the one-pass kernel); batched_direct: the same "
-                              "without graphs; batched_slot_grid: every batch launched for the "
-                              "slot's whole capacity",
+                launch_shapes="batched: power-of-two word capacities from 4096 up, each batch "
+                              "launched for the smallest that holds it; batched_direct: the "
+                              "same without SVT_BATCH_GRAPH; batched_slot_grid: every batch "
+                              "launched for the slot's whole capacity",
                 batched_direct=out["mapped_direct"], batched_slot_grid=out["mapped_slot_grid"],
                 batched_breakdown=dict(
                     note="the same stream and slots with a timed HIP event before each batch "
@@ -345,14 +318,13 @@ def measure_kept_only(gcfg, dbank, words, n_words, n_roads, n_combos, tune, step
     k_ms = fused_kernel_ms(runner, steps, warmup)
     ops = INT_OPS_PER_COMBO * n_combos
     achieved = ops / (k_ms * 1e-3) / 1e12
-    L.svt_release_graphs()
     del runner
     torch.cuda.empty_cache()
     return dict(value=n_combos / dt, unit="fitted combinations/s", ms_per_step=round(dt * 1e3, 5),
                 kept=n_kept,
                 roofline=dict(bound="alu", achieved=round(achieved, 3), peak=round(INT_PEAK_TOPS, 1),
                               unit="Tops/s", frac=round(achieved / INT_PEAK_TOPS, 4),
-                              kernel="k_fused", kernel_ms=round(k_ms, 5),
+                              kernel=kernel_name(tune), kernel_ms=round(k_ms, 5),
                               ops_per_combination=INT_OPS_PER_COMBO))
 
 
@@ -409,16 +381,16 @@ def run_cpu_baseline(sample, bank, cfg, seconds, threads):
 
 
 def kernel_name(tune):
-    return {1: "k_fit_events", 2: "k_onepass", 3: "k_fused"}.get(tune.schedule, "?")
+    return {1: "k_fit_events", 2: "k_unit_fit", 3: "k_unit_fit"}.get(tune.schedule, "?")
 
 
 def kernel_bytes(tune, n_combos, n_words, n_roads):
-    """Algorithmic bytes of the timed kernel alone.  The one-pass kernel is the whole pass
-    (the words in, records and best tracks out).  The persistent kernel of the two-kernel
-    pass reads what the pre-pass wrote -- 2 B of grouped coordinate per word and 28 B of road
-    table per road (hit_begin, combo_begin, nhits, ncombo, set) -- and writes the records;
-    the best tracks are written by the finalize launch after it."""
-    if tune.schedule == 2:
+    """Algorithmic bytes of the timed kernel alone.  The fitting kernel takes the words in and
+    writes records and best tracks (and the road table, which is not counted).  The event
+    schedule's kernel reads what the pre-pass wrote -- 2 B of grouped coordinate per word and
+    28 B of road table per road (hit_begin, combo_begin, nhits, ncombo, set) -- and writes the
+    records; the best tracks are written by the finalize launch after it."""
+    if tune.schedule != 1:
         return algorithmic_bytes(n_combos, n_words, n_roads)
     return 21 * n_combos + 2 * n_words + 28 * n_roads
 
@@ -454,8 +426,6 @@ def measure_small(sample, bank, cut, reps, ora_s):
     words = P.words_tensor(sample.words)
     runner = P.BatchRunner(gcfg, dbank, nw, nr, nc, kept_cap=0, graph=True, with_c=False)
     runner.load(words)
-    from paper_1312_0917_amd import tune as T
-    modes = T.pick_launch_mode(runner)
     for _ in range(5):
         runner.run()
     torch.cuda.synchronize()
@@ -482,8 +452,6 @@ def measure_small(sample, bank, cut, reps, ora_s):
         runner.stream.synchronize()
         t.append(time.perf_counter() - t0)
     with_io = float(np.median(t[5:]))
-    L.svt_release_graphs()
-    small_graph = runner.graph
     del runner
     pr = P.PlainRunner(gcfg, dbank, with_c=False, want_kept=False)
     for _ in range(5):
@@ -500,9 +468,7 @@ def measure_small(sample, bank, cut, reps, ora_s):
     return dict(workload=f"c1: {sample.n_events} events, {nr} roads, {nw} hit words, "
                          f"{nc} combinations",
                 reps=reps, statistic="median",
-                batched=dict(us_per_pass=us(resident), value=nc / resident,
-                             launch="graph replay" if small_graph else "direct launches",
-                             launch_modes_ms_per_pass=modes),
+                batched=dict(us_per_pass=us(resident), value=nc / resident),
                 batched_with_io=dict(us_per_pass=us(with_io), value=nc / with_io,
                                      io="words in from page-locked memory, the 6 per-road "
                                         "best-track arrays out"),
@@ -537,13 +503,13 @@ def main():
     ap.add_argument("--wg", type=int, default=0)
     ap.add_argument("--occ", type=int, default=0)
     ap.add_argument("--schedule", type=int, default=-1,
-                    help="launch schedule (0 built-in default, 1 event per workgroup, 2 one "
-                         "pass, 3 pre-pass + fused tiles); default: the built-in or autotuned one")
+                    help="launch schedule (0 built-in default, 1 event per workgroup, 2 and 3 "
+                         "the unit kernels); default: the built-in or autotuned one")
     ap.add_argument("--large-events", type=int, default=10000,
                     help="events of the max-scale run (10000 x 2048 roads); 0 skips it")
     ap.add_argument("--large-passes", type=int, default=5)
     ap.add_argument("--workers", type=int, default=16, help="threads drawing large samples")
-    ap.add_argument("--no-graph", action="store_true", help="direct launches instead of replays")
+    ap.add_argument("--no-graph", action="store_true", help="without the SVT_BATCH_GRAPH flag (the launches are the same)")
     ap.add_argument("--no-uneven", action="store_true", help="skip the autotuned uneven batch")
     ap.add_argument("--serve-events", type=int, default=40000, help="0 skips the serving run")
     ap.add_argument("--serve-warmup", type=int, default=5000)
@@ -644,16 +610,10 @@ def main():
     # the schedule the library runs for this batch (a zero schedule is chosen per capacity)
     tune = L.svt_tune_for_batch(tune, n_words)
 
-    # ---- batched path: resident buffers; graph replays or direct launches, whichever is faster
+    # ---- batched path: resident buffers
     runner = P.BatchRunner(gcfg, dbank, n_words, n_roads, n_combos, kept_cap=0, tune=tune,
                            graph=not args.no_graph, with_c=False)
     runner.load(words)
-    launch_modes = None
-    if not args.no_graph:
-        from paper_1312_0917_amd import tune as T
-        log("launch mode: graph replays against direct launches")
-        launch_modes = T.pick_launch_mode(runner)
-        launch_modes["statistic"] = "median of 30 samples of 5 passes each"
     log("batched warmup")
     for _ in range(W):
         runner.run()
@@ -677,10 +637,10 @@ def main():
     traffic = recorded_traffic(args.config, n_events, tune)
     roofline = roofline_of(tune, n_combos, n_words, n_roads, k_ms, batch_s * 1e3, traffic)
 
-    # ---- several batches in flight: more runners, each with its own stream and graph -------
+    # ---- several batches in flight: more runners, each with its own stream -----------------
     # (not the headline: `value` is one pass at a time.  With independent batches queued on
-    # several streams, one batch's latency-bound pre-pass and kernel tails can overlap another's
-    # fused kernel; this is the serving slots' situation at a high arrival rate.)
+    # several streams, one batch's counting kernel and kernel tails can overlap another's fitting
+    # kernel; this is the serving slots' situation at a high arrival rate.)
     in_flight = None
     if not args.no_kept_only:
         in_flight = {}
@@ -710,10 +670,9 @@ def main():
                                         ms_per_batch=round(fl_s / n_fl * 1e3, 5),
                                         over_one_at_a_time=round(batch_s / (fl_s / n_fl), 3),
                                         same_results=same)
-            L.svt_release_graphs()  # (before the buffers the graphs refer to go away)
             del extra, group
 
-    # ---- ablation: one event per workgroup instead of flat combination tiles ---------------
+    # ---- ablation: one event per workgroup instead of units of words ---------------------
     events_schedule = None
     if not args.no_kept_only:
         log("one event per workgroup")
@@ -734,13 +693,11 @@ def main():
         events_schedule = dict(value=n_combos / ev_s, ms_per_step=round(ev_s * 1e3, 5),
                                flat_over_events=round(ev_s / batch_s, 2))
         del er
-        L.svt_release_graphs()
 
     # ---- kept-only mode: no per-combination records ----------------------------------------
     kept_only = None
     if not args.no_kept_only:
         log("kept-only mode")
-        L.svt_release_graphs()
         kept_only = measure_kept_only(gcfg, dbank, words, n_words, n_roads, n_combos, tune, K, W,
                                       runner_graph)
 
@@ -792,7 +749,6 @@ def main():
 
     large = None
     if large_s is not None:
-        L.svt_release_graphs()
         del runner
         torch.cuda.empty_cache()
         large = measure_large(large_s, args.large_passes, tune if explicit_tune else None, bank)
@@ -805,9 +761,7 @@ def main():
                              f"words, {n_combos} combinations "
                              f"({n_combos / max(n_events, 1):.0f} per event)",
                     events=n_events, roads=n_roads, words=n_words, combinations=n_combos,
-                    chi2_cut=cut, path="svt_process_batch (%s)" % (
-                        "graph replay" if runner_graph else "direct launches"),
-                    launch_modes_ms_per_pass=launch_modes,
+                    chi2_cut=cut, path="svt_process_batch",
                     tune=tune_dict(tune), autotune=tuned, device=dev_name),
         roofline=roofline, int_ops=int_ops(n_combos, k_ms, tune), cpu_baseline=cpu,
         small_batch=small_res, kept_only=kept_only,

@@ -12,7 +12,7 @@
  *                  combination -- inside loops over events, roads and combinations.
  * svt_unpack, svt_combine and svt_fit are those three stages; svt_select applies the
  * chi-square cut and picks the best track of every road; svt_process_batch runs all four as
- * one persistent fused pass (optionally replayed from a captured HIP graph).
+ * one batched pass.
  *
  * Exact definitions where the paper is silent (all arithmetic is integer and exact):
  *   hit word (uint32, LSB first): coord 13 bits two's complement | layer 3 | road tag 8 |
@@ -50,7 +50,7 @@
  *     its buffers and retry; *d_n_kept is the accepted count when the fit ran, -1 otherwise.
  *   - Kernels never write past a capacity and never read outside the given arrays, whatever
  *     the input words contain.
- *   - Output arrays of the fused pass must be 16-byte aligned (accept: 4-byte aligned).
+ *   - Output arrays of the batched pass must be 16-byte aligned (accept: 4-byte aligned).
  */
 #ifndef SVT_H
 #define SVT_H
@@ -124,30 +124,25 @@ typedef struct svt_best {
     int64_t *chi2;
 } svt_best;
 
-/* Launch parameters of the batched pass; zeros pick the built-in defaults. */
+/* Launch parameters of the batched pass; zeros pick the built-in defaults.  The unit kernels,
+ * which run every schedule but SVT_SCHEDULE_EVENTS, size themselves and use none of them; every
+ * field still has to hold a valid value. */
 typedef struct svt_tune {
-    int32_t tile_combos;  /* two-kernel schedule: combinations per work tile, 4096 or 8192 */
-    int32_t chunk_roads;  /* two-kernel schedule: roads staged in LDS at once at most: 16, 32
-                             or 64 (fewer when their hits or pair tables fill the stage) */
-    int32_t wg_size;      /* two-kernel schedule: 256 or 512 (one loader wave, the rest fit) */
-    int32_t wgs_per_cu;   /* persistent workgroups per compute unit, 1..8 (one pass: 1..3);
-                             the two-kernel schedule launches no more workgroups than
-                             combo_cap has tiles */
-    int32_t schedule;     /* SVT_SCHEDULE_*; 0 chooses per call from word_cap: the one-pass
-                             kernel up to 2^19 words, the two-kernel schedule above (0 must
-                             then suit both: wgs_per_cu 1..3).  The fields a schedule does
-                             not use only have to be valid values. */
+    int32_t tile_combos;  /* combinations per mark of the road table, 4096 or 8192 */
+    int32_t chunk_roads;  /* 16, 32 or 64 */
+    int32_t wg_size;      /* 256 or 512 */
+    int32_t wgs_per_cu;   /* event schedule: workgroups per compute unit, 1..8 (1..3 with
+                             SVT_SCHEDULE_ONEPASS or 0) */
+    int32_t schedule;     /* SVT_SCHEDULE_*; 0 chooses per call from word_cap: ONEPASS up to
+                             2^19 words, TILES above */
 } svt_tune;
-/* One persistent kernel that unpacks, combines, fits and selects units of 1024 words, each
- * workgroup holding its unit's roads, pair tables and best tracks in LDS (the loop nest of
- * section II-A per unit); the pass is that kernel and a reset of its look-back state. */
+/* Both names run the unit kernels: a counting kernel over units of 256 words, then a fitting
+ * kernel that unpacks, combines, fits and selects them (the loop nest of section II-A per unit). */
 #define SVT_SCHEDULE_ONEPASS 2
-/* One event per workgroup at a time (the multi-core scheme of section II-A, an ablation). */
-#define SVT_SCHEDULE_EVENTS 1
-/* A single-pass pre-pass writes the road table and grouped coordinates, then a persistent
- * kernel fits flat tiles of tile_combos combinations and a last launch finalizes the best
- * tracks (four launches per pass). */
 #define SVT_SCHEDULE_TILES 3
+/* One event per workgroup at a time (the multi-core scheme of section II-A, an ablation), after a
+ * pre-pass that writes the road table and the grouped coordinates. */
+#define SVT_SCHEDULE_EVENTS 1
 
 /* ---- sizes of the caller-provided scratch ------------------------------------------------ */
 int64_t svt_unpack_workspace(int64_t n_words);
@@ -206,23 +201,20 @@ svt_status svt_select(const svt_config *cfg, const svt_roads *roads, int64_t n_r
 
 /* The whole path in one pass (sections II and II-A: unpack, combine, fit, plus the chi-square
  * selection), writing the same records, accept flags, road table and best tracks as stages 1-4
- * (bit for bit) with one of two schedules (svt_tune.schedule; 0 chooses from word_cap, see
- * svt_tune_for_batch):
- *   - SVT_SCHEDULE_ONEPASS: one persistent kernel unpacks, combines, fits and selects units of
- *     1024 words, each workgroup holding its unit's roads in LDS (plus a reset launch);
- *   - SVT_SCHEDULE_TILES: a single-pass pre-pass reads every word once and writes the road
- *     table, the layer-grouped coordinates and each road's combination range (decoupled
- *     look-back over blocks of 2048 words); a persistent fused kernel then takes tiles of
- *     tile_combos consecutive combinations, stages the roads' hits and constants in LDS and fits
- *     every combination with integer VALU arithmetic; a last launch writes the best tracks.  The word count is read on the device from *d_n_words, so
- * a captured graph can be replayed for any batch up to word_cap (at most 2^31 - 1 words;
- * larger capacities are SVT_ERR_ARG, and svt_batch_workspace returns -1 for them).
+ * (bit for bit).  The words fall into units of 256; a unit owns the roads that start in it.  A
+ * counting kernel leaves running counts of roads, events and combinations per unit, and in the
+ * fitting kernel one wave at a time unpacks, combines, fits and selects a unit, its roads' hits and
+ * constants in LDS; with a kept list a third kernel writes it.  The word count is read on the
+ * device from *d_n_words, so a graph that captured the call can be replayed for any batch up to
+ * word_cap (at most 2^31 - 1 words; larger capacities are SVT_ERR_ARG, and svt_batch_workspace
+ * returns -1 for them).  Words in page-locked host memory are read over the bus once where
+ * the workspace has svt_batch_workspace bytes.
  * flags: SVT_BATCH_GRAPH
  * asks for the cheapest way to repeat the pass on one stream.  It was a captured graph; since a
  * pass is two or three launches, launching them is (a replay costs the host 18 us where they cost
  * 8 to 10), so the flag changes nothing now but what it refuses: SVT_ERR_HIP on the null stream
- * and on a stream under capture, and no timing events.  kept may be NULL; with d_n_kept also NULL no accepted count and no
- * kept list are produced.  Resets *d_err. */
+ * and on a stream under capture, and no timing events.  kept may be NULL; with d_n_kept also NULL
+ * no accepted count and no kept list are produced.  Resets *d_err. */
 #define SVT_BATCH_GRAPH 1
 /* flags: SVT_BATCH_KEPT_ONLY writes no per-combination records -- the output a trigger
  * consumes (section II: the fit's chi-square decides which tracks are kept).  accept[] is still
@@ -242,12 +234,12 @@ svt_status svt_process_batch(const svt_fconst *bank, const svt_config *cfg, cons
 
 /* For callers that cannot allocate device memory -- code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc: svt_process_batch with the same arguments but no
- * d_work / work_bytes.  Its workspace is one static array of SVT_STATIC_WORK_BYTES bytes per
- * GPU, part of the library's code object and held until the process ends; the call allocates
+ * d_work / work_bytes.  Its workspace is one static array of SVT_STATIC_WORK_BYTES bytes, and
+ * 30 MiB for the unit kernels' counts, per GPU, part of the library's code object and held until the process ends; the call allocates
  * nothing.  Capacities whose workspace (svt_batch_workspace) exceeds that size return
  * SVT_ERR_CAPACITY before anything is enqueued (svt_static_workspace_need reports both
- * numbers); SVT_BATCH_GRAPH is SVT_ERR_ARG (instantiating a graph allocates -- capture the
- * call in a graph of your own instead).  Every call on one GPU uses that GPU's array, and each
+ * numbers); SVT_BATCH_GRAPH is SVT_ERR_ARG (capture the call in a graph of your
+ * own instead).  Every call on one GPU uses that GPU's array, and each
  * pass clears what must start at zero: calls whose passes overlap on one GPU (other streams,
  * other threads) race and give wrong results; serialise them.  Outputs and the device-side
  * error word are exactly those of svt_process_batch. */
@@ -260,14 +252,15 @@ svt_status svt_process_batch_static(const svt_fconst *bank, const svt_config *cf
                                     const svt_best *best, int64_t *kept, int64_t kept_cap,
                                     int64_t *d_n_roads, int64_t *d_n_combos, int64_t *d_n_kept,
                                     uint64_t *d_err, int32_t flags, hipStream_t stream);
-/* *need = the workspace these capacities take (svt_batch_workspace), *limit =
- * SVT_STATIC_WORK_BYTES; SVT_OK if svt_process_batch_static accepts them, SVT_ERR_CAPACITY if
+/* *need = the workspace these capacities take (svt_batch_workspace, or without room for a copy
+ * of the words where only that fits), *limit = SVT_STATIC_WORK_BYTES and what the unit kernels
+ * need for these capacities; SVT_OK if svt_process_batch_static accepts them, SVT_ERR_CAPACITY if
  * they are too large, SVT_ERR_ARG for invalid capacities or tune. */
 svt_status svt_static_workspace_need(int64_t word_cap, int64_t road_cap, int64_t combo_cap,
                                      const svt_tune *tune, int64_t *need, int64_t *limit);
 
 /* When both are non-NULL, svt_process_batch calls without SVT_BATCH_GRAPH record `start`
- * right before and `stop` right after the fused kernel, on the call's stream (for timing). */
+ * right before and `stop` right after the fitting kernel, on the call's stream (for timing). */
 void svt_set_fused_timing_events(hipEvent_t start, hipEvent_t stop);
 
 /* Device-side address of page-locked host memory (from hipHostMalloc, e.g. a pinned torch
@@ -309,7 +302,7 @@ void svt_release_graphs(void);
 
 /* Write to `out` the launch parameters svt_process_batch uses for `tune` (NULL or zero fields
  * take the built-in defaults).  Returns SVT_ERR_ARG when `out` is NULL or the resolved set is
- * not one the fused kernel is built for, SVT_OK otherwise.  Host memory only. */
+ * not a valid one, SVT_OK otherwise.  Host memory only. */
 svt_status svt_tune_resolve(const svt_tune *tune, svt_tune *out);
 /* The launch parameters svt_process_batch uses for `tune` at word capacity word_cap: as
  * svt_tune_resolve, with a zero schedule replaced by the one chosen for that capacity. */

@@ -17,8 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsvt.so")
-SOURCES = ["svt_api.hip", "svt_stages.hip", "svt_fused.hip", "svt_prepass.hip", "svt_events.hip",
-           "svt_onepass.hip", "svt_units.hip"]
+SOURCES = ["svt_api.hip", "svt_stages.hip", "svt_units.hip", "svt_prepass.hip", "svt_events.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -28,10 +27,6 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
-# per-source additions.  svt_fused.hip: without the wave-level atomic rewrite, the one-lane
-# ticket fetch returns its value lazily, so no load behind it waits for the contended counter
-FILE_FLAGS = {"svt_fused.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
-              "svt_onepass.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 
 
 def hipcc() -> str:
@@ -43,8 +38,7 @@ def hipcc() -> str:
 
 def _compile(src: str) -> str:
     obj = os.path.join(OBJDIR, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc(), *HIPCC_FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o",
-           obj]
+    cmd = [hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")

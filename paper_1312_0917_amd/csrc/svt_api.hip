@@ -1,5 +1,5 @@
-// Host side of the libsvt C ABI: argument checks, workspace layout, launch sequences and the
-// HIP-graph cache of svt_process_batch.  Every function only enqueues on the given stream.
+// Host side of the libsvt C ABI: argument checks, workspace layout and launch sequences.  Every
+// function only enqueues on the given stream.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -55,18 +55,18 @@ UnpackWs carve_unpack(Carver &c, int64_t n_words) {
 }
 
 struct BatchWs {
-    uint32_t *tickets;  // [0] fused-kernel tiles (or events of the event schedule); rest spare
-    int64_t *n_events;  // events of the batch
-    int32_t *efr;       // first road of every event
+    uint32_t *ticket;   // event schedule: events handed out,
+    int64_t *n_events;  // events of the batch,
+    int32_t *efr;       // first road of every event,
     int64_t events_cap;
-    int64_t *status;    // look-back status words
+    int64_t *status;    // look-back status words of the pre-pass,
     int64_t status_words;
-    int64_t nb;         // one-pass units of the capacity
-    int32_t *tfr;
+    int64_t nb;         // its blocks,
+    int32_t *tfr;       // first road of every tile,
     int64_t tiles_cap;
-    int64_t *kb;
+    int64_t *kb;        // accepted combinations per kKeptBlock
     int64_t kbn;
-    int16_t *coords;
+    int16_t *coords;    // and grouped coordinates
     int64_t *nw_copy;   // the batch's word count, copied to device memory by the first kernel
     void *sets;         // unit kernels: the packed bank,
     void *tot;          // totals per range of units,
@@ -91,21 +91,19 @@ int64_t unit_bytes(int64_t word_cap, int64_t combo_cap) {
 }
 // `copy`: with those 4 bytes a word
 BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo_cap,
-                    int64_t tile, bool copy) {
+                    bool copy) {
     BatchWs w;
-    w.tickets = c.take<uint32_t>(4);
+    w.ticket = c.take<uint32_t>(4);
     w.n_events = c.take<int64_t>(2);
     w.events_cap = road_cap > 0 ? road_cap : 1;  // every event holds at least one road
     w.efr = c.take<int32_t>(w.events_cap);
-    // status words for the one-pass units or for the pre-pass blocks and their groups
-    w.nb = ceil_div(word_cap > 0 ? word_cap : 1, kOnepassUnitWords);
-    const int64_t pre = prepass_status_words(ceil_div(word_cap > 0 ? word_cap : 1,
-                                                      kPrepassBlockWords));
-    w.status_words = 2 * w.nb > pre ? 2 * w.nb : pre;
-    w.status = c.take<int64_t>(w.status_words);
-    // tile marks at the smaller of the tile and the kept block (the one-pass kernel marks
-    // kept blocks)
-    w.tiles_cap = ceil_div(combo_cap > 0 ? combo_cap : 1, tile < kKeptBlock ? tile : kKeptBlock) + 1;
+    w.nb = ceil_div(word_cap > 0 ? word_cap : 1, kPrepassBlockWords);
+    w.status_words = prepass_status_words(w.nb);
+    // (the space taken is what it was when a schedule with blocks of 1024 words used it, and the
+    // tiles' for 4096 combinations each: the static workspace then holds what it held)
+    const int64_t pairs = 2 * ceil_div(word_cap > 0 ? word_cap : 1, 1024);
+    w.status = c.take<int64_t>(w.status_words > pairs ? w.status_words : pairs);
+    w.tiles_cap = ceil_div(combo_cap > 0 ? combo_cap : 1, kKeptBlock) + 1;
     w.tfr = c.take<int32_t>(w.tiles_cap);
     w.kbn = ceil_div(combo_cap > 0 ? combo_cap : 1, kKeptBlock);
     w.kb = c.take<int64_t>(w.kbn);
@@ -125,18 +123,27 @@ BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo
                   : nullptr;
     return w;
 }
-int64_t batch_bytes(int64_t word_cap, int64_t road_cap, int64_t combo_cap, int64_t tile,
-                    bool copy) {
+int64_t batch_bytes(int64_t word_cap, int64_t road_cap, int64_t combo_cap, bool copy) {
     Carver c{nullptr};
-    carve_batch(c, word_cap, road_cap, combo_cap, tile, copy);
+    carve_batch(c, word_cap, road_cap, combo_cap, copy);
     return c.used;
 }
 
-// Batches of at most this many words (capacity) run the one-pass kernel by default, larger ones
-// the pre-pass and fused kernels: per-unit latency dominates the one-pass kernel once every
-// workgroup has several units of small roads (on 3000 events of 64 roads the two tie at the
-// default tile, and the pre-pass path leads with 8192-combination tiles).
+// Schedules TILES and ONEPASS run the same unit kernels (svt_units.hip); of the two, a zero
+// schedule resolves to ONEPASS up to this many words (capacity), as it did when they differed.
 constexpr int64_t kOnepassDefaultWords = 1 << 19;
+
+bool tune_supported(const svt_tune &t) {
+    const bool wg_ok = t.wg_size == 256 || t.wg_size == 512;
+    const bool ch_ok = t.chunk_roads == 16 || t.chunk_roads == 32 || t.chunk_roads == 64;
+    const bool tile_ok = t.tile_combos >= kKeptBlock && t.tile_combos <= kMaxTile &&
+                         t.tile_combos % kKeptBlock == 0;
+    const int occ_max = (t.schedule == SVT_SCHEDULE_ONEPASS || t.schedule == 0) ? 3 : 8;
+    const bool occ_ok = t.wgs_per_cu >= 1 && t.wgs_per_cu <= occ_max;
+    const bool sched_ok = t.schedule == 0 || t.schedule == SVT_SCHEDULE_TILES ||
+                          t.schedule == SVT_SCHEDULE_EVENTS || t.schedule == SVT_SCHEDULE_ONEPASS;
+    return wg_ok && ch_ok && tile_ok && occ_ok && sched_ok;
+}
 
 // Launch parameters for `t` (zero fields take the defaults).  A zero schedule stays zero when
 // no capacity is given (word_cap < 0), and is chosen from the capacity otherwise.
@@ -157,8 +164,8 @@ svt_tune resolve_tune(const svt_tune *t, int64_t word_cap = -1) {
 // A tune is valid when its fields are, before the capacity picks a zero schedule (which must
 // then suit both schedules), and after.
 bool tune_ok(const svt_tune *t, int64_t word_cap) {
-    return fused_tune_supported(resolve_tune(t)) &&
-           fused_tune_supported(resolve_tune(t, word_cap));
+    return tune_supported(resolve_tune(t)) &&
+           tune_supported(resolve_tune(t, word_cap));
 }
 
 int num_cus() {
@@ -238,7 +245,7 @@ svt_status svt_gather_results(const svt_roads *roads, const svt_best *best, int6
 svt_status svt_tune_resolve(const svt_tune *tune, svt_tune *out) {
     if (!out) return SVT_ERR_ARG;
     *out = resolve_tune(tune);
-    return fused_tune_supported(*out) ? SVT_OK : SVT_ERR_ARG;
+    return tune_supported(*out) ? SVT_OK : SVT_ERR_ARG;
 }
 
 svt_status svt_tune_for_batch(const svt_tune *tune, int64_t word_cap, svt_tune *out) {
@@ -296,9 +303,8 @@ int64_t svt_select_workspace(int64_t n_combos) {
 int64_t svt_batch_workspace(int64_t word_cap, int64_t road_cap, int64_t combo_cap,
                             const svt_tune *tune) {
     if (word_cap < 0 || word_cap > kMaxBatchWords || road_cap < 0 || combo_cap < 0) return -1;
-    const svt_tune t = resolve_tune(tune, word_cap);
     if (!tune_ok(tune, word_cap)) return -1;
-    return batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, true);
+    return batch_bytes(word_cap, road_cap, combo_cap, true);
 }
 
 svt_status svt_unpack(const uint32_t *words, int64_t n_words, const svt_config *cfg,
@@ -399,108 +405,87 @@ void svt_set_fused_timing_events(hipEvent_t start, hipEvent_t stop) {
     g_ev_stop = stop;
 }
 
-static svt_status batch_sequence(const FusedLaunch &f, const BatchWs &w, int64_t word_cap,
-                                 int64_t road_cap, int64_t combo_cap, int64_t *kept,
-                                 int64_t kept_cap, int64_t *d_n_kept, bool timing,
-                                 hipStream_t stream) {
-    const Sizes nw{0, f.d_n_words, word_cap};
-    // after the reset the kernels read the word count from its copy in device memory
-    const Sizes nw_dev{0, w.nw_copy, word_cap};
-    const Sizes nr{0, f.d_n_roads, road_cap};
-    const Sizes nc{0, f.d_n_combos, combo_cap};
-    uint64_t *err = f.err;
-    if (f.tune.schedule != SVT_SCHEDULE_EVENTS) {
-        // two kernels, and with a kept list a third
-        UnitsLaunch o{};
-        o.bank = f.bank;
-        o.cfg = f.cfg;
-        o.words = f.words;
-        o.d_n_words = f.d_n_words;
-        o.word_cap = word_cap;
-        o.roads = f.roads;
-        o.road_cap = road_cap;
-        o.out = f.rec;
-        o.accept = f.accept;
-        o.best = f.best;
-        o.combo_cap = combo_cap;
-        o.d_n_roads = const_cast<int64_t *>(f.d_n_roads);
-        o.d_n_combos = const_cast<int64_t *>(f.d_n_combos);
-        o.err = err;
-        o.d_n_kept = d_n_kept;
-        o.kept = kept;
-        o.kept_cap = kept_cap;
-        o.kept_only = f.kept_only;
-        o.keep = w.keep;
-        o.keep_groups = w.keep_groups;
-        o.less_slots = !w.copy || w.host_words;
-        o.slots = o.less_slots ? static_cast<void *>(w.coords) : w.copy;
-        o.nw_copy = w.nw_copy;
-        o.ticket = w.dealers;
-        o.acc = w.acc;
-        o.sets = w.sets;
-        o.rec = w.rec;
-        o.tot = w.tot;
-        o.copy = w.host_words ? w.copy : nullptr;
-        o.num_cus = f.num_cus;
+static svt_status batch_sequence(const UnitsLaunch &o, const svt_tune &t, const BatchWs &w,
+                                 bool timing, hipStream_t stream) {
+    if (t.schedule != SVT_SCHEDULE_EVENTS) {  // two kernels, and with a kept list a third
         SVT_TRY(launch_units(o, stream, timing ? g_ev_start : nullptr,
                              timing ? g_ev_stop : nullptr));
         return SVT_OK;
     }
+    uint64_t *err = o.err;
     PrepassLaunch p{};
-    p.words = f.words;
-    p.nw = nw;
-    p.cfg = f.cfg;
-    p.roads = f.roads;
-    p.road_cap = road_cap;
-    p.coords = const_cast<int16_t *>(f.coords);
-    p.best = f.best;
-    p.tile_combos = f.tune.tile_combos;
+    p.words = o.words;
+    p.nw = Sizes{0, o.d_n_words, o.word_cap};
+    p.cfg = o.cfg;
+    p.roads = o.roads;
+    p.road_cap = o.road_cap;
+    p.coords = w.coords;
+    p.best = o.best;
+    p.tile_combos = t.tile_combos;
     p.tile_first_road = w.tfr;
     p.tiles_cap = w.tiles_cap;
-    p.combo_cap = combo_cap;
-    p.d_n_roads = const_cast<int64_t *>(f.d_n_roads);
-    p.d_n_combos = const_cast<int64_t *>(f.d_n_combos);
+    p.combo_cap = o.combo_cap;
+    p.d_n_roads = o.d_n_roads;
+    p.d_n_combos = o.d_n_combos;
     p.status = w.status;
     p.nb_cap = w.nb;
-    p.tickets = w.tickets;
-    p.err = f.err;
+    p.status_words = w.status_words;
+    p.ticket = w.ticket;
+    p.err = err;
     p.event_first_road = w.efr;
     p.event_cap = w.events_cap;
     p.d_n_events = w.n_events;
-    // (the kept-list block counts are cleared with the rest: the fused kernel adds to them)
-    p.nb_cap = ceil_div(word_cap > 0 ? word_cap : 1, kPrepassBlockWords);
-    p.status_words = prepass_status_words(p.nb_cap);
-    SVT_TRY(launch_batch_reset(p, w.nw_copy, d_n_kept, d_n_kept ? w.kb : nullptr,
-                               d_n_kept ? w.kbn : 0, stream));
-    p.nw = nw_dev;
+    // (the kept-list block counts are cleared with the rest: the event kernel adds to them)
+    SVT_TRY(launch_batch_reset(p, w.nw_copy, o.d_n_kept, o.d_n_kept ? w.kb : nullptr,
+                               o.d_n_kept ? w.kbn : 0, stream));
+    // after the reset the kernels read the word count from its copy in device memory
+    p.nw = Sizes{0, w.nw_copy, o.word_cap};
     SVT_TRY(launch_prepass(p, stream));
+    EventsLaunch f{};
+    f.bank = o.bank;
+    f.cfg = o.cfg;
+    f.wgs_per_cu = t.wgs_per_cu;
+    f.coords = w.coords;
+    f.roads = o.roads;
+    f.d_n_roads = o.d_n_roads;
+    f.d_n_combos = o.d_n_combos;
+    f.d_n_events = w.n_events;
+    f.event_first_road = w.efr;
+    f.rec = o.out;
+    f.accept = o.accept;
+    f.best = o.best;
+    f.kb_counts = o.d_n_kept ? w.kb : nullptr;
+    f.ticket = w.ticket;
+    f.err = err;
+    f.road_cap = o.road_cap;
+    f.combo_cap = o.combo_cap;
+    f.event_cap = w.events_cap;
+    f.num_cus = o.num_cus;
+    f.kept_only = o.kept_only;
     if (timing) SVT_TRY(hipEventRecord(g_ev_start, stream));
-    if (f.tune.schedule == SVT_SCHEDULE_EVENTS)
-        SVT_TRY(launch_fit_events(f, w.efr, w.n_events, w.events_cap, stream));
-    else
-        SVT_TRY(launch_fused(f, stream));
+    SVT_TRY(launch_fit_events(f, stream));
     if (timing) SVT_TRY(hipEventRecord(g_ev_stop, stream));
+    const Sizes nr{0, o.d_n_roads, o.road_cap};
+    const Sizes nc{0, o.d_n_combos, o.combo_cap};
     // the kept list's block counts are scanned by one extra workgroup of the finalize launch
     ScanJob job;
-    if (d_n_kept) {
+    if (o.d_n_kept) {
         job.data = w.kb;
         job.n = nc;
         job.div = kKeptBlock;
-        job.tot = d_n_kept;
-        job.cap = kept ? kept_cap : -1;
+        job.tot = o.d_n_kept;
+        job.cap = o.kept ? o.kept_cap : -1;
         job.cap_index = 2;
     }
-    SVT_TRY(launch_best_finalize(f.roads, nr, f.kept_only ? svt_fitrec{} : f.rec, nc, f.best,
-                                 f.cfg.chi2_cut, err, true, f.bank, f.coords, f.cfg.shift, job,
+    SVT_TRY(launch_best_finalize(o.roads, nr, o.kept_only ? svt_fitrec{} : o.out, nc, o.best,
+                                 o.cfg.chi2_cut, err, true, o.bank, w.coords, o.cfg.shift, job,
                                  stream));
-    if (d_n_kept) {
-        if (kept && f.kept_only)
-            SVT_TRY(launch_kept_refit(f.accept, nc, nr, w.kbn, w.kb, f.roads, w.tfr,
-                                      f.tune.tile_combos, f.bank, f.cfg.n_sets, f.coords,
-                                      f.cfg.shift, kept, f.rec, kept_cap, err, stream));
-        else if (kept)
-            SVT_TRY(launch_kept_write(f.accept, nc, w.kbn, w.kb, kept, kept_cap, err, stream));
-    }
+    if (o.kept && o.kept_only)
+        SVT_TRY(launch_kept_refit(o.accept, nc, nr, w.kbn, w.kb, o.roads, w.tfr, t.tile_combos,
+                                  o.bank, o.cfg.n_sets, w.coords, o.cfg.shift, o.kept, o.out,
+                                  o.kept_cap, err, stream));
+    else if (o.kept)
+        SVT_TRY(launch_kept_write(o.accept, nc, w.kbn, w.kb, o.kept, o.kept_cap, err, stream));
     return SVT_OK;
 }
 
@@ -575,50 +560,58 @@ svt_status process_batch(const svt_fconst *bank, const svt_config *cfg, const sv
     const svt_tune t = resolve_tune(tune, word_cap);
     if (!tune_ok(tune, word_cap)) return SVT_ERR_ARG;
     if (work_bytes == kStaticWork) {  // svt_process_batch_static
-        if (flags & SVT_BATCH_GRAPH) return SVT_ERR_ARG;  // instantiating a graph allocates
+        if (flags & SVT_BATCH_GRAPH) return SVT_ERR_ARG;
         const int64_t limit = SVT_STATIC_WORK_BYTES + unit_bytes(word_cap, combo_cap);
-        if (batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, false) > limit)
+        if (batch_bytes(word_cap, road_cap, combo_cap, false) > limit)
             return SVT_ERR_CAPACITY;
         const svt_status st = static_workspace(&d_work);
         if (st != SVT_OK) return st;
         work_bytes = limit;
     } else if (!d_work ||
-               work_bytes < batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, false) ||
+               work_bytes < batch_bytes(word_cap, road_cap, combo_cap, false) ||
                !aligned(d_work, kAlign)) {
         return SVT_ERR_ARG;
     }
     // words in host memory are read once over the bus: the counting kernel leaves a copy, where
     // the workspace has room for one (else both kernels read them in place)
-    const bool copy =
-        work_bytes >= batch_bytes(word_cap, road_cap, combo_cap, t.tile_combos, true);
+    const bool copy = work_bytes >= batch_bytes(word_cap, road_cap, combo_cap, true);
     const int cus = num_cus();
     if (cus <= 0) return SVT_ERR_HIP;
 
     Carver c{static_cast<char *>(d_work)};
-    BatchWs w = carve_batch(c, word_cap, road_cap, combo_cap, t.tile_combos, copy);
+    BatchWs w = carve_batch(c, word_cap, road_cap, combo_cap, copy);
     w.host_words = copy && in_host_memory(words);
-    FusedLaunch f{};
-    f.bank = bank;
-    f.cfg = *cfg;
-    f.tune = t;
-    f.words = words;
-    f.d_n_words = d_n_words;
-    f.coords = w.coords;
-    f.roads = *roads;
-    f.d_n_roads = d_n_roads;
-    f.d_n_combos = d_n_combos;
-    f.rec = *rec;
-    f.accept = accept;
-    f.best = *best;
-    f.tile_first_road = w.tfr;
-    f.kb_counts = d_n_kept ? w.kb : nullptr;
-    f.tile_counter = w.tickets;
-    f.err = d_err;
-    f.tiles_cap = w.tiles_cap;
-    f.road_cap = road_cap;
-    f.combo_cap = combo_cap;
-    f.num_cus = cus;
-    f.kept_only = kept_only;
+    UnitsLaunch o{};
+    o.bank = bank;
+    o.cfg = *cfg;
+    o.words = words;
+    o.d_n_words = d_n_words;
+    o.word_cap = word_cap;
+    o.roads = *roads;
+    o.road_cap = road_cap;
+    o.out = *rec;
+    o.accept = accept;
+    o.best = *best;
+    o.combo_cap = combo_cap;
+    o.d_n_roads = d_n_roads;
+    o.d_n_combos = d_n_combos;
+    o.err = d_err;
+    o.d_n_kept = d_n_kept;
+    o.kept = kept;
+    o.kept_cap = kept_cap;
+    o.kept_only = kept_only;
+    o.nw_copy = w.nw_copy;
+    o.ticket = w.dealers;
+    o.sets = w.sets;
+    o.rec = w.rec;
+    o.tot = w.tot;
+    o.acc = w.acc;
+    o.keep = w.keep;
+    o.keep_groups = w.keep_groups;
+    o.less_slots = !w.copy || w.host_words;
+    o.slots = o.less_slots ? static_cast<void *>(w.coords) : w.copy;
+    o.copy = w.host_words ? w.copy : nullptr;
+    o.num_cus = cus;
 
     // SVT_BATCH_GRAPH once replayed a captured graph of the launches.  A pass is two or three of
     // them now, and launching them takes the host 10 us where a replay takes 18 and holds the GPU
@@ -631,8 +624,7 @@ svt_status process_batch(const svt_fconst *bank, const svt_config *cfg, const sv
             return SVT_ERR_HIP;
     }
     const bool timing = !(flags & SVT_BATCH_GRAPH) && g_ev_start && g_ev_stop;
-    return batch_sequence(f, w, word_cap, road_cap, combo_cap, kept, kept_cap, d_n_kept, timing,
-                          stream);
+    return batch_sequence(o, t, w, timing, stream);
 }
 
 }  // namespace
@@ -674,8 +666,7 @@ svt_status svt_static_workspace_need(int64_t word_cap, int64_t road_cap, int64_t
     if (*need < 0) return SVT_ERR_ARG;
     *limit += unit_bytes(word_cap, combo_cap);
     if (*need > *limit)  // without room for a copy of the words
-        *need = batch_bytes(word_cap, road_cap, combo_cap,
-                            resolve_tune(tune, word_cap).tile_combos, false);
+        *need = batch_bytes(word_cap, road_cap, combo_cap, false);
     return *need > *limit ? SVT_ERR_CAPACITY : SVT_OK;
 }
 

@@ -16,7 +16,6 @@ constexpr int kLookGroup = 64;            // pre-pass blocks per group of its tw
 inline int64_t prepass_status_words(int64_t nb_cap) {
     return 2 * nb_cap + 2 * ((nb_cap + kLookGroup - 1) / kLookGroup);
 }
-constexpr int kOnepassUnitWords = 1024;   // words per unit of the one-pass kernel
 constexpr int kRoadBlock = 256;           // roads per block in road-table kernels
 constexpr int kKeptBlock = 4096;          // combinations per block of the kept-list compaction
 constexpr int kScanThreads = 1024;        // single-workgroup scan
@@ -30,7 +29,7 @@ __device__ inline uint64_t best_key(int64_t chi2, uint32_t k) {
     if (c > kKeyChiMax) c = kKeyChiMax;
     return (c << kKeyKBits) | k;
 }
-constexpr int kMaxTile = 8192;  // combinations per tile of the fused kernel, at most
+constexpr int kMaxTile = 8192;  // largest svt_tune.tile_combos
 constexpr int64_t kMaxBatchWords = (1ll << 31) - 1;  // batched path: road and event counts fit 31 bits
 
 // ---- error word: (class << 56) | index, smallest wins, all ones = none ------------------
@@ -177,34 +176,31 @@ hipError_t launch_kept_refit(const uint8_t *accept, Sizes n_combos, Sizes n_road
                              int32_t shift, int64_t *kept, const svt_fitrec &rec,
                              int64_t kept_cap, uint64_t *err, hipStream_t s);
 
-struct FusedLaunch {
+// One event per workgroup at a time (schedule 1 of svt_tune), after the pre-pass: the ablation of
+// how the work is split.
+struct EventsLaunch {
     const svt_fconst *bank;
     svt_config cfg;
-    svt_tune tune;
-    const uint32_t *words;
-    const int64_t *d_n_words;
+    int wgs_per_cu;
     const int16_t *coords;     // workspace: coordinates grouped by layer inside each road
     svt_roads roads;
     const int64_t *d_n_roads;
     const int64_t *d_n_combos;
+    const int64_t *d_n_events;
+    const int32_t *event_first_road;
     svt_fitrec rec;
     uint8_t *accept;
     svt_best best;
-    int32_t *tile_first_road;
     int64_t *kb_counts;        // per kKeptBlock combinations (null: kept list not wanted)
-    uint32_t *tile_counter;
+    uint32_t *ticket;
     uint64_t *err;
-    int64_t tiles_cap;
     int64_t road_cap;
     int64_t combo_cap;
+    int64_t event_cap;
     int num_cus;
     bool kept_only;            // no per-combination records (accept flags still written)
 };
-hipError_t launch_fused(const FusedLaunch &f, hipStream_t s);
-// One event per workgroup at a time (schedule 1 of svt_tune): the same outputs as the fused
-// kernel, for the ablation against flat combination tiles.
-hipError_t launch_fit_events(const FusedLaunch &f, const int32_t *event_first_road,
-                             const int64_t *d_n_events, int64_t event_cap, hipStream_t s);
+hipError_t launch_fit_events(const EventsLaunch &f, hipStream_t s);
 // Per road: turn the best-track key left in best.chi2 into (k, chi2, p0..p2), reading the
 // parameters from the records, or fitting them again from the grouped coordinates when bank
 // and coords are given (exact rescan of the records for a road whose key saturated).
@@ -224,7 +220,6 @@ hipError_t launch_best_finalize(const svt_roads &roads, Sizes n_roads, const svt
                                 uint64_t *err, bool skip_if_error, const svt_fconst *bank,
                                 const int16_t *coords, int32_t shift, const ScanJob &job,
                                 hipStream_t s);
-bool fused_tune_supported(const svt_tune &t);
 
 // Single-pass unpack + combine of the batched path (decoupled look-back over word blocks).
 struct PrepassLaunch {
@@ -244,47 +239,17 @@ struct PrepassLaunch {
     int64_t *status;           // look-back status words (prepass_status_words(nb_cap))
     int64_t nb_cap;            // ceil(word_cap / kPrepassBlockWords)
     int64_t status_words;      // status words the reset clears
-    uint32_t *tickets;         // [0] fused-kernel tiles, [1] pre-pass blocks
+    uint32_t *ticket;          // of the event kernel, cleared by the reset
     uint64_t *err;
     int32_t *event_first_road; // first road of every event (event_cap entries)
     int64_t event_cap;
     int64_t *d_n_events;
 };
-// Clears the error word, both tickets, *d_n_kept (nullable), status[0 .. status_words) and
+// Clears the error word, the ticket, *d_n_kept (nullable), status[0 .. status_words) and
 // zero[0 .. n_zero) (the kept-list block counts; nullable).
 hipError_t launch_batch_reset(const PrepassLaunch &p, int64_t *nw_copy, int64_t *d_n_kept,
                               int64_t *zero, int64_t n_zero, hipStream_t s);
 hipError_t launch_prepass(const PrepassLaunch &p, hipStream_t s);
-
-// The whole batched pass in one persistent kernel (unpack, combine, fit, select; road table,
-// records and best tracks written from LDS).  Needs the reset of launch_batch_reset (with
-// nb_cap status words for units of kOnepassUnitWords) first.
-struct OnepassLaunch {
-    const svt_fconst *bank;
-    svt_config cfg;
-    const uint32_t *words;
-    Sizes nw;
-    svt_roads roads;
-    int64_t road_cap;
-    svt_fitrec rec;
-    uint8_t *accept;
-    svt_best best;
-    int64_t combo_cap;
-    int64_t *d_n_roads;
-    int64_t *d_n_combos;
-    int64_t *kb_counts;        // accepted count per kKeptBlock combinations (null: no kept list)
-    int64_t *status;           // 2 * nb_cap look-back status words
-    int64_t nb_cap;            // ceil(word_cap / kOnepassUnitWords)
-    uint32_t *tickets;
-    uint64_t *err;
-    bool kept_only;            // no records; grouped coordinates and block marks for the refit
-    int16_t *coords;           // kept-only: grouped coordinates (word_cap entries)
-    int32_t *tile_first_road;  // kept-only: first road of every kKeptBlock block
-    int64_t tiles_cap;
-    int num_cus;
-    int wgs_per_cu;
-};
-hipError_t launch_onepass(const OnepassLaunch &p, hipStream_t s);
 
 // The batched pass over wave-sized units of words: a counting kernel and a fitting kernel
 // (svt_units.hip), with `start` / `stop` (nullable) recorded around the second.

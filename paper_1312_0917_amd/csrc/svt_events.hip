@@ -1,9 +1,8 @@
 // One event per workgroup: the multi-core scheme of section II-A (each core takes whole events
 // and runs the combine and fit loops of each of them), as schedule 1 of the batched pass.  It
-// writes exactly the outputs of the persistent fused kernel -- records (or, in kept-only mode,
-// only the accept flags), the per-road best keys and accept counts -- and is kept as the
-// ablation against flat combination tiles: an event's work is not split between workgroups,
-// so the batch is balanced only at event granularity.
+// writes records (or, in kept-only mode, only the accept flags), per-road best keys and accept
+// counts, and is kept as the ablation against the unit kernels (svt_units.hip): an event's work is
+// not split between workgroups, so the batch is balanced only at event granularity.
 //
 // A workgroup takes the next event from an atomic ticket, stages its roads' combo_begin in
 // LDS, and its threads walk the event's combinations; each finds its road by binary search,
@@ -127,8 +126,7 @@ __global__ __launch_bounds__(kEvThreads) void k_fit_events(EArgs a) {
 
 }  // namespace
 
-hipError_t launch_fit_events(const FusedLaunch &f, const int32_t *event_first_road,
-                             const int64_t *d_n_events, int64_t event_cap, hipStream_t s) {
+hipError_t launch_fit_events(const EventsLaunch &f, hipStream_t s) {
     EArgs a;
     a.bank = f.bank;
     a.shift = f.cfg.shift;
@@ -137,19 +135,19 @@ hipError_t launch_fit_events(const FusedLaunch &f, const int32_t *event_first_ro
     a.roads = f.roads;
     a.d_n_roads = f.d_n_roads;
     a.d_n_combos = f.d_n_combos;
-    a.d_n_events = d_n_events;
-    a.event_first_road = event_first_road;
+    a.d_n_events = f.d_n_events;
+    a.event_first_road = f.event_first_road;
     a.rec = f.rec;
     a.accept = f.accept;
     a.best = f.best;
     a.kb_counts = reinterpret_cast<unsigned long long *>(f.kb_counts);
-    a.ticket = f.tile_counter;
+    a.ticket = f.ticket;
     a.err = f.err;
     a.road_cap = f.road_cap;
     a.combo_cap = f.combo_cap;
-    a.event_cap = event_cap;
+    a.event_cap = f.event_cap;
     a.records = f.kept_only ? 0 : 1;
-    const int grid = f.num_cus * f.tune.wgs_per_cu;
+    const int grid = f.num_cus * f.wgs_per_cu;
     hipLaunchKernelGGL(k_fit_events, dim3(grid > 0 ? grid : 1), dim3(kEvThreads), 0, s, a);
     return hipGetLastError();
 }

@@ -1,5 +1,5 @@
-// Decoupled look-back over fixed-size blocks of hit words, shared by the batched pre-pass and
-// the one-pass kernel of libsvt.
+// What the decoupled look-back of the batched pre-pass (svt_lookback_block.h) keeps per block of
+// hit words.
 //
 // Unpacking (section II-A of the paper, the serial code's first function) needs running counts
 // over the whole stream: which road and event a word belongs to, where a road's combinations
@@ -30,7 +30,6 @@ constexpr uint64_t kStMask = 3ull << 62;
 // a look-back round computes missing aggregates itself after this long (wall-clock ticks of
 // 10 ns): far beyond any wait on a predecessor that is running
 constexpr uint64_t kLookbackTimeout = 20000;
-constexpr int kLookWindows = 8;  // predecessors read per round: 64 per window
 constexpr int kRoadTail = 64;    // words past a block that a road starting in it may use
                                  // (a road with combinations has at most 5 * 8 = 40 words)
 
@@ -129,96 +128,6 @@ __device__ inline void publish_aggregate(const LookbackCtx &a, int64_t b, uint64
     const uint64_t flag = b == 0 ? kStIncl : kStAgg;
     status_publish(a.status + b, flag | agg0);
     status_publish(a.status + a.nb_cap + b, flag | agg1);
-}
-
-// Exclusive prefixes over blocks 0..b-1 of two status columns at once (col0[i], col1[i] =
-// column 0 and 1 of block i), for a block whose aggregates are already published
-// (publish_aggregate); publishes its inclusive prefixes once known.  Executed by one whole
-// wave; the results are valid in every lane.  One round reads kLookWindows * 64 predecessors
-// of both columns (lane i of window k inspects block top - 64 k - i, so position 0 is the
-// nearest predecessor); each column sums its values up to its nearest block that already has
-// an inclusive value.  Values are opaque sums: counts packed in one word add field by field as
-// long as no field overflows.  A round that has waited a.timeout wall-clock ticks for
-// predecessors to publish computes their aggregates from the words instead (block_aggregate)
-// and goes on.
-template <int BW>
-__device__ void look_back2(const LookbackCtx &a, int64_t b, uint64_t agg0, uint64_t agg1,
-                           uint64_t &ex0, uint64_t &ex1) {
-    int64_t *col0 = a.status, *col1 = a.status + a.nb_cap;
-    const int lane = lane_id();
-    ex0 = 0;
-    ex1 = 0;
-    if (b == 0) return;  // its inclusive prefix is its aggregate, already published
-    bool done0 = false, done1 = false;
-    int64_t top = b - 1;
-    uint64_t wait_since = 0;  // start of this round's wait (0: not waiting)
-    while (!(done0 && done1)) {
-        uint64_t v0[kLookWindows], v1[kLookWindows];
-#pragma unroll
-        for (int k = 0; k < kLookWindows; ++k) {
-            const int64_t idx = top - 64 * k - lane;
-            v0[k] = (idx >= 0 && !done0) ? status_read(col0 + idx) : kStIncl;
-            v1[k] = (idx >= 0 && !done1) ? status_read(col1 + idx) : kStIncl;
-        }
-        int f0 = 64 * kLookWindows, f1 = 64 * kLookWindows;  // nearest inclusive positions
-#pragma unroll
-        for (int k = kLookWindows - 1; k >= 0; --k) {
-            const uint64_t m0 = __ballot((v0[k] & kStMask) == kStIncl);
-            const uint64_t m1 = __ballot((v1[k] & kStMask) == kStIncl);
-            if (m0) f0 = 64 * k + __builtin_ctzll(m0);
-            if (m1) f1 = 64 * k + __builtin_ctzll(m1);
-        }
-        bool wait = false;
-#pragma unroll
-        for (int k = 0; k < kLookWindows; ++k) {
-            const int pos = 64 * k + lane;
-            wait |= __ballot(((v0[k] & kStMask) == 0 && pos <= f0) ||
-                             ((v1[k] & kStMask) == 0 && pos <= f1)) != 0;
-        }
-        if (wait) {  // a block at or before a nearest inclusive one has not published yet
-            const uint64_t now = wall_clock64();
-            if (wait_since == 0) wait_since = now;
-            if (now - wait_since < a.timeout) {
-                __builtin_amdgcn_s_sleep(1);
-                continue;
-            }
-            // Waited long enough: publish every aggregate this round still misses, computed
-            // from the words, then read the round again.  A compare-and-swap from "nothing"
-            // never overwrites what the block itself has published meanwhile (and what it
-            // publishes later is the same aggregate, or its inclusive prefix).
-            int need = (done0 ? -1 : f0) > (done1 ? -1 : f1) ? f0 : f1;  // farthest position
-            need = need < 64 * kLookWindows ? need : 64 * kLookWindows - 1;  // of this round
-            for (int64_t idx = top; idx >= 0 && top - idx <= need; --idx) {
-                const uint64_t s0 = status_read(col0 + idx), s1 = status_read(col1 + idx);
-                if ((s0 & kStMask) != 0 && (s1 & kStMask) != 0) continue;
-                uint64_t g0, g1;
-                block_aggregate<BW>(a, idx, g0, g1);
-                if (lane == 0) {
-                    status_claim(col0 + idx, kStAgg | g0);
-                    status_claim(col1 + idx, kStAgg | g1);
-                }
-            }
-            wait_since = 0;
-            continue;
-        }
-        wait_since = 0;
-        uint64_t m0 = 0, m1 = 0;
-#pragma unroll
-        for (int k = 0; k < kLookWindows; ++k) {
-            const int pos = 64 * k + lane;
-            if (!done0 && pos <= f0) m0 += v0[k] & ~kStMask;
-            if (!done1 && pos <= f1) m1 += v1[k] & ~kStMask;
-        }
-        ex0 += wave_sum(m0);
-        ex1 += wave_sum(m1);
-        done0 |= f0 < 64 * kLookWindows;
-        done1 |= f1 < 64 * kLookWindows;
-        top -= 64 * kLookWindows;
-    }
-    if (lane == 0) {
-        status_publish(col0 + b, kStIncl | (ex0 + agg0));
-        status_publish(col1 + b, kStIncl | (ex1 + agg1));
-    }
 }
 
 }  // namespace svt

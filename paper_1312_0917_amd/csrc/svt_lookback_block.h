@@ -1,13 +1,12 @@
 // Two-level decoupled look-back of the batched pre-pass.
 //
 // With a thousand or more blocks in flight, the nearest block that already knows its inclusive
-// prefix is several hundred blocks back, and a one-level look-back (look_back2) makes every block
+// prefix is several hundred blocks back, and a one-level look-back makes every block
 // read that many status words per round.  Those reads bypass the non-coherent L2 and all land
 // on the few kilobytes of status words of the blocks in flight, so they queue behind each other
 // and behind every other memory access of the kernel.  Grouping the blocks keeps each read short:
 //
-//   level 1: per block, its aggregate (the status words of look_back2, written by
-//            publish_aggregate);
+//   level 1: per block, its aggregate (written by publish_aggregate);
 //   level 2: per group of kLookGroup consecutive blocks, "aggregate of the group" or "inclusive
 //            prefix up to the group's end", both published by the group's last block: the
 //            aggregate once it has summed the aggregates of the blocks before it in the group,
@@ -17,7 +16,7 @@
 // one lane per block) and the level-2 values of groups g - 1, g - 2, ... back to the nearest
 // inclusive one (wave 1, 64 groups per round).  The two reads share a round, and the waves'
 // results meet in LDS at one barrier per round.  At most a few dozen groups are in flight, so
-// one round usually suffices.  Waiting and the fallback follow look_back2: a round that has
+// one round usually suffices.  A round that has
 // waited `timeout` ticks computes the missing block aggregates from the words (block_aggregate),
 // sums a missing group from its blocks, and claims both with compare-and-swap from "empty".
 #pragma once

@@ -1,4 +1,4 @@
-// Single-pass unpack + combine of the batched path: one kernel reads every hit word once and
+// Single-pass unpack + combine before the event kernel (schedule 1): one kernel reads every hit word once and
 // writes the whole road table (event, set, hit_begin, nhits, ncombo, combo_begin), the
 // layer-grouped coordinates, the first road of every fit tile and the initial best-track keys.
 //
@@ -326,18 +326,17 @@ __global__ __launch_bounds__(kPT) void k_prepass(PArgs a) {
     }
 }
 
-// Clears the error word, the work tickets (the fused kernel's tile counter is the first), the
+// Clears the error word, the event kernel's ticket, the
 // kept count, the look-back status words in use and, when given, zero[0 .. n_zero) (the kept
-// list's per-block counts, which the fused kernel adds to); copies the word count into
+// list's per-block counts, which the event kernel adds to); copies the word count into
 // *nw_copy, where the pass's later kernels read it (the count may live in page-locked host
 // memory, and one read of it beats one per wave across the bus).
-__global__ void k_batch_reset(uint64_t *err, uint32_t *tickets, int64_t *d_n_kept,
+__global__ void k_batch_reset(uint64_t *err, uint32_t *ticket, int64_t *d_n_kept,
                               int64_t *status, int64_t n_status, Sizes nw, int64_t *nw_copy,
                               int64_t *zero, int64_t n_zero) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *err = SVT_NO_ERROR;
-        tickets[0] = 0;
-        tickets[1] = 0;
+        *ticket = 0;
         if (d_n_kept) *d_n_kept = 0;
         *nw_copy = nw.dev ? *nw.dev : nw.host;  // the one read of a (possibly host-side) count
     }
@@ -384,7 +383,7 @@ hipError_t launch_batch_reset(const PrepassLaunch &p, int64_t *nw_copy, int64_t 
     if (blocks < 1) blocks = 1;
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(k_batch_reset, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s,
-                       p.err, p.tickets, d_n_kept, p.status, p.status_words, p.nw, nw_copy, zero,
+                       p.err, p.ticket, d_n_kept, p.status, p.status_words, p.nw, nw_copy, zero,
                        zero ? n_zero : 0);
     return hipGetLastError();
 }

@@ -3,7 +3,7 @@
 ``PlainRunner`` drives the one-launch-per-stage path (svt_unpack -> svt_combine -> svt_fit ->
 svt_select) with the host synchronisations it needs to size each stage, like the staged
 kernels of the paper's GPU port.  ``BatchRunner`` keeps every buffer resident and runs the
-fused persistent pass (svt_process_batch), optionally replayed from a captured HIP graph.
+batched pass (svt_process_batch).
 """
 from __future__ import annotations
 
@@ -188,7 +188,7 @@ class PlainRunner:
 
 
 class BatchRunner:
-    """Resident buffers + svt_process_batch (fused persistent kernel, optional HIP graph)."""
+    """Resident buffers + svt_process_batch."""
 
     def __init__(self, cfg: L.svt_config, bank: torch.Tensor, word_cap: int, road_cap: int,
                  combo_cap: int, kept_cap: int = 0, tune: Optional[L.svt_tune] = None,
@@ -208,7 +208,7 @@ class BatchRunner:
         self.graph = graph
         self.word_cap, self.road_cap, self.combo_cap = word_cap, road_cap, combo_cap
         self.kept_cap = kept_cap
-        # graphs cannot be captured on the legacy default stream: own a stream
+        # SVT_BATCH_GRAPH is refused on the legacy default stream: own a stream
         self.stream = stream if stream is not None else torch.cuda.Stream(device=device)
         d = device
         self.words = torch.zeros(max(word_cap, 1), dtype=I32, device=d)
@@ -277,8 +277,7 @@ class BatchRunner:
         """One pass over the batch.  ``words``: another word buffer the kernels can read
         (a device tensor, or the device address of mapped host memory), default the
         resident one.  ``word_cap``: the capacity the pass is launched for (at least the
-        batch's word count, at most the runner's; default the runner's): with graphs, each
-        distinct value is one cached graph."""
+        batch's word count, at most the runner's; default the runner's)."""
         s = stream if stream is not None else self.stream
         src = self.words if words is None else words
         if word_cap is None or word_cap == self.word_cap:

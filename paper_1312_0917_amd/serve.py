@@ -2,15 +2,14 @@
 
 Events arrive over time (a Poisson stream in the benchmark).  The scheduler keeps a FIFO of
 arrived events and a few *slots*; each slot owns resident device buffers sized for one batch
-(the memory it may use), a stream, pinned host staging and, for the fused path, a captured HIP
-graph.  Whenever a slot is free, the scheduler admits the longest FIFO prefix of arrived events
-that fits the slot's memory (at most ``max_events`` events) and launches it: host-to-device copy
-of the packed words, the fit, device-to-host copy of the results, all asynchronous on the
+(the memory it may use), a stream and pinned host staging.  Whenever a slot is free, the
+scheduler admits the longest FIFO prefix of arrived events that fits the slot's memory (at most
+``max_events`` events) and launches it: host-to-device copy of the packed words, the fit, device-to-host copy of the results, all asynchronous on the
 slot's stream.  Several slots are in flight at once, so transfers and kernels of different
 batches overlap.  Latency of an event = time its results are on the host - its arrival time;
 it includes both transfers, as the paper's loop-latency measurements do (section IV-C).
 
-Slots are an interface: ``GpuSlot`` (fused persistent pass), ``PlainSlot`` (one launch per stage,
+Slots are an interface: ``GpuSlot`` (batched pass), ``PlainSlot`` (one launch per stage,
 host synchronisations in between) and, for CPU tests of the scheduling logic, any object with
 the same methods.
 """
@@ -220,23 +219,22 @@ def split_by_event(road_event: np.ndarray, arrays: dict, n_events: int) -> list:
 
 
 class GpuSlot:
-    """Fused persistent pass on its own stream, one batch at a time.
+    """Batched pass on its own stream, one batch at a time.
 
     ``io="mapped"`` (default): nothing is copied by a runtime call.  The slot writes the word
     count and the words into one page-locked buffer that the kernels read in place over the
     bus, and one small gather kernel (svt_gather_results) writes the sizes, the error word and
     the batch's n_roads per-road results straight into a second page-locked buffer.  A batch
-    is then one graph replay, one gather launch and one event: the runtime's copy calls, which
+    is then the pass, one gather launch and one event: the runtime's copy calls, which
     now and then spend milliseconds of host time inside the runtime, are off the loop.
 
-    ``io="copy"``: pinned words -> H2D -> graph replay -> D2H in two steps (the sizes and error
+    ``io="copy"``: pinned words -> H2D -> the pass -> D2H in two steps (the sizes and error
     word first, then exactly n_roads entries of each per-road array), kept for comparison.
 
     ``size_to_batch`` (default): each batch is launched for the smallest power-of-two word
     capacity (at least ``MIN_LAUNCH_WORDS``) that holds it, not for the slot's whole capacity,
-    so the persistent grids and look-back state match the batch; with graphs that is one
-    cached graph per capacity (``warm`` captures them all).  A zero schedule in ``tune`` is
-    then chosen per launch capacity, which puts small batches on the one-pass kernel.
+    so the grids match the batch.  A zero schedule in ``tune`` is then chosen per launch
+    capacity.
     """
 
     MIN_LAUNCH_WORDS = 4096
@@ -328,7 +326,7 @@ class GpuSlot:
         return launch_capacities(self.word_cap, self.MIN_LAUNCH_WORDS)
 
     def warm(self, words: np.ndarray):
-        """Run a small batch once per launch capacity (captures every graph before timing)."""
+        """Run a small batch once per launch capacity (loads every kernel before timing)."""
         for cap in self.launch_caps():
             self.batch = (words, 0, 1)
             self._enqueue(words, cap)

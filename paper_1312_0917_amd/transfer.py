@@ -9,7 +9,7 @@ of the total.  On one host the question left is how the packed hit words reach H
                 page-locked buffer (two host-side copies, like the scheme with two buffers);
   ``pinned``    words already in page-locked memory: one DMA straight into HBM (one shared
                 host buffer);
-  ``mapped``    no copy at all: the pre-pass kernel reads the page-locked words in place over
+  ``mapped``    no copy at all: the counting kernel reads the page-locked words in place over
                 the bus (zero-copy input).
 
 Results come back the same way for all three: the sizes, the error word and the per-road best

@@ -1,5 +1,4 @@
-"""Autotuner of the persistent fused pass: picks tile size, workgroup size and persistent
-workgroups per compute unit for a workload by timing graph replays of svt_process_batch.
+"""Autotuner of the batched pass: picks the schedule for a workload by timing svt_process_batch.
 
 Every candidate must write exactly the same bytes (the schedule does not change the result);
 the tuner checks this on each candidate, so tuning doubles as a race/determinism sweep.
@@ -20,11 +19,6 @@ import torch
 from . import _lib as L
 from . import pipeline as P
 
-TILES = (4096, 8192)
-WG_SIZES = (256, 512)
-OCCUPANCIES = (1, 2, 3, 4)
-ONEPASS_OCCUPANCIES = (1, 2, 3)
-CHUNK_ROADS = (32, 64)
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "svt_tune.json")
 
 
@@ -37,15 +31,12 @@ TIE = 0.025
 
 
 def candidates():
-    """The one-pass kernel at each resident grid size, the flat-tile shapes of the two-kernel
-    pass (tile, roads per chunk, workgroup size, workgroups per CU), and the
-    one-event-per-workgroup schedule."""
-    onepass = [L.make_tune(0, 0, 0, occ, L.SVT_SCHEDULE_ONEPASS) for occ in ONEPASS_OCCUPANCIES]
-    flat = [L.make_tune(t, ch, wg, occ, L.SVT_SCHEDULE_TILES)
-            for t in TILES for ch in CHUNK_ROADS for wg in WG_SIZES for occ in OCCUPANCIES]
+    """The unit kernels, under both schedules that name them (they take nothing else from a
+    tune), and the one-event-per-workgroup schedule."""
+    units = [L.make_tune(schedule=sc) for sc in (L.SVT_SCHEDULE_ONEPASS, L.SVT_SCHEDULE_TILES)]
     events = [L.make_tune(4096, 64, 256, occ, L.SVT_SCHEDULE_EVENTS)
               for occ in EVENT_OCCUPANCIES]
-    return [L.svt_tune_resolve(t) for t in onepass + flat + events]
+    return [L.svt_tune_resolve(t) for t in units + events]
 
 
 def tune_tuple(t: L.svt_tune):
@@ -79,11 +70,11 @@ def autotune(words: torch.Tensor, bank: torch.Tensor, cfg: L.svt_config, n_roads
              n_combos: int, samples: int = 30, per_sample: int = 5, warmup: int = 3,
              cands=None, cache_path: Optional[str] = DEFAULT_CACHE, use_cache: bool = True,
              log=None) -> TuneResult:
-    """Time every candidate on this batch (graph replays) and return the fastest (ties within
+    """Time every candidate on this batch and return the fastest (ties within
     TIE of it go to the earliest candidate in order).
 
     A candidate's time is the median over ``samples`` samples, each the mean of
-    ``per_sample`` back-to-back replays (host clock, synchronised around the sample), so one
+    ``per_sample`` back-to-back passes (host clock, synchronised around the sample), so one
     stall of the runtime moves one sample and not the pick.  ``words`` is a device int32
     tensor of the batch's hit words.  Raises if two candidates disagree on any output byte.
     """
@@ -124,13 +115,12 @@ def autotune(words: torch.Tensor, bank: torch.Tensor, cfg: L.svt_config, n_roads
         if log:
             log(f"tune {tune_tuple(t)}: {ms:.4f} ms")
         timed.append((t, ms))
-        L.svt_release_graphs()
         del runner
         torch.cuda.empty_cache()
     fastest = min(ms for _, ms in timed)
     best = next((t, ms) for t, ms in timed if ms <= fastest * (1 + TIE))
     res = TuneResult(best[0], best[1], table,
-                     f"median of {samples} samples of {per_sample} graph replays; within "
+                     f"median of {samples} samples of {per_sample} passes; within "
                      f"{TIE:.1%} of the fastest the first candidate in order")
     if cache_path:
         os.makedirs(os.path.dirname(cache_path), exist_ok=True)
@@ -148,12 +138,9 @@ def autotune(words: torch.Tensor, bank: torch.Tensor, cfg: L.svt_config, n_roads
 
 def pick_launch_mode(runner: P.BatchRunner, samples: int = 30, per_sample: int = 5,
                      warmup: int = 3):
-    """Time one batch runner with graph replays and with direct launches (the same statistic as
-    autotune) and leave it in the faster mode.  Returns {"graph": ms, "direct": ms}.
-
-    The pass is the same kernels either way; on ROCm a replayed graph costs several
-    microseconds more per pass than launching its kernels directly, which matters for batches
-    whose pass takes tens of microseconds."""
+    """Time one batch runner with and without SVT_BATCH_GRAPH (the same statistic as autotune) and
+    leave it in the faster mode.  Returns {"graph": ms, "direct": ms}; the pass is the same
+    launches either way, so the two differ by noise."""
     times = {}
     for graph in (True, False):
         runner.graph = graph

@@ -13,6 +13,7 @@ from tiny import stream
 
 from paper_1312_0917_amd import _lib as L
 from paper_1312_0917_amd import pipeline as P
+from paper_1312_0917_amd import synth
 
 pytestmark = pytest.mark.gpu
 CFG = oracle.make_config()
@@ -110,3 +111,15 @@ def test_kept_only_of_sliced_units(bank):
     kept = np.asarray(ref["kept"])
     for k in ("p0", "p1", "p2", "c0", "c1", "c2", "chi2"):
         assert np.array_equal(np.asarray(ref[k])[kept], got[f"kept_{k}"].cpu().numpy()), k
+
+
+def test_event_schedule_with_computed_look_back(bank, monkeypatch):
+    """The event schedule's pre-pass, several groups of blocks, with every wait of its look-back
+    answered by the words themselves."""
+    monkeypatch.setenv("SVT_LOOKBACK_TIMEOUT_TICKS", "0")
+    s = synth.make_sample("c2", bank=bank, n_events=1000)
+    cfg = oracle.make_config(chi2_cut=synth.config_chi2_cut("c2"))
+    ref = oracle.run(s.words, bank.f, bank.q, cfg)
+    got, _ = run_batch(s.words, bank.f, bank.q, cfg, ref=ref, graph=False,
+                       tune=L.make_tune(schedule=L.SVT_SCHEDULE_EVENTS))
+    compare(ref, got, BATCH_KEYS, "event schedule")
