@@ -129,6 +129,19 @@ __device__ __forceinline__ uint64_t uni(uint64_t x) {
     return static_cast<uint64_t>(uni(static_cast<uint32_t>(x))) |
            (static_cast<uint64_t>(uni(static_cast<uint32_t>(x >> 32))) << 32);
 }
+// __ballot takes an int: its argument goes through a register and is compared once more
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// A 32-bit offset in bytes from a pointer that is the same in all lanes.  offset_of keeps the
+// compiler from widening it where it is computed: widened next to the access, it needs no 64-bit
+// address.
+__device__ __forceinline__ uint32_t offset_of(uint32_t o) {
+    asm("" : "+v"(o));
+    return o;
+}
+template <typename T>
+__device__ __forceinline__ T *at_byte(T *p, uint32_t o) {
+    return reinterpret_cast<T *>(reinterpret_cast<char *>(p) + o);
+}
 // number of set bits of m below the calling lane
 __device__ __forceinline__ int bits_below(uint64_t m) {
     return static_cast<int>(__builtin_amdgcn_mbcnt_hi(

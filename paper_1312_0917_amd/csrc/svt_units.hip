@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 #pragma unroll
             for (int e = 0; e < kUnitLane; ++e)
                 any_bad |= w_layer(uw.w[e]) >= static_cast<uint32_t>(SVT_N_LAYERS);
-            const bool bad = __ballot(any_bad) != 0;
+            const bool bad = ballot(any_bad) != 0;
             UnitScan sc;
             if (nloc < kUnitSpan || bad)
                 sc = scan_unit<true>(uw, nloc);
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                     c = over ? 0 : road_combos(nh);
                 }
                 csum += c;
-                const uint64_t m = __ballot(over);
+                const uint64_t m = ballot(over);
                 if (m && my_over == ~0u) my_over = r0 + __builtin_ctzll(m);
             }
             cs = lane_value(scan64(csum), 63);
@@ -238,10 +238,10 @@ constexpr int kTabCap = 768;   // coordinate-pair table entries of the roads fit
 constexpr int kTabPad = 8;     // a dummy slot reads up to 3 entries before or after its table
 
 // Per road with combinations, while its tables are in LDS (two 16-byte reads per lane):
-//   a: division magic of n4 | n4 << 24; the same of n2 * n3; table of the (h0, h1) pairs | of the
-//      (h2, h3) pairs << 16; table of layer 4 | constant set << 16
-//   b: first combination, end (from GB, the unit's first combination rounded down to a multiple
-//      of 4), its first group less its first item, hits per layer
+//   a: division magic of n4 | n4 << 24; the same of n2 * n3; first combination, end (from GB, the
+//      unit's first combination rounded down to a multiple of 4)
+//   b: its first group less its first item; hits per layer | road << 24; table of the (h0, h1)
+//      pairs | of the (h2, h3) pairs << 16; table of layer 4 | constant set << 16
 struct RoadRow {
     uint4 a, b;
 };
@@ -251,12 +251,16 @@ struct alignas(16) WaveLds {
         uint2 ent[kEntries + 1];
         int32_t xt[kTabPad + kTabCap + kTabPad];
     };
-    uint32_t chi[4 * kWaveSize];
+    union {
+        struct {
+            uint32_t chi[4 * kWaveSize];
+            uint32_t mark[kWaveSize];  // window item -> a road starts there (zero between uses)
+        };
+        uint32_t place[SVT_N_LAYERS * kUnitFitRoads];  // layer, road: where its words' coordinates go
+    };
     RoadRow road[kUnitFitRoads];
     unsigned long long key[kUnitFitRoads];
     uint32_t nacc[kUnitFitRoads];
-    uint32_t mark[kWaveSize];  // window item -> a road starts there (zero between uses)
-    uint8_t fi[kUnitWords];    // road -> its index among the roads with combinations
 };
 
 constexpr uint64_t kComboMask = (1ull << kExtraShift) - 1;
@@ -324,7 +328,7 @@ __device__ __forceinline__ void row4(uint32_t f01, uint32_t f23, uint32_t f4, ui
         : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
         : "v"(f01), "v"(f23), "v"(f4), "v"(seed), "v"(x01[0]), "v"(x01[1]), "v"(x01[2]),
           "v"(x01[3]), "v"(x23[0]), "v"(x23[1]), "v"(x23[2]), "v"(x23[3]), "v"(x4[0]), "v"(x4[1]),
-          "v"(x4[2]), "v"(x4[3]), "s"(shift));
+          "v"(x4[2]), "v"(x4[3]), "v"(shift));
 }
 
 template <int MODE, int J0>
@@ -361,8 +365,8 @@ __device__ __forceinline__ Fit fit_one(const RoadRow &r, const UnitSet &c, const
     const uint32_t n4 = r.a.x >> 24, n23 = r.a.y >> 24;
     const uint32_t q4 = div_small(k, r.a.x), h4 = k - q4 * n4;
     const uint32_t i01 = div_small(q4, r.a.y), i23 = q4 - i01 * n23;
-    const int32_t x01 = xt[(r.a.z & 0xFFFFu) + i01], x23 = xt[(r.a.z >> 16) + i23],
-                  x4 = xt[(r.a.w & 0xFFFFu) + h4];
+    const int32_t x01 = xt[(r.b.z & 0xFFFFu) + i01], x23 = xt[(r.b.z >> 16) + i23],
+                  x4 = xt[(r.b.w & 0xFFFFu) + h4];
     Fit f;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
@@ -401,7 +405,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                                                          : 0xFFFFFFFFu;
     const int32_t g_abs = static_cast<int32_t>(GB >> 2) & (kLineGroups - 1);
     int rcur = c0 - 1 + static_cast<int>(__popcll(
-                            __ballot(lane >= c0 && lane < c1 && first_item <= from_item)));
+                            ballot(lane >= c0 && lane < c1 && first_item <= from_item)));
     for (uint32_t i0 = from_item; i0 < n_items;) {
         int nit = n_items - i0 < kWaveSize ? static_cast<int>(n_items - i0) : kWaveSize;
         const uint32_t i = i0 + lane;
@@ -409,17 +413,17 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         if (lane > rcur && lane < c1 && first_item - i0 < kWaveSize) W.mark[first_item - i0] = 1;
         lds_order();
         const uint32_t mk = W.mark[lane];
-        const uint64_t starts = __ballot(mk != 0);
+        const uint64_t starts = ballot(mk != 0);
         if (mk) W.mark[lane] = 0;
         const int ri = rcur + bits_below(starts) + static_cast<int>(mk);
         const uint4 ma = W.road[ri].a, mb = W.road[ri].b;
-        const int32_t rb = static_cast<int32_t>(mb.x), end = static_cast<int32_t>(mb.y);
-        const int32_t g = static_cast<int32_t>(i + mb.z);
+        const int32_t rb = static_cast<int32_t>(ma.z), end = static_cast<int32_t>(ma.w);
+        const int32_t g = static_cast<int32_t>(i + mb.x);
         if (i0 + nit < n_items) {
             // end the window where a line of the record arrays ends, and at a whole group
             const int32_t gl = static_cast<int32_t>(lane_value(g, nit - 1)) + g_abs;
             const int32_t stop = (gl & ~(kLineGroups - 1)) - g_abs;
-            nit = __popcll(__ballot(lane < nit && g < stop));
+            nit = __popcll(ballot(lane < nit && g < stop));
         }
         const bool active = lane < nit;
         const int32_t rel = 4 * g;
@@ -441,8 +445,8 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             int32_t h4 = k0 - static_cast<int32_t>(mul_u24(q4, n4));  // < 0 before the road
             uint32_t i01 = div_small(q4, ma.y);
             uint32_t i23 = q4 - mul_u24(i01, n23);
-            const int32_t *t01 = xt + (ma.z & 0xFFFFu), *t23 = xt + (ma.z >> 16),
-                          *t4 = xt + (ma.w & 0xFFFFu);
+            const int32_t *t01 = xt + (mb.z & 0xFFFFu), *t23 = xt + (mb.z >> 16),
+                          *t4 = xt + (mb.w & 0xFFFFu);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 x01[e] = t01[i01];
@@ -460,7 +464,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             }
         }
         Fit4<MODE, J0> f;
-        fit_rows<MODE, J0>(L.bank[ma.w >> 16], x01, x23, x4, shift, qlmask, f);
+        fit_rows<MODE, J0>(L.bank[mb.w >> 16], x01, x23, x4, shift, qlmask, f);
         uint32_t acc = 0;
         bool near;
         if (MODE == kFitNarrow) {
@@ -473,7 +477,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         } else {
             near = true;
         }
-        if (__ballot(near)) {  // a chi-square of the window may pass
+        if (ballot(near)) {  // a chi-square of the window may pass
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 acc |= static_cast<int64_t>(f.chi2[e]) <= a.cfg.chi2_cut ? 1u << e : 0u;
@@ -503,7 +507,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                     if (REC == kRecNone) {
                         if (pos < a.slot_bytes / 16)
                             reinterpret_cast<uint4 *>(keep_at)[pos] = make_uint4(
-                                c | (ma.w >> 16 << 24),
+                                c | (mb.w >> 16 << 24),
                                 static_cast<uint32_t>(pick(x01[0], x01[1], x01[2], x01[3])),
                                 static_cast<uint32_t>(pick(x23[0], x23[1], x23[2], x23[3])),
                                 static_cast<uint32_t>(pick(x4[0], x4[1], x4[2], x4[3])));
@@ -516,7 +520,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         // ---- groups cut by a road boundary: the first item's lane takes the others' slots
         const uint32_t gp = dpp<kDppPrev>(static_cast<uint32_t>(g), ~0u);
         const bool cont = active && lane > 0 && static_cast<uint32_t>(g) == gp;
-        for (uint64_t m = __ballot(cont); m; m &= m >> 1) {
+        for (uint64_t m = ballot(cont); m; m &= m >> 1) {
             // (a lane whose source is switched off keeps its value, so the lanes that give a
             // slot stay on with those that take it; what the givers are left with is not read)
             const uint32_t take = dpp<kDppNext>(cont ? slots | (acc << 8) : 0u);
@@ -546,10 +550,11 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         int64_t *pc = a.out.chi2 + GB;
         uint8_t *pa = a.accept + GB;
         if (head && slots == 0xFu) {
+            const uint32_t o1 = offset_of(at), o4 = offset_of(4 * at);
             if (REC != kRecNone) {
-                store_nt(p0 + at, f.v[0]);
-                store_nt(p1 + at, f.v[1]);
-                store_nt(p2 + at, f.v[2]);
+                store_nt(at_byte(p0, o4), f.v[0]);
+                store_nt(at_byte(p1, o4), f.v[1]);
+                store_nt(at_byte(p2, o4), f.v[2]);
                 if (MODE != kFitNarrow) {
                     store_nt(pc + at, static_cast<int64_t>(f.chi2[0]),
                              static_cast<int64_t>(f.chi2[1]));
@@ -558,11 +563,11 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                 }
             }
             if (REC == kRecRows) {
-                if (a.out.c0) store_nt(a.out.c0 + GB + at, f.v[3]);
-                if (a.out.c1) store_nt(a.out.c1 + GB + at, f.v[4]);
-                if (a.out.c2) store_nt(a.out.c2 + GB + at, f.v[5]);
+                if (a.out.c0) store_nt(at_byte(a.out.c0 + GB, o4), f.v[3]);
+                if (a.out.c1) store_nt(at_byte(a.out.c1 + GB, o4), f.v[4]);
+                if (a.out.c2) store_nt(at_byte(a.out.c2 + GB, o4), f.v[5]);
             }
-            *reinterpret_cast<uint32_t *>(pa + at) = mul_u24(acc, 0x204081u) & 0x01010101u;
+            *reinterpret_cast<uint32_t *>(at_byte(pa, o1)) = mul_u24(acc, 0x204081u) & 0x01010101u;
         } else if (head) {  // a group shared with the unit before or after this one
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -600,8 +605,8 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                 const uint2 c = *reinterpret_cast<const uint2 *>(W.chi + t);
                 int64_t *q = pc + 4 * g0;
                 if (t >= w0 && t + 2 <= w1)
-                    store_nt(q + static_cast<uint32_t>(t), static_cast<int64_t>(c.x),
-                             static_cast<int64_t>(c.y));
+                    store_nt(at_byte(q, offset_of(8 * static_cast<uint32_t>(t))),
+                             static_cast<int64_t>(c.x), static_cast<int64_t>(c.y));
                 else if (t + 1 >= w0 && t < w1) {
                     if (t >= w0) q[t] = c.x;
                     if (t + 1 < w1) q[t + 1] = c.y;
@@ -665,14 +670,16 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         const uint32_t cs = scan64(c);
         const uint32_t cb = c_run + cs - c;
         c_run += lane_value(cs, 63);
-        const uint64_t em = __ballot(ev), fm = __ballot(c > 0);
+        const uint64_t em = ballot(ev), fm = ballot(c > 0);
         const int fi = nf + bits_below(fm);
         nf += __popcll(fm);
         const uint32_t evn = ev_run + bits_below(em) + (ev ? 1u : 0u);
         ev_run += __popcll(em);
         if (mine) {
-            W.fi[rl] = static_cast<uint8_t>(c > 0 ? fi : 255);
-            if (c > 0) W.road[fi].b = make_uint4(o + cb, pos, tag, nh | (rl << 24));
+            // (for its words: its index among the roads that may be fitted now, past 63 for none)
+            W.ent[rl].y = pos | (tag << 16) |
+                          ((c > 0 ? static_cast<uint32_t>(fi - c0) : 255u) << 24);
+            if (c > 0) W.road[fi].b = make_uint4(o + cb, nh | (rl << 24), tag, 0);
         }
         if (mine && table) {
             const UArgs &a = L.args;
@@ -694,45 +701,48 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         }
     }
     if (nf == 0) return 0;
+    if (lane == 0) W.ent[nr].y = ~0u;  // (the same for words of no road of the unit)
     lds_order();
 
-    // ---- words: rank among the road's hits on the layer; coordinate and layer (16 bits),
-    // rank << 16, road with combinations << 24 (255: none)
-    uint32_t wd[kUnitLane];
+    // ---- words: rank among the road's hits on the layer, and the road's index; all entries are read
+    // before the first is used
+    uint32_t rank[kUnitLane], road_of[kUnitLane];
     {
+        uint2 ent[kUnitLane];
         uint32_t hits = sc.hits, rl = (sc.rd & 0xFFFFu) - 1u;
 #pragma unroll
         for (int e = 0; e < kUnitLane; ++e) {
             rl += (sc.starts >> e) & 1u;
-            const uint32_t x = uw.w[e];
-            uint32_t v = 255u << 24;
-            if (rl < nr && kUnitLane * lane + e < nloc) {
-                const uint32_t d = hits - W.ent[rl].x;
-                v = (x & 0xFFFFu) | (((d >> (6 * w_layer(x))) & 0xFu) << 16) |
-                    (static_cast<uint32_t>(W.fi[rl]) << 24);
-            }
-            wd[e] = v;
+            ent[e] = W.ent[rl < nr ? rl : nr];
+        }
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e) {
+            rank[e] = __builtin_amdgcn_ubfe(hits - ent[e].x, 6 * w_layer(uw.w[e]), 4);
+            road_of[e] = ent[e].y >> 24;
             hits += sc.hit[e];
         }
+        if (nloc < kUnitSpan)
+#pragma unroll
+            for (int e = 0; e < kUnitLane; ++e)
+                if (kUnitLane * lane + e >= nloc) road_of[e] = 255;
     }
     // ---- one road with combinations per lane: roads c0 .. c1 - 1 are fitted now -----------------
     const bool road = lane < nf && lane >= c0;
-    W.mark[lane] = 0;
     W.key[lane] = ~0ull;
     W.nacc[lane] = 0;
     const uint4 pre = road ? W.road[lane].b : make_uint4(0, 0, 0, 0);
     lds_order();
-    const uint32_t nh = pre.w, n4 = nh_of(nh, 4), n01 = nh_of(nh, 0) * nh_of(nh, 1),
+    const uint32_t nh = pre.y, n4 = nh_of(nh, 4), n01 = nh_of(nh, 0) * nh_of(nh, 1),
                    n23 = nh_of(nh, 2) * nh_of(nh, 3);
     const uint32_t ntab = n01 + n23 + n4, rb = pre.x, end = rb + n01 * n23 * n4;
     const uint32_t n_it = road ? ((end - 1) >> 2) - (rb >> 2) + 1 : 0;
     const uint32_t tend = scan64(ntab);
     const bool take = road && tend <= kTabCap;
-    const int c1 = c0 + __popcll(__ballot(take));
+    const int c1 = c0 + __popcll(ballot(take));
     const uint32_t it_end = scan64(take ? n_it : 0);
     const uint32_t item = it_end - n_it;
     uint32_t n_items = lane_value(it_end, 63), from_item = 0;
-    const bool narrow = __ballot(take && !L.bank[pre.z].narrow) == 0;
+    const bool narrow = ballot(take && !L.bank[pre.z].narrow) == 0;
     // groups ga .. gb - 1 of the unit are this slice's (the last slice takes what is left over)
     const uint32_t slices = SLICED && c_run > slice_len ? (c_run - 1) / slice_len + 1 : 1;
     const uint32_t slice_groups = slice_len / 4;
@@ -751,41 +761,49 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     if (take) {
         RoadRow row;
         const uint32_t t = tend - ntab;
-        row.a = make_uint4(L.magic[n4] | (n4 << 24), L.magic[n23] | (n23 << 24),
-                           t | ((t + n01) << 16), (t + n01 + n23) | (pre.z << 16));
-        row.b = make_uint4(rb, end, (rb >> 2) - item, nh);
+        row.a = make_uint4(L.magic[n4] | (n4 << 24), L.magic[n23] | (n23 << 24), rb, end);
+        row.b = make_uint4((rb >> 2) - item, nh, t | ((t + n01) << 16),
+                           (t + n01 + n23) | (pre.z << 16));
         W.road[lane] = row;
+        // Where a word's coordinate goes, by layer: bytes from the tables' start (12 bits), and on per
+        // rank (6 bits, from bit 12); bytes from one entry to the next (6 bits, from 18); entries.
+        const uint32_t n0 = nh_of(nh, 0), n1 = nh_of(nh, 1), n2 = nh_of(nh, 2), n3 = nh_of(nh, 3);
+        const uint32_t p01 = 4 * t, p23 = p01 + 4 * n01, p4 = p23 + 4 * n23;
+        uint32_t *place = W.place + (lane - c0);
+        place[0] = p01 | (n1 << 14) | (4u << 18) | (n1 << 24);
+        place[kUnitFitRoads] = (p01 + 2) | (4u << 12) | (n1 << 20) | (n0 << 24);
+        place[2 * kUnitFitRoads] = p23 | (n3 << 14) | (4u << 18) | (n3 << 24);
+        place[3 * kUnitFitRoads] = (p23 + 2) | (4u << 12) | (n3 << 20) | (n2 << 24);
+        place[4 * kUnitFitRoads] = p4 | (4u << 12) | (1u << 24);
     }
     lds_order();
     // Tables of coordinate pairs, (x0 | x1 << 16) at h0 * n1 + h1 and the same for layers 2 and 3,
-    // and of layer 4: each word writes its half of the entries it belongs to.
+    // and of layer 4: each word writes its half of the entries it belongs to, the lane's words
+    // side by side.
     {
-        int16_t *xh = reinterpret_cast<int16_t *>(W.xt + kTabPad);
+        char *xt = reinterpret_cast<char *>(W.xt + kTabPad);
+        uint32_t cnt[kUnitLane], step[kUnitLane], at[kUnitLane], most = 0;
+#pragma unroll
+        for (int e = 0; e < kUnitLane; ++e)
+            at[e] = W.place[w_layer(uw.w[e]) * kUnitFitRoads + (road_of[e] & (kUnitFitRoads - 1))];
 #pragma unroll
         for (int e = 0; e < kUnitLane; ++e) {
-            const uint32_t f = wd[e] >> 24;
-            if (f >= static_cast<uint32_t>(c0) && f < static_cast<uint32_t>(c1)) {
-                const uint4 ra = W.road[f].a;
-                const uint32_t l = (wd[e] >> 13) & 7u, rank = (wd[e] >> 16) & 0xFu;
-                const uint32_t h = W.road[f].b.w >> (l & 2u ? 8 : 0);  // its pair's hits
-                const uint32_t na = h & 0xFu, nb = (h >> 4) & 0xFu;
-                const uint32_t tb = l & 2u ? ra.z >> 16 : ra.z & 0xFFFFu;
-                const bool odd = l & 1u;
-                uint32_t cnt = odd ? na : nb;
-                const uint32_t step = odd ? 2 * nb : 2u;
-                uint32_t p = 2 * tb + (odd ? 2 * rank + 1 : 2 * rank * nb);
-                if (l == 4) {
-                    cnt = 1;
-                    p = 2 * ((ra.w & 0xFFFFu) + rank);
-                }
-                const int16_t x = static_cast<int16_t>(w_coord(wd[e]));
-                do {
-                    xh[p] = x;
-                    p += step;
-                } while (--cnt);
-            }
+            const uint32_t pl = at[e];
+            cnt[e] = road_of[e] < static_cast<uint32_t>(c1 - c0) ? pl >> 24 : 0u;
+            step[e] = (pl >> 18) & 0x3Fu;
+            at[e] = (pl & 0xFFFu) + mul_u24(rank[e], (pl >> 12) & 0x3Fu);
+            most = cnt[e] > most ? cnt[e] : most;
         }
+        for (uint32_t r = 0; ballot(r < most); ++r)
+#pragma unroll
+            for (int e = 0; e < kUnitLane; ++e) {
+                if (r < cnt[e])
+                    *reinterpret_cast<int16_t *>(xt + at[e]) = static_cast<int16_t>(w_coord(uw.w[e]));
+                at[e] += step[e];
+            }
     }
+    lds_order();
+    W.mark[lane] = 0;
     lds_order();
     uint32_t *keep_at = nullptr;
     if ((REC == kRecNone || hot.keep) && slices == 1)
@@ -807,7 +825,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         if (SLICED && slices > 1) {
             // a road with groups in other slices too: every one of them adds what it found, and
             // the last to do so has the whole of it
-            const uint32_t g_first = row.b.x >> 2, g_last = (row.b.y - 1) >> 2;
+            const uint32_t g_first = row.a.z >> 2, g_last = (row.a.w - 1) >> 2;
             const bool touched = g_last >= ga && g_first < gb;
             const bool cut = touched && (g_first < ga || g_last >= gb);
             whole = touched && !cut;
@@ -835,14 +853,14 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         }
         if (whole) {
             const UArgs &a = L.args;
-            const int64_t r = R0 + (row.b.w >> 24);
-            const UnitSet &c = L.bank[row.a.w >> 16];
+            const int64_t r = R0 + (row.b.y >> 24);
+            const UnitSet &c = L.bank[row.b.w >> 16];
             const int32_t *xt = W.xt + kTabPad;
             int32_t k = -1, v0 = INT32_MIN, v1 = INT32_MIN, v2 = INT32_MIN;
             int64_t chi2 = INT64_MAX;
             if (key != ~0ull && (key >> kKeyKBits) == kKeyChiMax) {
                 // saturated key (chi2 >= 2^49 - 1, extreme constants only): exact rescan
-                for (uint32_t q = 0; q < row.b.y - row.b.x; ++q) {
+                for (uint32_t q = 0; q < row.a.w - row.a.z; ++q) {
                     const int64_t c2 = fit_one(row, c, xt, q, shift, qlmask).chi2;
                     if (c2 <= a.cfg.chi2_cut && c2 < chi2) {
                         chi2 = c2;
@@ -891,7 +909,7 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
     const int lane = lane_id();
     int r = -1;  // last range whose extras start at or before e
     for (int r0 = 0; r0 < n_ranges; r0 += kWaveSize)
-        r += __popcll(__ballot(r0 + lane < n_ranges && L.range.base[r0 + lane].extra <= e));
+        r += __popcll(ballot(r0 + lane < n_ranges && L.range.base[r0 + lane].extra <= e));
     e -= uni(L.range.base[r].extra);
     const int64_t lo = r * per, hi = lo + per < nu ? lo + per : nu;
     int64_t u = lo - 1;  // last unit whose extras start at or before e
@@ -899,7 +917,7 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
     for (int64_t u0 = lo; u0 < hi; u0 += kWaveSize) {
         uint32_t x = ~0u;
         if (u0 + lane < hi) x = static_cast<uint32_t>(a.rec[u0 + lane].combos >> kExtraShift);
-        const uint64_t m = __ballot(x <= e);  // a prefix of the lanes
+        const uint64_t m = ballot(x <= e);  // a prefix of the lanes
         if (m == 0) break;
         u += __popcll(m);
         first = lane_value(x, 63 - __builtin_clzll(m));
@@ -983,7 +1001,7 @@ __device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges
         // the first error, in the ranges' order; a road's index from the wave's first range
         uint64_t err = SVT_NO_ERROR;
         const bool bad = tid < ranges && (t.bad_word & t.over_road & t.set_road) != ~0u;
-        if (__ballot(bad)) {
+        if (ballot(bad)) {
             auto note = [&](uint64_t cls, uint32_t idx, uint64_t from) {
                 const uint64_t v = (cls << 56) | (from + idx);
                 if (bad && idx != ~0u && v < err) err = v;
@@ -1330,7 +1348,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             uint2 e0 = make_uint2(0, 0);
             if (rl < nr) e0 = W.ent[rl];
             const bool ev = (e0.y >> 9) & 1u;
-            const uint64_t em = __ballot(ev);
+            const uint64_t em = ballot(ev);
             const uint32_t evn = ev_run + bits_below(em) + (ev ? 1u : 0u);
             ev_run += __popcll(em);
             if (rl < nr) {
