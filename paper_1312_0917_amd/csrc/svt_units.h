@@ -142,6 +142,21 @@ template <typename T>
 __device__ __forceinline__ T *at_byte(T *p, uint32_t o) {
     return reinterpret_cast<T *>(reinterpret_cast<char *>(p) + o);
 }
+__device__ __forceinline__ const int32_t *at_byte(const int32_t *p, uint32_t o) {
+    return reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(p) + o);
+}
+// LDS by 32-bit address
+typedef __attribute__((address_space(3))) const int32_t LdsInt;
+__device__ __forceinline__ uint32_t lds_address(const int32_t *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsInt *)p));
+}
+__device__ __forceinline__ int32_t lds_read(uint32_t at) { return *(LdsInt *)static_cast<uintptr_t>(at); }
+// bits off .. off + width - 1, both below 32
+__device__ __forceinline__ uint32_t bit_field(int32_t width, int32_t off) {
+    uint32_t r;
+    asm("v_bfm_b32 %0, %1, %2" : "=v"(r) : "v"(width), "v"(off));
+    return r;
+}
 // number of set bits of m below the calling lane
 __device__ __forceinline__ int bits_below(uint64_t m) {
     return static_cast<int>(__builtin_amdgcn_mbcnt_hi(

@@ -238,10 +238,10 @@ constexpr int kTabCap = 768;   // coordinate-pair table entries of the roads fit
 constexpr int kTabPad = 8;     // a dummy slot reads up to 3 entries before or after its table
 
 // Per road with combinations, while its tables are in LDS (two 16-byte reads per lane):
-//   a: division magic of n4 | n4 << 24; the same of n2 * n3; first combination, end (from GB, the
-//      unit's first combination rounded down to a multiple of 4)
+//   a: division magic of n4 | 4 * n4 << 24; of n2 * n3 | n2 * n3 << 24; first combination, end (from
+//      GB, the unit's first combination rounded down to a multiple of 4)
 //   b: its first group less its first item; hits per layer | road << 24; table of the (h0, h1)
-//      pairs | of the (h2, h3) pairs << 16; table of layer 4 | constant set << 16
+//      pairs | of the (h2, h3) pairs << 16; table of layer 4 | constant set << 16 (tables in bytes)
 struct RoadRow {
     uint4 a, b;
 };
@@ -362,11 +362,11 @@ __device__ __forceinline__ void fit_rows(const UnitSet &c, const int32_t *x01, c
 // One combination of a road from its tables, with 64-bit chi-square.
 __device__ __forceinline__ Fit fit_one(const RoadRow &r, const UnitSet &c, const int32_t *xt,
                                        uint32_t k, int32_t shift, uint32_t qlmask) {
-    const uint32_t n4 = r.a.x >> 24, n23 = r.a.y >> 24;
+    const uint32_t n4 = r.a.x >> 26, n23 = r.a.y >> 24;
     const uint32_t q4 = div_small(k, r.a.x), h4 = k - q4 * n4;
     const uint32_t i01 = div_small(q4, r.a.y), i23 = q4 - i01 * n23;
-    const int32_t x01 = xt[(r.b.z & 0xFFFFu) + i01], x23 = xt[(r.b.z >> 16) + i23],
-                  x4 = xt[(r.b.w & 0xFFFFu) + h4];
+    const int32_t x01 = *at_byte(xt + i01, r.b.z & 0xFFFFu), x23 = *at_byte(xt + i23, r.b.z >> 16),
+                  x4 = *at_byte(xt + h4, r.b.w & 0xFFFFu);
     Fit f;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
@@ -400,7 +400,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
     // Without records there is less to win and the lanes left idle weigh more.
     constexpr int kLineGroups = REC == kRecNone ? 4 : 8;
     const int lane = lane_id();
-    const int32_t *xt = W.xt + kTabPad;
+    const uint32_t xt_at = lds_address(W.xt + kTabPad);
     const uint32_t cut32 = a.cfg.chi2_cut < 0xFFFFFFFFll ? static_cast<uint32_t>(a.cfg.chi2_cut)
                                                          : 0xFFFFFFFFu;
     const int32_t g_abs = static_cast<int32_t>(GB >> 2) & (kLineGroups - 1);
@@ -423,72 +423,78 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             // end the window where a line of the record arrays ends, and at a whole group
             const int32_t gl = static_cast<int32_t>(lane_value(g, nit - 1)) + g_abs;
             const int32_t stop = (gl & ~(kLineGroups - 1)) - g_abs;
-            nit = __popcll(ballot(lane < nit && g < stop));
+            nit = __popcll(ballot(g < stop) & (~0ull >> (kWaveSize - nit)));
         }
-        const bool active = lane < nit;
+        const uint64_t active_m = ~0ull >> (kWaveSize - nit);  // (nit > 0)
+        const bool active = __builtin_amdgcn_inverse_ballot_w64(active_m);
         const int32_t rel = 4 * g;
-        const int32_t k0 = active ? rel - rb : 0;
-        uint32_t slots = 0;
+        const int32_t k0 = active ? rel - rb : 0, kc = k0 < 0 ? 0 : k0;
+        uint32_t slots;  // the group's combinations that are the road's
         {
-            const int32_t lo = k0 < 0 ? -k0 : 0;
-            int32_t out = rel + 4 - end;  // slots past the road's end
-            out = out < 0 ? 0 : out > 4 ? 4 : out;
-            slots = active ? (0xFu << lo) & (0xFu >> out) : 0u;
+            const int32_t lo = kc - k0, hi = end - rel < 4 ? end - rel : 4;
+            slots = bit_field(active ? hi - lo : 0, lo);
         }
         // ---- the four combinations' table entries, stepped with carries (a slot outside the
         // road reads a neighbouring entry and is not written)
         int32_t x01[4], x23[4], x4[4];
         {
-            const uint32_t kc = k0 < 0 ? 0u : static_cast<uint32_t>(k0);
-            const uint32_t n4 = ma.x >> 24, n23 = ma.y >> 24;
-            const uint32_t q4 = div_small(kc, ma.x);
-            int32_t h4 = k0 - static_cast<int32_t>(mul_u24(q4, n4));  // < 0 before the road
-            uint32_t i01 = div_small(q4, ma.y);
-            uint32_t i23 = q4 - mul_u24(i01, n23);
-            const int32_t *t01 = xt + (mb.z & 0xFFFFu), *t23 = xt + (mb.z >> 16),
-                          *t4 = xt + (mb.w & 0xFFFFu);
+            const uint32_t n4b = ma.x >> 24, n23 = ma.y >> 24;
+            const uint32_t s4 = xt_at + (mb.w & 0xFFFFu), s23 = xt_at + (mb.z >> 16);
+            const uint32_t q4 = div_small(static_cast<uint32_t>(kc), ma.x);
+            const uint32_t i01 = div_small(q4, ma.y), i23 = q4 - mul_u24(i01, n23);
+            uint32_t a4 = s4 + 4 * static_cast<uint32_t>(k0) - mul_u24(q4, n4b);  // < s4 before the road
+            uint32_t a23 = s23 + 4 * i23, a01 = xt_at + (mb.z & 0xFFFFu) + 4 * i01;
+            const uint32_t e4 = s4 + n4b, e23 = s23 + 4 * n23;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                x01[e] = t01[i01];
-                x23[e] = t23[i23];
-                x4[e] = t4[h4];
+                x01[e] = lds_read(a01);
+                x23[e] = lds_read(a23);
+                x4[e] = lds_read(a4);
                 if (e < 3) {
-                    ++h4;
-                    const bool c4 = h4 == static_cast<int32_t>(n4);
-                    h4 = c4 ? 0 : h4;
-                    i23 += c4 ? 1u : 0u;
-                    const bool c23 = i23 == n23;
-                    i23 = c23 ? 0u : i23;
-                    i01 += c23 ? 1u : 0u;
+                    a4 += 4;
+                    const bool c4 = a4 == e4;
+                    a4 = c4 ? s4 : a4;
+                    a23 = c4 ? a23 + 4 : a23;
+                    const bool c23 = a23 == e23;
+                    a23 = c23 ? s23 : a23;
+                    a01 = c23 ? a01 + 4 : a01;
                 }
             }
         }
         Fit4<MODE, J0> f;
         fit_rows<MODE, J0>(L.bank[mb.w >> 16], x01, x23, x4, shift, qlmask, f);
         uint32_t acc = 0;
-        bool near;
+        bool near = true;
         if (MODE == kFitNarrow) {
             const uint32_t c0 = static_cast<uint32_t>(f.chi2[0]),
                            c1_ = static_cast<uint32_t>(f.chi2[1]),
                            c2 = static_cast<uint32_t>(f.chi2[2]),
                            c3 = static_cast<uint32_t>(f.chi2[3]);
             const uint32_t m01 = c0 < c1_ ? c0 : c1_, m23 = c2 < c3 ? c2 : c3;
-            near = (m01 < m23 ? m01 : m23) <= cut32 && a.cfg.chi2_cut >= 0;
-        } else {
-            near = true;
+            near = ballot((m01 < m23 ? m01 : m23) <= cut32) != 0 && a.cfg.chi2_cut >= 0;
         }
-        if (ballot(near)) {  // a chi-square of the window may pass
+        if (near) {  // a chi-square of the window may pass
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc |= static_cast<int64_t>(f.chi2[e]) <= a.cfg.chi2_cut ? 1u << e : 0u;
+            for (int e = 0; e < 4; ++e) {
+                const bool ok = MODE == kFitNarrow
+                                    ? static_cast<uint32_t>(f.chi2[e]) <= cut32
+                                    : static_cast<int64_t>(f.chi2[e]) <= a.cfg.chi2_cut;
+                acc |= ok ? 1u << e : 0u;
+            }
             acc &= slots;
             const uint32_t cnt = static_cast<uint32_t>(__popc(acc));
             uint32_t pos = 0;
             if (REC == kRecNone || a.keep) {
                 // in the order of the combinations: the lanes' items are, and their slots
-                const uint32_t upto = scan64(cnt);
-                pos = kept + upto - cnt;
-                kept += lane_value(upto, 63);
+                const uint64_t some = ballot(acc != 0);
+                if (ballot(cnt > 1) == 0) {
+                    pos = kept + bits_below(some);
+                    kept += __popcll(some);
+                } else {
+                    const uint32_t upto = scan64(cnt);
+                    pos = kept + upto - cnt;
+                    kept += lane_value(upto, 63);
+                }
             }
             if (acc) atomicAdd(&W.nacc[ri], cnt);
             for (uint32_t m = acc; m; m &= m - 1, ++pos) {  // seldom more than one
@@ -519,8 +525,9 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         }
         // ---- groups cut by a road boundary: the first item's lane takes the others' slots
         const uint32_t gp = dpp<kDppPrev>(static_cast<uint32_t>(g), ~0u);
-        const bool cont = active && lane > 0 && static_cast<uint32_t>(g) == gp;
-        for (uint64_t m = ballot(cont); m; m &= m >> 1) {
+        const uint64_t cont_m = ballot(static_cast<uint32_t>(g) == gp) & active_m & ~1ull;
+        const bool cont = __builtin_amdgcn_inverse_ballot_w64(cont_m);
+        for (uint64_t m = cont_m; m; m &= m >> 1) {
             // (a lane whose source is switched off keeps its value, so the lanes that give a
             // slot stay on with those that take it; what the givers are left with is not read)
             const uint32_t take = dpp<kDppNext>(cont ? slots | (acc << 8) : 0u);
@@ -544,7 +551,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             acc |= take >> 8;
         }
         // ---- records
-        const bool head = active && !cont;
+        const bool head = __builtin_amdgcn_inverse_ballot_w64(active_m & ~cont_m);
         const uint32_t at = static_cast<uint32_t>(rel);  // from GB
         int32_t *p0 = a.out.p0 + GB, *p1 = a.out.p1 + GB, *p2 = a.out.p2 + GB;
         int64_t *pc = a.out.chi2 + GB;
@@ -761,14 +768,13 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     if (take) {
         RoadRow row;
         const uint32_t t = tend - ntab;
-        row.a = make_uint4(L.magic[n4] | (n4 << 24), L.magic[n23] | (n23 << 24), rb, end);
-        row.b = make_uint4((rb >> 2) - item, nh, t | ((t + n01) << 16),
-                           (t + n01 + n23) | (pre.z << 16));
+        const uint32_t p01 = 4 * t, p23 = p01 + 4 * n01, p4 = p23 + 4 * n23;
+        row.a = make_uint4(L.magic[n4] | (n4 << 26), L.magic[n23] | (n23 << 24), rb, end);
+        row.b = make_uint4((rb >> 2) - item, nh, p01 | (p23 << 16), p4 | (pre.z << 16));
         W.road[lane] = row;
         // Where a word's coordinate goes, by layer: bytes from the tables' start (12 bits), and on per
         // rank (6 bits, from bit 12); bytes from one entry to the next (6 bits, from 18); entries.
         const uint32_t n0 = nh_of(nh, 0), n1 = nh_of(nh, 1), n2 = nh_of(nh, 2), n3 = nh_of(nh, 3);
-        const uint32_t p01 = 4 * t, p23 = p01 + 4 * n01, p4 = p23 + 4 * n23;
         uint32_t *place = W.place + (lane - c0);
         place[0] = p01 | (n1 << 14) | (4u << 18) | (n1 << 24);
         place[kUnitFitRoads] = (p01 + 2) | (4u << 12) | (n1 << 20) | (n0 << 24);
