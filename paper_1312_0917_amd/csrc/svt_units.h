@@ -207,73 +207,70 @@ __device__ __forceinline__ UnitWords load_unit(const uint32_t *__restrict__ word
 // longer than 5 * 8 words is illegal whatever they hold).
 __device__ __forceinline__ uint32_t layer_unit(uint32_t w) { return 1u << (6 * w_layer(w)); }
 
-// Where roads and events start, and the running counts before each lane's words.
+// What a lane knows of its words.
 struct UnitScan {
-    uint32_t starts;        // bit e: word e starts a road; bit 8 + e: it starts an event
-    uint32_t hit[kUnitLane];  // what word e adds to the hit counts
-    uint32_t hits;          // hit counts before the lane's first word
-    uint32_t rd;            // roads started before it | events started before it << 16
-    uint32_t tot_hits, tot_rd;  // over the span (uniform)
-    uint32_t own;           // roads | events << 16 started among the unit's own words (uniform)
+    uint32_t hit[kUnitLane];   // what word e adds to the hit counts
+    uint32_t hits;             // hit counts before the lane's first word
+    uint32_t road[kUnitLane];  // word e's road, among those that start in the span (all ones: one that
+                               // starts before it)
+    uint32_t roads;            // roads that start among the unit's own words (uniform)
 };
 
+// A road's entry: x = hit counts before its first word; y = that word's index in the unit (9
+// bits), bits 16..31: its tags.  The road ends where the next entry starts; entry [roads owned] is
+// the end of the last one: the first road start past the unit, or the end of the staged words.
+__device__ __forceinline__ uint32_t entry_pos(uint2 e) { return e.y & 0x1FFu; }
+
+__device__ __forceinline__ uint64_t lanes_below(int k) { return k > 0 ? ~0ull >> (kWaveSize - k) : 0; }
+
+// Scan the words and write an entry for every road that starts in the span.  Road starts are kept as
+// one mask of lanes per word, in scalar registers: counting them there and with mbcnt took 35 fewer
+// vector instructions, of 250 in the counting kernel, than flags in a register and a scan.
 // CHECK: the span may hold words past the input or layer fields out of range, which count nothing.
 template <bool CHECK>
-__device__ __forceinline__ UnitScan scan_unit(const UnitWords &u, int nloc) {
+__device__ __forceinline__ UnitScan enter_unit(uint2 *S, const UnitWords &u, int nloc) {
     UnitScan s;
-    const int j0 = kUnitLane * lane_id();
-    uint32_t prev = dpp<kDppPrev>(u.w[kUnitLane - 1], u.before);
-    uint32_t starts = 0, hits = 0, rd = 0;
+    const uint32_t j0 = kUnitLane * lane_id();
+    uint64_t starts[kUnitLane];
+    uint32_t prev = dpp<kDppPrev>(u.w[kUnitLane - 1], u.before), hits = 0, before = 0;
+    uint32_t all = 0;
+    s.roads = 0;
 #pragma unroll
     for (int e = 0; e < kUnitLane; ++e) {
-        const uint32_t x = u.w[e], d = x ^ prev;
-        const bool in = !CHECK || j0 + e < nloc;
-        const bool r = in && d > 0xFFFFu, v = in && d > 0xFFFFFFu;
-        starts |= (r ? 1u << e : 0u) | (v ? 256u << e : 0u);
-        rd += (r ? 1u : 0u) + (v ? 1u << 16 : 0u);
+        const uint32_t x = u.w[e];
+        starts[e] = ballot((x ^ prev) > 0xFFFFu);
+        if (CHECK) starts[e] &= lanes_below((nloc - e + kUnitLane - 1) / kUnitLane);
+        const uint64_t own = starts[e] & lanes_below((kUnitWords - e + kUnitLane - 1) / kUnitLane);
+        all += __popcll(starts[e]);
+        s.roads += __popcll(own);
+        before = __builtin_amdgcn_mbcnt_hi(
+            static_cast<uint32_t>(starts[e] >> 32),
+            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(starts[e]), before));
         s.hit[e] = layer_unit(x);
-        if (CHECK && (!in || w_layer(x) >= SVT_N_LAYERS)) s.hit[e] = 0;
+        if (CHECK && (static_cast<int>(j0) + e >= nloc || w_layer(x) >= SVT_N_LAYERS)) s.hit[e] = 0;
         hits += s.hit[e];
         prev = x;
     }
-    const uint32_t ih = scan64(hits), ird = scan64(rd);
-    s.starts = starts;
+    const uint32_t ih = scan64(hits);
     s.hits = ih - hits;
-    s.rd = ird - rd;
-    s.tot_hits = lane_value(ih, 63);
-    s.tot_rd = lane_value(ird, 63);
-    // the first word past the unit is word `past` of lane `at`
-    constexpr int at = kUnitWords / kUnitLane, past = kUnitWords % kUnitLane;
-    uint32_t own = s.rd;
+    uint32_t h = s.hits, rd = before - 1u;
 #pragma unroll
-    for (int e = 0; e < past; ++e)
-        own += ((starts >> e) & 1u) + (((starts >> (8 + e)) & 1u) << 16);
-    s.own = lane_value(own, at);
+    for (int e = 0; e < kUnitLane; ++e) {
+        const bool start = __builtin_amdgcn_inverse_ballot_w64(starts[e]);
+        rd += start ? 1u : 0u;
+        s.road[e] = rd;
+        if (start) S[rd] = make_uint2(h, (u.w[e] & 0xFFFF0000u) | (j0 + e));
+        h += s.hit[e];
+    }
+    if (all == s.roads && lane_id() == 0)
+        S[all] = make_uint2(lane_value(ih, 63), static_cast<uint32_t>(nloc));
     return s;
 }
 
-// A road's entry: x = hit counts before its first word; y = that word's index in the unit (9
-// bits), bit 9: it starts an event, bits 16..23: its road tag.  The road ends where the next
-// entry starts; entry [roads owned] is the end of the last one: the first road start past the
-// unit, or the end of the staged words.
-__device__ __forceinline__ uint32_t entry_pos(uint2 e) { return e.y & 0x1FFu; }
-
-__device__ __forceinline__ void write_entries(uint2 *S, const UnitWords &u, const UnitScan &s,
-                                              uint32_t nr, int nloc) {
-    uint32_t hits = s.hits, rl = s.rd & 0xFFFFu;
-    const uint32_t j0 = kUnitLane * lane_id();
-#pragma unroll
-    for (int e = 0; e < kUnitLane; ++e) {
-        if ((s.starts >> e) & 1u) {
-            if (rl <= nr)
-                S[rl] = make_uint2(hits, (j0 + e) | (((s.starts >> (8 + e)) & 1u) << 9) |
-                                             (u.w[e] & 0xFF0000u));
-            ++rl;
-        }
-        hits += s.hit[e];
-    }
-    if ((s.tot_rd & 0xFFFFu) == nr && lane_id() == 0)
-        S[nr] = make_uint2(s.tot_hits, static_cast<uint32_t>(nloc));
+// Whether a road starts an event: its own entry against the road's before it, in the lane below (y0:
+// what lane 0 compares with, the word before the unit or the last entry of the 64 before).
+__device__ __forceinline__ bool starts_event(uint32_t y, uint32_t y0) {
+    return (y ^ dpp<kDppPrev>(y, y0)) > 0xFFFFFFu;
 }
 
 // Hits of the road between two entries: 4 bits per layer, and whether it is illegal (too many
@@ -282,9 +279,12 @@ __device__ __forceinline__ uint32_t road_hits(uint2 e0, uint2 e1, int max_hits, 
     const uint32_t d = e1.x - e0.x;
     const uint32_t c0 = d & 63u, c1 = (d >> 6) & 63u, c2 = (d >> 12) & 63u, c3 = (d >> 18) & 63u,
                    c4 = (d >> 24) & 63u;
-    const uint32_t m = static_cast<uint32_t>(max_hits);
-    over = static_cast<int>(entry_pos(e1) - entry_pos(e0)) > SVT_N_LAYERS * max_hits || c0 > m ||
-           c1 > m || c2 > m || c3 > m || c4 > m;
+    // A count above max_hits shows in bit 5 of its field, as it is (32..40, in a road of at most 40
+    // words) or with 31 - max_hits added; up to the lowest such field no addition carries.
+    constexpr uint32_t ones = 0x01041041u;
+    const uint32_t k = static_cast<uint32_t>(31 - max_hits) * ones;
+    over = static_cast<int>(entry_pos(e1) - entry_pos(e0)) > SVT_N_LAYERS * max_hits ||
+           ((d | (d + k)) & (ones << 5)) != 0;
     return (c0 & 0xFu) | ((c1 & 0xFu) << 4) | ((c2 & 0xFu) << 8) | ((c3 & 0xFu) << 12) |
            ((c4 & 0xFu) << 16);
 }

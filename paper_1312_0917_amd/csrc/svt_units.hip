@@ -22,7 +22,7 @@ namespace svt {
 namespace {
 
 constexpr int kThreads = kUnitWaves * kWaveSize;
-constexpr int kEntries = kUnitWords + 1;  // roads that start in a unit, and the end of the last
+constexpr int kEntries = kUnitSpan + 1;  // roads that start in a unit's span, and the end of the last
 
 // ---- counting -----------------------------------------------------------------------------------
 struct CArgs {
@@ -110,20 +110,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             const int nloc = static_cast<int>(n - base < kUnitSpan ? n - base : kUnitSpan);
             const UnitWords uw = load_unit(a.words, base, nloc);
             const int j0 = kUnitLane * lane;
-            bool any_bad = false;
+            uint32_t top = 0;
 #pragma unroll
-            for (int e = 0; e < kUnitLane; ++e)
-                any_bad |= w_layer(uw.w[e]) >= static_cast<uint32_t>(SVT_N_LAYERS);
-            const bool bad = ballot(any_bad) != 0;
+            for (int e = 0; e < kUnitLane; ++e) top = w_layer(uw.w[e]) > top ? w_layer(uw.w[e]) : top;
+            const bool bad = ballot(top >= static_cast<uint32_t>(SVT_N_LAYERS)) != 0;
+            lds_order();
             UnitScan sc;
             if (nloc < kUnitSpan || bad)
-                sc = scan_unit<true>(uw, nloc);
+                sc = enter_unit<true>(S, uw, nloc);
             else
-                sc = scan_unit<false>(uw, nloc);
-            agg = sc.own;
-            const uint32_t nr = sc.own & 0xFFFFu;
-            lds_order();
-            write_entries(S, uw, sc, nr, nloc);
+                sc = enter_unit<false>(S, uw, nloc);
+            const uint32_t nr = sc.roads;
             lds_order();
             if (a.copy) {
 #pragma unroll
@@ -141,31 +138,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 bad_word = b < bad_word ? b : bad_word;
             }
             if (a.cfg.n_sets < 256) {
-                uint32_t rl = sc.rd & 0xFFFFu, b = ~0u;
+                uint32_t b = ~0u;
 #pragma unroll
-                for (int e = 0; e < kUnitLane; ++e)
-                    if ((sc.starts >> e) & 1u) {
-                        if (rl < nr && b == ~0u &&
-                            w_rtag(uw.w[e]) >= static_cast<uint32_t>(a.cfg.n_sets))
-                            b = rl;
-                        ++rl;
-                    }
+                for (int e = kUnitLane - 1; e >= 0; --e)
+                    if (sc.road[e] < nr && j0 + e < nloc &&
+                        w_rtag(uw.w[e]) >= static_cast<uint32_t>(a.cfg.n_sets))
+                        b = sc.road[e];
                 my_set = wave_min(b);
             }
-            uint32_t csum = 0;
+            uint32_t csum = 0, ne = 0, y0 = uw.before;
             for (uint32_t r0 = 0; r0 < nr; r0 += kWaveSize) {
                 const uint32_t rl = r0 + lane;
+                const uint64_t mine = lanes_below(nr - r0 < kWaveSize ? nr - r0 : kWaveSize);
                 bool over = false;
                 uint32_t c = 0;
+                uint2 e0 = make_uint2(0, 0);
                 if (rl < nr) {
-                    const uint32_t nh = road_hits(S[rl], S[rl + 1], a.cfg.max_hits, over);
+                    e0 = S[rl];
+                    const uint32_t nh = road_hits(e0, S[rl + 1], a.cfg.max_hits, over);
                     c = over ? 0 : road_combos(nh);
                 }
+                ne += __popcll(ballot(starts_event(e0.y, y0)) & mine);
+                y0 = lane_value(e0.y, 63);
                 csum += c;
                 const uint64_t m = ballot(over);
                 if (m && my_over == ~0u) my_over = r0 + __builtin_ctzll(m);
             }
             cs = lane_value(scan64(csum), 63);
+            agg = nr | (ne << 16);
         }
         if (lane == 0) s_agg[buf][wave] = make_uint2(agg, cs);
         __syncthreads();  // (the other buffer takes the next round's counts)
@@ -248,7 +248,7 @@ struct RoadRow {
 
 struct alignas(16) WaveLds {
     union {
-        uint2 ent[kEntries + 1];
+        uint2 ent[kEntries];
         int32_t xt[kTabPad + kTabCap + kTabPad];
     };
     union {
@@ -651,41 +651,40 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     // ---- roads: entries, hits per layer, combinations, road table -------------------------------
     UnitScan sc;
     if (nloc < kUnitSpan)
-        sc = scan_unit<true>(uw, nloc);
+        sc = enter_unit<true>(W.ent, uw, nloc);
     else
-        sc = scan_unit<false>(uw, nloc);
-    const uint32_t nr = sc.own & 0xFFFFu;
+        sc = enter_unit<false>(W.ent, uw, nloc);
+    const uint32_t nr = sc.roads;
     if (nr == 0) return 0;
-    write_entries(W.ent, uw, sc, nr, nloc);
     lds_order();
-    uint32_t c_run = 0, ev_run = rec.events + rbase.events - 1;
+    uint32_t c_run = 0, ev_run = rec.events + rbase.events - 1, y0 = uw.before;
     int nf = 0;
     for (uint32_t r0 = 0; r0 < nr; r0 += kWaveSize) {
         const uint32_t rl = r0 + lane;
-        const bool mine = rl < nr;
-        uint32_t nh = 0, c = 0, tag = 0, pos = 0;
-        bool ev = false;
+        const uint64_t mine_m = lanes_below(nr - r0 < kWaveSize ? nr - r0 : kWaveSize);
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(mine_m);
+        uint32_t nh = 0, c = 0;
+        uint2 e0 = make_uint2(0, 0);
         if (mine) {
-            const uint2 e0 = W.ent[rl];
+            e0 = W.ent[rl];
             bool over;
             nh = road_hits(e0, W.ent[rl + 1], hot.cfg.max_hits, over);
             c = over ? 0 : road_combos(nh);
-            pos = entry_pos(e0);
-            ev = (e0.y >> 9) & 1u;
-            tag = (e0.y >> 16) & 0xFFu;
         }
+        const uint32_t pos = entry_pos(e0), tag = (e0.y >> 16) & 0xFFu;
         const uint32_t cs = scan64(c);
         const uint32_t cb = c_run + cs - c;
         c_run += lane_value(cs, 63);
-        const uint64_t em = ballot(ev), fm = ballot(c > 0);
+        const uint64_t em = ballot(starts_event(e0.y, y0)) & mine_m, fm = ballot(c > 0);
+        y0 = lane_value(e0.y, 63);
         const int fi = nf + bits_below(fm);
         nf += __popcll(fm);
-        const uint32_t evn = ev_run + bits_below(em) + (ev ? 1u : 0u);
+        const uint32_t evn = ev_run + bits_below(em) +
+                             (__builtin_amdgcn_inverse_ballot_w64(em) ? 1u : 0u);
         ev_run += __popcll(em);
         if (mine) {
             // (for its words: its index among the roads that may be fitted now, past 63 for none)
-            W.ent[rl].y = pos | (tag << 16) |
-                          ((c > 0 ? static_cast<uint32_t>(fi - c0) : 255u) << 24);
+            W.ent[rl].y = c > 0 ? static_cast<uint32_t>(fi - c0) : ~0u;
             if (c > 0) W.road[fi].b = make_uint4(o + cb, nh | (rl << 24), tag, 0);
         }
         if (mine && table) {
@@ -716,22 +715,19 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     uint32_t rank[kUnitLane], road_of[kUnitLane];
     {
         uint2 ent[kUnitLane];
-        uint32_t hits = sc.hits, rl = (sc.rd & 0xFFFFu) - 1u;
+        uint32_t hits = sc.hits;
 #pragma unroll
-        for (int e = 0; e < kUnitLane; ++e) {
-            rl += (sc.starts >> e) & 1u;
-            ent[e] = W.ent[rl < nr ? rl : nr];
-        }
+        for (int e = 0; e < kUnitLane; ++e) ent[e] = W.ent[sc.road[e] < nr ? sc.road[e] : nr];
 #pragma unroll
         for (int e = 0; e < kUnitLane; ++e) {
             rank[e] = __builtin_amdgcn_ubfe(hits - ent[e].x, 6 * w_layer(uw.w[e]), 4);
-            road_of[e] = ent[e].y >> 24;
+            road_of[e] = ent[e].y;
             hits += sc.hit[e];
         }
         if (nloc < kUnitSpan)
 #pragma unroll
             for (int e = 0; e < kUnitLane; ++e)
-                if (kUnitLane * lane + e >= nloc) road_of[e] = 255;
+                if (kUnitLane * lane + e >= nloc) road_of[e] = ~0u;
     }
     // ---- one road with combinations per lane: roads c0 .. c1 - 1 are fitted now -----------------
     const bool road = lane < nf && lane >= c0;
@@ -1310,7 +1306,7 @@ struct TArgs {
     uint64_t *err;
 };
 struct TWaveLds {
-    uint2 ent[kEntries + 1];
+    uint2 ent[kEntries];
     uint32_t nh[kUnitWords];
     int16_t coord[kUnitSpan];
 };
@@ -1338,24 +1334,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         const UnitWords uw = load_unit(a.words, base, nloc);
         const UnitRec rec = a.rec[u];
         const RangeBase rb = s_range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)];
+        lds_order();
         UnitScan sc;
         if (nloc < kUnitSpan)
-            sc = scan_unit<true>(uw, nloc);
+            sc = enter_unit<true>(W.ent, uw, nloc);
         else
-            sc = scan_unit<false>(uw, nloc);
-        const uint32_t nr = sc.own & 0xFFFFu;
+            sc = enter_unit<false>(W.ent, uw, nloc);
+        const uint32_t nr = sc.roads;
         if (nr == 0) continue;
         lds_order();
-        write_entries(W.ent, uw, sc, nr, nloc);
-        lds_order();
-        uint32_t ev_run = rec.events + rb.events - 1;
+        uint32_t ev_run = rec.events + rb.events - 1, y0 = uw.before;
         for (uint32_t r0 = 0; r0 < nr; r0 += kWaveSize) {
             const uint32_t rl = r0 + lane;
             uint2 e0 = make_uint2(0, 0);
             if (rl < nr) e0 = W.ent[rl];
-            const bool ev = (e0.y >> 9) & 1u;
-            const uint64_t em = ballot(ev);
-            const uint32_t evn = ev_run + bits_below(em) + (ev ? 1u : 0u);
+            const uint64_t em = ballot(starts_event(e0.y, y0)) &
+                                lanes_below(nr - r0 < kWaveSize ? nr - r0 : kWaveSize);
+            y0 = lane_value(e0.y, 63);
+            const uint32_t evn = ev_run + bits_below(em) +
+                                 (__builtin_amdgcn_inverse_ballot_w64(em) ? 1u : 0u);
             ev_run += __popcll(em);
             if (rl < nr) {
                 bool over;
@@ -1369,10 +1366,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             }
         }
         lds_order();
-        uint32_t hits = sc.hits, rl = (sc.rd & 0xFFFFu) - 1u;
+        uint32_t hits = sc.hits;
 #pragma unroll
         for (int e = 0; e < kUnitLane; ++e) {
-            rl += (sc.starts >> e) & 1u;
+            const uint32_t rl = sc.road[e];
             if (rl < nr && kUnitLane * lane + e < nloc) {
                 const uint2 ent = W.ent[rl];
                 const uint32_t l = w_layer(uw.w[e]), nh = W.nh[rl];
