@@ -145,6 +145,8 @@ __device__ __forceinline__ T *at_byte(T *p, uint32_t o) {
 __device__ __forceinline__ const int32_t *at_byte(const int32_t *p, uint32_t o) {
     return reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(p) + o);
 }
+// 8 bytes at an address that is a multiple of 4
+typedef uint32_t U32Pair __attribute__((ext_vector_type(2), aligned(4)));
 // LDS by 32-bit address
 typedef __attribute__((address_space(3))) const int32_t LdsInt;
 __device__ __forceinline__ uint32_t lds_address(const int32_t *p) {

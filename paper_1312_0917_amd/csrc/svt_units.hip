@@ -235,11 +235,11 @@ struct UArgs {
 };
 
 constexpr int kTabCap = 768;   // coordinate-pair table entries of the roads fitted together
-constexpr int kTabPad = 8;     // a dummy slot reads up to 3 entries before or after its table
+constexpr int kTabPad = 8;     // a dummy slot reads up to 7 entries before or after its table
 
 // Per road with combinations, while its tables are in LDS (two 16-byte reads per lane):
 //   a: division magic of n4 | 4 * n4 << 24; of n2 * n3 | n2 * n3 << 24; first combination, end (from
-//      GB, the unit's first combination rounded down to a multiple of 4)
+//      GB, the unit's first combination rounded down to a whole group)
 //   b: its first group less its first item; hits per layer | road << 24; table of the (h0, h1)
 //      pairs | of the (h2, h3) pairs << 16; table of layer 4 | constant set << 16 (tables in bytes)
 struct RoadRow {
@@ -294,12 +294,19 @@ struct ULds {
 };
 static_assert(sizeof(ULds) <= 160 * 1024, "LDS of a compute unit");
 
-// The rows of four consecutive combinations from their coordinate pairs.  J0..5: rows computed
+// A lane fits groups of 2^kGroupBits consecutive combinations: 4 with records, whose int32 arrays
+// take them as 16 bytes each; 8 without, which halves the windows and what each spends on finding
+// the lanes' roads and first combinations (4000 events of 2048 roads: 955 us a pass with 4, 905
+// with 8).
+template <int REC>
+constexpr int kGroupBits = REC == kRecNone ? 3 : 2;
+
+// The rows of G consecutive combinations from their coordinate pairs.  J0..5: rows computed
 // (the kept-only mode needs the chi-square rows only).
-template <int MODE, int J0>
-struct Fit4 {
-    int32_t v[6][4];
-    uint64_t chi2[4];  // MODE == kFitNarrow: below 2^32
+template <int MODE, int J0, int G>
+struct FitGroup {
+    int32_t v[6][G];
+    uint64_t chi2[G];  // MODE == kFitNarrow: below 2^32
 };
 
 // One row of four combinations: (seed + three dot products) >> shift.  Written out because the
@@ -331,23 +338,25 @@ __device__ __forceinline__ void row4(uint32_t f01, uint32_t f23, uint32_t f4, ui
           "v"(x4[2]), "v"(x4[3]), "v"(shift));
 }
 
-template <int MODE, int J0>
+template <int MODE, int J0, int G>
 __device__ __forceinline__ void fit_rows(const UnitSet &c, const int32_t *x01, const int32_t *x23,
                                          const int32_t *x4, int32_t shift, uint32_t qlmask,
-                                         Fit4<MODE, J0> &f) {
+                                         FitGroup<MODE, J0, G> &f) {
 #pragma unroll
     for (int j = J0; j < 6; ++j) {
         const uint4 r = c.row[j];
         const uint32_t seed = MODE == kFitNarrow ? r.w : r.w & qlmask;
-        row4(r.x, r.y, r.z, seed, x01, x23, x4, shift, f.v[j]);
+#pragma unroll
+        for (int h = 0; h < G; h += 4)
+            row4(r.x, r.y, r.z, seed, x01 + h, x23 + h, x4 + h, shift, f.v[j] + h);
         if (MODE != kFitNarrow) {
             const int32_t qh = static_cast<int32_t>(r.w) >> shift;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) f.v[j][e] += qh;
+            for (int e = 0; e < G; ++e) f.v[j][e] += qh;
         }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < G; ++e) {
         if (MODE == kFitNarrow)
             f.chi2[e] = static_cast<uint32_t>(
                 mad_i24(f.v[5][e], f.v[5][e],
@@ -382,10 +391,10 @@ __device__ __forceinline__ Fit fit_one(const RoadRow &r, const UnitSet &c, const
 }
 
 // Fit the combinations of roads c0 .. c1 - 1 of the unit, whose tables are in LDS, in windows of
-// up to 64 items, from item from_item to before n_items.  An item is the part of a group of 4 consecutive combinations (a 16-byte
-// store) that lies in one road: item j of a road covers its group j, so a lane finds its road
-// among the window's few by comparing with their first items, and fits with one road's
-// constants.  A group cut by a road boundary is two or more neighbouring items; the lane of its
+// up to 64 items, from item from_item to before n_items.  An item is the part of a group of G
+// consecutive combinations that lies in one road: item j of a road covers its group j, so a lane
+// finds its road among the window's few by comparing with their first items, and fits with one
+// road's constants.  A group cut by a road boundary is two or more neighbouring items; the lane of its
 // first one collects the others' slots from the lanes after it, so that every group of the
 // window is written by one lane with the same store instructions as its neighbours.
 template <int MODE, int REC>
@@ -397,13 +406,15 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
     // Windows end where a 128-byte line of the int32 record arrays does (8 groups): a line
     // written in two parts reaches memory in parts.  On 4000 events of 2048 roads windows that
     // end anywhere took 5.09 ms, at 8 groups 4.05 ms, at 32 (a line of accept bytes too) 4.34 ms.
-    // Without records there is less to win and the lanes left idle weigh more.
-    constexpr int kLineGroups = REC == kRecNone ? 4 : 8;
+    // Without records the lanes left idle weigh more (at 1, 2 and 4 groups of 8: 902, 908, 911 us).
+    constexpr int G = 1 << kGroupBits<REC>;
+    constexpr uint32_t kWhole = (1u << G) - 1u;
+    constexpr int kLineGroups = REC == kRecNone ? 1 : 8;
     const int lane = lane_id();
     const uint32_t xt_at = lds_address(W.xt + kTabPad);
     const uint32_t cut32 = a.cfg.chi2_cut < 0xFFFFFFFFll ? static_cast<uint32_t>(a.cfg.chi2_cut)
                                                          : 0xFFFFFFFFu;
-    const int32_t g_abs = static_cast<int32_t>(GB >> 2) & (kLineGroups - 1);
+    const int32_t g_abs = static_cast<int32_t>(GB >> kGroupBits<REC>) & (kLineGroups - 1);
     int rcur = c0 - 1 + static_cast<int>(__popcll(
                             ballot(lane >= c0 && lane < c1 && first_item <= from_item)));
     for (uint32_t i0 = from_item; i0 < n_items;) {
@@ -427,16 +438,16 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         }
         const uint64_t active_m = ~0ull >> (kWaveSize - nit);  // (nit > 0)
         const bool active = __builtin_amdgcn_inverse_ballot_w64(active_m);
-        const int32_t rel = 4 * g;
+        const int32_t rel = G * g;
         const int32_t k0 = active ? rel - rb : 0, kc = k0 < 0 ? 0 : k0;
         uint32_t slots;  // the group's combinations that are the road's
         {
-            const int32_t lo = kc - k0, hi = end - rel < 4 ? end - rel : 4;
+            const int32_t lo = kc - k0, hi = end - rel < G ? end - rel : G;
             slots = bit_field(active ? hi - lo : 0, lo);
         }
-        // ---- the four combinations' table entries, stepped with carries (a slot outside the
-        // road reads a neighbouring entry and is not written)
-        int32_t x01[4], x23[4], x4[4];
+        // ---- the combinations' table entries, stepped with carries (a slot outside the road
+        // reads a neighbouring entry and is not written)
+        int32_t x01[G], x23[G], x4[G];
         {
             const uint32_t n4b = ma.x >> 24, n23 = ma.y >> 24;
             const uint32_t s4 = xt_at + (mb.w & 0xFFFFu), s23 = xt_at + (mb.z >> 16);
@@ -446,11 +457,11 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             uint32_t a23 = s23 + 4 * i23, a01 = xt_at + (mb.z & 0xFFFFu) + 4 * i01;
             const uint32_t e4 = s4 + n4b, e23 = s23 + 4 * n23;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < G; ++e) {
                 x01[e] = lds_read(a01);
                 x23[e] = lds_read(a23);
                 x4[e] = lds_read(a4);
-                if (e < 3) {
+                if (e < G - 1) {
                     a4 += 4;
                     const bool c4 = a4 == e4;
                     a4 = c4 ? s4 : a4;
@@ -461,21 +472,22 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                 }
             }
         }
-        Fit4<MODE, J0> f;
-        fit_rows<MODE, J0>(L.bank[mb.w >> 16], x01, x23, x4, shift, qlmask, f);
+        FitGroup<MODE, J0, G> f;
+        fit_rows<MODE, J0, G>(L.bank[mb.w >> 16], x01, x23, x4, shift, qlmask, f);
         uint32_t acc = 0;
         bool near = true;
         if (MODE == kFitNarrow) {
-            const uint32_t c0 = static_cast<uint32_t>(f.chi2[0]),
-                           c1_ = static_cast<uint32_t>(f.chi2[1]),
-                           c2 = static_cast<uint32_t>(f.chi2[2]),
-                           c3 = static_cast<uint32_t>(f.chi2[3]);
-            const uint32_t m01 = c0 < c1_ ? c0 : c1_, m23 = c2 < c3 ? c2 : c3;
-            near = ballot((m01 < m23 ? m01 : m23) <= cut32) != 0 && a.cfg.chi2_cut >= 0;
+            uint32_t least = ~0u;
+#pragma unroll
+            for (int e = 0; e < G; ++e) {
+                const uint32_t c = static_cast<uint32_t>(f.chi2[e]);
+                least = c < least ? c : least;
+            }
+            near = ballot(least <= cut32) != 0 && a.cfg.chi2_cut >= 0;
         }
         if (near) {  // a chi-square of the window may pass
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < G; ++e) {
                 const bool ok = MODE == kFitNarrow
                                     ? static_cast<uint32_t>(f.chi2[e]) <= cut32
                                     : static_cast<int64_t>(f.chi2[e]) <= a.cfg.chi2_cut;
@@ -497,31 +509,28 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                 }
             }
             if (acc) atomicAdd(&W.nacc[ri], cnt);
-            for (uint32_t m = acc; m; m &= m - 1, ++pos) {  // seldom more than one
-                const bool odd = (m & 5u) == 0 || (m & 3u) == 2u, high = (m & 3u) == 0;
-                auto pick = [&](auto v0, auto v1, auto v2, auto v3) {
-                    const auto l = odd ? v1 : v0, h = odd ? v3 : v2;
-                    return high ? h : l;
-                };
-                const uint32_t e = (odd ? 1u : 0u) + (high ? 2u : 0u);
-                const uint64_t c2 = pick(f.chi2[0], f.chi2[1], f.chi2[2], f.chi2[3]);
-                atomicMin(&W.key[ri],
-                          static_cast<unsigned long long>(best_key(static_cast<int64_t>(c2),
-                                                                   static_cast<uint32_t>(k0) + e)));
-                if ((REC == kRecNone || a.keep) && keep_at) {
-                    const uint32_t c = static_cast<uint32_t>(rel) + e;
-                    if (REC == kRecNone) {
-                        if (pos < a.slot_bytes / 16)
-                            reinterpret_cast<uint4 *>(keep_at)[pos] = make_uint4(
-                                c | (mb.w >> 16 << 24),
-                                static_cast<uint32_t>(pick(x01[0], x01[1], x01[2], x01[3])),
-                                static_cast<uint32_t>(pick(x23[0], x23[1], x23[2], x23[3])),
-                                static_cast<uint32_t>(pick(x4[0], x4[1], x4[2], x4[3])));
-                    } else if (pos < a.slot_bytes / 4) {
-                        keep_at[pos] = c;
+            // (slot by slot: taking a lane's accepted ones in a loop, each picked out of the registers,
+            // costs as much with 4 and twice as much with 8)
+#pragma unroll
+            for (int e = 0; e < G; ++e)
+                if ((acc >> e) & 1u) {
+                    atomicMin(&W.key[ri],
+                              static_cast<unsigned long long>(best_key(
+                                  static_cast<int64_t>(f.chi2[e]), static_cast<uint32_t>(k0 + e))));
+                    if ((REC == kRecNone || a.keep) && keep_at) {
+                        const uint32_t c = static_cast<uint32_t>(rel + e);
+                        if (REC == kRecNone) {
+                            if (pos < a.slot_bytes / 16)
+                                reinterpret_cast<uint4 *>(keep_at)[pos] =
+                                    make_uint4(c | (mb.w >> 16 << 24), static_cast<uint32_t>(x01[e]),
+                                               static_cast<uint32_t>(x23[e]),
+                                               static_cast<uint32_t>(x4[e]));
+                        } else if (pos < a.slot_bytes / 4) {
+                            keep_at[pos] = c;
+                        }
                     }
+                    ++pos;
                 }
-            }
         }
         // ---- groups cut by a road boundary: the first item's lane takes the others' slots
         const uint32_t gp = dpp<kDppPrev>(static_cast<uint32_t>(g), ~0u);
@@ -533,7 +542,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
             const uint32_t take = dpp<kDppNext>(cont ? slots | (acc << 8) : 0u);
             const uint32_t on = (take & ~slots) | (cont ? slots : 0u);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < G; ++e)
                 if ((on >> e) & 1u) {
 #pragma unroll
                     for (int j = J0; j < (REC == kRecRows ? 6 : 3); ++j)
@@ -556,7 +565,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
         int32_t *p0 = a.out.p0 + GB, *p1 = a.out.p1 + GB, *p2 = a.out.p2 + GB;
         int64_t *pc = a.out.chi2 + GB;
         uint8_t *pa = a.accept + GB;
-        if (head && slots == 0xFu) {
+        if (head && slots == kWhole) {
             const uint32_t o1 = offset_of(at), o4 = offset_of(4 * at);
             if (REC != kRecNone) {
                 store_nt(at_byte(p0, o4), f.v[0]);
@@ -574,10 +583,15 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                 if (a.out.c1) store_nt(at_byte(a.out.c1 + GB, o4), f.v[4]);
                 if (a.out.c2) store_nt(at_byte(a.out.c2 + GB, o4), f.v[5]);
             }
-            *reinterpret_cast<uint32_t *>(at_byte(pa, o1)) = mul_u24(acc, 0x204081u) & 0x01010101u;
+            constexpr uint32_t spread = 0x204081u, ones = 0x01010101u;  // a bit to a byte
+            if (G == 4)
+                *reinterpret_cast<uint32_t *>(at_byte(pa, o1)) = mul_u24(acc, spread) & ones;
+            else
+                *reinterpret_cast<U32Pair *>(at_byte(pa, o1)) =
+                    U32Pair{mul_u24(acc & 0xFu, spread) & ones, mul_u24(acc >> 4, spread) & ones};
         } else if (head) {  // a group shared with the unit before or after this one
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < G; ++e)
                 if ((slots >> e) & 1u) {
                     if (REC != kRecNone) {
                         p0[at + e] = f.v[0][e];
@@ -645,7 +659,8 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     const int64_t R0 = static_cast<int64_t>(uni(rec.roads) + uni(rbase.roads));
     const int64_t CB0 = static_cast<int64_t>(uni(rec.combos) & kComboMask) +
                         static_cast<int64_t>(uni(rbase.combos));
-    const int64_t GB = CB0 & ~static_cast<int64_t>(3);
+    constexpr int kBits = kGroupBits<REC>;
+    const int64_t GB = CB0 & ~((1ll << kBits) - 1);
     const uint32_t o = static_cast<uint32_t>(CB0 - GB);
 
     // ---- roads: entries, hits per layer, combinations, road table -------------------------------
@@ -738,7 +753,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     const uint32_t nh = pre.y, n4 = nh_of(nh, 4), n01 = nh_of(nh, 0) * nh_of(nh, 1),
                    n23 = nh_of(nh, 2) * nh_of(nh, 3);
     const uint32_t ntab = n01 + n23 + n4, rb = pre.x, end = rb + n01 * n23 * n4;
-    const uint32_t n_it = road ? ((end - 1) >> 2) - (rb >> 2) + 1 : 0;
+    const uint32_t n_it = road ? ((end - 1) >> kBits) - (rb >> kBits) + 1 : 0;
     const uint32_t tend = scan64(ntab);
     const bool take = road && tend <= kTabCap;
     const int c1 = c0 + __popcll(ballot(take));
@@ -748,12 +763,12 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     const bool narrow = ballot(take && !L.bank[pre.z].narrow) == 0;
     // groups ga .. gb - 1 of the unit are this slice's (the last slice takes what is left over)
     const uint32_t slices = SLICED && c_run > slice_len ? (c_run - 1) / slice_len + 1 : 1;
-    const uint32_t slice_groups = slice_len / 4;
+    const uint32_t slice_groups = slice_len >> kBits;
     const uint32_t ga = slice * slice_groups,
                    gb = slice + 1 < slices ? ga + slice_groups : ~0u >> 1;
     if (SLICED && slices > 1) {
         // the items are in the order of their groups: count those before ga and before gb
-        const uint32_t g = rb >> 2;
+        const uint32_t g = rb >> kBits;
         uint32_t before = ga > g ? ga - g : 0, upto = gb > g ? gb - g : 0;
         before = take ? (before < n_it ? before : n_it) : 0;
         upto = take ? (upto < n_it ? upto : n_it) : 0;
@@ -766,7 +781,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         const uint32_t t = tend - ntab;
         const uint32_t p01 = 4 * t, p23 = p01 + 4 * n01, p4 = p23 + 4 * n23;
         row.a = make_uint4(L.magic[n4] | (n4 << 26), L.magic[n23] | (n23 << 24), rb, end);
-        row.b = make_uint4((rb >> 2) - item, nh, p01 | (p23 << 16), p4 | (pre.z << 16));
+        row.b = make_uint4((rb >> kBits) - item, nh, p01 | (p23 << 16), p4 | (pre.z << 16));
         W.road[lane] = row;
         // Where a word's coordinate goes, by layer: bytes from the tables' start (12 bits), and on per
         // rank (6 bits, from bit 12); bytes from one entry to the next (6 bits, from 18); entries.
@@ -827,7 +842,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         if (SLICED && slices > 1) {
             // a road with groups in other slices too: every one of them adds what it found, and
             // the last to do so has the whole of it
-            const uint32_t g_first = row.a.z >> 2, g_last = (row.a.w - 1) >> 2;
+            const uint32_t g_first = row.a.z >> kBits, g_last = (row.a.w - 1) >> kBits;
             const bool touched = g_last >= ga && g_first < gb;
             const bool cut = touched && (g_first < ga || g_last >= gb);
             whole = touched && !cut;
@@ -1202,7 +1217,8 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
         const uint32_t k = i - s_quick[lo];
         const int64_t pos = base + s_pre[lo] + k;
         if (pos >= a.kept_cap) continue;
-        const int64_t GB = static_cast<int64_t>(s_first[lo] & ~uint64_t{3});
+        constexpr int bits = kGroupBits<ONLY ? kRecNone : kRecFit>;
+        const int64_t GB = static_cast<int64_t>(s_first[lo] & ~((uint64_t{1} << bits) - 1));
         const uint32_t *slot = a.slots + (u0 + lo) * (a.slot_bytes / 4);
         if (ONLY) {
             const uint4 v = reinterpret_cast<const uint4 *>(slot)[k];

@@ -56,10 +56,10 @@ def test_word_counts_around_units(bank, n):
     check(words, bank, CFG, f"{n} words")
 
 
-@pytest.mark.parametrize("cfg", [CFG, OPEN], ids=["cut", "open"])
-@pytest.mark.parametrize("kind", ["ones", "mixture", "one_word", "giant", "wide_tables"])
-@pytest.mark.parametrize("n", [60, 1500])
-def test_road_mixtures(bank, kind, n, cfg):
+KINDS = ["ones", "mixture", "one_word", "giant", "wide_tables"]
+
+
+def kind_words(kind, n):
     """n = 60 roads stay within the finely sliced batches; of 1500, "mixture" and "wide_tables"
     have more than 64 units and units of more than 8192 combinations."""
     rng = np.random.default_rng(n + len(kind))
@@ -76,8 +76,37 @@ def test_road_mixtures(bank, kind, n, cfg):
     else:  # 128 table entries and few combinations
         hits = np.tile([8, 8, 1, 1, 1], (n, 1))
         hits[1::2] = [1, 1, 8, 8, 2]
-    words = stream(roads(rng, hits))
-    check(words, bank, cfg, f"{kind} {n}")
+    return stream(roads(rng, hits))
+
+
+@pytest.mark.parametrize("cfg", [CFG, OPEN], ids=["cut", "open"])
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [60, 1500])
+def test_road_mixtures(bank, kind, n, cfg):
+    check(kind_words(kind, n), bank, cfg, f"{kind} {n}")
+
+
+@pytest.mark.parametrize("cfg", [CFG, OPEN], ids=["cut", "open"])
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [60, 1500])
+def test_road_mixtures_kept_only(bank, kind, n, cfg):
+    """Kept-only mode fits groups of eight combinations; its accept flags here start at 4 bytes
+    past a multiple of 8."""
+    words = kind_words(kind, n)
+    ref = oracle.run(words, bank.f, bank.q, cfg)
+    wc, rc, cc = caps_for(words, ref)
+    r = P.BatchRunner(gpu_cfg(cfg), P.device_bank(bank.f, bank.q), wc, rc, cc, kept_cap=cc,
+                      graph=False, kept_only=True)
+    r.accept = torch.zeros(r.accept.numel() + 4, dtype=torch.uint8, device="cuda")[4:]
+    assert r.accept.data_ptr() % 8 == 4
+    r._calls.clear()
+    r._call = r._prepared(r.word_cap)
+    got = r.load(P.words_tensor(words)).run().result()
+    compare(ref, got, [k for k in BATCH_KEYS if k not in ("p0", "p1", "p2", "c0", "c1", "c2",
+                                                          "chi2")], f"kept only {kind} {n}")
+    kept = np.asarray(ref["kept"])
+    for k in ("p0", "p1", "p2", "c0", "c1", "c2", "chi2"):
+        assert np.array_equal(np.asarray(ref[k])[kept], got[f"kept_{k}"].cpu().numpy()), k
 
 
 def test_unaligned_and_host_words(bank):
