@@ -233,12 +233,13 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
 // ---- plain fit: one lane per listed combination ------------------------------------------------
 // The list may hold any combinations in any order; where it is the combine stage's, a tile of
 // 2048 names few roads, whose table entries and coordinates then come from LDS (every lane
-// gathering its own from memory took 86 us at 6.2e6 combinations, now 61 for 246 MB).  The constant bank is packed
+// gathering its own from memory took 86 us at 6.2e6 combinations, now 47 for 246 MB: 54 with 256
+// threads that take 8 each, 61 with 64-bit indices checked one by one).  The constant bank is packed
 // into LDS once per workgroup, in the pairs of the 16-bit dot products; with the offset split as
 // q = qh * 2^s + ql every sum stays inside int32 (svt_fit.h), where 64-bit products ran at a
 // quarter of the rate.
-constexpr int kFitThreads = 256;
-constexpr int kFitLane = 8;
+constexpr int kFitThreads = 512;
+constexpr int kFitLane = 4;
 constexpr int kFitTile = kFitThreads * kFitLane;
 constexpr int kFitRoads = 512;
 constexpr int kFitCoords = 4096;
@@ -247,8 +248,10 @@ struct alignas(16) PlainSet {  // row j: f0|f1, f2|f3, f4|0, q; 112 bytes spread
     uint4 row[6];
     uint32_t pad[4];
 };
+// A road of the tile: where its coordinates are staged (-1: not all of them, or its set is not in
+// the bank), hits per layer, set.
 struct PlainRoad {
-    int64_t hb;
+    int32_t at;
     uint32_t nh;
     int32_t set;
 };
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
     const uint32_t *__restrict__ combo_hits, int64_t n_combos, svt_fitrec out, uint64_t *err) {
     __shared__ PlainSet s_bank[256];
     __shared__ PlainRoad s_road[kFitRoads];
-    __shared__ int16_t s_coord[kFitCoords];
+    __shared__ int16_t s_coord[kFitCoords + 1];  // (one past the end is read for a layer without hits)
     __shared__ int32_t s_lo[2], s_hi[2];
     const int tid = threadIdx.x;
     const int32_t shift = cfg.shift;
@@ -308,23 +311,29 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
         lo = s_lo[par];
         hi = s_hi[par];
         const int span = hi >= lo && hi - lo < kFitRoads ? hi - lo + 1 : 0;
-        int64_t w_lo = 0;  // coordinates staged: w_lo .. w_lo + wn - 1
-        int wn = 0;
         if (tid == 0) {  // the other tile's bounds, for its next turn
             s_lo[par ^ 1] = INT32_MAX;
             s_hi[par ^ 1] = -1;
         }
         if (span > 0) {
-            for (int j = tid; j < span; j += kFitThreads) {
-                const int64_t q = lo + j;
-                s_road[j] = PlainRoad{roads.hit_begin[q], roads.nhits[q], roads.set[q]};
-            }
-            w_lo = roads.hit_begin[lo];
+            // coordinates staged: w_lo .. w_lo + wn - 1
+            const int64_t w_lo = roads.hit_begin[lo];
             const int64_t w_hi = roads.hit_begin[hi] + SVT_N_LAYERS * SVT_MAX_HITS;
+            int wn = 0;
             if (w_lo >= 0 && w_lo < n_hits && w_hi > w_lo) {
                 const int64_t stop = w_hi < n_hits ? w_hi : n_hits;
                 wn = static_cast<int>(stop - w_lo < kFitCoords ? stop - w_lo : kFitCoords);
                 for (int j = tid; j < wn; j += kFitThreads) s_coord[j] = hit_coord[w_lo + j];
+            }
+            for (int j = tid; j < span; j += kFitThreads) {
+                const int64_t q = lo + j, at = roads.hit_begin[q] - w_lo;
+                const uint32_t nh = roads.nhits[q];
+                const int32_t set = roads.set[q];
+                int n = 0;
+#pragma unroll
+                for (int l = 0; l < SVT_N_LAYERS; ++l) n += static_cast<int>(nh_of(nh, l));
+                const bool in = at >= 0 && at + n <= wn && set >= 0 && set < cfg.n_sets;
+                s_road[j] = PlainRoad{in ? static_cast<int32_t>(at) : -1, nh, set};
             }
         }
         __syncthreads();
@@ -333,26 +342,31 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
             const int64_t i = t0 + e * kFitThreads + tid;
             if (i >= n_combos) break;
             if (r[e] < 0 || r[e] >= n_roads) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
-            PlainRoad rd;
-            if (span > 0)
-                rd = s_road[r[e] - lo];
-            else
-                rd = PlainRoad{roads.hit_begin[r[e]], roads.nhits[r[e]], roads.set[r[e]]};
-            bool ok = rd.set >= 0 && rd.set < cfg.n_sets;
+            PlainRoad rd{-1, 0, 0};
+            if (span > 0) rd = s_road[r[e] - lo];
+            bool ok = true;
             int32_t x[SVT_N_LAYERS];
-            int64_t off = rd.hb;
+            if (rd.at >= 0) {
+                int32_t off = rd.at;
 #pragma unroll
-            for (int l = 0; l < SVT_N_LAYERS; ++l) {
-                const uint32_t d = (ph[e] >> (4 * l)) & 0xFu;
-                const uint32_t nl = nh_of(rd.nh, l);
-                const int64_t idx = off + d;
-                ok &= (d < nl) && idx >= 0 && idx < n_hits;
-                x[l] = 0;
-                if (ok) {
-                    const uint64_t w = static_cast<uint64_t>(idx - w_lo);
-                    x[l] = w < static_cast<uint64_t>(wn) ? s_coord[w] : hit_coord[idx];
+                for (int l = 0; l < SVT_N_LAYERS; ++l) {
+                    const uint32_t d = (ph[e] >> (4 * l)) & 0xFu, nl = nh_of(rd.nh, l);
+                    ok &= d < nl;
+                    x[l] = s_coord[off + static_cast<int32_t>(d < nl ? d : 0)];
+                    off += static_cast<int32_t>(nl);
                 }
-                off += nl;
+            } else {
+                rd = PlainRoad{0, roads.nhits[r[e]], roads.set[r[e]]};
+                ok = rd.set >= 0 && rd.set < cfg.n_sets;
+                int64_t off = roads.hit_begin[r[e]];
+#pragma unroll
+                for (int l = 0; l < SVT_N_LAYERS; ++l) {
+                    const uint32_t d = (ph[e] >> (4 * l)) & 0xFu, nl = nh_of(rd.nh, l);
+                    const int64_t idx = off + d;
+                    ok &= d < nl && idx >= 0 && idx < n_hits;
+                    x[l] = ok ? hit_coord[idx] : 0;
+                    off += nl;
+                }
             }
             if (!ok) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
             const PlainSet &F = s_bank[rd.set];
