@@ -296,7 +296,7 @@ static_assert(sizeof(ULds) <= 160 * 1024, "LDS of a compute unit");
 
 // A lane fits groups of 2^kGroupBits consecutive combinations: 4 with records, whose int32 arrays
 // take them as 16 bytes each; 8 without, which halves the windows and what each spends on finding
-// the lanes' roads and first combinations (4000 events of 2048 roads: 955 us a pass with 4, 905
+// the lanes' roads and first combinations (2000 events of 2048 roads: 955 us a pass with 4, 905
 // with 8).
 template <int REC>
 constexpr int kGroupBits = REC == kRecNone ? 3 : 2;
@@ -1122,6 +1122,7 @@ struct KArgs {
     const uint32_t *slots;
     uint32_t slot_bytes;
     const UnitSet *sets;
+    int32_t n_sets;
     const uint32_t *words;
     svt_roads roads;
     const uint8_t *accept;
@@ -1163,7 +1164,9 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     __shared__ uint64_t s_first[kKeepGroup];  // the unit's first combination
     __shared__ int32_t s_cb[kKeepGroup];      // a searched unit's roads: first combination
     __shared__ uint8_t s_list[kKeepGroup];    // the units to be searched
+    __shared__ int32_t s_item[kKeepGroup];    // accepted combinations of one, in order
     __shared__ uint64_t s_tmp[kKeepGroup / kWaveSize + 1];
+    __shared__ UnitSet s_bank[ONLY ? 256 : 1];
     const int tid = threadIdx.x;
     if (has_error(a.err)) {
         if (blockIdx.x == 0 && tid == 0) *a.d_n_kept = -1;
@@ -1208,27 +1211,62 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     __syncthreads();
     const uint32_t n_quick = static_cast<uint32_t>(tot >> 28) & 0xFFFFFu;
     const int n_search = static_cast<int>(tot >> 48);
-    for (uint32_t i = part * kKeepGroup + tid; i < n_quick; i += a.parts * kKeepGroup) {
-        int lo = 0, hi = kKeepGroup - 1;  // last unit that starts at or before i
+    // Every thread reads all six rows of a set, another one than its neighbours': from LDS where the
+    // workgroup has enough to fit for the copy to pay (3.1e6 kept of 4e8 combinations: 101 us with
+    // the rows from memory, 92 from LDS; at 84 thousand kept, three to a thread, 7.0 and 7.6).
+    const uint32_t stride = a.parts * kKeepGroup;
+    const bool staged = ONLY && n_quick > 4 * stride;
+    if (staged) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(a.sets);
+        uint4 *dst = reinterpret_cast<uint4 *>(s_bank);
+        const int n16 = a.n_sets * static_cast<int>(sizeof(UnitSet) / 16);
+        for (int i = tid; i < n16; i += kKeepGroup) dst[i] = src[i];
+        __syncthreads();
+    }
+    auto find = [&](uint32_t i, int &unit) {  // where accepted combination i of the group waits
+        int lo = 0, hi = kKeepGroup - 1;      // last unit that starts at or before it
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (s_quick[mid] <= i) lo = mid; else hi = mid - 1;
         }
-        const uint32_t k = i - s_quick[lo];
-        const int64_t pos = base + s_pre[lo] + k;
-        if (pos >= a.kept_cap) continue;
-        constexpr int bits = kGroupBits<ONLY ? kRecNone : kRecFit>;
-        const int64_t GB = static_cast<int64_t>(s_first[lo] & ~((uint64_t{1} << bits) - 1));
-        const uint32_t *slot = a.slots + (u0 + lo) * (a.slot_bytes / 4);
-        if (ONLY) {
-            const uint4 v = reinterpret_cast<const uint4 *>(slot)[k];
-            a.kept[pos] = GB + (v.x & 0xFFFFFFu);
-            keep_record(a, a.sets[v.x >> 24], pos, static_cast<int32_t>(v.y),
-                        static_cast<int32_t>(v.z), static_cast<int32_t>(v.w));
-        } else {
-            a.kept[pos] = GB + slot[k];
+        unit = lo;
+        return a.slots + (u0 + lo) * (a.slot_bytes / 4) + (ONLY ? 4 : 1) * (i - s_quick[lo]);
+    };
+    auto read = [&](const uint32_t *slot) {
+        return ONLY ? *reinterpret_cast<const uint4 *>(slot) : make_uint4(*slot, 0, 0, 0);
+    };
+    // Four at a time: a slot that is read behind stores waits until they are done, 5 us under load.
+    constexpr int kAtOnce = 4;
+    for (uint32_t i0 = part * kKeepGroup + tid; i0 < n_quick; i0 += kAtOnce * stride) {
+        int unit[kAtOnce];
+        uint4 v[kAtOnce];
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) {
+            const uint32_t i = i0 + e * stride;
+            if (i < n_quick) v[e] = read(find(i, unit[e]));
+        }
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) {
+            const uint32_t i = i0 + e * stride;
+            if (i >= n_quick) break;
+            const int64_t pos = base + s_pre[unit[e]] + (i - s_quick[unit[e]]);
+            if (pos >= a.kept_cap) break;
+            constexpr int bits = kGroupBits<ONLY ? kRecNone : kRecFit>;
+            const int64_t GB = static_cast<int64_t>(s_first[unit[e]] & ~((uint64_t{1} << bits) - 1));
+            if (ONLY) {
+                a.kept[pos] = GB + (v[e].x & 0xFFFFFFu);
+                const int32_t x01 = static_cast<int32_t>(v[e].y), x23 = static_cast<int32_t>(v[e].z),
+                              x4 = static_cast<int32_t>(v[e].w);
+                if (staged)
+                    keep_record(a, s_bank[v[e].x >> 24], pos, x01, x23, x4);
+                else
+                    keep_record(a, a.sets[v[e].x >> 24], pos, x01, x23, x4);
+            } else {
+                a.kept[pos] = GB + v[e].x;
+            }
         }
     }
+    constexpr int kWalk = 8;  // words read at once: one by one, a road's take 20 us
     // ---- units whose accepted combinations are found again: their accept flags in order, each
     // one's road by its first combination and its hits by walking the road's words
     for (int sq = part; sq < n_search; sq += a.parts) {
@@ -1263,11 +1301,19 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
                 bits |= static_cast<uint64_t>(((w * 0x10204080u) >> 28) & 0xFu) << (4 * v);
             }
             uint64_t all;
-            int64_t pos = at + static_cast<int64_t>(block_excl_scan<uint64_t, kKeepGroup>(
-                                   static_cast<uint64_t>(__popcll(bits)), s_tmp, all));
-            at += static_cast<int64_t>(all);
-            for (; bits && pos < a.kept_cap; bits &= bits - 1, ++pos) {
-                const int i = mine0 + __builtin_ctzll(bits);
+            const uint32_t rank = static_cast<uint32_t>(block_excl_scan<uint64_t, kKeepGroup>(
+                static_cast<uint64_t>(__popcll(bits)), s_tmp, all));
+            // dealt out again, one to a thread: accepted combinations come in runs (193 such units of
+            // 2e5 cost 32 us as the last ones to finish, now 9)
+            for (uint32_t first = 0; first < all; first += kKeepGroup) {
+                uint32_t r2 = rank - first;
+                for (uint64_t m = bits; m; m &= m - 1, ++r2)
+                    if (r2 < static_cast<uint32_t>(kKeepGroup)) s_item[r2] = mine0 + __builtin_ctzll(m);
+                __syncthreads();
+                const int i = s_item[tid];
+                __syncthreads();
+                const int64_t pos = at + first + tid;
+                if (first + tid >= all || pos >= a.kept_cap) continue;
                 a.kept[pos] = CB0 + i;
                 if (!ONLY) continue;
                 int lo = 0, hi = nr - 1;  // last road that starts at or before i
@@ -1289,17 +1335,25 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
                 const uint32_t *w = a.words + a.roads.hit_begin[r];
                 int32_t x[SVT_N_LAYERS] = {0, 0, 0, 0, 0};
                 uint32_t seen = 0;
-                for (uint32_t j = 0; j < words; ++j) {
-                    const uint32_t y = w[j], l = w_layer(y);
-                    const bool hit = ((seen >> (6 * l)) & 63u) == ((want >> (6 * l)) & 63u);
-                    seen += 1u << (6 * l);
+                for (uint32_t j0 = 0; j0 < words; j0 += kWalk) {
+                    uint32_t y[kWalk];
 #pragma unroll
-                    for (int q2 = 0; q2 < SVT_N_LAYERS; ++q2)
-                        if (hit && l == static_cast<uint32_t>(q2)) x[q2] = w_coord(y);
+                    for (int e = 0; e < kWalk; ++e) y[e] = w[j0 + e < words ? j0 + e : words - 1];
+#pragma unroll
+                    for (int e = 0; e < kWalk; ++e) {
+                        const uint32_t l = w_layer(y[e]);
+                        const bool hit = j0 + e < words &&
+                                         ((seen >> (6 * l)) & 63u) == ((want >> (6 * l)) & 63u);
+                        seen += 1u << (6 * l);
+#pragma unroll
+                        for (int q2 = 0; q2 < SVT_N_LAYERS; ++q2)
+                            if (hit && l == static_cast<uint32_t>(q2)) x[q2] = w_coord(y[e]);
+                    }
                 }
                 keep_record(a, a.sets[a.roads.set[r]], pos, pack16(x[0], x[1]), pack16(x[2], x[3]),
                             x[4]);
             }
+            at += static_cast<int64_t>(all);
         }
     }
 }
@@ -1525,6 +1579,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     k.slots = a.slots;
     k.slot_bytes = a.slot_bytes;
     k.sets = c.sets;
+    k.n_sets = p.cfg.n_sets;
     k.words = a.words;
     k.roads = p.roads;
     k.accept = p.accept;
