@@ -147,6 +147,15 @@ __device__ __forceinline__ const int32_t *at_byte(const int32_t *p, uint32_t o) 
 }
 // 8 bytes at an address that is a multiple of 4
 typedef uint32_t U32Pair __attribute__((ext_vector_type(2), aligned(4)));
+// A pointer that was itself read from LDS points to memory, which the compiler cannot know: it would
+// use flat accesses, and a flat store holds up every later wait for LDS until memory has taken it.
+template <typename T>
+using InMemory = __attribute__((address_space(1))) T;
+template <typename T>
+__device__ __forceinline__ InMemory<T> *in_memory(T *p) {
+    return (InMemory<T> *)p;
+}
+typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
 // LDS by 32-bit address
 typedef __attribute__((address_space(3))) const int32_t LdsInt;
 __device__ __forceinline__ uint32_t lds_address(const int32_t *p) {
@@ -177,6 +186,11 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 __device__ __forceinline__ void lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ UnitRec read_rec(const UnitRec *rec, int64_t u) {
+    const U32x4 v = *(in_memory(reinterpret_cast<const U32x4 *>(rec)) + u);
+    return UnitRec{v.x, v.y, v.z | (static_cast<uint64_t>(v.w) << 32)};
 }
 
 // ---- a unit's words ---------------------------------------------------------------------------

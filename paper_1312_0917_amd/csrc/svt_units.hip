@@ -401,7 +401,8 @@ template <int MODE, int REC>
 __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveLds &W, int c0,
                                             int c1, uint32_t first_item, uint32_t from_item,
                                             uint32_t n_items, int64_t GB, int32_t shift,
-                                            uint32_t qlmask, uint32_t *keep_at, uint32_t &kept) {
+                                            uint32_t qlmask, InMemory<uint32_t> *keep_at,
+                                            uint32_t &kept) {
     constexpr int J0 = REC == kRecNone ? 3 : 0;
     // Windows end where a 128-byte line of the int32 record arrays does (8 groups): a line
     // written in two parts reaches memory in parts.  On 4000 events of 2048 roads windows that
@@ -521,10 +522,9 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
                         const uint32_t c = static_cast<uint32_t>(rel + e);
                         if (REC == kRecNone) {
                             if (pos < a.slot_bytes / 16)
-                                reinterpret_cast<uint4 *>(keep_at)[pos] =
-                                    make_uint4(c | (mb.w >> 16 << 24), static_cast<uint32_t>(x01[e]),
-                                               static_cast<uint32_t>(x23[e]),
-                                               static_cast<uint32_t>(x4[e]));
+                                reinterpret_cast<InMemory<U32x4> *>(keep_at)[pos] =
+                                    U32x4{c | (mb.w >> 16 << 24), static_cast<uint32_t>(x01[e]),
+                                          static_cast<uint32_t>(x23[e]), static_cast<uint32_t>(x4[e])};
                         } else if (pos < a.slot_bytes / 4) {
                             keep_at[pos] = c;
                         }
@@ -653,7 +653,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     const int64_t base = u * kUnitWords;
     const int nloc = static_cast<int>(n - base < kUnitSpan ? n - base : kUnitSpan);
     const UnitWords uw = load_unit(hot.words, base, nloc);
-    const UnitRec rec = L.args.rec[u];
+    const UnitRec rec = read_rec(L.args.rec, u);
     const RangeBase rbase = L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)];
     const bool table = c0 == 0 && (!SLICED || slice == 0);  // the unit's road table is to be written
     const int64_t R0 = static_cast<int64_t>(uni(rec.roads) + uni(rbase.roads));
@@ -705,19 +705,19 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
         if (mine && table) {
             const UArgs &a = L.args;
             const int64_t r = R0 + rl;
-            a.roads.event[r] = static_cast<int32_t>(evn);
-            a.roads.set[r] = static_cast<int32_t>(tag);
-            a.roads.hit_begin[r] = base + pos;
-            a.roads.nhits[r] = nh;
-            a.roads.ncombo[r] = static_cast<int32_t>(c);
-            a.roads.combo_begin[r] = CB0 + cb;
+            in_memory(a.roads.event)[r] = static_cast<int32_t>(evn);
+            in_memory(a.roads.set)[r] = static_cast<int32_t>(tag);
+            in_memory(a.roads.hit_begin)[r] = base + pos;
+            in_memory(a.roads.nhits)[r] = nh;
+            in_memory(a.roads.ncombo)[r] = static_cast<int32_t>(c);
+            in_memory(a.roads.combo_begin)[r] = CB0 + cb;
             if (c == 0) {
-                a.best.n_accept[r] = 0;
-                a.best.k[r] = -1;
-                a.best.p0[r] = INT32_MIN;
-                a.best.p1[r] = INT32_MIN;
-                a.best.p2[r] = INT32_MIN;
-                a.best.chi2[r] = INT64_MAX;
+                in_memory(a.best.n_accept)[r] = 0;
+                in_memory(a.best.k)[r] = -1;
+                in_memory(a.best.p0)[r] = INT32_MIN;
+                in_memory(a.best.p1)[r] = INT32_MIN;
+                in_memory(a.best.p2)[r] = INT32_MIN;
+                in_memory(a.best.chi2)[r] = INT64_MAX;
             }
         }
     }
@@ -822,9 +822,9 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     lds_order();
     W.mark[lane] = 0;
     lds_order();
-    uint32_t *keep_at = nullptr;
+    InMemory<uint32_t> *keep_at = nullptr;
     if ((REC == kRecNone || hot.keep) && slices == 1)
-        keep_at = L.args.slots + u * (hot.slot_bytes / 4);
+        keep_at = in_memory(L.args.slots) + u * (hot.slot_bytes / 4);
     if (narrow)
         fit_windows<kFitNarrow, REC>(hot, L, W, c0, c1, item, from_item, n_items, GB, shift,
                                      qlmask, keep_at, kept);
@@ -851,7 +851,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 uint32_t s1 = g_last / slice_groups;
                 s1 = s1 < slices ? s1 : slices - 1;
                 // the batch's number of the slice after the road's first one
-                const UnitRec rc = L.args.rec[u];
+                const UnitRec rc = read_rec(L.args.rec, u);
                 const uint32_t x = static_cast<uint32_t>(rc.combos >> kExtraShift) +
                                    L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)]
                                        .extra + s0;
@@ -894,27 +894,29 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 v1 = f.v[1];
                 v2 = f.v[2];
             }
-            a.best.n_accept[r] = static_cast<int32_t>(nacc);
-            a.best.k[r] = k;
-            a.best.p0[r] = v0;
-            a.best.p1[r] = v1;
-            a.best.p2[r] = v2;
-            a.best.chi2[r] = chi2;
+            in_memory(a.best.n_accept)[r] = static_cast<int32_t>(nacc);
+            in_memory(a.best.k)[r] = k;
+            in_memory(a.best.p0)[r] = v0;
+            in_memory(a.best.p1)[r] = v1;
+            in_memory(a.best.p2)[r] = v2;
+            in_memory(a.best.chi2)[r] = chi2;
         }
     }
     lds_order();
     if (c1 < nf) return c1;
     if ((REC == kRecNone || hot.keep) && kept > 0 && lane == 0) {
-        UnitKeep &k = L.args.keep[u];
+        InMemory<UnitKeep> *k = in_memory(L.args.keep) + u;
         const uint32_t most = hot.slot_bytes / (REC == kRecNone ? 16 : 4);
         if (slices > 1)
-            atomicAdd(&k.count, kept);
+            __hip_atomic_fetch_add(&k->count, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else
-            k.count = kept | (kept > most ? kKeepSearch : 0u);
-        k.roads = nr;
-        k.combo = static_cast<uint64_t>(CB0);
-        k.road = static_cast<uint64_t>(R0);
-        atomicAdd(L.args.group + u / kKeepGroup * kKeepStride, static_cast<unsigned long long>(kept));
+            k->count = kept | (kept > most ? kKeepSearch : 0u);
+        k->roads = nr;
+        k->combo = static_cast<uint64_t>(CB0);
+        k->road = static_cast<uint64_t>(R0);
+        __hip_atomic_fetch_add(in_memory(L.args.group) + u / kKeepGroup * kKeepStride,
+                               static_cast<unsigned long long>(kept), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     }
     return 0;
 }
