@@ -105,7 +105,8 @@ __global__ __launch_bounds__(kRoadBlock) void k_combo_begin(svt_roads roads, Siz
 // ---- combine 3 (plain path): list every combination --------------------------------------
 // A workgroup lists kListTile consecutive combinations, however few or many roads they belong
 // to: by blocks of 256 roads, the workgroup with the largest roads took most of the time (190 us
-// for 1500 uneven events, now 19; 51 and 20 us for 3000 events of 64 roads, whose list is 49 MB).  k_combo_begin has left the road of the tile's first
+// for 1500 uneven events, now 19; 51 and 20 us for 3000 events of 64 roads, whose list is 49 MB;
+// tiles of 4096 and 8192 take 20 and 23).  k_combo_begin has left the road of the tile's first
 // combination in combo_road; the tile's roads are staged in LDS, up to kListRoads at a time.
 constexpr int kListRoads = 512;
 constexpr int kListThreads = 256;

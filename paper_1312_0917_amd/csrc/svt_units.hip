@@ -15,6 +15,10 @@
 // kernel as a road table and grouped coordinates.  Inside the fitting kernel nothing is shared
 // between waves but the constant bank: a wave's chain of loads, LDS writes and scans overlaps
 // the arithmetic and the stores of the 15 others.
+//
+// Measured on one GPU, us a pass: 3000 events of 64 roads 49 (four kernels before: a pre-pass with
+// look-back, fits of flat tiles, best tracks, a reset: 75), 4000 events of 2048 roads 3940 (4510),
+// 8192 uneven events with a kept list 247 (320), 100 events of 8 roads 16.4 back to back (23).
 #include "svt_fit.h"
 #include "svt_units.h"
 
@@ -69,6 +73,10 @@ __device__ __forceinline__ uint64_t with_extra(uint32_t combos, uint32_t extra) 
     return combos | (static_cast<uint64_t>(extra) << kExtraShift);
 }
 
+// Bound by vector instructions, some 190 a unit, where there are many units (2.6e8 words: 0.42 ms,
+// 2.4 TB/s; the pre-pass it replaces wrote 10 bytes a word more and took 1.55), by its latency where
+// there are few (1.9e6 words: 7.7 us of which a launch that does nothing is half).  Two workgroups
+// of 16 waves a compute unit: 64 registers a lane.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_unit_count(CArgs a) {
     __shared__ uint2 s_ent[kUnitWaves][kEntries + 1];
     __shared__ uint2 s_agg[2][kUnitWaves];
@@ -948,7 +956,7 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
 // The wave's units.  Seven eighths of them are dealt to the workgroups in contiguous ranges, so that
 // the record lines two neighbouring units share are written from one compute unit; the rest is
 // divided among the dealers and goes by ticket to the waves that finish first (one counter for all
-// of them would hand out a unit every 12 ns).  Slices past their unit's first come before
+// of them would hand out a unit every 12 ns: 93 us for 7500 units, 51 with 32).  Slices past their unit's first come before
 // everything else, dealt out to the workgroups in turn.
 template <int REC, bool SLICED>
 __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, int64_t nu,
@@ -1067,6 +1075,11 @@ __device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges
     return all;
 }
 
+// What bounds it: with records the stores of large batches (2e9 combinations: 44.7 GB in 9.45 ms,
+// 4.73 TB/s, where a copy of 4 GiB moves 4.78 and these stores alone 5.4), at 7500 units the
+// issue of vector instructions, 2000 a unit of which 0.4 unpack, and the last units' run-out (43 us
+// for 151 MB); without records the vector instructions (2e5 units: 4.15e8 wave instructions in 790
+// us).  One workgroup of 16 waves a compute unit is what LDS holds: 7 KB a wave and 42 KB for all.
 template <int REC>
 __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
     __shared__ ULds L;
@@ -1363,7 +1376,8 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
 // ---- the unpack stage on its own ------------------------------------------------------------------
 // The road table (event, set, hit_begin, nhits) and every word's coordinate at its place among its
 // road's hits grouped by layer.  No bank and no tables: two workgroups of 16 waves fit a compute
-// unit, and the waves take the units in turn.
+// unit, and the waves take the units in turn.  With the counting kernel 24 us at 1.9e6 words, half of
+// it the launches' own (33 before: flags, scan, lists and a kernel per road).
 struct TArgs {
     const uint32_t *words;
     int64_t n;
