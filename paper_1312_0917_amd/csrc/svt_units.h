@@ -24,9 +24,11 @@ constexpr int kMaxRanges = 512;    // contiguous ranges of units whose totals ar
 // A unit with many combinations is cut into slices of this many, so that no wave works long after
 // the others have finished (a unit of the largest roads holds 2e5 combinations, a usual one 800 to
 // 3000); a batch too small to fill the chip is cut finer, not so fine that every slice unpacks its
-// unit again for little: slices of 256, 512 and 1024 take 22.7, 19.2 and 18.5 us for the fits of 33
-// units, 48.8, 30.2 and 23.6 for 37 uneven events; up to 256 units instead of 64 change nothing.
-constexpr int kSliceCombos = 8192, kSliceCombosSmall = 1024;
+// unit again for little: the fits of 33 units take 17.2 us with slices of 1024, 15.8 with 512; of 37
+// uneven events 19.3 and 18.5.  Cutting in two what holds 1536 or more in batches of up to 2048 units
+// gave 3 us of 37 for 256 events of up to 256 roads, and cost 0.5 of 49 for 7500 units, whose slices
+// then have to be worked out one by one.
+constexpr int kSliceCombos = 8192, kSliceCombosSmall = 512;
 constexpr int kSmallUnits = 64;
 __host__ __device__ inline int slice_combos(int64_t nu) {
     return nu <= kSmallUnits ? kSliceCombosSmall : kSliceCombos;

@@ -863,12 +863,17 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 const uint32_t x = static_cast<uint32_t>(rc.combos >> kExtraShift) +
                                    L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)]
                                        .extra + s0;
-                SliceAcc *acc = L.args.acc + x;
-                atomicMax(&acc->key, ~key);
-                atomicAdd(&acc->nacc, nacc);
-                __threadfence();
-                whole = atomicAdd(&acc->arrived, 1u) == s1 - s0;
-                __threadfence();
+                // Everything here is an atomic at agent scope, so it is enough that the first two are
+                // done before the third starts; a fence would also write back what the L2 holds of
+                // the records (37 uneven events: 23.5 us with fences, 19.3 without; 1900 units cut in
+                // two: 241 and 24).
+                InMemory<SliceAcc> *acc = in_memory(L.args.acc) + x;
+                __hip_atomic_fetch_max(&acc->key, ~key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(&acc->nacc, nacc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                whole = __hip_atomic_fetch_add(&acc->arrived, 1u, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) == s1 - s0;
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if (whole) {
                     key = ~__hip_atomic_load(&acc->key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     nacc = __hip_atomic_load(&acc->nacc, __ATOMIC_RELAXED,

@@ -56,12 +56,13 @@ def test_word_counts_around_units(bank, n):
     check(words, bank, CFG, f"{n} words")
 
 
-KINDS = ["ones", "mixture", "one_word", "giant", "wide_tables"]
+KINDS = ["ones", "mixture", "one_word", "giant", "wide_tables", "quads"]
 
 
 def kind_words(kind, n):
     """n = 60 roads stay within the finely sliced batches; of 1500, "mixture" and "wide_tables"
-    have more than 64 units and units of more than 8192 combinations."""
+    have more than 64 units and units of more than 8192 combinations; the units of "quads" hold
+    about 2000."""
     rng = np.random.default_rng(n + len(kind))
     if kind == "ones":
         hits = np.ones((n, 5), int)
@@ -73,6 +74,8 @@ def kind_words(kind, n):
         hits[::37] = 1
     elif kind == "giant":
         hits = np.full((n // 10, 5), 8) if n < 100 else rng.integers(1, 9, size=(n // 4, 5))
+    elif kind == "quads":
+        hits = rng.integers(1, 5, size=(n, 5))
     else:  # 128 table entries and few combinations
         hits = np.tile([8, 8, 1, 1, 1], (n, 1))
         hits[1::2] = [1, 1, 8, 8, 2]
@@ -82,8 +85,9 @@ def kind_words(kind, n):
 @pytest.mark.parametrize("cfg", [CFG, OPEN], ids=["cut", "open"])
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("n", [60, 1500])
-def test_road_mixtures(bank, kind, n, cfg):
-    check(kind_words(kind, n), bank, cfg, f"{kind} {n}")
+@pytest.mark.parametrize("kept", [True, False], ids=["kept", "no_list"])
+def test_road_mixtures(bank, kind, n, cfg, kept):
+    check(kind_words(kind, n), bank, cfg, f"{kind} {n}", kept=kept)
 
 
 @pytest.mark.parametrize("cfg", [CFG, OPEN], ids=["cut", "open"])
