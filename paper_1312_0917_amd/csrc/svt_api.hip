@@ -67,7 +67,8 @@ struct BatchWs {
     int64_t *kb;        // accepted combinations per kKeptBlock
     int64_t kbn;
     int16_t *coords;    // and grouped coordinates
-    int64_t *nw_copy;   // the batch's word count, copied to device memory by the first kernel
+    int64_t *nw_copy;   // the batch's word count, copied to device memory by the first kernel; in
+                        // the unit kernels [1] tells the last one whether the fits ran
     void *sets;         // unit kernels: the packed bank,
     void *tot;          // totals per range of units,
     uint32_t *dealers;  // counters of the units dealt out late,
@@ -111,7 +112,7 @@ BatchWs carve_batch(Carver &c, int64_t word_cap, int64_t road_cap, int64_t combo
     // their accepted combinations there when they have no better place
     const int64_t slots = unit_slot_bytes(word_cap > 0 ? word_cap : 1, true) / 2;
     w.coords = c.take<int16_t>(word_cap + 16 > slots ? word_cap + 16 : slots);
-    w.nw_copy = c.take<int64_t>(1);
+    w.nw_copy = c.take<int64_t>(2);
     w.sets = c.take<char>(unit_bank_bytes());
     w.tot = c.take<char>(unit_range_bytes());
     w.dealers = c.take<uint32_t>(unit_ticket_bytes() / 4);

@@ -42,6 +42,16 @@ __device__ inline bool has_error(const uint64_t *err) {
     return *reinterpret_cast<const volatile uint64_t *>(err) != SVT_NO_ERROR;
 }
 
+// The same for a whole workgroup, read once: a kernel that reports errors itself changes the word
+// while its workgroups start, and of one workgroup's waves some could leave and the others go on
+// without them.  Contains a barrier.
+__device__ inline bool block_has_error(const uint64_t *err) {
+    __shared__ bool found;
+    if (threadIdx.x == 0) found = has_error(err);
+    __syncthreads();
+    return found;
+}
+
 // ---- hit word fields (coord int13 | layer 3 | road tag 8 | event tag 8) -------------------
 __device__ inline int32_t w_coord(uint32_t w) {
     return static_cast<int32_t>(w << 19) >> 19;  // sign-extend the low 13 bits
@@ -272,7 +282,7 @@ struct UnitsLaunch {
     int64_t *kept;             // null: the count alone
     int64_t kept_cap;
     bool kept_only;            // no records but those of the kept list
-    int64_t *nw_copy;          // workspace: the word count in device memory,
+    int64_t *nw_copy;          // workspace: the word count in device memory, and a word beside it,
     uint32_t *ticket;          // counters (unit_ticket_bytes),
     void *sets;                // the packed bank (unit_bank_bytes),
     void *rec;                 // running counts per unit (unit_rec_bytes),

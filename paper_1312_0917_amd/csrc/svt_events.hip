@@ -39,7 +39,7 @@ struct EArgs {
 __global__ __launch_bounds__(kEvThreads) void k_fit_events(EArgs a) {
     __shared__ int64_t s_cb[kEvRoads];
     __shared__ int64_t s_e;
-    if (has_error(a.err)) return;
+    if (block_has_error(a.err)) return;
     const int64_t n_roads = *a.d_n_roads;
     const int64_t n_combos = *a.d_n_combos;
     const int64_t n_events = *a.d_n_events;

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int64_t *data, int64_t co
                                                        int32_t skip_if_error) {
     __shared__ int64_t tmp[kScanThreads / kWaveSize + 1];
     int64_t *tot = blockIdx.x == 0 ? tot0 : tot1;
-    if (skip_if_error && has_error(err)) {
+    if (skip_if_error && block_has_error(err)) {
         if (threadIdx.x == 0 && tot) *tot = -1;
         return;
     }
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(256) void k_best_finalize(svt_roads roads, Sizes n_
     const int64_t road_blocks = job.data ? gridDim.x - 1 : gridDim.x;
     if (job.data && blockIdx.x == road_blocks) {
         __shared__ int64_t tmp[256 / kWaveSize + 1];
-        if (skip_if_error && has_error(err)) {
+        if (skip_if_error && block_has_error(err)) {
             if (threadIdx.x == 0 && job.tot) *job.tot = -1;
             return;
         }

@@ -32,7 +32,7 @@ constexpr int kEntries = kUnitSpan + 1;  // roads that start in a unit's span, a
 struct CArgs {
     const uint32_t *words;
     Sizes nw;
-    int64_t *nw_copy;        // the word count for the later kernels
+    int64_t *nw_copy;        // the word count for the later kernels (nw_copy[1] is the fit kernel's)
     uint32_t *ticket;        // units dealt out late, cleared here
     svt_config cfg;
     const svt_fconst *bank;  // nullable: unpack only
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 // ---- fitting ------------------------------------------------------------------------------------
 struct UArgs {
     const uint32_t *words;   // in device memory
-    const int64_t *d_nw;     // the word count (nw_copy)
+    int64_t *d_nw;           // the word count (nw_copy); d_nw[1]: left 1 if the batch has an error
     int64_t word_cap;
     uint32_t *ticket;
     int32_t ranges;          // ranges the counting kernel dealt units to
@@ -1115,6 +1115,7 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
         scan_ranges(t, a.ranges, per, nw, a.word_cap, a.road_cap, a.combo_cap, L.range);
     if (blockIdx.x == 0 && tid == 0) {
         *a.err = all.err;
+        a.d_nw[1] = all.err != SVT_NO_ERROR;
         *a.d_n_roads = all.n_roads;
         *a.d_n_combos = all.n_combos;
     }
@@ -1134,8 +1135,12 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
 // threads, each fitting from the coordinates that the unit's wave left (neither the accept flags
 // nor the road table is read: with those, scan and refit took 410 us behind the fits of 4e8
 // combinations).
+//
+// Whether the fits ran is read from a word that only the fitting kernel writes: a list that is too
+// short is reported in the error word by this kernel, while other workgroups start.  With records the
+// list then holds its first kept_cap entries; in kept-only mode nothing is written to it.
 struct KArgs {
-    const int64_t *d_nw;
+    const int64_t *d_nw;   // word count; [1]: the batch has an error
     int64_t word_cap;
     const UnitKeep *keep;
     const unsigned long long *group;
@@ -1186,9 +1191,10 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     __shared__ uint8_t s_list[kKeepGroup];    // the units to be searched
     __shared__ int32_t s_item[kKeepGroup];    // accepted combinations of one, in order
     __shared__ uint64_t s_tmp[kKeepGroup / kWaveSize + 1];
+    __shared__ ulonglong2 s_sum[kKeepGroup / kWaveSize];
     __shared__ UnitSet s_bank[ONLY ? 256 : 1];
     const int tid = threadIdx.x;
-    if (has_error(a.err)) {
+    if (a.d_nw[1] != 0) {
         if (blockIdx.x == 0 && tid == 0) *a.d_n_kept = -1;
         return;
     }
@@ -1198,21 +1204,40 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     const int64_t groups = (nu + kKeepGroup - 1) / kKeepGroup;
     const int64_t g = blockIdx.x / a.parts;
     const int part = static_cast<int>(blockIdx.x) % a.parts;
-    if (blockIdx.x == 0) {  // the total, and whether the list has room for it
-        uint64_t sum = 0;
-        for (int64_t i = tid; i < groups; i += kKeepGroup) sum += a.group[i * kKeepStride];
-        sum = block_sum<uint64_t, kKeepGroup>(sum, s_tmp);
-        if (tid == 0) {
-            *a.d_n_kept = static_cast<int64_t>(sum);
-            if (a.kept && static_cast<int64_t>(sum) > a.kept_cap)
-                report(a.err, SVT_ERRCLASS_CAPACITY, 2);
+    // accepted in the groups before this one, and in all of them: one barrier for both, four counts
+    // read at once
+    const bool some = g < groups && a.kept && a.group[g * kKeepStride] != 0;
+    if (blockIdx.x != 0 && !some) return;
+    uint64_t before = 0, sum = 0;
+    for (int64_t i0 = tid; i0 < groups; i0 += 4 * kKeepGroup) {
+        uint64_t c[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t i = i0 + e * kKeepGroup;
+            c[e] = i < groups ? a.group[i * kKeepStride] : 0;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sum += c[e];
+            before += i0 + e * kKeepGroup < g ? c[e] : 0;
         }
     }
-    if (g >= groups || !a.kept || a.group[g * kKeepStride] == 0) return;
-    uint64_t before = 0;
-    for (int64_t i = tid; i < g; i += kKeepGroup) before += a.group[i * kKeepStride];
-    const int64_t base =
-        static_cast<int64_t>(block_sum<uint64_t, kKeepGroup>(before, s_tmp));
+    before = scan64(before);
+    sum = scan64(sum);
+    if (lane_id() == kWaveSize - 1) s_sum[tid / kWaveSize] = make_ulonglong2(before, sum);
+    __syncthreads();
+    before = sum = 0;
+    for (int w = 0; w < kKeepGroup / kWaveSize; ++w) {
+        before += s_sum[w].x;
+        sum += s_sum[w].y;
+    }
+    const int64_t base = static_cast<int64_t>(before);
+    const bool over = a.kept && static_cast<int64_t>(sum) > a.kept_cap;
+    if (blockIdx.x == 0 && tid == 0) {
+        *a.d_n_kept = static_cast<int64_t>(sum);
+        if (over) report(a.err, SVT_ERRCLASS_CAPACITY, 2);
+    }
+    if (!some || (ONLY && over)) return;
     const int64_t u0 = g * kKeepGroup;
     UnitKeep mine{};
     if (u0 + tid < nu) mine = a.keep[u0 + tid];
