@@ -312,6 +312,29 @@ __device__ __forceinline__ uint32_t road_combos(uint32_t nh) {
     return nh_of(nh, 0) * nh_of(nh, 1) * nh_of(nh, 2) * nh_of(nh, 3) * nh_of(nh, 4);
 }
 
+// Who fits which of nu units: workgroup `block` of `grid` takes units lo .. hi - 1 first; then, with the
+// workgroups of the same dealer, what is left of p_lo .. p_hi - 1, `batch` units at a time.  Seven
+// eighths of the units are dealt out beforehand, in contiguous ranges, so that the record lines two
+// neighbouring units share are written from one compute unit; all of them where a wave has no second
+// one to take, or where the workgroups are too few to serve every dealer.
+struct UnitShare {
+    int64_t lo, hi, p_lo, p_hi, batch;
+    int dealer;
+};
+__host__ __device__ inline UnitShare unit_share(int64_t nu, int block, int grid) {
+    const int64_t fixed =
+        nu <= static_cast<int64_t>(grid) * kUnitWaves || grid < kDealers ? nu : nu - nu / 8;
+    const int64_t pool = nu - fixed;
+    UnitShare s;
+    s.lo = fixed * block / grid;
+    s.hi = fixed * (block + 1) / grid;
+    s.dealer = block % kDealers;
+    s.p_lo = fixed + pool * s.dealer / kDealers;
+    s.p_hi = fixed + pool * (s.dealer + 1) / kDealers;
+    s.batch = 1 + pool / (kDealers * 512);
+    return s;
+}
+
 // Units of a range when nu units are dealt to at most `ranges` of them: a multiple of the waves
 // of a workgroup.
 __host__ __device__ inline int64_t units_per_range(int64_t nu, int64_t ranges) {

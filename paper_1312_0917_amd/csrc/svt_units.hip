@@ -958,21 +958,15 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
     return u;
 }
 
-// The wave's units.  Seven eighths of them are dealt to the workgroups in contiguous ranges, so that
-// the record lines two neighbouring units share are written from one compute unit; the rest is
-// divided among the dealers and goes by ticket to the waves that finish first (one counter for all
-// of them would hand out a unit every 12 ns: 93 us for 7500 units, 51 with 32).  Slices past their unit's first come before
-// everything else, dealt out to the workgroups in turn.
+// The wave's units (unit_share).  The last eighth is divided among the dealers and goes by ticket to the
+// waves that finish first (one counter for all of them would hand out a unit every 12 ns: 93 us for
+// 7500 units, 51 with 32).  Slices past their unit's first come before everything else, dealt out to
+// the workgroups in turn.
 template <int REC, bool SLICED>
 __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, int64_t nu,
                                           int64_t per, int n_ranges, uint32_t extra) {
     const int wave = threadIdx.x / kWaveSize, lane = lane_id();
-    const int64_t fixed = nu <= static_cast<int64_t>(gridDim.x) * kUnitWaves ? nu : nu - nu / 8;
-    const int64_t lo = fixed * blockIdx.x / gridDim.x, hi = fixed * (blockIdx.x + 1) / gridDim.x;
-    const int dealer = static_cast<int>(blockIdx.x) % kDealers;
-    const int64_t pool = nu - fixed, p_lo = fixed + pool * dealer / kDealers,
-                  p_hi = fixed + pool * (dealer + 1) / kDealers;
-    const int64_t batch = 1 + pool / (kDealers * 512);
+    const UnitShare share = unit_share(nu, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
     const uint32_t slice_len = static_cast<uint32_t>(slice_combos(nu));
     const uint32_t my_extra =
         SLICED && extra > blockIdx.x ? (extra - blockIdx.x - 1) / gridDim.x + 1 : 0;
@@ -988,17 +982,17 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
                 if (SLICED && k < my_extra) {
                     u = find_extra(a, L, blockIdx.x + k * gridDim.x, nu, per, n_ranges, slice);
                 } else {
-                    u = lo + (k - my_extra);
-                    late = u >= hi;
+                    u = share.lo + (k - my_extra);
+                    late = u >= share.hi;
                 }
                 past = u + 1;
             }
             if (late) {
-                if (p_lo >= p_hi) break;
-                if (lane == 0) k = atomicAdd(a.ticket + dealer * kDealerStride, 1u);
-                u = p_lo + uni(k) * batch;
-                past = u + batch < p_hi ? u + batch : p_hi;
-                if (u >= p_hi) break;
+                if (share.p_lo >= share.p_hi) break;
+                if (lane == 0) k = atomicAdd(a.ticket + share.dealer * kDealerStride, 1u);
+                u = share.p_lo + uni(k) * share.batch;
+                past = u + share.batch < share.p_hi ? u + share.batch : share.p_hi;
+                if (u >= share.p_hi) break;
             }
         }
         int c = 0;
