@@ -207,8 +207,7 @@ svt_status svt_select(const svt_config *cfg, const svt_roads *roads, int64_t n_r
  * constants in LDS; with a kept list a third kernel writes it.  The word count is read on the
  * device from *d_n_words, so a graph that captured the call can be replayed for any batch up to
  * word_cap (at most 2^31 - 1 words; larger capacities are SVT_ERR_ARG, and svt_batch_workspace
- * returns -1 for them).  Words in page-locked host memory are read over the bus once where
- * the workspace has svt_batch_workspace bytes.
+ * returns -1 for them).  Words in page-locked host memory are read over the bus once.
  * flags: SVT_BATCH_GRAPH
  * asks for the cheapest way to repeat the pass on one stream.  It was a captured graph; since a
  * pass is two or three launches, launching them is (a replay costs the host 18 us where they cost

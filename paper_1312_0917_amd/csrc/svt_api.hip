@@ -568,13 +568,12 @@ svt_status process_batch(const svt_fconst *bank, const svt_config *cfg, const sv
         const svt_status st = static_workspace(&d_work);
         if (st != SVT_OK) return st;
         work_bytes = limit;
-    } else if (!d_work ||
-               work_bytes < batch_bytes(word_cap, road_cap, combo_cap, false) ||
+    } else if (!d_work || work_bytes < svt_batch_workspace(word_cap, road_cap, combo_cap, &t) ||
                !aligned(d_work, kAlign)) {
         return SVT_ERR_ARG;
     }
-    // words in host memory are read once over the bus: the counting kernel leaves a copy, where
-    // the workspace has room for one (else both kernels read them in place)
+    // words in host memory are read once over the bus: the counting kernel leaves a copy, where the
+    // static workspace has room for one too (else both kernels read them in place)
     const bool copy = work_bytes >= batch_bytes(word_cap, road_cap, combo_cap, true);
     const int cus = num_cus();
     if (cus <= 0) return SVT_ERR_HIP;
