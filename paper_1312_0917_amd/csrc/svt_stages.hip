@@ -108,8 +108,13 @@ __global__ __launch_bounds__(kRoadBlock) void k_combo_begin(svt_roads roads, Siz
 // for 1500 uneven events, now 19; 51 and 20 us for 3000 events of 64 roads, whose list is 49 MB;
 // tiles of 4096 and 8192 take 20 and 23).  k_combo_begin has left the road of the tile's first
 // combination in combo_road; the tile's roads are staged in LDS, up to kListRoads at a time.
+//
+// The grid is what the chip holds, and its workgroups take tiles in turn: the list's capacity says
+// nothing about its length (400 roads listed by a caller with room for 4e8 combinations: 52 us with a
+// workgroup per tile of the capacity, 21 now).
 constexpr int kListRoads = 512;
 constexpr int kListThreads = 256;
+constexpr int kListGrid = 2048;
 
 __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, int64_t n_roads,
                                                               const int64_t *d_n_combos,
@@ -128,106 +133,108 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
                         reinterpret_cast<uintptr_t>(combo_hits)) & 15) == 0;
     const int64_t total = *d_n_combos;
     if (total > combo_cap) return;
-    const int64_t c_lo = static_cast<int64_t>(blockIdx.x) * kListTile;
-    if (c_lo >= total) return;
-    const int len = static_cast<int>(total - c_lo < kListTile ? total - c_lo : kListTile);
-    if (threadIdx.x == 0) {
-        int64_t r;
-        if (combo_road) {
-            r = combo_road[c_lo];
-        } else {  // last road that starts at or before the tile
-            int64_t lo = 0, hi = n_roads - 1;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi + 1) >> 1;
-                if (roads.combo_begin[mid] <= c_lo) lo = mid; else hi = mid - 1;
+    for (int64_t c_lo = static_cast<int64_t>(blockIdx.x) * kListTile; c_lo < total;
+         c_lo += static_cast<int64_t>(gridDim.x) * kListTile) {
+        const int len = static_cast<int>(total - c_lo < kListTile ? total - c_lo : kListTile);
+        if (threadIdx.x == 0) {
+            int64_t r;
+            if (combo_road) {
+                r = combo_road[c_lo];
+            } else {  // last road that starts at or before the tile
+                int64_t lo = 0, hi = n_roads - 1;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi + 1) >> 1;
+                    if (roads.combo_begin[mid] <= c_lo) lo = mid; else hi = mid - 1;
+                }
+                r = lo;
             }
-            r = lo;
-        }
-        s_first = r;
-    }
-    __syncthreads();
-    int64_t r0 = s_first;
-    for (int done = 0; done < len; r0 += kListRoads) {
-        const int nr = static_cast<int>(n_roads - r0 < kListRoads ? n_roads - r0 : kListRoads);
-        if (nr <= 0) break;  // (never on a consistent table)
-        for (int j = threadIdx.x; j < nr; j += kListThreads) {
-            const int64_t rel = roads.combo_begin[r0 + j] - c_lo;
-            const uint32_t nh = roads.nhits[r0 + j];
-            s_begin[j] = static_cast<int32_t>(rel < kListTile ? rel : kListTile);
-            s_nh[j] = nh;
-            if (j == nr - 1) {
-                const int64_t e = rel + roads.ncombo[r0 + j];
-                s_end = static_cast<int32_t>(e < len ? e : len);
-            }
+            s_first = r;
         }
         __syncthreads();
-        const int end = s_end;
-        // four consecutive combinations per lane: one search, then steps
-        for (int i0 = (done & ~3) + 4 * static_cast<int>(threadIdx.x); i0 < end;
-             i0 += 4 * kListThreads) {
-            const int first = i0 > done ? i0 : done;
-            int lo = 0, hi = nr - 1;  // last road with begin <= first (it has combinations)
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_begin[mid] <= first) lo = mid; else hi = mid - 1;
-            }
-            uint32_t nh = s_nh[lo], digits = 0;
-            uint32_t k = static_cast<uint32_t>(first - s_begin[lo]);
-#pragma unroll
-            for (int l = SVT_N_LAYERS - 1; l > 0; --l) {  // layer 0 most significant
-                const uint32_t nl = nh_of(nh, l);
-                // floor(k / nl) for k < 2^15, nl <= 8 (see div_small)
-                const uint32_t q = div_small(k, s_magic[nl]);
-                digits |= (k - q * nl) << (4 * l);
-                k = q;
-            }
-            digits |= k;
-            int32_t rd[4] = {0, 0, 0, 0};
-            uint32_t ht[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = i0 + e;
-                if (i < first || i >= end) continue;
-                rd[e] = static_cast<int32_t>(r0 + lo);
-                ht[e] = digits;
-                // the next combination: carry from layer 4 to layer 0, then the next road that
-                // has combinations
-                digits += 1u << 16;
-                bool past = false;
-#pragma unroll
-                for (int l = SVT_N_LAYERS - 1; l >= 0; --l)
-                    if (nh_of(digits, l) == nh_of(nh, l)) {
-                        digits &= ~(0xFu << (4 * l));
-                        if (l > 0) digits += 1u << (4 * (l - 1));
-                        past = l == 0;
-                    } else {
-                        break;
-                    }
-                if (past && i + 1 < end) {
-                    do ++lo;
-                    while (lo < nr - 1 && s_begin[lo + 1] <= i + 1);
-                    nh = s_nh[lo];
-                    digits = 0;
+        int64_t r0 = s_first;
+        for (int done = 0; done < len; r0 += kListRoads) {
+            const int nr = static_cast<int>(n_roads - r0 < kListRoads ? n_roads - r0 : kListRoads);
+            if (nr <= 0) break;  // (never on a consistent table)
+            for (int j = threadIdx.x; j < nr; j += kListThreads) {
+                const int64_t rel = roads.combo_begin[r0 + j] - c_lo;
+                const uint32_t nh = roads.nhits[r0 + j];
+                s_begin[j] = static_cast<int32_t>(rel < kListTile ? rel : kListTile);
+                s_nh[j] = nh;
+                if (j == nr - 1) {
+                    const int64_t e = rel + roads.ncombo[r0 + j];
+                    s_end = static_cast<int32_t>(e < len ? e : len);
                 }
             }
-            if (wide && i0 >= done && i0 + 4 <= end) {
-                if (combo_road)
-                    *reinterpret_cast<int4 *>(combo_road + c_lo + i0) =
-                        make_int4(rd[0], rd[1], rd[2], rd[3]);
-                if (combo_hits)
-                    *reinterpret_cast<uint4 *>(combo_hits + c_lo + i0) =
-                        make_uint4(ht[0], ht[1], ht[2], ht[3]);
-            } else {
+            __syncthreads();
+            const int end = s_end;
+            // four consecutive combinations per lane: one search, then steps
+            for (int i0 = (done & ~3) + 4 * static_cast<int>(threadIdx.x); i0 < end;
+                 i0 += 4 * kListThreads) {
+                const int first = i0 > done ? i0 : done;
+                int lo = 0, hi = nr - 1;  // last road with begin <= first (it has combinations)
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (s_begin[mid] <= first) lo = mid; else hi = mid - 1;
+                }
+                uint32_t nh = s_nh[lo], digits = 0;
+                uint32_t k = static_cast<uint32_t>(first - s_begin[lo]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (i0 + e >= first && i0 + e < end) {
-                        if (combo_road) combo_road[c_lo + i0 + e] = rd[e];
-                        if (combo_hits) combo_hits[c_lo + i0 + e] = ht[e];
+                for (int l = SVT_N_LAYERS - 1; l > 0; --l) {  // layer 0 most significant
+                    const uint32_t nl = nh_of(nh, l);
+                    // floor(k / nl) for k < 2^15, nl <= 8 (see div_small)
+                    const uint32_t q = div_small(k, s_magic[nl]);
+                    digits |= (k - q * nl) << (4 * l);
+                    k = q;
+                }
+                digits |= k;
+                int32_t rd[4] = {0, 0, 0, 0};
+                uint32_t ht[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = i0 + e;
+                    if (i < first || i >= end) continue;
+                    rd[e] = static_cast<int32_t>(r0 + lo);
+                    ht[e] = digits;
+                    // the next combination: carry from layer 4 to layer 0, then the next road that
+                    // has combinations
+                    digits += 1u << 16;
+                    bool past = false;
+#pragma unroll
+                    for (int l = SVT_N_LAYERS - 1; l >= 0; --l)
+                        if (nh_of(digits, l) == nh_of(nh, l)) {
+                            digits &= ~(0xFu << (4 * l));
+                            if (l > 0) digits += 1u << (4 * (l - 1));
+                            past = l == 0;
+                        } else {
+                            break;
+                        }
+                    if (past && i + 1 < end) {
+                        do ++lo;
+                        while (lo < nr - 1 && s_begin[lo + 1] <= i + 1);
+                        nh = s_nh[lo];
+                        digits = 0;
                     }
+                }
+                if (wide && i0 >= done && i0 + 4 <= end) {
+                    if (combo_road)
+                        *reinterpret_cast<int4 *>(combo_road + c_lo + i0) =
+                            make_int4(rd[0], rd[1], rd[2], rd[3]);
+                    if (combo_hits)
+                        *reinterpret_cast<uint4 *>(combo_hits + c_lo + i0) =
+                            make_uint4(ht[0], ht[1], ht[2], ht[3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (i0 + e >= first && i0 + e < end) {
+                            if (combo_road) combo_road[c_lo + i0 + e] = rd[e];
+                            if (combo_hits) combo_hits[c_lo + i0 + e] = ht[e];
+                        }
+                }
             }
+            done = end > done ? end : done;
+            __syncthreads();
         }
-        done = end > done ? end : done;
-        __syncthreads();
+        __syncthreads();  // s_first is written again for the next tile
     }
 }
 
@@ -828,8 +835,8 @@ hipError_t launch_materialize(const svt_roads &roads, int64_t n_roads, const int
                               int64_t combo_cap, int32_t *combo_road, uint32_t *combo_hits,
                               uint64_t *err, hipStream_t s) {
     if (n_roads <= 0 || (!combo_road && !combo_hits)) return hipSuccess;
-    const int64_t g = (combo_cap + kListTile - 1) / kListTile;
-    if (g < 1) return hipSuccess;
+    if (combo_cap < 1) return hipSuccess;
+    const int64_t g = clamp_grid((combo_cap - 1) / kListTile + 1, kListGrid);
     hipLaunchKernelGGL(k_materialize, dim3(static_cast<unsigned>(g)), dim3(kListThreads), 0, s,
                        roads, n_roads, d_n_combos, combo_cap, combo_road, combo_hits, err);
     return hipGetLastError();

@@ -1,0 +1,61 @@
+"""The combine stage's list, for tables and capacities that the generator's batches do not have."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1312_0917_amd import _lib as L
+from paper_1312_0917_amd import pipeline as P
+
+pytestmark = pytest.mark.gpu
+
+
+def expected(nh):
+    """ncombo, combo_begin, combo_road, combo_hits of roads with hits nh (n, 5), by definition."""
+    nh = np.asarray(nh, np.int64)
+    n = nh.prod(1)
+    begin = np.cumsum(n) - n
+    road = np.repeat(np.arange(len(nh)), n)
+    k = np.arange(int(n.sum())) - begin[road]
+    hits = np.zeros(len(k), np.int64)
+    for l in range(4, -1, -1):  # layer 0 most significant
+        hits |= (k % nh[road, l]) << (4 * l)
+        k = k // nh[road, l]
+    return n, begin, road, hits
+
+
+def combine(nh, cap=None, only=None):
+    """svt_combine over a table that the caller filled; `cap`: the capacity it states."""
+    nh = np.asarray(nh, np.int64)
+    n, begin, road, hits = expected(nh)
+    total = int(n.sum())
+    table = P._alloc_roads(len(nh), "cuda")
+    packed = sum(nh[:, l] << (4 * l) for l in range(5))
+    table["nhits"].copy_(torch.from_numpy(packed.astype(np.uint32).view(np.int32)))
+    got_road = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    got_hits = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    d_n = torch.zeros(1, dtype=torch.int64, device="cuda")
+    err = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+    work = P._ws(L.svt_combine_workspace(len(nh)), "cuda")
+    st = L.svt_combine(table, len(nh), L.make_config(), None if only == "hits" else got_road,
+                       None if only == "road" else got_hits, total if cap is None else cap, d_n,
+                       err, work)
+    assert st == L.SVT_OK
+    torch.cuda.synchronize()
+    assert int(d_n) == total and int(err) == -1
+    assert np.array_equal(table["ncombo"][:len(nh)].cpu().numpy(), n)
+    assert np.array_equal(table["combo_begin"][:len(nh)].cpu().numpy(), begin)
+    if only != "hits":
+        assert np.array_equal(got_road.cpu().numpy(), road)
+    if only != "road":
+        assert np.array_equal(got_hits.cpu().numpy(), hits)
+
+
+@pytest.mark.parametrize("only", [None, "road", "hits"])
+@pytest.mark.parametrize("cap", [None, 10**7, 2**40, 2**63 - 1])
+def test_the_capacity_may_be_any_size(cap, only):
+    """A caller's capacity bounds the list and does not shape the launch: 2^63 - 1 says "no bound"."""
+    combine(np.random.default_rng(1).integers(1, 4, size=(500, 5)), cap, only)
+
+
+def test_more_tiles_than_workgroups():
+    combine(np.full((5000, 5), 4))  # 2500 tiles of 2048 combinations
