@@ -124,11 +124,11 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
                                                               uint64_t *err) {
     __shared__ int32_t s_begin[kListRoads];  // first combination, from the tile's first
     __shared__ uint32_t s_nh[kListRoads];
-    __shared__ uint32_t s_magic[16];
+    __shared__ float s_inverse[16];
     __shared__ int64_t s_first;
     __shared__ int32_t s_end;
     if (has_error(err)) return;
-    if (threadIdx.x < 16) s_magic[threadIdx.x] = magic_of(threadIdx.x ? threadIdx.x : 1u);
+    if (threadIdx.x < 16) s_inverse[threadIdx.x] = 1.0f / static_cast<float>(threadIdx.x);
     const bool wide = ((reinterpret_cast<uintptr_t>(combo_road) |
                         reinterpret_cast<uintptr_t>(combo_hits)) & 15) == 0;
     const int64_t total = *d_n_combos;
@@ -178,11 +178,17 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
                 }
                 uint32_t nh = s_nh[lo], digits = 0;
                 uint32_t k = static_cast<uint32_t>(first - s_begin[lo]);
+                // A caller's table may hold up to 15 hits a layer, 15^5 combinations a road.  k is below
+                // nl * 15^4, so the quotient is below 2^16, k / nl in float is within 2^-7 of it, and a
+                // quotient that is no whole number is at least 1/15 below the next: with 1/32 added it
+                // rounds down to floor(k / nl).  (Three instructions; the 24-bit multiplication of
+                // div_small holds for k < 2^15 only, a 32-bit one in its place costs 6.2e6
+                // combinations 1 us of 31.)
 #pragma unroll
                 for (int l = SVT_N_LAYERS - 1; l > 0; --l) {  // layer 0 most significant
                     const uint32_t nl = nh_of(nh, l);
-                    // floor(k / nl) for k < 2^15, nl <= 8 (see div_small)
-                    const uint32_t q = div_small(k, s_magic[nl]);
+                    const uint32_t q = static_cast<uint32_t>(
+                        __fmaf_rn(static_cast<float>(k), s_inverse[nl], 0.03125f));
                     digits |= (k - q * nl) << (4 * l);
                     k = q;
                 }

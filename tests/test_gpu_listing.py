@@ -59,3 +59,11 @@ def test_the_capacity_may_be_any_size(cap, only):
 
 def test_more_tiles_than_workgroups():
     combine(np.full((5000, 5), 4))  # 2500 tiles of 2048 combinations
+
+
+@pytest.mark.parametrize("only", [None, "road", "hits"])
+def test_tables_with_up_to_15_hits_on_a_layer(only):
+    """A table that the caller filled may hold whatever 4 bits a layer can: 15^5 combinations a road."""
+    nh = np.random.default_rng(2).integers(1, 16, size=(24, 5))
+    nh[3], nh[11], nh[17] = 15, [9, 15, 15, 15, 1], [1, 15, 9, 1, 15]
+    combine(nh, None, only)
