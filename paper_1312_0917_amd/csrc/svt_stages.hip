@@ -109,13 +109,15 @@ __global__ __launch_bounds__(kRoadBlock) void k_combo_begin(svt_roads roads, Siz
 // tiles of 4096 and 8192 take 20 and 23).  k_combo_begin has left the road of the tile's first
 // combination in combo_road; the tile's roads are staged in LDS, up to kListRoads at a time.
 //
-// The grid is what the chip holds, and its workgroups take tiles in turn: the list's capacity says
-// nothing about its length (400 roads listed by a caller with room for 4e8 combinations: 52 us with a
-// workgroup per tile of the capacity, 21 now).
+// The list's capacity says nothing about its length: up to kListGrid tiles of it get a workgroup each
+// (16.8e6 combinations), above that (LOOP) the workgroups take the tiles in turn.  400 roads listed by a
+// caller with room for 4e8 combinations take 21 us, with a workgroup per tile of the capacity 52; the
+// loop costs 1 us of 20 where a tile each would do.
 constexpr int kListRoads = 512;
 constexpr int kListThreads = 256;
-constexpr int kListGrid = 2048;
+constexpr int kListGrid = 8192;
 
+template <bool LOOP>
 __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, int64_t n_roads,
                                                               const int64_t *d_n_combos,
                                                               int64_t combo_cap,
@@ -240,6 +242,7 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
             done = end > done ? end : done;
             __syncthreads();
         }
+        if (!LOOP) break;
         __syncthreads();  // s_first is written again for the next tile
     }
 }
@@ -842,9 +845,14 @@ hipError_t launch_materialize(const svt_roads &roads, int64_t n_roads, const int
                               uint64_t *err, hipStream_t s) {
     if (n_roads <= 0 || (!combo_road && !combo_hits)) return hipSuccess;
     if (combo_cap < 1) return hipSuccess;
-    const int64_t g = clamp_grid((combo_cap - 1) / kListTile + 1, kListGrid);
-    hipLaunchKernelGGL(k_materialize, dim3(static_cast<unsigned>(g)), dim3(kListThreads), 0, s,
-                       roads, n_roads, d_n_combos, combo_cap, combo_road, combo_hits, err);
+    const int64_t tiles = (combo_cap - 1) / kListTile + 1;
+    if (tiles <= kListGrid)
+        hipLaunchKernelGGL(k_materialize<false>, dim3(static_cast<unsigned>(tiles)),
+                           dim3(kListThreads), 0, s, roads, n_roads, d_n_combos, combo_cap,
+                           combo_road, combo_hits, err);
+    else
+        hipLaunchKernelGGL(k_materialize<true>, dim3(kListGrid), dim3(kListThreads), 0, s, roads,
+                           n_roads, d_n_combos, combo_cap, combo_road, combo_hits, err);
     return hipGetLastError();
 }
 

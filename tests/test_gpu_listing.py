@@ -57,8 +57,12 @@ def test_the_capacity_may_be_any_size(cap, only):
     combine(np.random.default_rng(1).integers(1, 4, size=(500, 5)), cap, only)
 
 
-def test_more_tiles_than_workgroups():
-    combine(np.full((5000, 5), 4))  # 2500 tiles of 2048 combinations
+@pytest.mark.parametrize("n,cap", [(5000, None), (5000, 8192 * 2048), (5000, 8192 * 2048 + 1),
+                                   (17000, None)])
+def test_a_workgroup_per_tile_or_tiles_in_turn(n, cap):
+    """2500 tiles of 2048 combinations at the largest capacity with a workgroup each and one above it,
+    and 8500 tiles, more than the workgroups that take them in turn."""
+    combine(np.full((n, 5), 4), cap)
 
 
 @pytest.mark.parametrize("only", [None, "road", "hits"])
