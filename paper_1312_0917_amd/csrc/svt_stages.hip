@@ -113,9 +113,61 @@ __global__ __launch_bounds__(kRoadBlock) void k_combo_begin(svt_roads roads, Siz
 // (16.8e6 combinations), above that (LOOP) the workgroups take the tiles in turn.  400 roads listed by a
 // caller with room for 4e8 combinations take 21 us, with a workgroup per tile of the capacity 52; the
 // loop costs 1 us of 20 where a tile each would do.
+//
+// Where kListRoads roads have fewer than kListSparse combinations, nearly all of them none, the rest of
+// the tile is not staged: a lane searches the table for its combinations' roads.  The stage for 1e6 roads
+// of which one in N has 32 combinations, staged throughout / so: N = 5000 720 / 27 us, 500 156 / 27,
+// 100 47 / 28, 50 37 / 30; 20 has 800 combinations per 512 roads and takes 30 staged.
 constexpr int kListRoads = 512;
 constexpr int kListThreads = 256;
+constexpr int kListSparse = 400;
 constexpr int kListGrid = 8192;
+
+// The last road of lo .. hi that starts at or before combination c (lo does).  Seven probes at a time:
+// one waits for memory as long as seven do.
+__device__ int64_t road_of(const int64_t *__restrict__ begin, int64_t lo, int64_t hi, int64_t c) {
+    while (lo < hi) {
+        const int64_t step = (hi - lo) / 8 + 1;
+        int64_t b[7];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+            const int64_t p = lo + (q + 1) * step;
+            b[q] = p <= hi ? begin[p] : INT64_MAX;
+        }
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) n += b[q] <= c ? 1 : 0;
+        lo += n * step;
+        hi = lo + step - 1 < hi ? lo + step - 1 : hi;
+    }
+    return lo;
+}
+
+// Combinations c_lo .. c_lo + len - 1 (at most kListTile), which belong to roads r0 .. last.
+__device__ __forceinline__ void list_sparse(const svt_roads &roads, int64_t r0, int64_t last,
+                                         int64_t c_lo, int len, int32_t *combo_road,
+                                         uint32_t *combo_hits) {
+    constexpr int kPer = kListTile / kListThreads;
+    int i = kPer * static_cast<int>(threadIdx.x);
+    const int stop = i + kPer < len ? i + kPer : len;
+    while (i < stop) {
+        r0 = road_of(roads.combo_begin, r0, last, c_lo + i);
+        const uint32_t nh = roads.nhits[r0];
+        uint32_t at = static_cast<uint32_t>(c_lo + i - roads.combo_begin[r0]), n = 1;
+#pragma unroll
+        for (int l = 0; l < SVT_N_LAYERS; ++l) n *= nh_of(nh, l);
+        for (; i < stop && at < n; ++i, ++at) {
+            uint32_t k = at, digits = 0;
+            for (int l = SVT_N_LAYERS - 1; l >= 0; --l) {  // layer 0 most significant
+                const uint32_t nl = nh_of(nh, l);
+                digits |= (k % nl) << (4 * l);
+                k /= nl;
+            }
+            if (combo_road) combo_road[c_lo + i] = static_cast<int32_t>(r0);
+            if (combo_hits) combo_hits[c_lo + i] = digits;
+        }
+    }
+}
 
 template <bool LOOP>
 __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, int64_t n_roads,
@@ -138,20 +190,8 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
     for (int64_t c_lo = static_cast<int64_t>(blockIdx.x) * kListTile; c_lo < total;
          c_lo += static_cast<int64_t>(gridDim.x) * kListTile) {
         const int len = static_cast<int>(total - c_lo < kListTile ? total - c_lo : kListTile);
-        if (threadIdx.x == 0) {
-            int64_t r;
-            if (combo_road) {
-                r = combo_road[c_lo];
-            } else {  // last road that starts at or before the tile
-                int64_t lo = 0, hi = n_roads - 1;
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi + 1) >> 1;
-                    if (roads.combo_begin[mid] <= c_lo) lo = mid; else hi = mid - 1;
-                }
-                r = lo;
-            }
-            s_first = r;
-        }
+        if (threadIdx.x == 0)  // the road of the tile's first combination
+            s_first = combo_road ? combo_road[c_lo] : road_of(roads.combo_begin, 0, n_roads - 1, c_lo);
         __syncthreads();
         int64_t r0 = s_first;
         for (int done = 0; done < len; r0 += kListRoads) {
@@ -239,7 +279,13 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
                         }
                 }
             }
-            done = end > done ? end : done;
+            const int more = end > done ? end - done : 0;
+            done += more;
+            if (done < len && more < kListSparse && r0 + nr < n_roads) {
+                list_sparse(roads, r0 + nr, n_roads - 1, c_lo + done, len - done, combo_road,
+                            combo_hits);
+                break;
+            }
             __syncthreads();
         }
         if (!LOOP) break;

@@ -71,3 +71,47 @@ def test_tables_with_up_to_15_hits_on_a_layer(only):
     nh = np.random.default_rng(2).integers(1, 16, size=(24, 5))
     nh[3], nh[11], nh[17] = 15, [9, 15, 15, 15, 1], [1, 15, 9, 1, 15]
     combine(nh, None, only)
+
+
+def sparse(n, every, rng):
+    """n roads of which one in `every` has combinations, the first of them after a run without."""
+    nh = np.zeros((n, 5), np.int64)
+    nh[:, 2] = 1
+    at = np.arange(every - 1, n, every)
+    nh[at] = rng.integers(1, 5, size=(len(at), 5))
+    return nh
+
+
+@pytest.mark.parametrize("n", [512, 513, 767, 768, 769, 1025, 70000, 300001])
+@pytest.mark.parametrize("every", [500, 511, 513, 1000, 66000])
+def test_runs_of_roads_without_combinations(n, every):
+    if n >= every:
+        combine(sparse(n, every, np.random.default_rng(n + every)))
+
+
+def test_a_run_of_roads_without_combinations_costs_little():
+    """The list of a million roads of which 200 have combinations, against that of those 200 alone: by
+    steps of 512 roads it took 35 times as long, in one workgroup."""
+    def best_of(nh):
+        n = len(nh)
+        table = P._alloc_roads(n, "cuda")
+        packed = sum(nh[:, l] << (4 * l) for l in range(5))
+        table["nhits"].copy_(torch.from_numpy(packed.astype(np.uint32).view(np.int32)))
+        total = int(nh.prod(1).sum())
+        road, hits = (torch.empty(total, dtype=torch.int32, device="cuda") for _ in range(2))
+        d_n = torch.zeros(1, dtype=torch.int64, device="cuda")
+        err = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+        work = P._ws(L.svt_combine_workspace(n), "cuda")
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                L.svt_combine(table, n, L.make_config(), road, hits, total, d_n, err, work)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        assert int(err) == -1
+        return min(times)
+    nh = sparse(10**6, 5000, np.random.default_rng(3))
+    assert best_of(nh) < 8 * best_of(nh[nh.prod(1) > 0])
