@@ -173,8 +173,8 @@ svt_status svt_combine(const svt_roads *roads, int64_t n_roads, const svt_config
                        hipStream_t stream);
 
 /* Stage 3, fit (section II, the scalar-product equation): one fit per listed combination.
- * bank[n_sets] device array of svt_fconst; hit_coord[n_hits] from svt_unpack; combo_road /
- * combo_hits[n_combos] from svt_combine.  Writes out->p0..p2, out->chi2 and, when non-NULL,
+ * bank[n_sets] device array of svt_fconst; hit_coord[n_hits] from svt_unpack, or any int16 (the sums
+ * are exact for all of them); combo_road / combo_hits[n_combos] from svt_combine.  Writes out->p0..p2, out->chi2 and, when non-NULL,
  * out->c0..c2.  Indices outside the road table or the hit array are reported in *d_err (class
  * INDEX, index = combination) and that combination is skipped. */
 svt_status svt_fit(const svt_fconst *bank, const svt_config *cfg, const svt_roads *roads,

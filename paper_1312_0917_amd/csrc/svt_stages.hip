@@ -299,8 +299,10 @@ __global__ __launch_bounds__(kListThreads) void k_materialize(svt_roads roads, i
 // gathering its own from memory took 86 us at 6.2e6 combinations, now 47 for 246 MB: 54 with 256
 // threads that take 8 each, 61 with 64-bit indices checked one by one).  The constant bank is packed
 // into LDS once per workgroup, in the pairs of the 16-bit dot products; with the offset split as
-// q = qh * 2^s + ql every sum stays inside int32 (svt_fit.h), where 64-bit products ran at a
-// quarter of the rate.
+// q = qh * 2^s + ql every sum of 13-bit coordinates stays inside int32 (svt_fit.h), where 64-bit
+// products ran at a quarter of the rate.  A caller's coordinates may be any int16: they are looked at
+// when staged, and a tile with one outside 13 bits is summed in 64 bits (3000 events
+// of 64 roads 45.5 us before this check and 46.3 with it, 2 more with every tile so).
 constexpr int kFitThreads = 512;
 constexpr int kFitLane = 4;
 constexpr int kFitTile = kFitThreads * kFitLane;
@@ -319,6 +321,9 @@ struct PlainRoad {
     int32_t set;
 };
 
+// c ^ (c >> 15) of a 13-bit coordinate is at most this
+constexpr int32_t kInt13 = 4095;
+
 __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
     const svt_fconst *__restrict__ bank, svt_config cfg, svt_roads roads, int64_t n_roads,
     const int16_t *__restrict__ hit_coord, int64_t n_hits, const int32_t *__restrict__ combo_road,
@@ -326,7 +331,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
     __shared__ PlainSet s_bank[256];
     __shared__ PlainRoad s_road[kFitRoads];
     __shared__ int16_t s_coord[kFitCoords + 1];  // (one past the end is read for a layer without hits)
-    __shared__ int32_t s_lo[2], s_hi[2];
+    __shared__ int32_t s_lo[2], s_hi[2], s_wide[2];  // (s_wide: a staged coordinate needs 64-bit sums)
     const int tid = threadIdx.x;
     const int32_t shift = cfg.shift;
     const uint32_t qlmask = (1u << shift) - 1u;
@@ -342,6 +347,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
     if (tid < 2) {
         s_lo[tid] = INT32_MAX;
         s_hi[tid] = -1;
+        s_wide[tid] = 0;
     }
     __syncthreads();
     int par = 0;
@@ -377,6 +383,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
         if (tid == 0) {  // the other tile's bounds, for its next turn
             s_lo[par ^ 1] = INT32_MAX;
             s_hi[par ^ 1] = -1;
+            s_wide[par ^ 1] = 0;
         }
         if (span > 0) {
             // coordinates staged: w_lo .. w_lo + wn - 1
@@ -386,7 +393,13 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
             if (w_lo >= 0 && w_lo < n_hits && w_hi > w_lo) {
                 const int64_t stop = w_hi < n_hits ? w_hi : n_hits;
                 wn = static_cast<int>(stop - w_lo < kFitCoords ? stop - w_lo : kFitCoords);
-                for (int j = tid; j < wn; j += kFitThreads) s_coord[j] = hit_coord[w_lo + j];
+                int32_t past = 0;
+                for (int j = tid; j < wn; j += kFitThreads) {
+                    const int16_t c = hit_coord[w_lo + j];
+                    s_coord[j] = c;
+                    past |= c ^ (c >> 15);
+                }
+                if (past > kInt13) s_wide[par] = 1;
             }
             for (int j = tid; j < span; j += kFitThreads) {
                 const int64_t q = lo + j, at = roads.hit_begin[q] - w_lo;
@@ -400,6 +413,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
             }
         }
         __syncthreads();
+        const bool wide_tile = __builtin_amdgcn_readfirstlane(s_wide[par]) != 0;
 #pragma unroll
         for (int e = 0; e < kFitLane; ++e) {
             const int64_t i = t0 + e * kFitThreads + tid;
@@ -407,7 +421,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
             if (r[e] < 0 || r[e] >= n_roads) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
             PlainRoad rd{-1, 0, 0};
             if (span > 0) rd = s_road[r[e] - lo];
-            bool ok = true;
+            bool ok = true, wide = wide_tile;
             int32_t x[SVT_N_LAYERS];
             if (rd.at >= 0) {
                 int32_t off = rd.at;
@@ -428,21 +442,36 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_plain(
                     const int64_t idx = off + d;
                     ok &= d < nl && idx >= 0 && idx < n_hits;
                     x[l] = ok ? hit_coord[idx] : 0;
+                    wide |= (x[l] ^ (x[l] >> 15)) > kInt13;
                     off += nl;
                 }
             }
             if (!ok) { report(err, SVT_ERRCLASS_INDEX, i); continue; }
             const PlainSet &F = s_bank[rd.set];
-            const int32_t x01 = pack16(x[0], x[1]), x23 = pack16(x[2], x[3]);
             int32_t v[6];
+            if (__builtin_amdgcn_ballot_w64(wide) == 0) {
+                const int32_t x01 = pack16(x[0], x[1]), x23 = pack16(x[2], x[3]);
 #pragma unroll
-            for (int j = 0; j < 6; ++j) {
-                const uint4 w = F.row[j];
-                int32_t acc = dot2(static_cast<int32_t>(w.x), x01,
-                                   static_cast<int32_t>(w.w & qlmask));
-                acc = dot2(static_cast<int32_t>(w.y), x23, acc);
-                acc = dot2(static_cast<int32_t>(w.z), x[4], acc);
-                v[j] = (acc >> shift) + (static_cast<int32_t>(w.w) >> shift);
+                for (int j = 0; j < 6; ++j) {
+                    const uint4 w = F.row[j];
+                    int32_t acc = dot2(static_cast<int32_t>(w.x), x01,
+                                       static_cast<int32_t>(w.w & qlmask));
+                    acc = dot2(static_cast<int32_t>(w.y), x23, acc);
+                    acc = dot2(static_cast<int32_t>(w.z), x[4], acc);
+                    v[j] = (acc >> shift) + (static_cast<int32_t>(w.w) >> shift);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const uint4 w = F.row[j];
+                    int64_t acc = static_cast<int32_t>(w.w);
+                    acc += static_cast<int64_t>(static_cast<int16_t>(w.x)) * x[0];
+                    acc += static_cast<int64_t>(static_cast<int16_t>(w.x >> 16)) * x[1];
+                    acc += static_cast<int64_t>(static_cast<int16_t>(w.y)) * x[2];
+                    acc += static_cast<int64_t>(static_cast<int16_t>(w.y >> 16)) * x[3];
+                    acc += static_cast<int64_t>(static_cast<int16_t>(w.z)) * x[4];
+                    v[j] = static_cast<int32_t>(acc >> shift);
+                }
             }
             out.p0[i] = v[0];
             out.p1[i] = v[1];
