@@ -54,10 +54,16 @@ struct alignas(16) SliceAcc {
 // uneven ones (512 bytes, where the workspace has no more: 4 and 9 in 100).
 struct UnitKeep {
     uint32_t count;   // | kKeepSearch
-    uint32_t roads;
+    uint32_t size;    // roads (at most 256) | combinations (at most 2.4e5) << kKeepRoadBits
     uint64_t combo, road;  // the unit's first of either
 };
 constexpr uint32_t kKeepSearch = 1u << 31;
+constexpr int kKeepRoadBits = 9;
+// Accept flags that a workgroup of k_unit_keep goes through at a time, of a unit that is searched: 16 a
+// thread.  A unit of the largest roads has 2e5, and at an open cut all of them set: with one workgroup
+// for all of a unit's, a pass over 1000 uneven events, every combination accepted, took 562 us, 1050
+// kept-only (167 and 379 now; scan, compaction and refit of the flat list had taken 406 and 570).
+constexpr int kKeepFlags = 4096;
 constexpr int kKeepSlots = 1024, kKeepSlotsLess = 512;  // bytes per unit
 constexpr int kKeepGroup = 256;   // units a workgroup of k_unit_keep takes, with a common count,
 constexpr int kKeepStride = 16;   // a 128-byte line apart: every unit adds to one (side by side

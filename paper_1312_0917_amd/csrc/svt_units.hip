@@ -924,7 +924,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
             __hip_atomic_fetch_add(&k->count, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else
             k->count = kept | (kept > most ? kKeepSearch : 0u);
-        k->roads = nr;
+        k->size = nr | (c_run << kKeepRoadBits);
         k->combo = static_cast<uint64_t>(CB0);
         k->road = static_cast<uint64_t>(R0);
         __hip_atomic_fetch_add(in_memory(L.args.group) + u / kKeepGroup * kKeepStride,
@@ -1182,7 +1182,7 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     __shared__ uint32_t s_quick[kKeepGroup];  // those of them that wait in slots
     __shared__ uint64_t s_first[kKeepGroup];  // the unit's first combination
     __shared__ int32_t s_cb[kKeepGroup];      // a searched unit's roads: first combination
-    __shared__ uint8_t s_list[kKeepGroup];    // the units to be searched
+    __shared__ uint16_t s_part[kKeepGroup];   // parts of kKeepFlags flags to be searched before the unit's
     __shared__ int32_t s_item[kKeepGroup];    // accepted combinations of one, in order
     __shared__ uint64_t s_tmp[kKeepGroup / kWaveSize + 1];
     __shared__ ulonglong2 s_sum[kKeepGroup / kWaveSize];
@@ -1238,15 +1238,16 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     const uint32_t cnt = mine.count & ~kKeepSearch;
     const uint32_t quick = mine.count & kKeepSearch ? 0 : cnt;
     uint64_t tot;
-    // (26 bits of accepted combinations and 17 of those in slots are what 256 units can hold)
-    const bool search = cnt > quick;
+    // (26 bits of accepted combinations, 17 of those in slots and 14 of parts are what 256 units can hold)
+    const uint32_t parts_of =
+        cnt > quick ? ((mine.size >> kKeepRoadBits) + (mine.combo & 3) + kKeepFlags - 1) / kKeepFlags : 0;
     const uint64_t ex = block_excl_scan<uint64_t, kKeepGroup>(
-        cnt | (static_cast<uint64_t>(quick) << 28) | (static_cast<uint64_t>(search) << 48), s_tmp,
+        cnt | (static_cast<uint64_t>(quick) << 28) | (static_cast<uint64_t>(parts_of) << 48), s_tmp,
         tot);
     s_pre[tid] = static_cast<uint32_t>(ex & 0xFFFFFFFu);
     s_quick[tid] = static_cast<uint32_t>(ex >> 28) & 0xFFFFFu;
     s_first[tid] = mine.combo;
-    if (search) s_list[ex >> 48] = static_cast<uint8_t>(tid);
+    s_part[tid] = static_cast<uint16_t>(ex >> 48);
     __syncthreads();
     const uint32_t n_quick = static_cast<uint32_t>(tot >> 28) & 0xFFFFFu;
     const int n_search = static_cast<int>(tot >> 48);
@@ -1309,90 +1310,98 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     // ---- units whose accepted combinations are found again: their accept flags in order, each
     // one's road by its first combination and its hits by walking the road's words
     for (int sq = part; sq < n_search; sq += a.parts) {
-        const int q = s_list[sq];
+        int q = 0;  // last unit whose parts start at or before this one: it has parts
+        for (int hi = kKeepGroup - 1; q < hi;) {
+            const int mid = (q + hi + 1) >> 1;
+            if (s_part[mid] <= sq) q = mid; else hi = mid - 1;
+        }
         const UnitKeep k = a.keep[u0 + q];
-        const int nr = static_cast<int>(k.roads);
+        const int nr = static_cast<int>(k.size & ((1u << kKeepRoadBits) - 1)),
+                  len = static_cast<int>(k.size >> kKeepRoadBits);
         const int64_t CB0 = static_cast<int64_t>(k.combo), R0 = static_cast<int64_t>(k.road);
         __syncthreads();
         if (tid < nr) s_cb[tid] = static_cast<int32_t>(a.roads.combo_begin[R0 + tid] - CB0);
-        __syncthreads();
-        const int len = s_cb[nr - 1] + a.roads.ncombo[R0 + nr - 1];
-        int64_t at = base + s_pre[q];
-        // up to 64 flags per thread, in whole 4-byte words where those lie inside the unit's flags
-        const int off = static_cast<int>(CB0 & 3);
-        int per = (len + off + kKeepGroup - 1) / kKeepGroup;
-        per = per > 60 ? 64 : (per + 3) & ~3;
-        for (int i0 = -off; i0 < len; i0 += per * kKeepGroup) {
-            const int mine0 = i0 + per * tid;
-            uint64_t bits = 0;
-            for (int v = 0; 4 * v < per; ++v) {
-                const int i = mine0 + 4 * v;
-                uint32_t w = 0;
-                if (i >= 0 && i + 4 <= len) {
-                    w = *reinterpret_cast<const uint32_t *>(a.accept + CB0 + i);
-                } else {
+        // the unit's flags, in whole 4-byte words where those lie inside them; this part's start at i0
+        const int off = static_cast<int>(CB0 & 3), i0 = (sq - s_part[q]) * kKeepFlags - off;
+        const int end = i0 + kKeepFlags < len ? i0 + kKeepFlags : len;
+        auto flags = [&](int i) {
+            uint32_t w = 0;
+            if (i >= 0 && i + 4 <= len) {
+                w = *reinterpret_cast<const uint32_t *>(a.accept + CB0 + i);
+            } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (i + e >= 0 && i + e < len)
-                            w |= static_cast<uint32_t>(a.accept[CB0 + i + e]) << (8 * e);
-                }
-                // flag bytes are 0 or 1: bits 0, 8, 16, 24 to 4 v .. 4 v + 3
-                bits |= static_cast<uint64_t>(((w * 0x10204080u) >> 28) & 0xFu) << (4 * v);
+                for (int e = 0; e < 4; ++e)
+                    if (i + e >= 0 && i + e < len)
+                        w |= static_cast<uint32_t>(a.accept[CB0 + i + e]) << (8 * e);
             }
-            uint64_t all;
-            const uint32_t rank = static_cast<uint32_t>(block_excl_scan<uint64_t, kKeepGroup>(
-                static_cast<uint64_t>(__popcll(bits)), s_tmp, all));
-            // dealt out again, one to a thread: accepted combinations come in runs (193 such units of
-            // 2e5 cost 32 us as the last ones to finish, now 9)
-            for (uint32_t first = 0; first < all; first += kKeepGroup) {
-                uint32_t r2 = rank - first;
-                for (uint64_t m = bits; m; m &= m - 1, ++r2)
-                    if (r2 < static_cast<uint32_t>(kKeepGroup)) s_item[r2] = mine0 + __builtin_ctzll(m);
-                __syncthreads();
-                const int i = s_item[tid];
-                __syncthreads();
-                const int64_t pos = at + first + tid;
-                if (first + tid >= all || pos >= a.kept_cap) continue;
-                a.kept[pos] = CB0 + i;
-                if (!ONLY) continue;
-                int lo = 0, hi = nr - 1;  // last road that starts at or before i
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_cb[mid] <= i) lo = mid; else hi = mid - 1;
-                }
-                const int64_t r = R0 + lo;
-                const uint32_t nh = a.roads.nhits[r];
-                uint32_t c = static_cast<uint32_t>(i - s_cb[lo]);
-                uint32_t want = 0, words = 0;  // hit index per layer, 6 bits a layer
-#pragma unroll
-                for (int l = SVT_N_LAYERS - 1; l >= 0; --l) {  // layer 0 most significant
-                    const uint32_t nl = nh_of(nh, l);
-                    want |= (c % nl) << (6 * l);
-                    c /= nl;
-                    words += nl;
-                }
-                const uint32_t *w = a.words + a.roads.hit_begin[r];
-                int32_t x[SVT_N_LAYERS] = {0, 0, 0, 0, 0};
-                uint32_t seen = 0;
-                for (uint32_t j0 = 0; j0 < words; j0 += kWalk) {
-                    uint32_t y[kWalk];
-#pragma unroll
-                    for (int e = 0; e < kWalk; ++e) y[e] = w[j0 + e < words ? j0 + e : words - 1];
-#pragma unroll
-                    for (int e = 0; e < kWalk; ++e) {
-                        const uint32_t l = w_layer(y[e]);
-                        const bool hit = j0 + e < words &&
-                                         ((seen >> (6 * l)) & 63u) == ((want >> (6 * l)) & 63u);
-                        seen += 1u << (6 * l);
-#pragma unroll
-                        for (int q2 = 0; q2 < SVT_N_LAYERS; ++q2)
-                            if (hit && l == static_cast<uint32_t>(q2)) x[q2] = w_coord(y[e]);
-                    }
-                }
-                keep_record(a, a.sets[a.roads.set[r]], pos, pack16(x[0], x[1]), pack16(x[2], x[3]),
-                            x[4]);
+            return w;
+        };
+        // accepted in the unit's parts before this one
+        uint32_t skip = 0;
+#pragma unroll 8
+        for (int i = 4 * tid - off; i < i0; i += 4 * kKeepGroup) skip += __popc(flags(i));
+        skip = static_cast<uint32_t>(block_sum<int32_t, kKeepGroup>(
+            static_cast<int32_t>(skip), reinterpret_cast<int32_t *>(s_tmp)));
+        const int64_t at = base + s_pre[q] + skip;
+        const int per = ((end - i0 + kKeepGroup - 1) / kKeepGroup + 3) & ~3;  // at most 16
+        const int mine0 = i0 + per * tid;
+        uint64_t bits = 0;
+        for (int v = 0; 4 * v < per; ++v)
+            // flag bytes are 0 or 1: bits 0, 8, 16, 24 to 4 v .. 4 v + 3
+            bits |= static_cast<uint64_t>(((flags(mine0 + 4 * v) * 0x10204080u) >> 28) & 0xFu)
+                    << (4 * v);
+        uint64_t all;
+        const uint32_t rank = static_cast<uint32_t>(block_excl_scan<uint64_t, kKeepGroup>(
+            static_cast<uint64_t>(__popcll(bits)), s_tmp, all));
+        // dealt out again, one to a thread: accepted combinations come in runs (193 such units of
+        // 2e5 cost 32 us as the last ones to finish, now 9)
+        for (uint32_t first = 0; first < all; first += kKeepGroup) {
+            uint32_t r2 = rank - first;
+            for (uint64_t m = bits; m; m &= m - 1, ++r2)
+                if (r2 < static_cast<uint32_t>(kKeepGroup)) s_item[r2] = mine0 + __builtin_ctzll(m);
+            __syncthreads();
+            const int i = s_item[tid];
+            __syncthreads();
+            const int64_t pos = at + first + tid;
+            if (first + tid >= all || pos >= a.kept_cap) continue;
+            a.kept[pos] = CB0 + i;
+            if (!ONLY) continue;
+            int lo = 0, hi = nr - 1;  // last road that starts at or before i
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_cb[mid] <= i) lo = mid; else hi = mid - 1;
             }
-            at += static_cast<int64_t>(all);
+            const int64_t r = R0 + lo;
+            const uint32_t nh = a.roads.nhits[r];
+            uint32_t c = static_cast<uint32_t>(i - s_cb[lo]);
+            uint32_t want = 0, words = 0;  // hit index per layer, 6 bits a layer
+#pragma unroll
+            for (int l = SVT_N_LAYERS - 1; l >= 0; --l) {  // layer 0 most significant
+                const uint32_t nl = nh_of(nh, l);
+                want |= (c % nl) << (6 * l);
+                c /= nl;
+                words += nl;
+            }
+            const uint32_t *w = a.words + a.roads.hit_begin[r];
+            int32_t x[SVT_N_LAYERS] = {0, 0, 0, 0, 0};
+            uint32_t seen = 0;
+            for (uint32_t j0 = 0; j0 < words; j0 += kWalk) {
+                uint32_t y[kWalk];
+#pragma unroll
+                for (int e = 0; e < kWalk; ++e) y[e] = w[j0 + e < words ? j0 + e : words - 1];
+#pragma unroll
+                for (int e = 0; e < kWalk; ++e) {
+                    const uint32_t l = w_layer(y[e]);
+                    const bool hit = j0 + e < words &&
+                                     ((seen >> (6 * l)) & 63u) == ((want >> (6 * l)) & 63u);
+                    seen += 1u << (6 * l);
+#pragma unroll
+                    for (int q2 = 0; q2 < SVT_N_LAYERS; ++q2)
+                        if (hit && l == static_cast<uint32_t>(q2)) x[q2] = w_coord(y[e]);
+                }
+            }
+            keep_record(a, a.sets[a.roads.set[r]], pos, pack16(x[0], x[1]), pack16(x[2], x[3]),
+                        x[4]);
         }
     }
 }
@@ -1553,6 +1562,13 @@ hipError_t launch_unpack(const uint32_t *words, int64_t n_words, const svt_confi
     return hipGetLastError();
 }
 
+// Workgroups of k_unit_keep that share a group of units, of n groups.
+static int64_t keep_parts(int64_t n) {
+    const int64_t most = 2048 / n, few = 1024 / n < 128 ? 1024 / n : 128;
+    const int64_t parts = few > 32 ? few : 32;
+    return most < 1 ? 1 : parts < most ? parts : most;
+}
+
 hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
     const int64_t units = unit_count(p.word_cap > 0 ? p.word_cap : 1);
     const int ranges = unit_ranges(p.word_cap);
@@ -1629,10 +1645,11 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     k.kept_cap = p.kept_cap;
     k.d_n_kept = p.d_n_kept;
     k.err = p.err;
-    // few groups are shared by several workgroups each, to fill the chip and for the sliced units
-    // of a small batch
-    k.parts = c.n_group < 2048 ? static_cast<int32_t>(2048 / c.n_group) : 1;
-    if (k.parts > 32) k.parts = 32;
+    // Few groups are shared by several workgroups each: by 32 where that fills the chip (30 groups of
+    // units, 84 thousand kept: 6.8 us, with 68 9.5), by up to 128 where there are fewer still (a pass
+    // over 1000 uneven events, 7 groups, every combination accepted: 270 us with 32, 167 with 128; the
+    // list of 37 such events at the usual cut 11.4 and 7.9).
+    k.parts = static_cast<int32_t>(keep_parts(c.n_group));
     const int kgrid = p.kept ? static_cast<int>(c.n_group) * k.parts : 1;
     if (p.kept_only)
         hipLaunchKernelGGL(k_unit_keep<true>, dim3(kgrid), dim3(kKeepGroup), 0, s, k);
