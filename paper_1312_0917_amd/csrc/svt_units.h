@@ -21,17 +21,24 @@ constexpr int kDealers = 32;       // counters that deal out the last units,
 constexpr int kDealerStride = 32;  // a 128-byte line apart
 constexpr int kMaxRanges = 512;    // contiguous ranges of units whose totals are scanned together
 
-// A unit with many combinations is cut into slices of this many, so that no wave works long after
-// the others have finished (a unit of the largest roads holds 2e5 combinations, a usual one 800 to
-// 3000); a batch too small to fill the chip is cut finer, not so fine that every slice unpacks its
-// unit again for little: the fits of 33 units take 17.2 us with slices of 1024, 15.8 with 512; of 37
-// uneven events 19.3 and 18.5.  Cutting in two what holds 1536 or more in batches of up to 2048 units
-// gave 3 us of 37 for 256 events of up to 256 roads, and cost 0.5 of 49 for 7500 units, whose slices
-// then have to be worked out one by one.
-constexpr int kSliceCombos = 8192, kSliceCombosSmall = 512;
-constexpr int kSmallUnits = 64;
-__host__ __device__ inline int slice_combos(int64_t nu) {
-    return nu <= kSmallUnits ? kSliceCombosSmall : kSliceCombos;
+// A unit with many combinations is cut into slices, so that no wave works long after the others have
+// finished (a unit of the largest roads holds 2e5 combinations, a usual one 800 to 3000).  The fewer the
+// units are against the 4096 waves that could each take one, the smaller the slices: 8192 combinations
+// from 1025 units on, half as much for half as many and so on, in powers of two, down to 512.  A pass
+// without a list over 65, 512 and 1024 units of uneven roads takes 22, 32 and 45 us so; with 8192
+// throughout 51, 56 and 58.  Counting on all 4096 waves instead of half gave 22, 29 and 41, and 69 of 80
+// at 2048 units, but cost 0.4 of 37.7 where one unit in a hundred is cut (256 events of up to 256 roads).
+// In kept-only mode a unit's fits take half the time, and what a cut unit accepted is found again from its
+// flags, 6 us for the list kernel, so an eighth of the waves is counted on (256 units of up to 4 hits a
+// layer: 27 us with slices of 4096, 34 with 1024, 40 with 512).
+constexpr int kMinSliceBits = 9, kMaxSliceBits = 13;
+constexpr int kSliceWaves = 2048, kSliceWavesKeptOnly = 512;
+// the smallest slice of at least 8192 * nu / waves, in its bits
+__host__ __device__ inline int slice_bits(int64_t nu, bool kept_only) {
+    const uint32_t times = (1u << kMaxSliceBits) / (kept_only ? kSliceWavesKeptOnly : kSliceWaves);
+    const uint32_t n = nu < 1 ? 1u : nu < 4096 ? static_cast<uint32_t>(nu) : 4096u;
+    const int bits = 32 - __builtin_clz(n * times - 1);
+    return bits < kMinSliceBits ? kMinSliceBits : bits < kMaxSliceBits ? bits : kMaxSliceBits;
 }
 // Counts before a unit, from the start of its range.
 struct alignas(16) UnitRec {

@@ -45,6 +45,7 @@ struct CArgs {
     int64_t n_group;
     SliceAcc *acc;           // to clear
     int64_t n_acc;
+    bool kept_only;
 };
 
 // Row j of a constant set in the fit's layout, for every set of the bank.
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         return;
     }
     uint2 *S = s_ent[wave];
-    const uint32_t slice = static_cast<uint32_t>(slice_combos(nu));
+    const int slice = slice_bits(nu, a.kept_only);
     uint32_t roads = 0, events = 0;  // of the range, before the units in hand
     uint64_t combos = 0;
     uint32_t bad_word = ~0u, over_road = ~0u, set_road = ~0u;
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         // or events: 16 bits each)
         uint2 v = make_uint2(0, 0);
         if (lane < kUnitWaves) v = s_agg[buf][lane];
-        const uint32_t more = v.y > 0 ? (v.y - 1) / slice : 0;  // slices past the first
+        const uint32_t more = v.y > 0 ? (v.y - 1) >> slice : 0;  // slices past the first
         const uint32_t sre = scan16(v.x), scn = scan16(v.y), sme = scan16(more);
         const uint32_t ex = lane_value(sre - v.x, wave), ex_c = lane_value(scn - v.y, wave),
                        ex_m = lane_value(sme - more, wave);
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         if (u < hi_u) {
             if (lane == 0) {
                 a.rec[u] = UnitRec{roads + ex_r, events + ex_e, combos + with_extra(ex_c, ex_m)};
-                if (a.keep) a.keep[u].count = cs > slice ? kKeepSearch : 0u;
+                if (a.keep) a.keep[u].count = cs > 1u << slice ? kKeepSearch : 0u;
             }
             if (my_over != ~0u && over_road == ~0u) over_road = roads + ex_r + my_over;
             if (my_set != ~0u && set_road == ~0u) set_road = roads + ex_r + my_set;
@@ -653,7 +654,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
 // left over, for a further call, or 0.
 template <int REC, bool SLICED>
 __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds &W, int64_t u,
-                                        uint32_t slice, uint32_t slice_len, int c0, uint32_t &kept,
+                                        uint32_t slice, int bits, int c0, uint32_t &kept,
                                         int64_t n, int64_t per) {
     const int lane = lane_id();
     const int32_t shift = hot.cfg.shift;
@@ -770,10 +771,10 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     uint32_t n_items = lane_value(it_end, 63), from_item = 0;
     const bool narrow = ballot(take && !L.bank[pre.z].narrow) == 0;
     // groups ga .. gb - 1 of the unit are this slice's (the last slice takes what is left over)
-    const uint32_t slices = SLICED && c_run > slice_len ? (c_run - 1) / slice_len + 1 : 1;
-    const uint32_t slice_groups = slice_len >> kBits;
-    const uint32_t ga = slice * slice_groups,
-                   gb = slice + 1 < slices ? ga + slice_groups : ~0u >> 1;
+    const uint32_t slices = SLICED && c_run > 1u << bits ? ((c_run - 1) >> bits) + 1 : 1;
+    const int group_bits = bits - kBits;
+    const uint32_t ga = slice << group_bits,
+                   gb = slice + 1 < slices ? ga + (1u << group_bits) : ~0u >> 1;
     if (SLICED && slices > 1) {
         // the items are in the order of their groups: count those before ga and before gb
         const uint32_t g = rb >> kBits;
@@ -855,8 +856,8 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
             const bool cut = touched && (g_first < ga || g_last >= gb);
             whole = touched && !cut;
             if (cut) {
-                const uint32_t s0 = g_first / slice_groups;
-                uint32_t s1 = g_last / slice_groups;
+                const uint32_t s0 = g_first >> group_bits;
+                uint32_t s1 = g_last >> group_bits;
                 s1 = s1 < slices ? s1 : slices - 1;
                 // the batch's number of the slice after the road's first one
                 const UnitRec rc = read_rec(L.args.rec, u);
@@ -967,7 +968,7 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
                                           int64_t per, int n_ranges, uint32_t extra) {
     const int wave = threadIdx.x / kWaveSize, lane = lane_id();
     const UnitShare share = unit_share(nu, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
-    const uint32_t slice_len = static_cast<uint32_t>(slice_combos(nu));
+    const int bits = slice_bits(nu, REC == kRecNone);
     const uint32_t my_extra =
         SLICED && extra > blockIdx.x ? (extra - blockIdx.x - 1) / gridDim.x + 1 : 0;
     bool late = false;
@@ -998,7 +999,7 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
         int c = 0;
         uint32_t kept = 0;
         do {
-            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, slice_len, c, kept, n, per);
+            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, bits, c, kept, n, per);
         } while (c != 0);
         ++u;
     }
@@ -1515,9 +1516,11 @@ int64_t unit_rec_bytes(int64_t words) {
     return static_cast<int64_t>(sizeof(UnitRec)) * unit_count(words);
 }
 int64_t unit_range_bytes() { return static_cast<int64_t>(sizeof(RangeTot)) * kMaxRanges; }
+// Slices past their unit's first: a batch's combinations over the slice, and where the slice is not the
+// largest, at most its units (kSliceWaves * slice / 8192) times the 28 * 8192 / slice that one has.
 int64_t unit_slices(int64_t combos) {
-    const int64_t small = combos / kSliceCombosSmall, most = int64_t{kSmallUnits} * 2048;
-    return combos / kSliceCombos + (small < most ? small : most) + 1;
+    const int64_t small = combos >> kMinSliceBits, most = int64_t{kSliceWaves} * 32;
+    return (combos >> kMaxSliceBits) + (small < most ? small : most) + 1;
 }
 int64_t unit_acc_bytes(int64_t combos) {
     return static_cast<int64_t>(sizeof(SliceAcc)) * unit_slices(combos);
@@ -1588,6 +1591,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     c.n_group = (units + kKeepGroup - 1) / kKeepGroup;
     c.acc = static_cast<SliceAcc *>(p.acc);
     c.n_acc = unit_slices(p.combo_cap);
+    c.kept_only = p.kept_only;
     hipLaunchKernelGGL(k_unit_count, dim3(ranges + 1), dim3(kThreads), 0, s,
                        c);
     hipError_t e = hipGetLastError();
