@@ -1518,6 +1518,7 @@ int64_t unit_rec_bytes(int64_t words) {
 int64_t unit_range_bytes() { return static_cast<int64_t>(sizeof(RangeTot)) * kMaxRanges; }
 // Slices past their unit's first: a batch's combinations over the slice, and where the slice is not the
 // largest, at most its units (kSliceWaves * slice / 8192) times the 28 * 8192 / slice that one has.
+constexpr int64_t kUnitSlices = (7 * 32768) >> kMinSliceBits;  // of 7 roads of 8^5 in a unit
 int64_t unit_slices(int64_t combos) {
     const int64_t small = combos >> kMinSliceBits, most = int64_t{kSliceWaves} * 32;
     return (combos >> kMaxSliceBits) + (small < most ? small : most) + 1;
@@ -1590,7 +1591,11 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     c.group = reinterpret_cast<unsigned long long *>(p.keep_groups);
     c.n_group = (units + kKeepGroup - 1) / kKeepGroup;
     c.acc = static_cast<SliceAcc *>(p.acc);
-    c.n_acc = unit_slices(p.combo_cap);
+    // (cleared by as many workgroups as the words need: not for more slices than those can have, 448 a
+    // unit of 7 roads of 8^5 combinations.  3000 words under a capacity of 8e8 combinations: 24.4 us a
+    // pass with room for all of those cleared, 16.3 now)
+    const int64_t slices = unit_slices(p.combo_cap), most = kUnitSlices * units;
+    c.n_acc = slices < most ? slices : most;
     c.kept_only = p.kept_only;
     hipLaunchKernelGGL(k_unit_count, dim3(ranges + 1), dim3(kThreads), 0, s,
                        c);

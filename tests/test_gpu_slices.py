@@ -70,3 +70,22 @@ def test_one_more_unit_makes_no_step(bank, want):
         return min(times)
     for units in (32, 64, 128, 256, 512, 1024):
         assert best_of(units + 1) < 1.5 * best_of(units), units
+
+
+@pytest.mark.parametrize("units", [1, 3, 20])
+@pytest.mark.parametrize("combo_cap", [None, 10**7, 2 * 10**8])
+def test_units_of_as_many_slices_as_there_can_be(bank, units, combo_cap):
+    """Roads of 8^5 combinations, seven to a unit, under a capacity of their number and far above it:
+    what the slices of a unit share is counted by the words as well as by the capacity."""
+    rng = np.random.default_rng(units)
+    n = (256 * units + 39) // 40
+    layer = np.repeat(np.tile(np.arange(5), n), 8)
+    road = np.repeat(np.arange(n), 40)
+    words = (rng.integers(0, 8192, 40 * n) | layer << 13 | (3 * road + 1) % 256 << 16).astype(np.uint32)
+    ref = oracle.run(words, bank.f, bank.q, CFG)
+    assert ref["n_combos"] == 32768 * n
+    r = P.BatchRunner(gpu_cfg(CFG), P.device_bank(bank.f, bank.q), len(words), n,
+                      combo_cap or ref["n_combos"], kept_cap=ref["n_kept"] + 1, graph=False)
+    for _ in range(2):
+        got = r.load(P.words_tensor(words)).run().result()
+        compare(ref, got, BATCH_KEYS, f"{units} units, capacity {combo_cap}")
