@@ -343,8 +343,8 @@ svt_status svt_combine(const svt_roads *roads, int64_t n_roads, const svt_config
     const Sizes nr{n_roads, nullptr, n_roads};
     const bool listing = combo_road || combo_hits;
     SVT_TRY(launch_combo_count(*roads, nr, rbn, rb, d_err, stream));
-    SVT_TRY(launch_scan(rb, 0, 1, nr, kRoadBlock, d_n_combos, nullptr, listing ? combo_cap : -1,
-                        1, d_err, true, stream));
+    SVT_TRY(launch_scan(rb, nr, kRoadBlock, d_n_combos, listing ? combo_cap : -1, 1, d_err, true,
+                        stream));
     SVT_TRY(launch_combo_begin(*roads, nr, rbn, rb, listing ? combo_road : nullptr, combo_cap,
                                d_err, stream));
     if (listing)
@@ -393,8 +393,8 @@ svt_status svt_select(const svt_config *cfg, const svt_roads *roads, int64_t n_r
                           d_err, stream));
     if (d_n_kept) {
         const Sizes nc{n_combos, nullptr, n_combos};
-        SVT_TRY(launch_scan(kb, 0, 1, nc, kKeptBlock, d_n_kept, nullptr, kept ? kept_cap : -1, 2,
-                            d_err, true, stream));
+        SVT_TRY(launch_scan(kb, nc, kKeptBlock, d_n_kept, kept ? kept_cap : -1, 2, d_err, true,
+                            stream));
         if (kept && n_combos > 0)
             SVT_TRY(launch_kept_write(accept, nc, kbn, kb, kept, kept_cap, d_err, stream));
     }

@@ -146,12 +146,10 @@ __device__ inline int64_t load_size(const Sizes &s) {
     return v < 0 ? 0 : v;
 }
 
-// In-place exclusive scan of ncols (1 or 2) int64 columns of ceil(n / items_div) entries,
-// one workgroup per column; column c's total goes to tot[c] (may be null).  When the total
-// of column 0 exceeds cap0 (>= 0), a capacity error with index cap_index is reported.  With
-// skip_if_error, an error already in *err makes it write -1 totals and do nothing else.
-hipError_t launch_scan(int64_t *data, int64_t col_stride, int ncols, Sizes n,
-                       int64_t items_div, int64_t *tot0, int64_t *tot1, int64_t cap0,
+// In-place exclusive scan of ceil(n / div) int64 entries by one workgroup; the total goes to *tot (may
+// be null).  When it exceeds cap (>= 0), a capacity error with index cap_index is reported.  With
+// skip_if_error, an error already in *err makes it write a total of -1 and do nothing else.
+hipError_t launch_scan(int64_t *data, Sizes n, int64_t div, int64_t *tot, int64_t cap,
                        uint32_t cap_index, uint64_t *err, bool skip_if_error, hipStream_t s);
 hipError_t launch_combo_count(const svt_roads &roads, Sizes n_roads, int64_t grid_blocks,
                               int64_t *rb_sums, uint64_t *err, hipStream_t s);

@@ -40,23 +40,19 @@ __device__ int64_t scan_column(int64_t *col, int64_t n, int64_t *tot, int64_t *t
     return carry;
 }
 
-// One workgroup per column; column 0's total is checked against cap0 (class CAPACITY, index
-// cap_index) when cap0 >= 0.
-__global__ __launch_bounds__(kScanThreads) void k_scan(int64_t *data, int64_t col_stride,
-                                                       Sizes n_s, int64_t div, int64_t *tot0,
-                                                       int64_t *tot1, int64_t cap0,
+// The total is checked against cap (class CAPACITY, index cap_index) when cap >= 0.
+__global__ __launch_bounds__(kScanThreads) void k_scan(int64_t *data, Sizes n_s, int64_t div,
+                                                       int64_t *tot, int64_t cap,
                                                        uint32_t cap_index, uint64_t *err,
                                                        int32_t skip_if_error) {
     __shared__ int64_t tmp[kScanThreads / kWaveSize + 1];
-    int64_t *tot = blockIdx.x == 0 ? tot0 : tot1;
     if (skip_if_error && block_has_error(err)) {
         if (threadIdx.x == 0 && tot) *tot = -1;
         return;
     }
     const int64_t n = (load_size(n_s) + div - 1) / div;
-    const int64_t carry = scan_column<kScanThreads>(data + blockIdx.x * col_stride, n, tot, tmp);
-    if (threadIdx.x == 0 && blockIdx.x == 0 && cap0 >= 0 && carry > cap0)
-        report(err, SVT_ERRCLASS_CAPACITY, cap_index);
+    const int64_t carry = scan_column<kScanThreads>(data, n, tot, tmp);
+    if (threadIdx.x == 0 && cap >= 0 && carry > cap) report(err, SVT_ERRCLASS_CAPACITY, cap_index);
 }
 
 // ---- combine 1: combinations per road and per-block sums ---------------------------------
@@ -890,11 +886,10 @@ inline int64_t clamp_grid(int64_t blocks, int64_t maxb) {
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
-hipError_t launch_scan(int64_t *data, int64_t col_stride, int ncols, Sizes n, int64_t div,
-                       int64_t *tot0, int64_t *tot1, int64_t cap0, uint32_t cap_index,
-                       uint64_t *err, bool skip_if_error, hipStream_t s) {
-    hipLaunchKernelGGL(k_scan, dim3(ncols), dim3(kScanThreads), 0, s, data, col_stride, n, div,
-                       tot0, tot1, cap0, cap_index, err, static_cast<int32_t>(skip_if_error));
+hipError_t launch_scan(int64_t *data, Sizes n, int64_t div, int64_t *tot, int64_t cap,
+                       uint32_t cap_index, uint64_t *err, bool skip_if_error, hipStream_t s) {
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanThreads), 0, s, data, n, div, tot, cap, cap_index,
+                       err, static_cast<int32_t>(skip_if_error));
     return hipGetLastError();
 }
 

@@ -31,9 +31,9 @@ TIE = 0.025
 
 
 def candidates():
-    """The unit kernels, under both schedules that name them (they take nothing else from a
-    tune), and the one-event-per-workgroup schedule."""
-    units = [L.make_tune(schedule=sc) for sc in (L.SVT_SCHEDULE_ONEPASS, L.SVT_SCHEDULE_TILES)]
+    """The unit kernels, which take nothing from a tune but the schedule (either name of theirs), and
+    the one-event-per-workgroup schedule."""
+    units = [L.make_tune(schedule=L.SVT_SCHEDULE_ONEPASS)]
     events = [L.make_tune(4096, 64, 256, occ, L.SVT_SCHEDULE_EVENTS)
               for occ in EVENT_OCCUPANCIES]
     return [L.svt_tune_resolve(t) for t in units + events]
@@ -134,27 +134,3 @@ def autotune(words: torch.Tensor, bank: torch.Tensor, cfg: L.svt_config, n_roads
         json.dump(data, open(tmp, "w"), indent=1)
         os.replace(tmp, cache_path)
     return res
-
-
-def pick_launch_mode(runner: P.BatchRunner, samples: int = 30, per_sample: int = 5,
-                     warmup: int = 3):
-    """Time one batch runner with and without SVT_BATCH_GRAPH (the same statistic as autotune) and
-    leave it in the faster mode.  Returns {"graph": ms, "direct": ms}; the pass is the same
-    launches either way, so the two differ by noise."""
-    times = {}
-    for graph in (True, False):
-        runner.graph = graph
-        for _ in range(warmup):
-            runner.run()
-        torch.cuda.synchronize()
-        ts = []
-        for _ in range(samples):
-            t0 = time.perf_counter()
-            for _ in range(per_sample):
-                runner.run()
-            torch.cuda.synchronize()
-            ts.append((time.perf_counter() - t0) / per_sample * 1e3)
-        times["graph" if graph else "direct"] = round(float(np.median(ts)), 5)
-    runner.graph = times["graph"] <= times["direct"]
-    return times
-
