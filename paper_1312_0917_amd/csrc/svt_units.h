@@ -22,55 +22,58 @@ constexpr int kDealerStride = 32;  // a 128-byte line apart
 constexpr int kMaxRanges = 512;    // contiguous ranges of units whose totals are scanned together
 
 // A unit with many combinations is cut into slices, so that no wave works long after the others have
-// finished (a unit of the largest roads holds 2e5 combinations, a usual one 800 to 3000).  The fewer the
-// units are against the 4096 waves that could each take one, the smaller the slices: 8192 combinations
-// from 1025 units on, half as much for half as many and so on, in powers of two, down to 512.  A pass
-// without a list over 65, 512 and 1024 units of uneven roads takes 22, 32 and 45 us so; with 8192
-// throughout 51, 56 and 58.  Counting on all 4096 waves instead of half gave 22, 29 and 41, and 69 of 80
-// at 2048 units, but cost 0.4 of 37.7 where one unit in a hundred is cut (256 events of up to 256 roads).
-// In kept-only mode a unit's fits take half the time, and what a cut unit accepted is found again from its
-// flags, 6 us for the list kernel, so an eighth of the waves is counted on (256 units of up to 4 hits a
-// layer: 27 us with slices of 4096, 34 with 1024, 40 with 512).
-constexpr int kMinSliceBits = 9, kMaxSliceBits = 13;
-constexpr int kSliceWaves = 2048, kSliceWavesKeptOnly = 512;
-// the smallest slice of at least 8192 * nu / waves, in its bits
-__host__ __device__ inline int slice_bits(int64_t nu, bool kept_only) {
-    const uint32_t times = (1u << kMaxSliceBits) / (kept_only ? kSliceWavesKeptOnly : kSliceWaves);
-    const uint32_t n = nu < 1 ? 1u : nu < 4096 ? static_cast<uint32_t>(nu) : 4096u;
-    const int bits = 32 - __builtin_clz(n * times - 1);
-    return bits < kMinSliceBits ? kMinSliceBits : bits < kMaxSliceBits ? bits : kMaxSliceBits;
-}
+// finished (a unit of the largest roads holds 2e5 combinations, a usual one 800 to 3000).  The counting
+// kernel counts the slices past each unit's first for three lengths, and the fitting kernel takes the
+// smallest of 512, 2048 and 8192 combinations that leaves at most kPieces units and slices together, half
+// of the chip's 4096 waves: a slice unpacks its unit again, so slices pay while waves would be idle.  Us
+// a pass with records, 8192 for all / by this rule / with all 4096 waves: 65 units of uneven roads 51 / 23
+// / 23, 512 of them 55 / 33 / 31, 1024 57 / 58 / 42, but 1024 units of 800 combinations 24 / 24 / 26.  (Going
+// by the number of units alone, 94 units of roads of 8^5 were cut into 38 thousand slices: 375, now 150.)
+// In kept-only mode a unit's fits take half the time, and what a cut unit accepted is found again from
+// its flags, 6 us for the list kernel: with 256 and 512 pieces 128 units of 800 combinations take 24 and 29.
+constexpr int kSliceBits[3] = {9, 11, 13};
+constexpr int kPieces = 2048, kPiecesKeptOnly = 256;
+static_assert(kPiecesKeptOnly <= kPieces, "the slices' accumulators are sized for kPieces (unit_slices)");
 // Counts before a unit, from the start of its range.
 struct alignas(16) UnitRec {
     uint32_t roads, events;
-    uint64_t combos;     // 40 bits; above them the slices past each unit's first
+    uint64_t combos;     // 40 bits; above them the slices of 8192 past each unit's first
 };
 constexpr int kExtraShift = 40;
+// The slices of 512 and 2048 beside them, where there are fewer units than pieces: a range then has 16
+// units, with at most 104 roads of 40 words, so 13 bits of the one and 11 of the other.
+constexpr int kFineBits = 13;
+__host__ __device__ inline uint32_t fine_slices(uint32_t x, int step) {
+    return step == 1 ? x >> kFineBits : x & ((1u << kFineBits) - 1);
+}
 // What the slices of a unit find out together about a road cut by a slice's end, at the first such
-// end: zero to start with.
+// end, and the slice that ends there about itself: zero to start with.
 struct alignas(16) SliceAcc {
     unsigned long long key;  // complement of the smallest key
     uint32_t nacc;
-    uint32_t arrived;        // slices that have added theirs
+    uint32_t arrived;        // slices that have added theirs | the slice's accepted combinations << 8
 };
 // What a unit's wave leaves for the kept list: the number of its accepted combinations, and where
 // its roads and combinations are.  The accepted combinations themselves wait in the unit's slots,
 // as indices (4 bytes) or with their coordinates (16).  A unit that accepts more than it has slots,
-// or is cut into slices, has kKeepSearch set, and they are found again from the accept flags.
+// or is cut into slices (kKeepCut), is searched: they are found again from the accept flags, in parts
+// of a slice or 2^kKeepPartBits combinations, each by a workgroup that has the counts of the slices
+// before it from their accumulators.
+// (With one workgroup for a whole unit a pass over 1000 uneven events, every combination accepted,
+// took 562 us, 1050 kept-only: 233 and 407 now; scan, compaction and refit of the flat list 406 and 570.)
 // With 1024 bytes of slots that is one unit in 1000 of 2048-road events and one in 200 of the
 // uneven ones (512 bytes, where the workspace has no more: 4 and 9 in 100).
 struct UnitKeep {
     uint32_t count;   // | kKeepSearch
-    uint32_t size;    // roads (at most 256) | combinations (at most 2.4e5) << kKeepRoadBits
-    uint64_t combo, road;  // the unit's first of either
+    uint32_t size;    // roads (at most 256) | combinations (at most 2.4e5) << kKeepRoadBits | kKeepCut
+    uint64_t combo;   // the unit's first
+    uint32_t road;    // the same of the roads
+    uint32_t acc;     // accumulator of the end of the unit's first slice
 };
 constexpr uint32_t kKeepSearch = 1u << 31;
+constexpr uint32_t kKeepCut = 1u << 31;
 constexpr int kKeepRoadBits = 9;
-// Accept flags that a workgroup of k_unit_keep goes through at a time, of a unit that is searched: 16 a
-// thread.  A unit of the largest roads has 2e5, and at an open cut all of them set: with one workgroup
-// for all of a unit's, a pass over 1000 uneven events, every combination accepted, took 562 us, 1050
-// kept-only (167 and 379 now; scan, compaction and refit of the flat list had taken 406 and 570).
-constexpr int kKeepFlags = 4096;
+constexpr int kKeepPartBits = 12;
 constexpr int kKeepSlots = 1024, kKeepSlotsLess = 512;  // bytes per unit
 constexpr int kKeepGroup = 256;   // units a workgroup of k_unit_keep takes, with a common count,
 constexpr int kKeepStride = 16;   // a 128-byte line apart: every unit adds to one (side by side
@@ -82,7 +85,7 @@ struct alignas(16) RangeTot {
     uint32_t bad_word;   // word with a layer field out of range (index in the range)
     uint32_t over_road;  // road with too many hits on a layer (index in the range)
     uint32_t set_road;   // road whose tag has no constant set (index in the range)
-    uint32_t pad;
+    uint32_t fine;       // slices of 512 and 2048 (fine_slices)
 };
 
 // A constant set as the fit reads it: row j is f0|f1, f2|f3, f4|0 (int16 pairs) and the offset.

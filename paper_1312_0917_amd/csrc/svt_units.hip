@@ -39,13 +39,13 @@ struct CArgs {
     UnitSet *sets;           // the packed bank
     UnitRec *rec;            // per unit
     RangeTot *tot;           // per range
+    uint32_t *fine;          // per unit (fine_slices), of the first kPieces (nullable: not wanted)
     uint32_t *copy;          // words in device memory (nullable: they are there already)
     UnitKeep *keep;          // to start at no accepted combination (nullable: no kept list),
     unsigned long long *group;  // and the counts per kKeepGroup units
     int64_t n_group;
     SliceAcc *acc;           // to clear
     int64_t n_acc;
-    bool kept_only;
 };
 
 // Row j of a constant set in the fit's layout, for every set of the bank.
@@ -106,9 +106,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         return;
     }
     uint2 *S = s_ent[wave];
-    const int slice = slice_bits(nu, a.kept_only);
+    const bool few = a.fine && nu < kPieces;
     uint32_t roads = 0, events = 0;  // of the range, before the units in hand
     uint64_t combos = 0;
+    uint32_t fine_all = 0;
     uint32_t bad_word = ~0u, over_road = ~0u, set_road = ~0u;
     int buf = 0;
     for (int64_t u0 = lo_u; u0 < hi_u; u0 += kUnitWaves, buf ^= 1) {
@@ -182,15 +183,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         // or events: 16 bits each)
         uint2 v = make_uint2(0, 0);
         if (lane < kUnitWaves) v = s_agg[buf][lane];
-        const uint32_t more = v.y > 0 ? (v.y - 1) >> slice : 0;  // slices past the first
-        const uint32_t sre = scan16(v.x), scn = scan16(v.y), sme = scan16(more);
+        const uint32_t past = v.y > 0 ? v.y - 1 : 0, more = past >> kSliceBits[2];
+        const uint32_t fine = (past >> kSliceBits[0]) | ((past >> kSliceBits[1]) << kFineBits);
+        const uint32_t sre = scan16(v.x), scn = scan16(v.y), sme = scan16(more), sf = scan16(fine);
         const uint32_t ex = lane_value(sre - v.x, wave), ex_c = lane_value(scn - v.y, wave),
-                       ex_m = lane_value(sme - more, wave);
+                       ex_m = lane_value(sme - more, wave), ex_f = lane_value(sf - fine, wave);
         const uint32_t ex_r = ex & 0xFFFFu, ex_e = ex >> 16;
         if (u < hi_u) {
             if (lane == 0) {
                 a.rec[u] = UnitRec{roads + ex_r, events + ex_e, combos + with_extra(ex_c, ex_m)};
-                if (a.keep) a.keep[u].count = cs > 1u << slice ? kKeepSearch : 0u;
+                if (few) a.fine[u] = ex_f;
+                if (a.keep) a.keep[u].count = 0;
             }
             if (my_over != ~0u && over_road == ~0u) over_road = roads + ex_r + my_over;
             if (my_set != ~0u && set_road == ~0u) set_road = roads + ex_r + my_set;
@@ -199,6 +202,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         roads += all & 0xFFFFu;
         events += all >> 16;
         combos += with_extra(lane_value(scn, kUnitWaves - 1), lane_value(sme, kUnitWaves - 1));
+        fine_all = lane_value(sf, kUnitWaves - 1);  // (of use where these are the range's only units)
     }
     if (lane == 0) {
         s_err[0][wave] = bad_word;
@@ -212,14 +216,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             over_road = s_err[1][w] < over_road ? s_err[1][w] : over_road;
             set_road = s_err[2][w] < set_road ? s_err[2][w] : set_road;
         }
-        a.tot[blockIdx.x] = RangeTot{roads, events, combos, bad_word, over_road, set_road, 0};
+        a.tot[blockIdx.x] =
+            RangeTot{roads, events, combos, bad_word, over_road, set_road, fine_all};
     }
 }
 
 // ---- fitting ------------------------------------------------------------------------------------
 struct UArgs {
     const uint32_t *words;   // in device memory
-    int64_t *d_nw;           // the word count (nw_copy); d_nw[1]: left 1 if the batch has an error
+    int64_t *d_nw;           // the word count (nw_copy); d_nw[1]: for k_unit_keep (KArgs)
     int64_t word_cap;
     uint32_t *ticket;
     int32_t ranges;          // ranges the counting kernel dealt units to
@@ -227,6 +232,7 @@ struct UArgs {
     const UnitSet *sets;
     const UnitRec *rec;
     const RangeTot *tot;
+    const uint32_t *fine;
     svt_roads roads;
     int64_t road_cap;
     svt_fitrec out;
@@ -242,6 +248,13 @@ struct UArgs {
     uint32_t slot_bytes;
     SliceAcc *acc;
 };
+
+// Slices of the given length before a unit, from the start of its range.
+__device__ __forceinline__ uint32_t slices_before(const UnitRec *rec, const uint32_t *fine, int64_t u,
+                                                  int step) {
+    return step == 2 ? static_cast<uint32_t>(read_rec(rec, u).combos >> kExtraShift)
+                     : fine_slices(in_memory(fine)[u], step);
+}
 
 constexpr int kTabCap = 768;   // coordinate-pair table entries of the roads fitted together
 constexpr int kTabPad = 8;     // a dummy slot reads up to 7 entries before or after its table
@@ -282,13 +295,14 @@ struct RangeBase {
 // Running counts at the start of every range, as each workgroup works them out for itself.
 struct RangeLds {
     RangeBase base[kMaxRanges];
-    uint64_t roads[kUnitWaves], combos[kUnitWaves], err[kUnitWaves];
+    uint64_t roads[kUnitWaves], combos[kUnitWaves], err[kUnitWaves], fine[kUnitWaves];
     uint32_t events[kUnitWaves], extra[kUnitWaves];
 };
 struct BatchTotals {
     int64_t n_roads, n_combos;
     uint64_t err;    // the first error found in the words, or a capacity that is too small
     uint32_t extra, events;
+    int step;        // the slices' length: kSliceBits[step]
 };
 
 struct ULds {
@@ -654,7 +668,7 @@ __device__ __forceinline__ void fit_windows(const UArgs &a, const ULds &L, WaveL
 // left over, for a further call, or 0.
 template <int REC, bool SLICED>
 __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds &W, int64_t u,
-                                        uint32_t slice, int bits, int c0, uint32_t &kept,
+                                        uint32_t slice, int step, int c0, uint32_t &kept,
                                         int64_t n, int64_t per) {
     const int lane = lane_id();
     const int32_t shift = hot.cfg.shift;
@@ -771,6 +785,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     uint32_t n_items = lane_value(it_end, 63), from_item = 0;
     const bool narrow = ballot(take && !L.bank[pre.z].narrow) == 0;
     // groups ga .. gb - 1 of the unit are this slice's (the last slice takes what is left over)
+    const int bits = SLICED ? kSliceBits[0] + 2 * step : kSliceBits[2];
     const uint32_t slices = SLICED && c_run > 1u << bits ? ((c_run - 1) >> bits) + 1 : 1;
     const int group_bits = bits - kBits;
     const uint32_t ga = slice << group_bits,
@@ -860,8 +875,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 uint32_t s1 = g_last >> group_bits;
                 s1 = s1 < slices ? s1 : slices - 1;
                 // the batch's number of the slice after the road's first one
-                const UnitRec rc = read_rec(L.args.rec, u);
-                const uint32_t x = static_cast<uint32_t>(rc.combos >> kExtraShift) +
+                const uint32_t x = slices_before(L.args.rec, L.args.fine, u, step) +
                                    L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)]
                                        .extra + s0;
                 // Everything here is an atomic at agent scope, so it is enough that the first two are
@@ -872,8 +886,8 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
                 __hip_atomic_fetch_max(&acc->key, ~key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_fetch_add(&acc->nacc, nacc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                whole = __hip_atomic_fetch_add(&acc->arrived, 1u, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT) == s1 - s0;
+                whole = (__hip_atomic_fetch_add(&acc->arrived, 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) & 0xFFu) == s1 - s0;
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if (whole) {
                     key = ~__hip_atomic_load(&acc->key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -921,13 +935,21 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
     if ((REC == kRecNone || hot.keep) && kept > 0 && lane == 0) {
         InMemory<UnitKeep> *k = in_memory(L.args.keep) + u;
         const uint32_t most = hot.slot_bytes / (REC == kRecNone ? 16 : 4);
-        if (slices > 1)
-            __hip_atomic_fetch_add(&k->count, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            k->count = kept | (kept > most ? kKeepSearch : 0u);
-        k->size = nr | (c_run << kKeepRoadBits);
+        k->size = nr | (c_run << kKeepRoadBits) | (slices > 1 ? kKeepCut : 0u);
         k->combo = static_cast<uint64_t>(CB0);
-        k->road = static_cast<uint64_t>(R0);
+        k->road = static_cast<uint32_t>(R0);
+        if (slices > 1) {
+            const uint32_t x =
+                slices_before(L.args.rec, L.args.fine, u, step) +
+                L.range.base[static_cast<uint32_t>(u) / static_cast<uint32_t>(per)].extra;
+            k->acc = x;
+            __hip_atomic_fetch_add(&k->count, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (slice + 1 < slices)
+                __hip_atomic_fetch_add(&in_memory(L.args.acc)[x + slice].arrived, kept << 8,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            k->count = kept | (kept > most ? kKeepSearch : 0u);
+        }
         __hip_atomic_fetch_add(in_memory(L.args.group) + u / kKeepGroup * kKeepStride,
                                static_cast<unsigned long long>(kept), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -938,7 +960,7 @@ __device__ __forceinline__ int run_unit(const UArgs &hot, const ULds &L, WaveLds
 // The unit and slice of the batch's extra slice number e (slices past their unit's first, counted
 // in the units' order).  One wave; 64 units or ranges are compared at a time.
 __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t nu, int64_t per,
-                              int n_ranges, uint32_t &slice) {
+                              int n_ranges, int step, uint32_t &slice) {
     const int lane = lane_id();
     int r = -1;  // last range whose extras start at or before e
     for (int r0 = 0; r0 < n_ranges; r0 += kWaveSize)
@@ -949,7 +971,7 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
     uint32_t first = 0;
     for (int64_t u0 = lo; u0 < hi; u0 += kWaveSize) {
         uint32_t x = ~0u;
-        if (u0 + lane < hi) x = static_cast<uint32_t>(a.rec[u0 + lane].combos >> kExtraShift);
+        if (u0 + lane < hi) x = slices_before(a.rec, a.fine, u0 + lane, step);
         const uint64_t m = ballot(x <= e);  // a prefix of the lanes
         if (m == 0) break;
         u += __popcll(m);
@@ -965,10 +987,9 @@ __device__ int64_t find_extra(const UArgs &a, const ULds &L, uint32_t e, int64_t
 // the workgroups in turn.
 template <int REC, bool SLICED>
 __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, int64_t nu,
-                                          int64_t per, int n_ranges, uint32_t extra) {
+                                          int64_t per, int n_ranges, uint32_t extra, int step) {
     const int wave = threadIdx.x / kWaveSize, lane = lane_id();
     const UnitShare share = unit_share(nu, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
-    const int bits = slice_bits(nu, REC == kRecNone);
     const uint32_t my_extra =
         SLICED && extra > blockIdx.x ? (extra - blockIdx.x - 1) / gridDim.x + 1 : 0;
     bool late = false;
@@ -981,7 +1002,7 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
                 if (lane == 0) k = atomicAdd(&L.next, 1u);
                 k = uni(k);
                 if (SLICED && k < my_extra) {
-                    u = find_extra(a, L, blockIdx.x + k * gridDim.x, nu, per, n_ranges, slice);
+                    u = find_extra(a, L, blockIdx.x + k * gridDim.x, nu, per, n_ranges, step, slice);
                 } else {
                     u = share.lo + (k - my_extra);
                     late = u >= share.hi;
@@ -999,7 +1020,7 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
         int c = 0;
         uint32_t kept = 0;
         do {
-            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, bits, c, kept, n, per);
+            c = run_unit<REC, SLICED>(a, L, L.w[wave], u, slice, step, c, kept, n, per);
         } while (c != 0);
         ++u;
     }
@@ -1007,19 +1028,26 @@ __device__ __forceinline__ void run_units(const UArgs &a, ULds &L, int64_t n, in
 
 // Scan the totals of the ranges, whose totals t the first threads have loaded (`per` units each);
 // all threads of the workgroup.
-__device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges, int64_t per,
+__device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges, int64_t nu,
+                                                   int64_t per,
                                                    int64_t nw, int64_t word_cap, int64_t road_cap,
-                                                   int64_t combo_cap, RangeLds &L) {
+                                                   int64_t combo_cap, int pieces, RangeLds &L) {
     const int tid = threadIdx.x, wave = tid / kWaveSize, lane = lane_id();
     const int waves = (ranges + kWaveSize - 1) / kWaveSize;  // that hold ranges, at most 8
     const uint64_t cc = t.combos & kComboMask;
     const uint32_t ee = static_cast<uint32_t>(t.combos >> kExtraShift);
+    uint64_t fine_before = 0;  // slices of 512, and of 2048 in the upper half
     RangeBase b{};
     if (wave < waves) {
         const uint64_t ir = scan64(static_cast<uint64_t>(t.roads)), ic = scan64(cc);
         const uint32_t iv = scan64(t.events), ie = scan64(ee);
         b = RangeBase{ir - t.roads, ic - cc, iv - t.events, ie - ee};
+        const uint64_t f = fine_slices(t.fine, 0) |
+                           (static_cast<uint64_t>(fine_slices(t.fine, 1)) << 32);
+        const uint64_t sf = scan64(f);
+        fine_before = sf - f;
         if (lane == kWaveSize - 1) {
+            L.fine[wave] = sf;
             L.roads[wave] = ir;
             L.combos[wave] = ic;
             L.events[wave] = iv;
@@ -1045,8 +1073,8 @@ __device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges
         if (lane == 0) L.err[wave] = err;
     }
     __syncthreads();
-    BatchTotals all{0, 0, SVT_NO_ERROR, 0, 0};
-    uint64_t first = SVT_NO_ERROR;
+    BatchTotals all{0, 0, SVT_NO_ERROR, 0, 0, 2};
+    uint64_t first = SVT_NO_ERROR, fine_all = 0;
     for (int w = 0; w < waves; ++w) {
         uint64_t e = L.err[w];
         if (e != SVT_NO_ERROR && (e >> 56) != SVT_ERRCLASS_LAYER)
@@ -1057,11 +1085,26 @@ __device__ __forceinline__ BatchTotals scan_ranges(const RangeTot &t, int ranges
             b.combos += static_cast<uint64_t>(all.n_combos);
             b.events += all.events;
             b.extra += all.extra;
+            fine_before += fine_all;
         }
         all.n_roads += static_cast<int64_t>(L.roads[w]);
         all.n_combos += static_cast<int64_t>(L.combos[w]);
         all.events += L.events[w];
         all.extra += L.extra[w];
+        fine_all += L.fine[w];
+    }
+    if (nu < pieces) {  // the smallest slices that leave at most `pieces` (and so fit their accumulators)
+        const uint32_t room = pieces - static_cast<uint32_t>(nu);
+        const uint32_t e0 = static_cast<uint32_t>(fine_all), e1 = static_cast<uint32_t>(fine_all >> 32);
+        if (e0 <= room) {
+            all.step = 0;
+            all.extra = e0;
+            b.extra = static_cast<uint32_t>(fine_before);
+        } else if (e1 <= room) {
+            all.step = 1;
+            all.extra = e1;
+            b.extra = static_cast<uint32_t>(fine_before >> 32);
+        }
     }
     if (tid < ranges) L.base[tid] = b;
     auto cap_err = [](uint64_t i) {
@@ -1107,10 +1150,11 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
     const int64_t per = units_per_range(nu, a.ranges);
     const int n_ranges = a.ranges;
     const BatchTotals all =
-        scan_ranges(t, a.ranges, per, nw, a.word_cap, a.road_cap, a.combo_cap, L.range);
+        scan_ranges(t, a.ranges, nu, per, nw, a.word_cap, a.road_cap, a.combo_cap,
+                    REC == kRecNone ? kPiecesKeptOnly : kPieces, L.range);
     if (blockIdx.x == 0 && tid == 0) {
         *a.err = all.err;
-        a.d_nw[1] = all.err != SVT_NO_ERROR;
+        a.d_nw[1] = all.err != SVT_NO_ERROR ? -1 : kSliceBits[0] + 2 * all.step;
         *a.d_n_roads = all.n_roads;
         *a.d_n_combos = all.n_combos;
     }
@@ -1118,9 +1162,9 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
 
     const uint32_t extra = uni(all.extra);
     if (extra == 0)
-        run_units<REC, false>(a, L, n, nu, per, n_ranges, extra);
+        run_units<REC, false>(a, L, n, nu, per, n_ranges, extra, 0);
     else
-        run_units<REC, true>(a, L, n, nu, per, n_ranges, extra);
+        run_units<REC, true>(a, L, n, nu, per, n_ranges, extra, all.step);
 }
 
 // ---- the kept list ---------------------------------------------------------------------------------
@@ -1135,10 +1179,11 @@ __global__ __launch_bounds__(kThreads) void k_unit_fit(UArgs a) {
 // short is reported in the error word by this kernel, while other workgroups start.  With records the
 // list then holds its first kept_cap entries; in kept-only mode nothing is written to it.
 struct KArgs {
-    const int64_t *d_nw;   // word count; [1]: the batch has an error
+    const int64_t *d_nw;   // word count; [1]: bits of the slices' length, -1 if the batch has an error
     int64_t word_cap;
     const UnitKeep *keep;
     const unsigned long long *group;
+    const SliceAcc *acc;
     const uint32_t *slots;
     uint32_t slot_bytes;
     const UnitSet *sets;
@@ -1183,13 +1228,13 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     __shared__ uint32_t s_quick[kKeepGroup];  // those of them that wait in slots
     __shared__ uint64_t s_first[kKeepGroup];  // the unit's first combination
     __shared__ int32_t s_cb[kKeepGroup];      // a searched unit's roads: first combination
-    __shared__ uint16_t s_part[kKeepGroup];   // parts of kKeepFlags flags to be searched before the unit's
+    __shared__ uint16_t s_part[kKeepGroup];   // parts to be searched before the unit's
     __shared__ int32_t s_item[kKeepGroup];    // accepted combinations of one, in order
     __shared__ uint64_t s_tmp[kKeepGroup / kWaveSize + 1];
     __shared__ ulonglong2 s_sum[kKeepGroup / kWaveSize];
     __shared__ UnitSet s_bank[ONLY ? 256 : 1];
     const int tid = threadIdx.x;
-    if (a.d_nw[1] != 0) {
+    if (a.d_nw[1] < 0) {
         if (blockIdx.x == 0 && tid == 0) *a.d_n_kept = -1;
         return;
     }
@@ -1237,11 +1282,17 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
     UnitKeep mine{};
     if (u0 + tid < nu) mine = a.keep[u0 + tid];
     const uint32_t cnt = mine.count & ~kKeepSearch;
-    const uint32_t quick = mine.count & kKeepSearch ? 0 : cnt;
+    const uint32_t quick = (mine.count & kKeepSearch) || (mine.size & kKeepCut) ? 0 : cnt;
     uint64_t tot;
     // (26 bits of accepted combinations, 17 of those in slots and 14 of parts are what 256 units can hold)
-    const uint32_t parts_of =
-        cnt > quick ? ((mine.size >> kKeepRoadBits) + (mine.combo & 3) + kKeepFlags - 1) / kKeepFlags : 0;
+    const int slice_bits = static_cast<int>(a.d_nw[1]);
+    const int part_bits = slice_bits > kKeepPartBits ? slice_bits : kKeepPartBits;
+    auto parts_in = [&](uint32_t size) {
+        return size & kKeepCut
+                   ? static_cast<int>((((size & ~kKeepCut) >> kKeepRoadBits) - 1) >> part_bits) + 1
+                   : 1;
+    };
+    const uint32_t parts_of = cnt > quick ? parts_in(mine.size) : 0;
     const uint64_t ex = block_excl_scan<uint64_t, kKeepGroup>(
         cnt | (static_cast<uint64_t>(quick) << 28) | (static_cast<uint64_t>(parts_of) << 48), s_tmp,
         tot);
@@ -1318,33 +1369,47 @@ __global__ __launch_bounds__(kKeepGroup) void k_unit_keep(KArgs a) {
         }
         const UnitKeep k = a.keep[u0 + q];
         const int nr = static_cast<int>(k.size & ((1u << kKeepRoadBits) - 1)),
-                  len = static_cast<int>(k.size >> kKeepRoadBits);
+                  len = static_cast<int>((k.size & ~kKeepCut) >> kKeepRoadBits);
         const int64_t CB0 = static_cast<int64_t>(k.combo), R0 = static_cast<int64_t>(k.road);
+        // the part, and the accepted combinations in it and before it
+        const int at_part = sq - s_part[q], parts = parts_in(k.size);
+        const int to = part_bits - slice_bits, s0 = at_part << to, s1 = s0 + (1 << to);
+        uint32_t skip = 0, here = 0;
+        if (parts > 1) {
+            for (int i = tid; i < s1; i += kKeepGroup) {  // (counts of the last slice are not kept)
+                const uint32_t c = i < s0 || at_part + 1 < parts ? a.acc[k.acc + i].arrived >> 8 : 0;
+                skip += i < s0 ? c : 0;
+                here += i < s0 ? 0 : c;
+            }
+            const uint64_t sums = block_sum<uint64_t, kKeepGroup>(
+                skip | (static_cast<uint64_t>(here) << 32), s_tmp);
+            skip = static_cast<uint32_t>(sums);
+            here = static_cast<uint32_t>(sums >> 32);
+        }
+        if (at_part + 1 == parts) here = (k.count & ~kKeepSearch) - skip;
+        if (here == 0) continue;
         __syncthreads();
         if (tid < nr) s_cb[tid] = static_cast<int32_t>(a.roads.combo_begin[R0 + tid] - CB0);
-        // the unit's flags, in whole 4-byte words where those lie inside them; this part's start at i0
-        const int off = static_cast<int>(CB0 & 3), i0 = (sq - s_part[q]) * kKeepFlags - off;
-        const int end = i0 + kKeepFlags < len ? i0 + kKeepFlags : len;
+        // its combinations, from the unit's first: i0 .. end - 1, in whole 4-byte words of flags where
+        // those lie inside (parts are cut at whole groups, multiples of 4)
+        constexpr int kGroup = 1 << kGroupBits<ONLY ? kRecNone : kRecFit>;
+        const int in_group = static_cast<int>(CB0 & (kGroup - 1));
+        const int i0 = at_part > 0 ? (at_part << part_bits) - in_group : -static_cast<int>(CB0 & 3);
+        const int end = at_part + 1 < parts ? ((at_part + 1) << part_bits) - in_group : len;
         auto flags = [&](int i) {
             uint32_t w = 0;
-            if (i >= 0 && i + 4 <= len) {
+            if (i >= 0 && i + 4 <= end) {
                 w = *reinterpret_cast<const uint32_t *>(a.accept + CB0 + i);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (i + e >= 0 && i + e < len)
+                    if (i + e >= 0 && i + e < end)
                         w |= static_cast<uint32_t>(a.accept[CB0 + i + e]) << (8 * e);
             }
             return w;
         };
-        // accepted in the unit's parts before this one
-        uint32_t skip = 0;
-#pragma unroll 8
-        for (int i = 4 * tid - off; i < i0; i += 4 * kKeepGroup) skip += __popc(flags(i));
-        skip = static_cast<uint32_t>(block_sum<int32_t, kKeepGroup>(
-            static_cast<int32_t>(skip), reinterpret_cast<int32_t *>(s_tmp)));
         const int64_t at = base + s_pre[q] + skip;
-        const int per = ((end - i0 + kKeepGroup - 1) / kKeepGroup + 3) & ~3;  // at most 16
+        const int per = ((end - i0 + kKeepGroup - 1) / kKeepGroup + 3) & ~3;  // at most 36
         const int mine0 = i0 + per * tid;
         uint64_t bits = 0;
         for (int v = 0; 4 * v < per; ++v)
@@ -1441,7 +1506,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     RangeTot t{};
     if (static_cast<int>(threadIdx.x) < a.ranges) t = a.tot[threadIdx.x];
     const BatchTotals all =
-        scan_ranges(t, a.ranges, per, a.n, a.n, a.road_cap, INT64_MAX, s_range);
+        scan_ranges(t, a.ranges, nu, per, a.n, a.n, a.road_cap, INT64_MAX, 0, s_range);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *a.err = all.err;
         *a.d_n_roads = all.n_roads;
@@ -1515,13 +1580,16 @@ int64_t unit_count(int64_t words) { return (words + kUnitWords - 1) / kUnitWords
 int64_t unit_rec_bytes(int64_t words) {
     return static_cast<int64_t>(sizeof(UnitRec)) * unit_count(words);
 }
-int64_t unit_range_bytes() { return static_cast<int64_t>(sizeof(RangeTot)) * kMaxRanges; }
-// Slices past their unit's first: a batch's combinations over the slice, and where the slice is not the
-// largest, at most its units (kSliceWaves * slice / 8192) times the 28 * 8192 / slice that one has.
-constexpr int64_t kUnitSlices = (7 * 32768) >> kMinSliceBits;  // of 7 roads of 8^5 in a unit
+// (and behind the ranges' totals the counts of fine slices per unit)
+int64_t unit_range_bytes() {
+    return static_cast<int64_t>(sizeof(RangeTot)) * kMaxRanges + 4ll * kPieces;
+}
+// Slices past their unit's first, and so accumulators: a batch's combinations over the largest slice, or
+// where a smaller one is taken fewer than the pieces that it may leave (scan_ranges).
+constexpr int64_t kUnitSlices = (7 * 32768) >> kSliceBits[0];  // of 7 roads of 8^5 in a unit
 int64_t unit_slices(int64_t combos) {
-    const int64_t small = combos >> kMinSliceBits, most = int64_t{kSliceWaves} * 32;
-    return (combos >> kMaxSliceBits) + (small < most ? small : most) + 1;
+    const int64_t small = combos >> kSliceBits[0];
+    return (combos >> kSliceBits[2]) + (small < kPieces ? small : kPieces) + 1;
 }
 int64_t unit_acc_bytes(int64_t combos) {
     return static_cast<int64_t>(sizeof(SliceAcc)) * unit_slices(combos);
@@ -1586,6 +1654,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     c.sets = static_cast<UnitSet *>(p.sets);
     c.rec = static_cast<UnitRec *>(p.rec);
     c.tot = static_cast<RangeTot *>(p.tot);
+    c.fine = reinterpret_cast<uint32_t *>(c.tot + kMaxRanges);
     c.copy = p.copy;
     c.keep = p.d_n_kept ? static_cast<UnitKeep *>(p.keep) : nullptr;
     c.group = reinterpret_cast<unsigned long long *>(p.keep_groups);
@@ -1596,7 +1665,6 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     // pass with room for all of those cleared, 16.3 now)
     const int64_t slices = unit_slices(p.combo_cap), most = kUnitSlices * units;
     c.n_acc = slices < most ? slices : most;
-    c.kept_only = p.kept_only;
     hipLaunchKernelGGL(k_unit_count, dim3(ranges + 1), dim3(kThreads), 0, s,
                        c);
     hipError_t e = hipGetLastError();
@@ -1611,6 +1679,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     a.sets = c.sets;
     a.rec = c.rec;
     a.tot = c.tot;
+    a.fine = c.fine;
     a.roads = p.roads;
     a.road_cap = p.road_cap;
     a.out = p.out;
@@ -1641,6 +1710,7 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     k.word_cap = p.word_cap;
     k.keep = c.keep;
     k.group = c.group;
+    k.acc = c.acc;
     k.slots = a.slots;
     k.slot_bytes = a.slot_bytes;
     k.sets = c.sets;
@@ -1656,8 +1726,8 @@ hipError_t launch_units(const UnitsLaunch &p, hipStream_t s, hipEvent_t start, h
     k.err = p.err;
     // Few groups are shared by several workgroups each: by 32 where that fills the chip (30 groups of
     // units, 84 thousand kept: 6.8 us, with 68 9.5), by up to 128 where there are fewer still (a pass
-    // over 1000 uneven events, 7 groups, every combination accepted: 270 us with 32, 167 with 128; the
-    // list of 37 such events at the usual cut 11.4 and 7.9).
+    // over 1000 uneven events, 7 groups, every combination accepted, its flags searched in parts of 4096:
+    // 270 us with 32, 167 with 128; the list of 37 such events at the usual cut 11.4 and 7.9).
     k.parts = static_cast<int32_t>(keep_parts(c.n_group));
     const int kgrid = p.kept ? static_cast<int>(c.n_group) * k.parts : 1;
     if (p.kept_only)

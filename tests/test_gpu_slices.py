@@ -1,6 +1,5 @@
-"""Batches on both sides of the numbers of units at which the slices that a unit is cut into get longer
-(32 to 1024 units, by what is wanted back), of heavy roads: every output against the oracle, and no
-step in the time of a pass."""
+"""Batches on both sides of the sizes at which the slices that a unit is cut into get longer, of heavy
+roads: every output against the oracle, and no step in the time of a pass."""
 import numpy as np
 import pytest
 import torch
@@ -47,29 +46,40 @@ def test_both_sides_of_a_slice_length(bank, units, want):
         assert np.array_equal(np.asarray(ref[k])[kept], got[f"kept_{k}"].cpu().numpy()), k
 
 
+def best_of(bank, words, want):
+    """The least time of ten passes over these words, in ms."""
+    _, nr, _, nc, _ = oracle.count(words, CFG)
+    r = P.BatchRunner(gpu_cfg(oracle.make_config()), P.device_bank(bank.f, bank.q), len(words),
+                      nr + 1, nc + 4, kept_cap=0 if want == "records" else nc, graph=False,
+                      with_c=False, kept_only=want == "kept_only")
+    r.load(P.words_tensor(words))
+    times = []
+    for _ in range(12):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(r.stream)
+        for _ in range(10):
+            r.run()
+        b.record(r.stream)
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
 @pytest.mark.parametrize("want", ["records", "list", "kept_only"])
 def test_one_more_unit_makes_no_step(bank, want):
     """A pass over 65 units took more than twice as long as one over 64 when the slices got 16 times as
     long there."""
-    def best_of(units):
-        words = heavy_words(units, 8, np.random.default_rng(7))
-        _, nr, _, nc, _ = oracle.count(words, CFG)
-        r = P.BatchRunner(gpu_cfg(oracle.make_config()), P.device_bank(bank.f, bank.q), len(words),
-                          nr + 1, nc + 4, kept_cap=0 if want == "records" else nc, graph=False,
-                          kept_only=want == "kept_only")
-        r.load(P.words_tensor(words))
-        times = []
-        for _ in range(12):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record(r.stream)
-            for _ in range(10):
-                r.run()
-            b.record(r.stream)
-            torch.cuda.synchronize()
-            times.append(a.elapsed_time(b))
-        return min(times)
     for units in (32, 64, 128, 256, 512, 1024):
-        assert best_of(units + 1) < 1.5 * best_of(units), units
+        few, more = (best_of(bank, heavy_words(n, 8, np.random.default_rng(7)), want)
+                     for n in (units, units + 1))
+        assert more < 1.5 * few, units
+
+
+def giant_words(n, rng):
+    """n roads of 8^5 combinations."""
+    layer = np.repeat(np.tile(np.arange(5), n), 8)
+    road = np.repeat(np.arange(n), 40)
+    return (rng.integers(0, 8192, 40 * n) | layer << 13 | (3 * road + 1) % 256 << 16).astype(np.uint32)
 
 
 @pytest.mark.parametrize("units", [1, 3, 20])
@@ -77,11 +87,8 @@ def test_one_more_unit_makes_no_step(bank, want):
 def test_units_of_as_many_slices_as_there_can_be(bank, units, combo_cap):
     """Roads of 8^5 combinations, seven to a unit, under a capacity of their number and far above it:
     what the slices of a unit share is counted by the words as well as by the capacity."""
-    rng = np.random.default_rng(units)
     n = (256 * units + 39) // 40
-    layer = np.repeat(np.tile(np.arange(5), n), 8)
-    road = np.repeat(np.arange(n), 40)
-    words = (rng.integers(0, 8192, 40 * n) | layer << 13 | (3 * road + 1) % 256 << 16).astype(np.uint32)
+    words = giant_words(n, np.random.default_rng(units))
     ref = oracle.run(words, bank.f, bank.q, CFG)
     assert ref["n_combos"] == 32768 * n
     r = P.BatchRunner(gpu_cfg(CFG), P.device_bank(bank.f, bank.q), len(words), n,
