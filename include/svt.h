@@ -221,7 +221,8 @@ svt_status svt_select(const svt_config *cfg, const svt_roads *roads, int64_t n_r
  * ascending indices of the accepted combinations and rec their fit values, compacted: entry i
  * of rec->p0..p2, chi2 (and c0..c2 when non-NULL) belongs to combination kept[i], kept_cap
  * entries each.  The values are fitted again for the accepted combinations only, with the
- * same integer arithmetic, so they equal the records of the default mode bit for bit. */
+ * same integer arithmetic, so they equal the records of the default mode bit for bit.  Where the
+ * list is too short, neither is written (with records the list holds its first kept_cap entries). */
 #define SVT_BATCH_KEPT_ONLY 2
 svt_status svt_process_batch(const svt_fconst *bank, const svt_config *cfg, const svt_tune *tune,
                              const uint32_t *words, const int64_t *d_n_words, int64_t word_cap,
@@ -233,12 +234,14 @@ svt_status svt_process_batch(const svt_fconst *bank, const svt_config *cfg, cons
 
 /* For callers that cannot allocate device memory -- code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc: svt_process_batch with the same arguments but no
- * d_work / work_bytes.  Its workspace is one static array of SVT_STATIC_WORK_BYTES bytes, and
- * 30 MiB for the unit kernels' counts, per GPU, part of the library's code object and held until the process ends; the call allocates
- * nothing.  Capacities whose workspace (svt_batch_workspace) exceeds that size return
- * SVT_ERR_CAPACITY before anything is enqueued (svt_static_workspace_need reports both
- * numbers); SVT_BATCH_GRAPH is SVT_ERR_ARG (capture the call in a graph of your
- * own instead).  Every call on one GPU uses that GPU's array, and each
+ * d_work / work_bytes.  Its workspace is one static array per GPU, part of the library's code
+ * object and held until the process ends; the call allocates nothing.  The array has
+ * SVT_STATIC_WORK_BYTES for what grows with the words and roads, and beside them 30 MiB, more than
+ * the unit kernels' counts can take with that.  Capacities that need more than the first return
+ * SVT_ERR_CAPACITY before anything is enqueued (svt_static_workspace_need reports need and limit,
+ * both with the unit kernels' part); SVT_BATCH_GRAPH is SVT_ERR_ARG (capture the call in a graph of
+ * your own instead).  Words in page-locked host memory are read over the bus twice where there is
+ * no room for a copy.  Every call on one GPU uses that GPU's array, and each
  * pass clears what must start at zero: calls whose passes overlap on one GPU (other streams,
  * other threads) race and give wrong results; serialise them.  Outputs and the device-side
  * error word are exactly those of svt_process_batch. */
@@ -251,10 +254,10 @@ svt_status svt_process_batch_static(const svt_fconst *bank, const svt_config *cf
                                     const svt_best *best, int64_t *kept, int64_t kept_cap,
                                     int64_t *d_n_roads, int64_t *d_n_combos, int64_t *d_n_kept,
                                     uint64_t *d_err, int32_t flags, hipStream_t stream);
-/* *need = the workspace these capacities take (svt_batch_workspace, or without room for a copy
- * of the words where only that fits), *limit = SVT_STATIC_WORK_BYTES and what the unit kernels
- * need for these capacities; SVT_OK if svt_process_batch_static accepts them, SVT_ERR_CAPACITY if
- * they are too large, SVT_ERR_ARG for invalid capacities or tune. */
+/* *need = the workspace these capacities take (svt_batch_workspace, or that without room for a copy
+ * of the words where only this fits), *limit = SVT_STATIC_WORK_BYTES and the unit kernels' part for
+ * these capacities; SVT_OK if svt_process_batch_static accepts them, SVT_ERR_CAPACITY if they are too
+ * large, SVT_ERR_ARG for invalid capacities or tune. */
 svt_status svt_static_workspace_need(int64_t word_cap, int64_t road_cap, int64_t combo_cap,
                                      const svt_tune *tune, int64_t *need, int64_t *limit);
 

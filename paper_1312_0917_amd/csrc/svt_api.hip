@@ -500,7 +500,7 @@ namespace {
 // with hipGetSymbolAddress and used everywhere instead.
 // (The unit kernels' part comes on top of SVT_STATIC_WORK_BYTES.  A batch that the rest admits has
 // fewer than 2^24 words and 12e9 combinations, for they take 2 bytes a word and 12 bytes per 4096
-// combinations there: 3 MiB for the units, 24 MB and 2 MiB for the slices.)
+// combinations there: 3 MiB for the units, 24 MB for the slices.)
 constexpr int64_t kStaticUnitBytes = 30ll << 20;
 static __device__ __align__(256) char scratch[SVT_STATIC_WORK_BYTES + kStaticUnitBytes];
 constexpr int kMaxDevices = 64;
