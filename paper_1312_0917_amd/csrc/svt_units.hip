@@ -18,7 +18,7 @@
 //
 // Measured on one GPU, us a pass: 3000 events of 64 roads 49 (four kernels before: a pre-pass with
 // look-back, fits of flat tiles, best tracks, a reset: 75), 4000 events of 2048 roads 3940 (4510),
-// 8192 uneven events with a kept list 235 to 240 (320), 100 events of 8 roads 16.4 back to back (23).
+// 8192 uneven events with a kept list 237 (320), 100 events of 8 roads 17 back to back (23).
 #include "svt_fit.h"
 #include "svt_units.h"
 
